@@ -20,7 +20,8 @@ LIB = os.path.join(LIBDIR, "libtempo.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["tempo_api.hip", "kv_store.hip", "attn_partial_bf16.hip", "attn_partial_f32.hip",
-           "attn_combine.hip", "stream_read.hip", "rope.hip", "attn_prefill_bf16.hip", "worklist.hip", "discounted_sum.hip"]
+           "attn_combine.hip", "stream_read.hip", "rope.hip", "attn_prefill_bf16.hip", "attn_block_bf16.hip",
+           "worklist.hip", "discounted_sum.hip"]
 HEADERS = [os.path.join(CSRC, "tempo_internal.h"), os.path.join(CSRC, "attn_bf16_common.h"),
            os.path.join(CSRC, "attn_combine.h"), os.path.join(ROOT, "include", "tempo.h")]
 
@@ -66,7 +67,8 @@ def _drop_remarks(lines):
 # register count over the edge fails the build instead of silently costing 30%.
 MIN_OCCUPANCY = [
     ("attn_partial_bf16ILi128E", 3),           # decode kernel, D = 128: <= 170 VGPRs
-    ("attn_prefill_bf16ILi128ELi8ELb", 4),   # prompt kernel, D = 128: two workgroups of 8 per compute unit
+    ("attn_block_bf16ILi128ELi8E", 4),         # LDS-staged block kernel, D = 128: two workgroups of 8 per compute unit
+    ("attn_prefill_bf16ILi128E", 2),           # prompt kernel, D = 128: two wavefronts of 32 columns per SIMD
 ]
 
 

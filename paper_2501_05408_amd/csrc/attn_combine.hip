@@ -18,8 +18,7 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
   const int b = blockIdx.y;  // blockIdx.x runs over the sequence's (query step, query head) rows
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
-  const SeqRange rg = seq_range(t_b, p.window, p.tps_log2, p.queries, p.pad_t);
-  const int n = rg.nchunks < p.num_splits ? rg.nchunks : p.num_splits;
+  const int n = row_splits(p, t_b, blockIdx.x);
   const int64_t row = (int64_t)b * gridDim.x + blockIdx.x;
   const int64_t orow = (int64_t)b * p.io_steps * p.Hq + blockIdx.x;  // rows of `out` may be strided per sequence
   const int esz = kBf16 ? 2 : 4;
@@ -35,11 +34,11 @@ __global__ __launch_bounds__(256) void attn_combine_few(AttnParams p, int rows) 
   const int row = idx / C4, c4 = idx - row * C4;
   if (row >= rows) return;
   const int b = row / (p.Hq * p.queries);
-  const int64_t orow = (int64_t)b * p.io_steps * p.Hq + (row - b * (p.Hq * p.queries));
+  const int in_call = row - b * (p.Hq * p.queries);
+  const int64_t orow = (int64_t)b * p.io_steps * p.Hq + in_call;
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
-  const SeqRange rg = seq_range(t_b, p.window, p.tps_log2, p.queries, p.pad_t);
-  const int n = rg.nchunks < p.num_splits ? rg.nchunks : p.num_splits;  // 1..8
+  const int n = row_splits(p, t_b, in_call);  // 1..8
   const float* ml = p.ws_ml + (int64_t)row * p.num_splits * 2;
   const float* acc = p.ws_acc + (int64_t)row * p.num_splits * D + 4 * c4;
   float m[U], l[U];

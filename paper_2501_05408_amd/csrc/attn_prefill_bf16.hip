@@ -4,26 +4,34 @@
 // What is computed (Section 2, Eq. 1 for every step t .. t+count-1 of a sequence,
 // with the causal or window pattern; Section 4.3 index masks): exactly what the
 // decode kernel computes for each of those steps, one after the other.  With many
-// steps per key the products dominate the reads: this kernel is bound by the
-// matrix cores and the softmax arithmetic, not by HBM.
+// steps per key the products dominate the reads.
 //
-// Mapping.  One workgroup = one (sequence, kv head, block of QB query steps); its
-// columns are the block's (step, head) pairs, 16 per wavefront (column = c*G + g).
-// Every wavefront walks ALL 32-slot groups of the block's key range, so each
-// column's softmax is finished inside one wavefront: no partials, no combine, the
-// output is written directly.  The key/value image of a group (16 KiB at D = 128)
-// is the same for all wavefronts: the workgroup copies it once from the pool into
-// LDS (it is already in MFMA operand order there, 1 KiB units) and every wavefront
-// reads its operands from LDS.  Two key and two value buffers: the copies for later
-// groups (global -> LDS loads issued at the top of an iteration, waited for at its
-// end) overlap the arithmetic of the iteration; one barrier per group.
+// Mapping.  One workgroup = one (sequence, kv head, block of QB query steps, split of the
+// block's key range; normally one split); its columns are the block's (step, head) pairs,
+// 32 per wavefront (column = c*G + g), as the columns of 32x32x16 products:
+//   logits tile  = K (32 slots x 16 dims) * Q^T (16 dims x 32 columns)   D/16 steps
+//   output tiles = V^T (32 dims x 16 slots) * P^T (16 slots x 32 columns)  D/32 tiles x 2 steps
+// A lane then holds logits, weights, sum and output of ONE column: no exchange but one lane
+// swap for the maximum, and the weights of a lane are the operand of the second product as
+// they stand.  The block store's units, made for 16x16x32 operands, are read as 32x32x16
+// ones by taking two units side by side (16-lane runs of 256 bytes: no bank conflict).
+// Every wavefront walks ALL 32-slot groups of the block's key range, so each column's
+// softmax is finished inside one wavefront.  A group's key/value image (16 KiB at D = 128)
+// is the same for all wavefronts: it is copied once per workgroup from the pool into LDS.
+// 32 columns per wavefront, because LDS operand reads are per wavefront: 16 columns
+// (16x16x32 products) read twice as much for the same products.
 //
-// Blocks against a long history.  The same kernel serves a block of up to 128
-// columns in front of a long key range (chunked prompt processing, speculative
-// decoding with many steps): the key range is then cut into splits as in the decode
-// kernel, one workgroup per (sequence, kv head, split) writes a partial
-// (reference, sum, accumulator) per column, and the split combine finishes.  The
-// keys/values are read from HBM once per workgroup for all its columns.
+// What bounds it.  Matrix cores: 16 products of 32 cycles per wavefront and group = 512
+// cycles; vector ALU 450 cycles; two wavefronts per SIMD.  A wavefront issues about one
+// instruction in five cycles, so what is not a product has to lie between products, and
+// products that queue behind a busy matrix core keep the SIMD's other wavefront from
+// issuing LDS and memory instructions (measured: two copies 148 cycles alone, 658 beside
+// back-to-back products; separate product and softmax phases of the two wavefronts, with a
+// barrier between, were slower than this order for that reason).  Measured on 16 prompts of
+// 4096 steps, 24 query heads in 8 groups, D = 128 (1.65 Tflop): 16-column kernel 2082 us a
+// call, this one 1877 us (back to back; 1750 us in short runs, before the clock drops);
+// 1750 cycles per group and pair of wavefronts (1020 of them
+// products), 9900 before the first and 4100 after the last group of a workgroup.
 //
 // Workgroups of one (sequence, head) are adjacent in the work list and run together on
 // one die, so the pool is streamed from HBM about once per (sequence, head) and the
@@ -35,12 +43,27 @@ namespace tempo {
 namespace {
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
-typedef const __attribute__((address_space(1))) void* global_ptr;
 
+// Three-operand maximum that propagates NaN (v_maximum3_f32).  fmaxf() would first
+// canonicalise each matrix-core result, and inline assembly would hide from the compiler that
+// it must wait for one.
 __device__ inline float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+
+// Accumulator tile of a 32x32x16 product: lane (column & 31) + 32 h holds rows
+// 8 (r / 4) + 4 h + (r mod 4), r = 0 .. 15.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Maximum over the two lanes that share a column (l and l ^ 32), left in both.
+__device__ inline float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1]));
+}
+__device__ inline float half_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Online softmax of one group for this kernel, with a LAZY reference: weights are
@@ -48,76 +71,84 @@ __device__ inline float max3(float a, float b, float c) {
 // grown by more than kSlack (in log2 units) since ref was set, so weights stay
 // below 2^kSlack (exact in fp32 sums, same relative rounding in bf16) and the
 // accumulators are rescaled a few times per column instead of at every new
-// maximum.  The result acc / sum does not depend on ref.  The running sum is one
-// more accumulator tile (weights times a column of ones on the matrix cores).
+// maximum.  The result acc / sum does not depend on ref.
 constexpr float kSlack = 8.0f;
 
-// First half: move the reference if this group's maximum calls for it.  x holds the
-// RAW dot products (masked ones are -inf); `scale` > 0 is s * log2(e).
+// Maximum of the group's logits over the column, in log2 units.  x holds the RAW dot
+// products (masked ones are -inf); `scale` > 0 is s * log2(e).
+__device__ inline float tile_max(const f32x16& x, float scale) {
+  const float a = max3(x[0], x[1], x[2]), b = max3(x[3], x[4], x[5]), c = max3(x[6], x[7], x[8]);
+  const float d = max3(x[9], x[10], x[11]), e = max3(x[12], x[13], x[14]);
+  return half_max(max3(max3(a, b, c), max3(d, e, x[15]), x[15])) * scale;
+}
+
+// First half: move the reference if this group's maximum calls for it.  A lane's
+// sixteen logits, its accumulators and its share of the sum all belong to ONE column,
+// so the rescale factor needs no exchange.
 template <int D>
-__device__ inline void softmax_reference(const float* x, float scale, int lane, float& ref, f32x4* acc,
-                                         f32x4& acc_l) {
-  constexpr int DT = D / 16;
-  const int c = lane >> 4;
-  // (three-operand maxima written out: fmaxf() first canonicalises each matrix-core result)
-  float mx = max3(max3(max3(max3(x[0], x[1], x[2]), x[3], x[4]), x[5], x[6]), x[7], x[7]);
-  mx = column_max(mx) * scale;
+__device__ inline void softmax_reference(float mx, float& ref, float& base, f32x16* acc, float& sum) {
   // ref = -inf until the column sees its first key; -inf + kSlack = -inf, so any finite mx moves it
   const bool move = mx > ref + kSlack;
   if (__any(move)) {
-    const float ref_new = move ? mx : ref;
-    const float alpha = move ? fast_exp2(ref - ref_new) : 1.0f;  // exp2(-inf) = 0 on the first key
-    ref = ref_new;
-    float a[4];
+    const float alpha = move ? fast_exp2(ref - mx) : 1.0f;  // exp2(-inf) = 0 on the first key
+    ref = move ? mx : ref;
+    base = ref == -INFINITY ? 0.f : ref;  // a column that has seen no key yet: weights exp2(-inf - 0) = 0
+    sum *= alpha;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = __shfl(alpha, 4 * c + r);
+    for (int ot = 0; ot < D / 32; ++ot) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[dt][r] *= a[r];
+      for (int r = 0; r < 16; ++r) acc[ot][r] *= alpha;
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc_l[r] *= a[r];
   }
 }
 
 // Second half: the bf16 weights 2^(scale * x - ref), the scale applied inside one fused
-// multiply-add.
-__device__ inline bf16x8 softmax_weights(const float* x, float scale, float ref) {
-  const float base = ref == -INFINITY ? 0.f : ref;  // a column that has seen no key yet: weights exp2(-inf) = 0
-  bf16x8 pa;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) pa[i] = (__bf16)fast_exp2(fmaf(x[i], scale, -base));
-  return pa;
+// multiply-add, in the order of the two 16-key steps of the weights x values product:
+// a value unit (column tile, c) holds slots 4c .. 4c+3 and 16+4c .. 16+4c+3, and step
+// `chunk` gives lane half h the units c = 2 chunk + h, i.e. accumulator registers
+// 4 chunk .. +3 and 8 + 4 chunk .. +3 of this lane.  The sum is taken over the rounded
+// weights, so the output stays a convex combination of value rows.  One call does logit i
+// of sixteen (the odd ones finish a pair), so that the caller can put matrix instructions between them.
+__device__ inline void softmax_weight(const f32x16& x, float scale, float base, int i, float& even, u32x4* pa, float& sum) {
+  const int chunk = i >> 3, e = i & 7;
+  const float w = fast_exp2(fmaf(x[(e < 4 ? e : 4 + e) + 4 * chunk], scale, -base));
+  if ((i & 1) == 0) {
+    even = w;
+    return;
+  }
+  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  const bf16x2 both = {(__bf16)even, (__bf16)w};
+  pa[chunk][e >> 1] = __builtin_bit_cast(uint32_t, both);
+  sum = __builtin_amdgcn_fdot2_f32_bf16(both, ones, sum, false);
 }
 
-// Steps per workgroup for a query group of G heads: all 16 x `waves` columns.
-__host__ __device__ inline int prefill_block_steps(int G, int waves) { return (16 * waves) / G; }
+// Index mask of a group that some column's range cuts: -inf outside THIS lane's column
+// range [lo_col, hi_col].
+__device__ inline void mask_tile(int grp, int lo_col, int hi_col, int lane, f32x16& x) {
+  const int j0 = (grp << 5) + 4 * (lane >> 5);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int j = j0 + 8 * (r >> 2) + (r & 3);
+    x[r] = (j >= lo_col && j <= hi_col) ? x[r] : -INFINITY;
+  }
+}
 
-// NW wavefronts per workgroup, 16 columns per wavefront.  (Two column tiles per
-// wavefront would halve the LDS reads per column, but the accumulators then cost a
-// wavefront of occupancy: measured slower, 2.56 against 2.45 ms on the 4096-step prompt.)
-//
-// The loop is software-pipelined by one group: iteration n computes the logits of group
-// n + 1 (matrix cores) next to the softmax of group n (vector ALU), then the
-// weights x values products of group n.  The two kinds of work of one wavefront are
-// independent inside an iteration, so they overlap instead of alternating.  Keys
-// therefore run one group ahead of values through LDS: two key buffers (groups n + 1,
-// n + 2) and two value buffers (groups n, n + 1).
-template <int D, int NW, bool kRope, bool kStream>
-__global__ __launch_bounds__(64 * NW) void attn_prefill_bf16(AttnParams p) {
-  constexpr int KS = D / 32;
-  constexpr int DT = D / 16;
-  constexpr int KU = 2 * KS;                  // 1 KiB units of one group's keys
-  constexpr int UNITS = KU + DT;              // ... and of its keys and values together
-  constexpr int PER_THREAD = (UNITS + NW - 1) / NW;  // units each wavefront copies per iteration (at most)
-  // A block in front of a long history reads every key/value once and no other workgroup reads
-  // them again: non-temporal copies (the cache-policy bit the decode kernel's loads carry) keep
-  // them from displacing anything.  The blocks of a prompt share keys/values through L2: cached.
-  constexpr int kCachePolicy = kStream ? 2 : 0;
-  extern __shared__ u32x4 lds[];              // keys [2][KU][64] x 16 bytes, then values [2][DT][64] x 16 bytes
-  u32x4* const lds_k = lds;
-  u32x4* const lds_v = lds + 2 * KU * 64;
+// Columns per wavefront, and steps per workgroup for a query group of G heads.
+constexpr int kWaveColumns = 32;
+__host__ __device__ inline int prefill_block_steps(int G, int waves) { return (kWaveColumns * waves) / G; }
+
+template <int D, int NW, int NBUF, bool kRope>
+__global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(AttnParams p) {
+  constexpr int KT = D / 16;                  // 16-dim contraction steps of the logits
+  constexpr int OT = D / 32;                  // 32-dim tiles of the output
+  constexpr int KU = D / 16;                  // 1 KiB units of one group's keys
+  constexpr int UNITS = 2 * KU;               // ... and of its keys and values together
+  constexpr int PER_WAVE = UNITS / NW;        // units each wavefront copies per group
+  static_assert(UNITS % NW == 0 && (NBUF == 4 || NBUF == 8), "copy split");
+  constexpr bool kEarly = NBUF > 4;           // first operands of an iteration are read at the end of the one before
+  constexpr int kPair = kEarly ? 2 : 1;       // groups per barrier
+  constexpr int kRead = KT;                   // operands read ahead of the matrix instruction that takes them
+  extern __shared__ u32x4 lds[];              // [NBUF][UNITS][64] x 16 bytes: a group's keys, then its values
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int QB = prefill_block_steps(p.G, NW);
@@ -161,10 +192,10 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_bf16(AttnParams p) {
   const int end = t_last < ce ? t_last : ce;
   const int g_first = start >> 5, g_last = end >> 5;
 
-  // wavefront-uniform bounds over this wavefront's 16 columns, cut to the split:
+  // wavefront-uniform bounds over this wavefront's columns, cut to the split:
   // the groups it has any work in, and those no column cuts
-  const int first_col = 16 * wave;
-  const int last_col = (first_col + 15) < ncols - 1 ? (first_col + 15) : ncols - 1;
+  const int first_col = kWaveColumns * wave;
+  const int last_col = (first_col + kWaveColumns - 1) < ncols - 1 ? (first_col + kWaveColumns - 1) : ncols - 1;
   const bool idle = first_col >= ncols;                             // a wavefront beyond the block's columns
   const int own_hi = t_first + (idle ? 0 : last_col / p.G);         // newest key any of its columns sees
   const int own_hi_min = t_first + (idle ? 0 : first_col / p.G);    // newest key ALL of its columns see
@@ -173,76 +204,91 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_bf16(AttnParams p) {
   const int w_hi = own_hi < end ? own_hi : end, w_hi_min = own_hi_min < end ? own_hi_min : end;
   const int w_lo_first = own_lo_first > start ? own_lo_first : start;
   const int w_lo_last = own_lo_last > start ? own_lo_last : start;
-  // has this wavefront any work in group g / does some column's range cut group g?  (wave-uniform)
-  auto active = [&](int g) { return !idle && (g << 5) <= w_hi && (g << 5) + 31 >= w_lo_first; };
-  auto is_cut = [&](int g) { return (g << 5) < w_lo_last || (g << 5) + 31 > w_hi_min; };
 
   // This lane's column (unused columns behave like the block's last step with q = 0),
-  // its range, its query operand, its softmax state.
-  const int col = first_col + (lane & 15);
+  // its range, its query operand (lane half h: dims 16 s + 8 h .. +7), its softmax state.
+  const int half = lane >> 5;
+  const int col = first_col + (lane & 31);
   const int cq = col < ncols ? col / p.G : C - 1;
   const int gq = col < ncols ? col - cq * p.G : 0;
   const int step = t_first + cq;               // the column's own step: its newest key and its position
   const int hi_col = step < end ? step : end;
   const int lo_own = (p.window > 0 && step - p.window + 1 > 0) ? step - p.window + 1 : 0;
   const int lo_col = lo_own > start ? lo_own : start;
-  u32x4 qreg[KS];
+  u32x4 qreg[KT];
   {
-    const int c = lane >> 4;
     const uint16_t* qp = static_cast<const uint16_t*>(p.q) +
-                         (((int64_t)b * p.io_steps + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 8 * c;
+                         (((int64_t)b * p.io_steps + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 8 * half;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
+    for (int s = 0; s < KT; ++s) {
       const u32x4 zero = {0u, 0u, 0u, 0u};
-      const u32x4 v = *reinterpret_cast<const u32x4*>(qp + 32 * s);
+      const u32x4 v = *reinterpret_cast<const u32x4*>(qp + 16 * s);
       qreg[s] = col < ncols ? v : zero;
     }
-    if (kRope) rotate_query<D>(p, step, lane, qreg);  // queries arrive unrotated
-  }
-  float m_run = -INFINITY;                     // softmax reference of column lane&15 (log2 units)
-  f32x4 acc[DT];                               // lane (n + 16c): dims 16dt + n of columns 4c .. 4c+3
-  f32x4 acc_l = {0.f, 0.f, 0.f, 0.f};          // running sums of columns 4c .. 4c+3 (the same in every n)
+    if (kRope) {  // queries arrive unrotated; a dim's partner D/2 further sits in the same lane
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};  // bf16 1.0 x 8
+      for (int s = 0; s < KT / 2; ++s)
+        rotate_pieces(p.rope_cos, p.rope_sin, step, D / 2, 16 * s + 8 * half, qreg[s], qreg[s + KT / 2]);
+    }
+  }
+  float m_run = -INFINITY;                     // softmax reference of this lane's column (log2 units)
+  float l_run = 0.f;                           // running sum over this lane's slots
+  f32x16 acc[OT];                              // dims 32 ot + 8 (r / 4) + 4 h + (r mod 4) of this lane's column
+#pragma unroll
+  for (int ot = 0; ot < OT; ++ot) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[ot][r] = 0.f;
+  }
 
   // Copy of a group: wavefront w moves units w, w + NW, ... of the group's 1 KiB units
   // (keys first, then values).  The pool image is already what the consumers read, so
   // the copy goes from global memory straight into LDS (gfx950's 16-byte global -> LDS
   // load: lane i's piece lands at the wavefront's LDS base + 16 i); completion is counted
-  // by the vector-memory counter.
-  // Where a group sits in either pool: its block-table entry (a scalar load, asked for
-  // one iteration before it is needed so that nobody waits for it) and the offset that
-  // follows from it.
-  const_i32_ptr table = (const_i32_ptr)p.block_table + (int64_t)b * p.max_blocks_per_seq;
-  auto entry_of = [&](int g) {
-    const int gc = g < g_last ? g : g_last;  // never past the range's last tile
-    return table[((gc << 5) >> p.z_log2) & p.tile_mask];
+  // by the vector-memory counter.  Where a group sits in either pool follows from its
+  // block-table entry.  The range's entries are fetched 64 at a time, one per lane, and read
+  // from there: a scalar load inside the loop would share the LDS reads' counter, and as the
+  // two kinds return out of order every wait for an operand would become a wait for all.  Beyond the range's last group the last one is
+  // copied again (into a buffer nobody reads any more): every iteration then issues the
+  // same number of copies, and "the group before the newest has landed" is one counted wait.
+  const int32_t* table = p.block_table + (int64_t)b * p.max_blocks_per_seq;
+  const int tile_groups = p.z_log2 - 5;             // log2(groups per tile)
+  const int tile_last = g_last >> tile_groups;
+  int tile_base = g_first >> tile_groups;           // lane i holds the byte offset, in either pool, of tile tile_base + i
+  uint32_t tile_lo, tile_hi;
+  auto load_tiles = [&]() {
+    const int tile = tile_base + lane < tile_last ? tile_base + lane : tile_last;  // never past the range's last tile
+    const int phys = clamp_block(table[tile & p.tile_mask], p.num_blocks);
+    const uint64_t at = ((uint64_t)((int64_t)phys * p.Hkv + hkv) << p.z_log2) * (D * 2);
+    tile_lo = (uint32_t)at;
+    tile_hi = (uint32_t)(at >> 32);
+    // waited for here: the use in the loop must not become a wait for the copies in flight
+    asm volatile("" : "+v"(tile_lo), "+v"(tile_hi));
   };
-  auto offset_of = [&](int entry, int g) -> int64_t {
-    const int phys = clamp_block(entry, p.num_blocks);
-    return (((int64_t)phys * p.Hkv + hkv) << p.z_log2) * D + (int64_t)((g << 5) & ((1 << p.z_log2) - 1)) * D;
-  };
-  auto issue_keys = [&](int gk, int64_t offset) {
-    if (gk > g_last) return;  // uniform over the workgroup
-    const char* from = reinterpret_cast<const char*>(static_cast<const uint16_t*>(p.k_pool) + offset);
+  load_tiles();
+  const char* from_pool[PER_WAVE];                  // this wavefront's units in the pools' first group
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int u = wave + NW * i;  // wave-uniform
-      if (u < KU)  // (wavefronts beyond the units copy nothing)
-        __builtin_amdgcn_global_load_lds((global_ptr)(from + u * 1024 + lane * 16),
-                                         (lds_ptr)(lds_k + ((gk & 1) * KU + u) * 64), 16, 0, kCachePolicy);
+  for (int i = 0; i < PER_WAVE; ++i) {
+    const int u = wave + NW * i;                    // wave-uniform
+    from_pool[i] = u < KU ? static_cast<const char*>(p.k_pool) + u * 1024
+                          : static_cast<const char*>(p.v_pool) + (u - KU) * 1024;
+  }
+  const uint32_t lane_bytes = 16u * (uint32_t)lane;
+  auto issue = [&](int at, int g) {                 // `at`: the buffer's offset in LDS, in 16-byte pieces
+    const int gc = g < g_last ? g : g_last;
+    const int tile = gc >> tile_groups;
+    if (tile - tile_base >= 64) {
+      tile_base = tile;
+      load_tiles();
     }
-  };
-  auto issue_values = [&](int gv, int64_t offset) {
-    if (gv > g_last) return;
-    const char* from = reinterpret_cast<const char*>(static_cast<const uint16_t*>(p.v_pool) + offset);
+    const uint32_t lo = __builtin_amdgcn_readlane(tile_lo, tile - tile_base);
+    const uint32_t hi = __builtin_amdgcn_readlane(tile_hi, tile - tile_base);
+    const uint64_t from = (((uint64_t)hi << 32) | lo) + (uint32_t)(gc & ((1 << tile_groups) - 1)) * (64u * D);
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int u = wave + NW * i - KU;
-      if (u >= 0 && u < DT)
-        __builtin_amdgcn_global_load_lds((global_ptr)(from + u * 1024 + lane * 16),
-                                         (lds_ptr)(lds_v + ((gv & 1) * DT + u) * 64), 16, 0, kCachePolicy);
+    for (int i = 0; i < PER_WAVE; ++i) {
+      // (the buffer form: the compiler takes the global form for a flat access that may also be
+      // an LDS access, and then waits for ALL outstanding LDS reads wherever it waits for one)
+      const auto unit = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(from_pool[i] + from), 0, 1024, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
     }
   };
   // Slots beyond the block's last step may be unwritten (NaN): the 0 mask under the
@@ -251,116 +297,188 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_bf16(AttnParams p) {
   // lane of every 16-byte piece, so a lane masks the slots its consumers will read from
   // it).  Masked slots inside the range hold written data and weight 0.
   const bool tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
-  auto mask_values = [&](int gv) {  // gv == g_last, and tail
+  auto mask_values = [&](int at) {  // the buffer of g_last, and tail
     uint32_t keep[4];
-    value_masks(gv, 0, t_last, lane, keep);
+    value_masks(g_last, 0, t_last, lane, keep);
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int u = wave + NW * i - KU;
-      if (u < 0 || u >= DT) continue;
-      u32x4* at = lds_v + ((gv & 1) * DT + u) * 64 + lane;
-      u32x4 v = *at;
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const int u = wave + NW * i;
+      if (u < KU) continue;
+      u32x4* piece = lds + at + u * 64 + lane;
+      u32x4 v = *piece;
       v.x &= keep[0]; v.y &= keep[1]; v.z &= keep[2]; v.w &= keep[3];
-      *at = v;
+      *piece = v;
     }
   };
-  // End of an iteration: wait until this wavefront's copies have landed, fix up what it
-  // must, wait for its LDS stores, then meet the other wavefronts.  Written out instead
-  // of __syncthreads() so that the waits are the ones this loop needs; the "memory"
-  // clobbers keep the compiler from moving LDS accesses across.
-  auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-  auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-
-  // Raw dot products of this wavefront's columns with the 32 keys of group g (two row tiles).
-  auto logits = [&](int g, float* x) {
-    const u32x4* src = lds_k + (g & 1) * KU * 64 + lane;
-    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(src[s * 64]), as_bf16x8(qreg[s]), sa, 0, 0, 0);
-      sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(src[(KS + s) * 64]), as_bf16x8(qreg[s]), sb, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) { x[r] = sa[r]; x[4 + r] = sb[r]; }
+  // Waits and barriers are written out instead of __syncthreads() so that they are the ones
+  // this loop needs (builtins, not assembly: the compiler then knows what has been waited for
+  // and counts its own waits for LDS operands); the empty statements with a "memory" clobber
+  // keep it from moving LDS accesses across.
+  // landed(): all but the newest kPair groups' copies of this wavefront are in LDS.
+  auto landed = [&]() {
+    constexpr int kLeft = PER_WAVE * kPair;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((kLeft & 15) | 0x0F70 | ((kLeft >> 4) << 14));  // vmcnt only
+    asm volatile("" ::: "memory");
+  };
+  auto meet = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  int64_t off_v;     // offset of group n + 1: its keys were copied an iteration before its values
-  int entry_next;    // block-table entry of group n + 2
-  {
-    const int e0 = entry_of(g_first), e1 = entry_of(g_first + 1);
-    entry_next = entry_of(g_first + 2);
-    const int64_t off0 = offset_of(e0, g_first);
-    off_v = offset_of(e1, g_first + 1);
-    issue_keys(g_first, off0);
-    issue_keys(g_first + 1, off_v);
-    issue_values(g_first, off0);
-  }
-  landed();
-  if (tail && g_first == g_last) mask_values(g_first);
+  // Raw dot products of this wavefront's columns with the 32 keys of the group in `buf`.
+  // Key row l & 31 of the operand is slot l & 31: unit (slot / 16, s / 2), lanes
+  // (slot & 15) + 16 (2 (s & 1) + h).
+  const int k_lane = ((lane >> 4) & 1) * (D / 32) * 64 + (lane & 15) + 16 * half;
+  auto key_operand = [&](int at, int s) { return as_bf16x8(lds[at + k_lane + (s >> 1) * 64 + (s & 1) * 32]); };
+  // Value rows: dim l & 31 of tile ot is unit 2 ot + (dim / 16), lanes (dim & 15) + 16 (2 chunk + h).
+  const int v_lane = KU * 64 + ((lane >> 4) & 1) * 64 + (lane & 15) + 16 * half;
+  auto value_operand = [&](int at, int chunk, int ot) { return as_bf16x8(lds[at + v_lane + ot * 128 + chunk * 32]); };
+
+  // The groups this wavefront has work in: own_first .. own_last.  The others it only helps
+  // to copy: loops of their own, so that no path around the arithmetic carries the accumulators.
+  const int own_first = idle ? g_last + 1 : (w_lo_first > (g_first << 5) ? w_lo_first >> 5 : g_first);
+  const int own_last = idle ? g_last : w_hi >> 5;
+
+  int grp = g_first;
+  // LDS offset of the buffer of group grp + ahead (NBUF is a power of two)
+  constexpr int kBuf = UNITS * 64;
+  int at0 = 0;
+  auto next = [&](int ahead) { return (at0 + ahead * kBuf) & (NBUF * kBuf - 1); };
+  // Into the buffer of group grp - kPair, which everybody finished before the last barrier.
+  auto copies = [&]() { issue(next(NBUF - kPair), grp + NBUF - kPair); };
+  // The groups no column's range cuts: first_whole .. last_whole.
+  const int first_whole = (w_lo_last + 31) >> 5, last_whole = ((w_hi_min + 1) >> 5) - 1;
+  float base = 0.f;                            // m_run, or 0 while the column has seen no key
+  // mask and reference of group g, whose logits are in x
+  auto enter = [&](int g, f32x16& x, float mx) {
+    if (g < first_whole || g > last_whole) {
+      mask_tile(g, lo_col, hi_col, lane, x);
+      mx = tile_max(x, p.scale_log2e);
+    }
+    softmax_reference<D>(mx, m_run, base, acc, l_run);
+  };
+  // End of an iteration.  After a barrier the next kPair groups, the group behind them (its
+  // logits are computed one group ahead) and, with early operand reads, one more are in LDS.
+  constexpr int kAhead = 2 * kPair;            // of grp, which may be the second of a pair
+  auto finish = [&]() {
+    if (kPair == 1 || ((grp - g_first) & 1)) {
+      landed();
+      if (tail && g_last <= grp + kAhead && g_last > grp + kAhead - kPair) mask_values(next(g_last - grp));
+      meet();
+    }
+    at0 = next(1);
+    ++grp;
+  };
+
+#pragma unroll
+  for (int i = 0; i < NBUF - kPair; ++i) issue(i * kBuf, g_first + i);
+  landed();                                    // groups g_first .. g_first + kAhead - 1
+  if (tail && g_last - g_first < kAhead) mask_values((g_last - g_first) * kBuf);
   meet();
-  float xc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // logits of the current group
-  if (active(g_first)) logits(g_first, xc);
-
-  for (int grp = g_first; grp <= g_last; ++grp) {
-    // Buffers (g + 2) & 1 of the keys and (g + 1) & 1 of the values held groups g and
-    // g - 1, which everybody finished in the previous iteration.
-    const int64_t off_k = offset_of(entry_next, grp + 2);
-    entry_next = entry_of(grp + 3);
-    issue_keys(grp + 2, off_k);
-    issue_values(grp + 1, off_v);
-    off_v = off_k;
-
-    if (active(grp)) {
-      if (is_cut(grp)) mask_logits(grp, lo_col, hi_col, lane, xc);
-      softmax_reference<D>(xc, p.scale_log2e, lane, m_run, acc, acc_l);
-      // The next group's logits: independent of the softmax below.  Beyond the last group
-      // this reads a key buffer of an earlier group (or LDS nobody wrote); the result is unused.
-      float xn[8];
-      logits(grp + 1, xn);
-      const bf16x8 pa = softmax_weights(xc, p.scale_log2e, m_run);
-      acc_l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, as_bf16x8(ones), acc_l, 0, 0, 0);
-      const u32x4* src = lds_v + (grp & 1) * DT * 64 + lane;
+  for (; grp < own_first && grp <= g_last; finish()) copies();
+  // operand i of an iteration: keys of group grp + 1, then values of group grp
+  constexpr int kSlots = KT + 2 * OT;
+  bf16x8 op[kSlots];
+  auto read_operand = [&](int i) {
+    op[i] = i < KT ? key_operand(next(1), i) : value_operand(at0, (i - KT) / OT, (i - KT) % OT);
+  };
+  f32x16 xc;                                   // logits of group grp, masked, its reference already moved
+  if (grp <= own_last) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, as_bf16x8(src[dt * 64]), acc[dt], 0, 0, 0);
+    for (int r = 0; r < 16; ++r) xc[r] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) xc[i] = xn[i];
-    } else if (grp + 1 <= g_last && active(grp + 1)) {
-      logits(grp + 1, xc);
+    for (int s = 0; s < KT; ++s)
+      xc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(key_operand(at0, s), as_bf16x8(qreg[s]), xc, 0, 0, 0);
+    enter(grp, xc, tile_max(xc, p.scale_log2e));
+    if (kEarly) {
+#pragma unroll
+      for (int i = 0; i < kRead; ++i) read_operand(i);
     }
-
-    landed();
-    if (tail && grp + 1 == g_last) mask_values(grp + 1);
-    meet();  // groups n + 1 (values) and n + 2 (keys) are in LDS; nobody reads group n any more
   }
-
-  // Columns (4c + r) of acc, value dims 16dt + n.  Whole range: every column saw its own
-  // key, so its sum is > 0 and the output is acc / sum.  One split of the range: the
-  // column's partial (reference, sum, accumulator) goes to the workspace; a column
-  // that saw no key in this split leaves (-inf, 0, 0).
-  const int n = lane & 15, c = lane >> 4;
+  for (; grp <= own_last; finish()) {
+    if (!kEarly) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = first_col + 4 * c + r;
-    const float l_j = acc_l[r];
-    const float ref_j = __shfl(m_run, 4 * c + r);  // the reference lives in lane (column & 15)
-    if (j < ncols) {
-      const int jc = j / p.G, jg = j - jc * p.G;
-      if (p.direct) {
-        __bf16* orow = static_cast<__bf16*>(p.out) +
-                       (((int64_t)b * p.io_steps + c0 + jc) * p.Hq + (int64_t)hkv * p.G + jg) * D;
-        const float inv = 1.0f / l_j;
+      for (int i = 0; i < kRead; ++i) read_operand(i);
+    }
+    u32x4 pa[2];
+    float even, mx[5];
+    f32x16 xn;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) orow[16 * dt + n] = (__bf16)(acc[dt][r] * inv);
+    for (int r = 0; r < 16; ++r) xn[r] = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+      if (s < KT) {
+        xn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], as_bf16x8(qreg[s]), xn, 0, 0, 0);
       } else {
-        const int64_t row = ((int64_t)b * p.queries + c0 + jc) * p.Hq + (int64_t)hkv * p.G + jg;
-        const int64_t part = row * p.num_splits + split;
+        const int ot = (s - KT) % OT;
+        acc[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], as_bf16x8(pa[(s - KT) / OT]), acc[ot], 0, 0, 0);
+      }
+      if (s + kRead < kSlots) read_operand(s + kRead);
+      else if (kEarly) op[s + kRead - kSlots] = key_operand(next(2), s + kRead - kSlots);
+      if (s == KT + OT) copies();
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) p.ws_acc[part * D + 16 * dt + n] = acc[dt][r];
-        if (n == 0) {
-          p.ws_ml[part * 2] = ref_j;
-          p.ws_ml[part * 2 + 1] = l_j;
+      for (int i = 0; i < 16; ++i) {
+        if (i * (KT + OT) / 16 == s) softmax_weight(xc, p.scale_log2e, base, i, even, pa, l_run);
+      }
+      if (s >= KT + OT) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          if (i * OT / 5 == s - KT - OT) {
+            mx[i] = max3(xn[3 * i], xn[3 * i + 1], xn[3 * i + 2]);
+            asm volatile("" : "+v"(mx[i]));    // here, not behind the products
+          }
         }
+      }
+      asm volatile("" : "+v"(l_run));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    xc = xn;
+    enter(grp + 1, xc, half_max(max3(max3(mx[0], mx[1], mx[2]), max3(mx[3], mx[4], xn[15]), xn[15])) * p.scale_log2e);
+  }
+  for (; grp <= g_last; finish()) copies();
+  // the copies issued last may still be in flight: they must land before the LDS is given up
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  // Whole range: every column saw its own key, so its sum is > 0 and the output is
+  // acc / sum.  One split of the range: the column's partial (reference, sum,
+  // accumulator) goes to the workspace; a column that saw no key in this split leaves
+  // (-inf, 0, 0).
+  const float l_j = half_sum(l_run);
+  if (col < ncols) {
+    if (p.direct) {
+      __bf16* orow = static_cast<__bf16*>(p.out) +
+                     (((int64_t)b * p.io_steps + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 4 * half;
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      const float inv = 1.0f / l_j;
+#pragma unroll
+      for (int ot = 0; ot < OT; ++ot) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          bf16x4 o;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[r] = (__bf16)(acc[ot][4 * i + r] * inv);
+          *reinterpret_cast<bf16x4*>(orow + 32 * ot + 8 * i) = o;
+        }
+      }
+    } else {
+      const int64_t row = ((int64_t)b * p.queries + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq;
+      const int64_t part = row * p.num_splits + split;
+      float* arow = p.ws_acc + part * D + 4 * half;
+#pragma unroll
+      for (int ot = 0; ot < OT; ++ot) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<f32x4*>(arow + 32 * ot + 8 * i) =
+              f32x4{acc[ot][4 * i], acc[ot][4 * i + 1], acc[ot][4 * i + 2], acc[ot][4 * i + 3]};
+      }
+      if (half == 0) {
+        p.ws_ml[part * 2] = m_run;
+        p.ws_ml[part * 2 + 1] = l_j;
       }
     }
   }
@@ -368,48 +486,43 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_bf16(AttnParams p) {
 
 }  // namespace
 
-// The prompt path uses kPromptWaves wavefronts; a single block of fewer columns gets a
-// workgroup of just enough wavefronts (2, 4 or 8), so that several workgroups share a
-// compute unit and the kernel stays bound by HBM.
-constexpr int kPromptWaves = 8;
-
-int prefill_bf16_block_steps(int G) { return prefill_block_steps(G, kPromptWaves); }
+int prefill_bf16_block_steps(int G, int waves) { return prefill_block_steps(G, waves); }
 
 namespace {
 template <int NW>
 hipError_t launch_prefill_nw(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
+  // Eight wavefronts (one workgroup per compute unit at D = 128): eight buffers, two groups per
+  // barrier, an iteration's first operands read in the one before.  Fewer: four buffers, so that
+  // at least two workgroups share a compute unit.
+  constexpr int NBUF = NW == 8 ? 8 : 4;
   const int QB = prefill_block_steps(p.G, NW);
-  const int nblocks = (p.queries + QB - 1) / QB;
+  if (QB < 1) return hipErrorInvalidConfiguration;
+  const int64_t nblocks = (p.queries + QB - 1) / QB;
   // the kernel renumbers its workgroups with 32-bit arithmetic on the linear index
-  if ((int64_t)nblocks * grid_splits * p.Hkv * batch > INT32_MAX) return hipErrorInvalidConfiguration;
-  const dim3 grid(nblocks * grid_splits, p.Hkv, batch);
+  if (nblocks * grid_splits * p.Hkv * batch > INT32_MAX) return hipErrorInvalidConfiguration;
+  const dim3 grid((unsigned)(nblocks * grid_splits), p.Hkv, batch);
   const dim3 block(64 * NW);
-  const size_t lds = 2 * (size_t)(2 * (D / 32) + D / 16) * 1024;
-  const bool stream_once = !p.direct;  // split path: each workgroup's range is read by nobody else
+  const size_t lds = NBUF * (size_t)(D / 8) * 1024;
   if (p.rope_cos) {
-    if (D == 128) {
-      return stream_once ? launch((attn_prefill_bf16<128, NW, true, true>), grid, block, lds, stream, p)
-                         : launch((attn_prefill_bf16<128, NW, true, false>), grid, block, lds, stream, p);
-    }
-    return stream_once ? launch((attn_prefill_bf16<64, NW, true, true>), grid, block, lds, stream, p)
-                       : launch((attn_prefill_bf16<64, NW, true, false>), grid, block, lds, stream, p);
+    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, true>), grid, block, lds, stream, p);
+    return launch((attn_prefill_bf16<64, NW, NBUF, true>), grid, block, lds, stream, p);
   }
-  if (D == 128) {
-    return stream_once ? launch((attn_prefill_bf16<128, NW, false, true>), grid, block, lds, stream, p)
-                       : launch((attn_prefill_bf16<128, NW, false, false>), grid, block, lds, stream, p);
-  }
-  return stream_once ? launch((attn_prefill_bf16<64, NW, false, true>), grid, block, lds, stream, p)
-                     : launch((attn_prefill_bf16<64, NW, false, false>), grid, block, lds, stream, p);
+  if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false>), grid, block, lds, stream, p);
+  return launch((attn_prefill_bf16<64, NW, NBUF, false>), grid, block, lds, stream, p);
 }
 }  // namespace
 
-// grid_splits: splits of the key range to launch (1 = every workgroup walks its
-// block's whole range and writes `out`; p.tps_log2 must then be 30).
-hipError_t launch_prefill_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
-  const int columns = p.queries * p.G;
-  if (columns <= 32) return launch_prefill_nw<2>(p, batch, D, grid_splits, stream);
-  if (columns <= 64) return launch_prefill_nw<4>(p, batch, D, grid_splits, stream);
-  return launch_prefill_nw<kPromptWaves>(p, batch, D, grid_splits, stream);
+// waves: 1, 2, 4 or 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
+// grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
+// range and writes `out`; p.tps_log2 must then be 30).
+hipError_t launch_prefill_bf16(const AttnParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {
+  switch (waves) {
+    case 1: return launch_prefill_nw<1>(p, batch, D, grid_splits, stream);
+    case 2: return launch_prefill_nw<2>(p, batch, D, grid_splits, stream);
+    case 4: return launch_prefill_nw<4>(p, batch, D, grid_splits, stream);
+    case 8: return launch_prefill_nw<8>(p, batch, D, grid_splits, stream);
+    default: return hipErrorInvalidConfiguration;
+  }
 }
 
 }  // namespace tempo

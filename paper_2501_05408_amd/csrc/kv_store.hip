@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void kv_append_bf16(StoreParams p, const uint1
   const int head = (idx / D) % p.Hkv;
   const int c = (idx / (D * p.Hkv)) % p.count;
   const int b = idx / (D * p.Hkv * p.count);
-  if (p.row0 + c >= rows_of(p, b)) return;
+  if (c >= rows_of(p, b)) return;
   const int t = step_of(p, b) + c;
   const int Z = 1 << p.z_log2;
   const int tile = t >> p.z_log2, slot = t & (Z - 1);
@@ -62,14 +62,15 @@ __global__ __launch_bounds__(256) void kv_append_bf16(StoreParams p, const uint1
   }
 }
 
-// bf16, whole 32-slot groups: one wavefront per (sequence, head, group) turns 32
-// consecutive rows of k_new / v_new into the group's operand-major image and writes
-// it as full 1 KiB units.  Keys: every 16-byte piece of a unit is 8 consecutive dims
-// of one row, so it is a gather of 16-byte pieces.  Values: a 16-byte piece holds one
-// dim of 8 slots, so the 32 x D tile goes through LDS (row stride D + 2 elements,
-// which spreads the four rows a column tile's lanes read over different banks).
-// p.t is the first step of the first group (a multiple of 32), p.count the number of
-// groups times 32; rows of sequence b start at k_new[b][0].
+// bf16, by 32-slot groups: one wavefront per (sequence, head, group) turns up to 32
+// consecutive rows of k_new / v_new into the group's operand-major image and writes it as
+// 1 KiB units.  Keys: every 16-byte piece of a unit is 8 consecutive dims of one row, so it
+// is a gather of 16-byte pieces.  Values: a 16-byte piece holds one dim of 8 slots, so the
+// 32 x D tile goes through LDS (row stride D + 2 elements, which spreads the four rows a
+// column tile's lanes read over different banks).  The call's first and last group may be
+// partly covered: their other slots keep what the pool holds (values are read, merged and
+// written back; no other workgroup of the launch touches the group, see launch_append), so
+// one launch writes a prompt that starts or ends anywhere (three launches before).
 template <int D>
 __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const uint16_t* __restrict__ k_new,
                                                             const uint16_t* __restrict__ v_new) {
@@ -77,22 +78,25 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
   __shared__ uint16_t tile[32 * LD];
   const int lane = threadIdx.x;
   const int g = blockIdx.x, head = blockIdx.y, b = blockIdx.z;
-  // slots of this group that sequence b writes: all 32, or fewer where its rows end inside the group
-  const int rows_b = rows_of(p, b);
-  const int valid = rows_b == INT32_MAX ? 32 : rows_b - (p.row0 + 32 * g);
-  if (valid <= 0) return;  // uniform over the workgroup
-  const int t0 = p.t + 32 * g;  // first step of this group
+  // slots of this group that sequence b writes: lo .. hi-1
+  const int rows_b = rows_of(p, b) < p.count ? rows_of(p, b) : p.count;
+  const int t0 = ((p.t >> 5) + g) << 5;                 // first step of this group
+  const int first_row = t0 - p.t;                       // source row of slot 0 (negative: before the call)
+  const int lo = first_row < 0 ? -first_row : 0;
+  const int hi = rows_b - first_row < 32 ? rows_b - first_row : 32;
+  if (hi <= lo) return;  // uniform over the workgroup
   const int Z = 1 << p.z_log2;
   const int phys = clamp_block(p.block_table[(int64_t)b * p.max_blocks_per_seq + ((t0 >> p.z_log2) & p.tile_mask)],
                                p.num_blocks);
   const int64_t base = (((int64_t)phys * p.Hkv + head) << p.z_log2) * D + (int64_t)(t0 & (Z - 1)) * D;
-  const int64_t row0 = ((int64_t)b * p.src_steps + 32 * g) * p.Hkv + head;  // source row of slot 0 (rows are Hkv apart)
+  const int64_t row0 = ((int64_t)b * p.src_steps + first_row) * p.Hkv + head;  // source row of slot 0 (rows are Hkv apart)
 
   // values -> LDS, 16 bytes per lane and load
 #pragma unroll
   for (int i = 0; i < (32 * D / 8) / 64; ++i) {
     const int piece = lane + 64 * i, row = piece / (D / 8), d8 = (piece % (D / 8)) * 8;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(v_new + (row0 + (int64_t)row * p.Hkv) * D + d8);
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (row >= lo && row < hi) v = *reinterpret_cast<const u32x4*>(v_new + (row0 + (int64_t)row * p.Hkv) * D + d8);
     uint32_t* dst = reinterpret_cast<uint32_t*>(tile + row * LD + d8);  // 4-byte aligned: LD and d8 are even
     dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
   }
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
     for (int tl = 0; tl < 2; ++tl) {
 #pragma unroll
       for (int s = 0; s < KS / 2; ++s) {
-        if (16 * tl + row < valid) {
+        if (16 * tl + row >= lo && 16 * tl + row < hi) {
           const uint16_t* src = k_new + (row0 + (int64_t)(16 * tl + row) * p.Hkv) * D + 32 * s + 8 * c;
           u32x4 lo = *reinterpret_cast<const u32x4*>(src);            // dims 32s + 8c .. +7
           u32x4 hi = *reinterpret_cast<const u32x4*>(src + D / 2);    // the same dims + D/2: unit s + KS/2
@@ -132,12 +136,12 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
       u32x4 o;
       o.x = e[0] | (e[1] << 16); o.y = e[2] | (e[3] << 16);
       o.z = e[4] | (e[5] << 16); o.w = e[6] | (e[7] << 16);
-      if (valid < 32) {  // the rows end inside this group: keep what the pool holds in the other slots
+      if (lo > 0 || hi < 32) {  // partly covered: keep what the pool holds in the other slots
         uint32_t m[8];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          m[r] = (4 * c + r) < valid ? 0xFFFFu : 0u;
-          m[4 + r] = (16 + 4 * c + r) < valid ? 0xFFFFu : 0u;
+          m[r] = (4 * c + r) >= lo && (4 * c + r) < hi ? 0xFFFFu : 0u;
+          m[4 + r] = (16 + 4 * c + r) >= lo && (16 + 4 * c + r) < hi ? 0xFFFFu : 0u;
         }
         const u32x4 old = vp[dt * 64];
         const uint32_t mx = m[0] | (m[1] << 16), my = m[2] | (m[3] << 16);
@@ -161,7 +165,7 @@ __global__ __launch_bounds__(256) void kv_append_f32(StoreParams p, const float*
   const int head = (idx / (D / 4)) % p.Hkv;
   const int c = (idx / ((D / 4) * p.Hkv)) % p.count;
   const int b = idx / ((D / 4) * p.Hkv * p.count);
-  if (p.row0 + c >= rows_of(p, b)) return;
+  if (c >= rows_of(p, b)) return;
   const int t = step_of(p, b) + c;
   const int Z = 1 << p.z_log2;
   const int tile = t >> p.z_log2, slot = t & (Z - 1);
@@ -200,63 +204,52 @@ __global__ __launch_bounds__(256) void kv_gather(StoreParams p, T* __restrict__ 
   }
 }
 
+hipError_t launch_elements_bf16(const StoreParams& p, const uint16_t* k, const uint16_t* v, int D, hipStream_t stream) {
+  const int threads = 256;
+  const int total = p.batch * p.count * p.Hkv * D;
+  const dim3 grid((total + threads - 1) / threads);
+  if (D == 128) return launch(kv_append_bf16<128>, grid, dim3(threads), 0, stream, p, k, v);
+  return launch(kv_append_bf16<64>, grid, dim3(threads), 0, stream, p, k, v);
+}
+
 }  // namespace
 
 hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_new, int D,
                          int dtype, hipStream_t stream) {
-  // bf16, uniform first step, at least one whole 32-slot group: the groups go through
-  // the group kernel, the rows before the first and after the last whole group
-  // through the element-wise kernel.
+  // bf16, uniform first step, 32 rows or more: the group kernel (4096 rows of 16 sequences in 8
+  // heads: 86 us, element-wise 315 us).  A group takes one workgroup however few of its rows the
+  // call holds; from a group's worth of rows on that is the faster way.
   if (dtype == TEMPO_BF16 && !p.t_per_seq && p.count >= 32) {
-    const int g0 = (p.t + 31) >> 5, g1 = ((p.t + p.count) >> 5) - 1;  // whole groups g0 .. g1
-    if (g1 >= g0) {
-      const uint16_t* k = static_cast<const uint16_t*>(k_new);
-      const uint16_t* v = static_cast<const uint16_t*>(v_new);
-      const int64_t row_elems = (int64_t)p.Hkv * D;
-      const int head_rows = 32 * g0 - p.t, tail_first = 32 * (g1 + 1), tail_rows = p.t + p.count - tail_first;
-      hipError_t e = hipSuccess;
-      if (head_rows > 0) {
-        StoreParams h = p;
-        h.count = head_rows;  // row0 stays: these are the call's first rows
-        e = launch_append(h, k, v, D, dtype, stream);
-        if (e != hipSuccess) return e;
-      }
-      StoreParams m = p;
-      m.t = 32 * g0;
-      m.count = 32 * (g1 - g0 + 1);
-      m.row0 = p.row0 + head_rows;
-      const dim3 grid(g1 - g0 + 1, p.Hkv, p.batch);
-      const uint16_t* km = k + head_rows * row_elems;
-      const uint16_t* vm = v + head_rows * row_elems;
-      e = D == 128 ? launch(kv_append_groups_bf16<128>, grid, dim3(64), 0, stream, m, km, vm)
-                   : launch(kv_append_groups_bf16<64>, grid, dim3(64), 0, stream, m, km, vm);
+    const int groups = ((p.t + p.count - 1) >> 5) - (p.t >> 5) + 1;
+    // A ring whose every slot is written, from the middle of a group on: the last group lies in the
+    // same slots as the first.  Its rows go in a launch behind the others.
+    const int64_t ring_slots = p.tile_mask == INT32_MAX ? INT64_MAX : ((int64_t)p.tile_mask + 1) << p.z_log2;
+    if ((int64_t)groups * 32 > ring_slots) {
+      StoreParams rest = p;
+      rest.count = p.count - 32;
+      hipError_t e = launch_append(rest, k_new, v_new, D, dtype, stream);
       if (e != hipSuccess) return e;
-      if (tail_rows > 0) {
-        StoreParams tl = p;
-        tl.t = tail_first;
-        tl.count = tail_rows;
-        tl.row0 = p.row0 + (tail_first - p.t);
-        e = launch_append(tl, k + (tail_first - p.t) * row_elems, v + (tail_first - p.t) * row_elems, D, dtype, stream);
-      }
-      return e;
+      rest.t = p.t + rest.count;
+      rest.count = 32;
+      const int64_t skip = (int64_t)(p.count - 32) * p.Hkv * D;
+      return launch_elements_bf16(rest, static_cast<const uint16_t*>(k_new) + skip,
+                                  static_cast<const uint16_t*>(v_new) + skip, D, stream);
     }
-  }
-  const int threads = 256;
-  if (dtype == TEMPO_BF16) {
-    const int total = p.batch * p.count * p.Hkv * D;
-    const dim3 grid((total + threads - 1) / threads);
+    const dim3 grid(groups, p.Hkv, p.batch);
     const uint16_t* k = static_cast<const uint16_t*>(k_new);
     const uint16_t* v = static_cast<const uint16_t*>(v_new);
-    if (D == 128) return launch(kv_append_bf16<128>, grid, dim3(threads), 0, stream, p, k, v);
-    else return launch(kv_append_bf16<64>, grid, dim3(threads), 0, stream, p, k, v);
-  } else {
-    const int total = p.batch * p.count * p.Hkv * (D / 4);
-    const dim3 grid((total + threads - 1) / threads);
-    const float* k = static_cast<const float*>(k_new);
-    const float* v = static_cast<const float*>(v_new);
-    if (D == 128) return launch(kv_append_f32<128>, grid, dim3(threads), 0, stream, p, k, v);
-    else return launch(kv_append_f32<64>, grid, dim3(threads), 0, stream, p, k, v);
+    if (D == 128) return launch(kv_append_groups_bf16<128>, grid, dim3(64), 0, stream, p, k, v);
+    return launch(kv_append_groups_bf16<64>, grid, dim3(64), 0, stream, p, k, v);
   }
+  if (dtype == TEMPO_BF16)
+    return launch_elements_bf16(p, static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), D, stream);
+  const int threads = 256;
+  const int total = p.batch * p.count * p.Hkv * (D / 4);
+  const dim3 grid((total + threads - 1) / threads);
+  const float* k = static_cast<const float*>(k_new);
+  const float* v = static_cast<const float*>(v_new);
+  if (D == 128) return launch(kv_append_f32<128>, grid, dim3(threads), 0, stream, p, k, v);
+  return launch(kv_append_f32<64>, grid, dim3(threads), 0, stream, p, k, v);
 }
 
 hipError_t launch_gather(const StoreParams& p, void* k_out, void* v_out, int D, int dtype, int j0,

@@ -294,6 +294,7 @@ AttnParams attn_params(const tempo_kv* kv, const void* q, void* out, int32_t Hq,
   p.num_splits = plan->num_splits;
   p.queries = queries;
   p.io_steps = queries;
+  p.block_steps = 0;
   p.pad_t = pad_t;
   p.direct = 0;
   p.scale_log2e = scale * 1.44269504088896340736f;
@@ -317,7 +318,6 @@ StoreParams store_params(const tempo_kv* kv, int32_t batch, int32_t t, const int
   p.count = count;
   p.src_steps = count;
   p.count_per_seq = nullptr;
-  p.row0 = 0;
   p.rope_cos = nullptr;
   p.rope_sin = nullptr;
   return p;
@@ -375,7 +375,7 @@ int do_partial(const tempo_kv* kv, const void* q, const void* k_new, const void*
   }
   const int32_t gs = grid_splits(plan, t, t_per_seq, window, queries, pad_t);
   if (kv->dtype == TEMPO_BF16 && queries * p.G > kNarrowColumns)  // a wide block: the LDS-staged kernel, key range split as planned
-    return launch_status(launch_prefill_bf16(p, batch, kv->head_dim, gs, stream), "attn_block_partial");
+    return launch_status(launch_block_bf16(p, batch, kv->head_dim, gs, stream), "attn_block_partial");
   const hipError_t e = kv->dtype == TEMPO_BF16
                            ? launch_partial_bf16(p, batch, kv->head_dim, gs, plan->waves, stream)
                            : launch_partial_f32(p, batch, kv->head_dim, gs, plan->waves, stream);
@@ -834,14 +834,103 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
                 workspace_bytes, stream, 1, rope);
 }
 
-// Does a prompt of `count` steps go through the prompt kernel (one launch after the
-// block-store write) rather than block by block?  It does when its query blocks fill
-// the part; a ring store and fp32 always go block by block.
-bool prefill_in_one_launch(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t count) {
-  if (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0) return false;
-  if ((int64_t)batch * count * kv->num_kv_heads * kv->head_dim > INT32_MAX) return false;
-  const int32_t qb = prefill_bf16_block_steps(Hq / kv->num_kv_heads);
-  return (int64_t)((count + qb - 1) / qb) * kv->num_kv_heads * batch >= kComputeUnits;
+// How the prompt kernel takes a prompt: wavefronts of 32 columns per workgroup, and splits of
+// a block's key range (tps_log2 = 30, splits = 1: none).
+struct PromptPlan {
+  int waves, tps_log2, splits;
+};
+
+// A time model of the launch, in nanoseconds, with constants measured on MI355X (D = 128, scaled
+// by the head dim).  A compute unit holds one workgroup of 8 wavefronts, or two of fewer (64 KiB
+// of LDS each); a workgroup spends about 5 us before its first and after its last group, and an
+// iteration over a 32-slot group takes 0.55 us with one wavefront on a SIMD and 0.78 us with two.
+// So wide workgroups win once they fill the part; narrow ones, and a key range cut into splits
+// (with a combine launch of about 5 us, and partials of (D + 2) * 4 bytes per column and
+// split), when the query columns alone do not.
+bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
+  const int32_t QB = prefill_bf16_block_steps(G, 4);
+  return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
+}
+
+PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
+                       size_t workspace_bytes) {
+  const int G = Hq / kv->num_kv_heads;
+  const double scale = kv->head_dim / 128.0;
+  PromptPlan best = {8, 30, 1};
+  double best_ns = -1.0;
+  const bool may_split = !prompt_fills_part(kv, batch, G, count);
+  for (int waves = 8; waves >= 1; waves /= 2) {
+    const int32_t QB = prefill_bf16_block_steps(G, waves);
+    if (QB < 1) break;
+    const int64_t blocks = (count + QB - 1) / QB, pairs = (int64_t)batch * kv->num_kv_heads;
+    const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
+    const int resident = waves == 8 ? 1 : 2;
+    for (int k = 30; k >= 7; k = k == 30 ? 13 : k - 1) {
+      const int splits = k == 30 ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
+      if (k != 30 && !may_split) break;
+      if (k != 30 && splits == 1) continue;
+      if (splits > 8) break;  // the combine reads up to 8 splits in one batch
+      const int64_t rows = (int64_t)batch * count * Hq;
+      if (k != 30 && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
+      const int64_t workgroups = blocks * pairs * splits;
+      const int64_t rounds = (workgroups + resident * kComputeUnits - 1) / (resident * kComputeUnits);
+      const bool shared_simd = waves == 8 || (waves == 4 && workgroups > kComputeUnits);
+      const int64_t span = k == 30 || keys < ((int64_t)1 << k) ? keys : (int64_t)1 << k;
+      // a causal prompt's blocks are half the longest on average: beyond the first round that counts
+      const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;
+      double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (shared_simd ? 780.0 : 550.0) * scale);
+      if (splits > 1) ns += 5000.0 + 2.0 * (double)rows * splits * kv->head_dim * 4 / 4000.0;
+      if (best_ns < 0.0 || ns < 0.97 * best_ns) {  // the wider workgroup and the fewer splits unless clearly slower
+        best_ns = ns;
+        best = {waves, k, splits};
+      }
+    }
+  }
+  return best;
+}
+
+// Does the prompt kernel take calls on this store?  (bf16, and an index range it can count.)
+bool prompt_kernel_serves(const tempo_kv* kv, int32_t batch, int32_t count) {
+  return kv->dtype == TEMPO_BF16 && (int64_t)batch * count * kv->num_kv_heads * kv->head_dim <= INT32_MAX;
+}
+
+// A ring store holds a limited range: the most steps from t on that one chunk may write and
+// answer (every tile of the chunk's ranges resident), ending on a 32-slot group if that leaves
+// at least `block` steps, which are known to fit.
+int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, int32_t block) {
+  int32_t C = left;
+  if (kv->ring_blocks) {
+    const int64_t slots = (int64_t)kv->ring_blocks * kv->block_size;
+    // check_ring_covers: ceil((window + C - 2) / Z) + 1 <= ring_blocks, or the whole history fits
+    const int64_t most = t + (int64_t)left <= slots ? left : slots - kv->block_size - window + 2;
+    C = most < left ? (int32_t)(most < 1 ? 1 : most) : left;
+    if (C < block) C = left < block ? left : block;
+    const int32_t aligned = ((t + C) & ~31) - t;
+    if (C < left && aligned >= block) C = aligned;
+  }
+  return C;
+}
+
+// One launch of the prompt kernel (and the combine, if it splits key ranges) for `count` steps
+// from t on, already in the store.  q, out: the caller's, `io_steps` steps per sequence.
+int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, int32_t Hq, int32_t t, int32_t count,
+                  int32_t io_steps, const int32_t* count_per_seq, int32_t window, float scale, void* workspace,
+                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope) {
+  // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
+  const PromptPlan plan = plan_prompt(kv, batch, Hq, t, count, window, count_per_seq ? 0 : workspace_bytes);
+  const tempo_plan cut = {1 << plan.tps_log2, plan.splits, 8};
+  AttnParams p = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
+  p.io_steps = io_steps;
+  p.direct = plan.splits == 1;
+  p.block_steps = plan.splits > 1 ? prefill_bf16_block_steps(p.G, plan.waves) : 0;
+  p.count_per_seq = count_per_seq;
+  if (rope) {
+    p.rope_cos = rope->cos;
+    p.rope_sin = rope->sin;
+  }
+  int rc = launch_status(launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s), "attn_prefill");
+  if (rc != TEMPO_OK || plan.splits == 1) return rc;
+  return launch_status(launch_combine(p, batch, kv->head_dim, kv->dtype, s), "attn_prefill_combine");
 }
 
 // Prompt processing: `count` steps per sequence, written and answered in blocks of
@@ -874,35 +963,33 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     if (kv->ring_blocks && (int64_t)C > (int64_t)kv->ring_blocks * kv->block_size) return TEMPO_ERR_RANGE;
   }
 
-  // Enough query blocks to fill the part: write the whole prompt, then one launch of
-  // the prompt kernel (each workgroup walks its block's whole key range; no partials).
   // per-sequence prompt lengths and the rotary producer exist in the prompt kernel only
-  if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 ||
-                                  (int64_t)batch * count * kv->num_kv_heads * kv->head_dim > INT32_MAX))
-    return TEMPO_ERR_SHAPE;
+  if ((count_per_seq || rope) && (kv->ring_blocks != 0 || !prompt_kernel_serves(kv, batch, count))) return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
-  if (count_per_seq || rope || prefill_in_one_launch(kv, batch, Hq, count)) {
-    StoreParams sp = store_params(kv, batch, t, nullptr, count);
-    sp.count_per_seq = count_per_seq;
-    if (rope) {
-      sp.rope_cos = rope->cos;
-      sp.rope_sin = rope->sin;
+  // bf16: write the prompt, then the prompt kernel; on a ring store in chunks that it can hold.
+  if (prompt_kernel_serves(kv, batch, count)) {
+    for (int32_t c0 = 0; c0 < count;) {
+      const int32_t C = ring_chunk(kv, t + c0, count - c0, window, block);
+      const size_t kv_at = (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz, q_at = (size_t)c0 * Hq * kv->head_dim * esz;
+      StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
+      sp.src_steps = count;
+      sp.count_per_seq = count_per_seq;
+      if (rope) {
+        sp.rope_cos = rope->cos;
+        sp.rope_sin = rope->sin;
+      }
+      if ((rc = launch_status(launch_append(sp, static_cast<const char*>(k_new) + kv_at, static_cast<const char*>(v_new) + kv_at,
+                                            kv->head_dim, kv->dtype, s), "kv_append_block")) != TEMPO_OK)
+        return rc;
+      if ((rc = attend_prompt(kv, static_cast<const char*>(q) + q_at, static_cast<char*>(out) + q_at, batch, Hq, t + c0, C,
+                              count, count_per_seq, window, scale, workspace, workspace_bytes, s, rope)) != TEMPO_OK)
+        return rc;
+      c0 += C;
     }
-    if ((rc = launch_status(launch_append(sp, k_new, v_new, kv->head_dim, kv->dtype, s), "kv_append_block")) != TEMPO_OK)
-      return rc;
-    const tempo_plan whole = {1 << 30, 1, 8};  // no split of the key range: every workgroup walks its block's own
-    AttnParams p = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &whole, workspace, batch, count);
-    p.direct = 1;
-    p.count_per_seq = count_per_seq;
-    if (rope) {
-      p.rope_cos = rope->cos;
-      p.rope_sin = rope->sin;
-    }
-    return launch_status(launch_prefill_bf16(p, batch, kv->head_dim, 1, s), "attn_prefill");
+    return TEMPO_OK;
   }
 
-  // Otherwise block by block: split-KV partial attention keeps the part busy when the
-  // blocks are few and the history is long.
+  // Otherwise (fp32) block by block.
   for (int32_t c0 = 0; c0 < count; c0 += block) {
     const int32_t C = count - c0 < block ? count - c0 : block;
     tempo_plan plan;
@@ -964,8 +1051,9 @@ int tempo_rope_prefill_window(const tempo_kv* kv, const tempo_rope* rope, const 
 
 int tempo_prefill_launches(const tempo_kv* kv, int32_t batch, int32_t num_q_heads, int32_t count) {
   if (check_layout(kv) != TEMPO_OK || check_heads(kv, batch, num_q_heads) != TEMPO_OK || count < 1) return 0;
-  if (prefill_in_one_launch(kv, batch, num_q_heads, count)) return 2;
-  const int32_t block = kMaxColumns / (num_q_heads / kv->num_kv_heads);
+  const int32_t G = num_q_heads / kv->num_kv_heads, block = kMaxColumns / G;
+  if (kv->ring_blocks == 0 && prompt_kernel_serves(kv, batch, count))
+    return prompt_fills_part(kv, batch, G, count) ? 2 : 3;  // then no key range is split
   return 3 * ((count + block - 1) / block);
 }
 

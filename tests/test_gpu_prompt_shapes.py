@@ -1,0 +1,91 @@
+"""GPU parity of prompts over the sizes at which the prompt kernel's launch changes shape (1, 2, 4 or 8
+wavefronts of 32 columns per workgroup, split key ranges, ring stores answered in chunks), against the
+fp64 CPU oracle; and of block-store writes that begin or end inside a 32-slot group, bit for bit.
+Tolerances are those of test_gpu_parity.py.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tempo_oracle as oracle
+from paper_2501_05408_amd import tempo as T
+from paper_2501_05408_amd.store import BlockStore
+
+from test_gpu_parity import DEV, assert_close, dev, host_inputs, np64, random_table
+
+pytestmark = pytest.mark.gpu
+
+
+def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70):
+    Hq, steps = Hkv * G, t + count
+    q, K, V = host_inputs(seed, B, steps, Hq, Hkv, D, dtype)
+    if ring:
+        block = 128 // G
+        ring_blocks = T.tempo_ring_blocks(window, Z, min(count, block))
+        table, nb = random_table(seed, B, ring_blocks)
+        st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, dtype, num_blocks=nb, block_table=table, fill="nan",
+                        ring_blocks=ring_blocks)
+    else:
+        table, nb = random_table(seed, B, (steps - 1) // Z + 1)
+        st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, dtype, num_blocks=nb, block_table=table, fill="nan")
+    Kd, Vd = dev(K, dtype), dev(V, dtype)
+    at = 0
+    while at < t:                                        # the history, in pieces a ring store accepts
+        n = min(t - at, ring_blocks * Z) if ring else t
+        st.append_block(Kd[:, at:at + n].contiguous(), Vd[:, at:at + n].contiguous(), at, n)
+        at += n
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
+    out = torch.empty_like(qd)
+    st.prefill_attend(qd, Kd[:, t:].contiguous(), Vd[:, t:].contiguous(), out, t, count, window)
+    got = np64(out)
+    K64, V64 = K.astype(np.float64), V.astype(np.float64)
+    picks = sorted({0, 1, count // 2, count - 2, count - 1} | set(range(0, count, max(1, count // 40))))
+    for c in [c for c in picks if 0 <= c < count]:
+        ref = oracle.attend(q[t + c].astype(np.float64), K64, V64, t + c, window, 1.0 / np.sqrt(D))
+        assert_close(got[:, c], ref, dtype, f"prompt step {t + c} of {t}..{steps - 1} G={G} D={D} w={window} ring={ring}")
+    # what the store must hold now: the last steps of a ring, everything of a linear store
+    first = max(0, steps - ring_blocks * Z) if ring else 0
+    kg, vg = st.gather(first, steps - first)
+    assert torch.equal(kg, Kd[:, first:steps]) and torch.equal(vg, Vd[:, first:steps])
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,t,count,window", [
+    (1, 8, 4, 64, 0, 499, 0), (1, 2, 3, 128, 1500, 37, 0), (1, 1, 8, 128, 700, 65, 300), (2, 4, 3, 128, 5, 700, 0),
+    (1, 1, 128, 64, 40, 9, 0), (1, 2, 40, 128, 31, 33, 0), (2, 1, 20, 128, 0, 64, 31), (1, 1, 1, 128, 3000, 1, 0),
+    (1, 1, 1, 64, 2047, 33, 0), (1, 2, 3, 128, 1023, 43, 1024), (4, 8, 3, 128, 0, 341, 0), (16, 8, 3, 128, 64, 171, 0)])
+def test_prompt_shapes(B, Hkv, G, D, t, count, window):
+    run_prompt(B, Hkv, G, D, 32, t, count, window, False, T.TEMPO_BF16)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window", [
+    (2, 2, 3, 128, 32, 0, 700, 100), (1, 4, 4, 64, 64, 0, 333, 33), (3, 1, 8, 128, 32, 77, 400, 64),
+    (1, 2, 1, 64, 32, 1000, 129, 1), (1, 2, 3, 128, 256, 0, 900, 512), (2, 1, 3, 128, 256, 300, 513, 512)])
+def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window):
+    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16)
+
+
+@pytest.mark.parametrize("t,count", [(0, 32), (1, 32), (31, 33), (5, 59), (33, 95), (17, 64), (40, 200)])
+def test_append_block_edges(t, count):
+    """Writes that begin and end inside groups keep every other slot of those groups as it was."""
+    B, Hkv, D, Z, steps = 2, 3, 128, 64, 256
+    _, K, V = host_inputs(71, B, steps, Hkv, Hkv, D, T.TEMPO_BF16)
+    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
+    st = BlockStore(B, Hkv, Hkv, D, Z, steps - 1, T.TEMPO_BF16)
+    st.append_block(Kd, Vd, 0, steps)
+    k2, v2 = -Kd[:, t:t + count].contiguous(), -Vd[:, t:t + count].contiguous()
+    st.append_block(k2, v2, t, count)
+    want_k, want_v = Kd.clone(), Vd.clone()
+    want_k[:, t:t + count], want_v[:, t:t + count] = k2, v2
+    kg, vg = st.gather(0, steps)
+    assert torch.equal(kg, want_k) and torch.equal(vg, want_v)
+
+
+def test_append_block_that_fills_a_ring_from_inside_a_group():
+    B, Hkv, D, Z, R, t = 2, 2, 64, 32, 4, 45
+    count = R * Z
+    _, K, V = host_inputs(72, B, t + count, Hkv, Hkv, D, T.TEMPO_BF16)
+    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
+    st = BlockStore(B, Hkv, Hkv, D, Z, 10 ** 6, T.TEMPO_BF16, ring_blocks=R)
+    st.append_block(Kd[:, t:].contiguous(), Vd[:, t:].contiguous(), t, count)
+    kg, vg = st.gather(t, count)
+    assert torch.equal(kg, Kd[:, t:]) and torch.equal(vg, Vd[:, t:])
