@@ -154,9 +154,10 @@ double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int b
 // assumes and it is unevenly spread, so their splits are capped at 1024 keys to
 // keep the long sequences from becoming single long-running workgroups.
 void make_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t_max, int32_t window,
-               bool ragged, tempo_plan* plan) {
-  // bf16 shares one key/value read across the query group; fp32 launches per query head.
-  const int64_t pairs = (int64_t)batch * (kv->dtype == TEMPO_BF16 ? kv->num_kv_heads : Hq);
+               bool ragged, int32_t queries, tempo_plan* plan) {
+  // one workgroup serves a query group; fp32 takes 16 (step, head) columns per workgroup
+  const int64_t columns = (int64_t)queries * (Hq / kv->num_kv_heads);
+  const int64_t pairs = (int64_t)batch * kv->num_kv_heads * (kv->dtype == TEMPO_F32 ? (columns + 15) / 16 : 1);
   const int64_t len = (window > 0 && window < (int64_t)t_max + 1) ? window : (int64_t)t_max + 1;
   const int bytes_per_key = 2 * kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);  // K and V of one head
   const int k_max = ragged ? 10 : 30;
@@ -397,7 +398,7 @@ int do_combine(const tempo_kv* kv, void* out, int32_t batch, int32_t Hq, int32_t
 // and wavefront) fits the LDS a workgroup may ask for.
 void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window,
                      bool ragged, int32_t queries, tempo_plan* plan) {
-  make_plan(kv, batch, Hq, last_step(t, queries), union_window(window, queries), ragged, plan);
+  make_plan(kv, batch, Hq, last_step(t, queries), union_window(window, queries), ragged, queries, plan);
   if (kv->dtype != TEMPO_BF16) return;
   const int columns = queries * (Hq / kv->num_kv_heads);
   if (columns > kNarrowColumns) {
@@ -889,9 +890,31 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
   return best;
 }
 
-// Does the prompt kernel take calls on this store?  (bf16, and an index range it can count.)
-bool prompt_kernel_serves(const tempo_kv* kv, int32_t batch, int32_t count) {
-  return kv->dtype == TEMPO_BF16 && (int64_t)batch * count * kv->num_kv_heads * kv->head_dim <= INT32_MAX;
+// Does one launch answer all steps of a prompt (of a ring store's chunk)?  It does unless the call
+// is too large for the index range of its launches.
+bool prompt_in_one_launch(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t count) {
+  const int32_t heads = kv->dtype == TEMPO_BF16 ? kv->num_kv_heads : Hq;
+  return (int64_t)batch * count * heads * kv->head_dim <= INT32_MAX;
+}
+
+// fp32: tiles of 16 (step, head) columns, the keys of a tile spread over 8 wavefronts.  A tile's
+// group of 16 keys costs about 1 us at D = 128; the key range is split (and combined, 5 us) only
+// if the tiles leave most of the part idle and a wavefront would walk more than 8 groups.
+PromptPlan plan_prompt_f32(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
+                           size_t workspace_bytes) {
+  const int64_t columns = (int64_t)count * (Hq / kv->num_kv_heads);
+  const int64_t tiles = (columns + 15) / 16 * kv->num_kv_heads * batch, rows = (int64_t)batch * count * Hq;
+  PromptPlan plan = {8, 30, 1};
+  const int64_t keys = window > 0 && window + count < (int64_t)t + count ? (int64_t)window + count : (int64_t)t + count;
+  if (keys <= 256) plan.waves = 4;
+  for (int k = 10; k <= 20 && tiles < kComputeUnits / 2; ++k) {
+    const int splits = splits_bound(t + count - 1, union_window(window, count), k);
+    if (splits == 1) break;
+    if (splits > 8 || tiles * splits > 2 * kComputeUnits || plan_bytes(kv, rows, splits) > workspace_bytes) continue;
+    plan = {8, k, splits};
+    break;
+  }
+  return plan;
 }
 
 // A ring store holds a limited range: the most steps from t on that one chunk may write and
@@ -911,30 +934,34 @@ int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, 
   return C;
 }
 
-// One launch of the prompt kernel (and the combine, if it splits key ranges) for `count` steps
-// from t on, already in the store.  q, out: the caller's, `io_steps` steps per sequence.
+// One launch (and the combine, if it splits key ranges) for `count` steps from t on, already in
+// the store.  q, out: the caller's, `io_steps` steps per sequence.
 int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, int32_t Hq, int32_t t, int32_t count,
                   int32_t io_steps, const int32_t* count_per_seq, int32_t window, float scale, void* workspace,
                   size_t workspace_bytes, hipStream_t s, const tempo_rope* rope) {
+  const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
-  const PromptPlan plan = plan_prompt(kv, batch, Hq, t, count, window, count_per_seq ? 0 : workspace_bytes);
+  const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq ? 0 : workspace_bytes)
+                               : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
   const tempo_plan cut = {1 << plan.tps_log2, plan.splits, 8};
   AttnParams p = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
   p.io_steps = io_steps;
   p.direct = plan.splits == 1;
-  p.block_steps = plan.splits > 1 ? prefill_bf16_block_steps(p.G, plan.waves) : 0;
+  p.block_steps = bf16 && plan.splits > 1 ? prefill_bf16_block_steps(p.G, plan.waves) : 0;
   p.count_per_seq = count_per_seq;
   if (rope) {
     p.rope_cos = rope->cos;
     p.rope_sin = rope->sin;
   }
-  int rc = launch_status(launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s), "attn_prefill");
+  const hipError_t e = bf16 ? launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s)
+                            : launch_partial_f32(p, batch, kv->head_dim, plan.splits, plan.waves, s);
+  const int rc = launch_status(e, "attn_prefill");
   if (rc != TEMPO_OK || plan.splits == 1) return rc;
   return launch_status(launch_combine(p, batch, kv->head_dim, kv->dtype, s), "attn_prefill_combine");
 }
 
-// Prompt processing: `count` steps per sequence, written and answered in blocks of
-// as many steps as the column tiles hold.
+// Prompt processing: `count` steps per sequence, written and answered in one launch each, or
+// in blocks of as many steps as the column tiles hold.
 static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
             int32_t Hq, int32_t t, int32_t count, const int32_t* count_per_seq, int32_t window, float scale,
             void* workspace, size_t workspace_bytes, void* stream, const tempo_rope* rope = nullptr) {
@@ -964,10 +991,11 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   }
 
   // per-sequence prompt lengths and the rotary producer exist in the prompt kernel only
-  if ((count_per_seq || rope) && (kv->ring_blocks != 0 || !prompt_kernel_serves(kv, batch, count))) return TEMPO_ERR_SHAPE;
+  if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
+    return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
-  // bf16: write the prompt, then the prompt kernel; on a ring store in chunks that it can hold.
-  if (prompt_kernel_serves(kv, batch, count)) {
+  // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
+  if (prompt_in_one_launch(kv, batch, Hq, count)) {
     for (int32_t c0 = 0; c0 < count;) {
       const int32_t C = ring_chunk(kv, t + c0, count - c0, window, block);
       const size_t kv_at = (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz, q_at = (size_t)c0 * Hq * kv->head_dim * esz;
@@ -989,7 +1017,7 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     return TEMPO_OK;
   }
 
-  // Otherwise (fp32) block by block.
+  // A call beyond that range goes block by block.
   for (int32_t c0 = 0; c0 < count; c0 += block) {
     const int32_t C = count - c0 < block ? count - c0 : block;
     tempo_plan plan;
@@ -1052,8 +1080,8 @@ int tempo_rope_prefill_window(const tempo_kv* kv, const tempo_rope* rope, const 
 int tempo_prefill_launches(const tempo_kv* kv, int32_t batch, int32_t num_q_heads, int32_t count) {
   if (check_layout(kv) != TEMPO_OK || check_heads(kv, batch, num_q_heads) != TEMPO_OK || count < 1) return 0;
   const int32_t G = num_q_heads / kv->num_kv_heads, block = kMaxColumns / G;
-  if (kv->ring_blocks == 0 && prompt_kernel_serves(kv, batch, count))
-    return prompt_fills_part(kv, batch, G, count) ? 2 : 3;  // then no key range is split
+  if (kv->ring_blocks == 0 && prompt_in_one_launch(kv, batch, num_q_heads, count))
+    return kv->dtype == TEMPO_BF16 && prompt_fills_part(kv, batch, G, count) ? 2 : 3;  // then no key range is split
   return 3 * ((count + block - 1) / block);
 }
 

@@ -64,6 +64,40 @@ def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window):
     run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16)
 
 
+@pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
+    (1, 2, 4, 64, 64, 0, 300, 0, False), (2, 2, 3, 128, 4, 13, 70, 0, False), (1, 1, 1, 64, 8, 2500, 9, 0, False),
+    (1, 1, 20, 128, 16, 37, 30, 33, False), (1, 1, 3, 128, 16, 3000, 5, 0, False), (2, 1, 3, 64, 8, 50, 260, 40, True)])
+def test_f32_prompt_shapes(B, Hkv, G, D, Z, t, count, window, ring):
+    run_prompt(B, Hkv, G, D, Z, t, count, window, ring, T.TEMPO_F32)
+
+
+@pytest.mark.parametrize("D,G,window", [(64, 3, 0), (128, 1, 9)])
+def test_f32_values_that_are_not_finite_reach_only_the_steps_that_see_them(D, G, window):
+    """The steps of a prompt share key/value reads; an infinite value of key j may show in the
+    outputs of steps that see j, in no other step's."""
+    B, Hkv, Z, count, j = 1, 1, 16, 40, 21
+    q, K, V = host_inputs(73, B, count, G, Hkv, D, T.TEMPO_F32)
+    outs = []
+    for bad in (False, True):
+        Vx = V.copy()
+        if bad:
+            Vx[:, j, :, 3] = np.inf
+        st = BlockStore(B, G, Hkv, D, Z, count - 1, T.TEMPO_F32, fill="nan")
+        out = torch.empty((B, count, G, D), dtype=torch.float32, device=DEV)
+        st.prefill_attend(dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))), T.TEMPO_F32), dev(K, T.TEMPO_F32),
+                          dev(Vx, T.TEMPO_F32), out, 0, count, window)
+        outs.append(np64(out))
+    for t in range(count):
+        sees = j <= t and (window == 0 or j > t - window)
+        rest = [d for d in range(D) if d != 3]
+        # bound: the two runs may take the products of a group in another order (32-bit sums of <= 40 terms)
+        assert np.abs(outs[1][:, t][..., rest] - outs[0][:, t][..., rest]).max() <= 1e-5
+        if sees:
+            assert np.isposinf(outs[1][:, t][..., 3]).all()
+        else:
+            assert np.abs(outs[1][:, t] - outs[0][:, t]).max() <= 1e-5
+
+
 @pytest.mark.parametrize("t,count", [(0, 32), (1, 32), (31, 33), (5, 59), (33, 95), (17, 64), (40, 200)])
 def test_append_block_edges(t, count):
     """Writes that begin and end inside groups keep every other slot of those groups as it was."""
