@@ -86,16 +86,17 @@ __device__ inline bf16x8 softmax_weights(const float* x, float scale, float ref)
 // independent inside an iteration, so they overlap instead of alternating.  Keys
 // therefore run one group ahead of values through LDS: two key buffers (groups n + 1,
 // n + 2) and two value buffers (groups n, n + 1).
-template <int D, int NW, bool kRope>
+template <int D, int NW, bool kRope, bool kStream>
 __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
   constexpr int KU = 2 * KS;                  // 1 KiB units of one group's keys
   constexpr int UNITS = KU + DT;              // ... and of its keys and values together
   constexpr int PER_THREAD = (UNITS + NW - 1) / NW;  // units each wavefront copies per iteration (at most)
-  // Every key/value is read once and no other workgroup reads it again: non-temporal copies
-  // (the cache-policy bit the decode kernel's loads carry) keep it from displacing anything.
-  constexpr int kCachePolicy = 2;
+  // Long ranges: every key/value is read once, non-temporal copies (the cache-policy bit the decode
+  // kernel's loads carry) keep it from displacing anything.  A range of one split is short and may
+  // well be in the caches already (11 steps behind 190 keys, 9 sequences: 14.2 us cached, 14.6 us not).
+  constexpr int kCachePolicy = kStream ? 2 : 0;
   extern __shared__ u32x4 lds[];              // keys [2][KU][64] x 16 bytes, then values [2][DT][64] x 16 bytes
   u32x4* const lds_k = lds;
   u32x4* const lds_v = lds + 2 * KU * 64;
@@ -341,12 +342,21 @@ hipError_t launch_block_nw(const AttnParams& p, int batch, int D, int grid_split
   const dim3 grid(grid_splits, p.Hkv, batch);
   const dim3 block(64 * NW);
   const size_t lds = 2 * (size_t)(2 * (D / 32) + D / 16) * 1024;
+  const bool stream_once = !p.direct;
   if (p.rope_cos) {
-    if (D == 128) return launch((attn_block_bf16<128, NW, true>), grid, block, lds, stream, p);
-    return launch((attn_block_bf16<64, NW, true>), grid, block, lds, stream, p);
+    if (D == 128) {
+      return stream_once ? launch((attn_block_bf16<128, NW, true, true>), grid, block, lds, stream, p)
+                         : launch((attn_block_bf16<128, NW, true, false>), grid, block, lds, stream, p);
+    }
+    return stream_once ? launch((attn_block_bf16<64, NW, true, true>), grid, block, lds, stream, p)
+                       : launch((attn_block_bf16<64, NW, true, false>), grid, block, lds, stream, p);
   }
-  if (D == 128) return launch((attn_block_bf16<128, NW, false>), grid, block, lds, stream, p);
-  return launch((attn_block_bf16<64, NW, false>), grid, block, lds, stream, p);
+  if (D == 128) {
+    return stream_once ? launch((attn_block_bf16<128, NW, false, true>), grid, block, lds, stream, p)
+                       : launch((attn_block_bf16<128, NW, false, false>), grid, block, lds, stream, p);
+  }
+  return stream_once ? launch((attn_block_bf16<64, NW, false, true>), grid, block, lds, stream, p)
+                     : launch((attn_block_bf16<64, NW, false, false>), grid, block, lds, stream, p);
 }
 
 }  // namespace

@@ -18,7 +18,8 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
   const int b = blockIdx.y;  // blockIdx.x runs over the sequence's (query step, query head) rows
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
-  const int n = row_splits(p, t_b, blockIdx.x);
+  const SeqRange rg = seq_range(t_b, p.window, p.tps_log2, p.queries, p.pad_t);
+  const int n = rg.nchunks < p.num_splits ? rg.nchunks : p.num_splits;
   const int64_t row = (int64_t)b * gridDim.x + blockIdx.x;
   const int64_t orow = (int64_t)b * p.io_steps * p.Hq + blockIdx.x;  // rows of `out` may be strided per sequence
   const int esz = kBf16 ? 2 : 4;
@@ -26,19 +27,26 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
                                  p.num_splits, n, 1, static_cast<char*>(p.out) + orow * D * esz, smem);
 }
 
+// One float4 column of a row per thread; block_steps > 0: ranges by blocks of steps.
 template <int D, bool kBf16>
-__global__ __launch_bounds__(256) void attn_combine_few(AttnParams p, int rows) {
+__device__ __forceinline__ void combine_few(const AttnParams& p, int rows, int block_steps) {
   constexpr int C4 = D / 4;
   constexpr int U = 8;
   const int idx = blockIdx.x * 256 + threadIdx.x;
   const int row = idx / C4, c4 = idx - row * C4;
   if (row >= rows) return;
   const int b = row / (p.Hq * p.queries);
-  const int in_call = row - b * (p.Hq * p.queries);
-  const int64_t orow = (int64_t)b * p.io_steps * p.Hq + in_call;
+  const int64_t orow = (int64_t)b * p.io_steps * p.Hq + (row - b * (p.Hq * p.queries));
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
-  const int n = row_splits(p, t_b, in_call);  // 1..8
+  int t_first = t_b, steps = p.queries;
+  if (block_steps > 0) {
+    const int c0 = (row / p.Hq - b * p.queries) / block_steps * block_steps;
+    t_first += c0;
+    steps = steps - c0 < block_steps ? steps - c0 : block_steps;
+  }
+  const SeqRange rg = seq_range(t_first, p.window, p.tps_log2, steps, p.pad_t);
+  const int n = rg.nchunks < p.num_splits ? rg.nchunks : p.num_splits;  // 1..8
   const float* ml = p.ws_ml + (int64_t)row * p.num_splits * 2;
   const float* acc = p.ws_acc + (int64_t)row * p.num_splits * D + 4 * c4;
   float m[U], l[U];
@@ -78,6 +86,16 @@ __global__ __launch_bounds__(256) void attn_combine_few(AttnParams p, int rows) 
   }
 }
 
+template <int D, bool kBf16>
+__global__ __launch_bounds__(256) void attn_combine_few(AttnParams p, int rows) {
+  combine_few<D, kBf16>(p, rows, 0);
+}
+
+// A prompt: every block of p.block_steps steps has split its own key range.
+template <int D>
+__global__ __launch_bounds__(256) void attn_combine_prompt(PromptParams p, int rows) {
+  combine_few<D, true>(p, rows, p.block_steps);
+}
 }  // namespace
 
 hipError_t launch_combine(const AttnParams& p, int batch, int D, int dtype, hipStream_t stream) {
@@ -102,6 +120,15 @@ hipError_t launch_combine(const AttnParams& p, int batch, int D, int dtype, hipS
     if (D == 128) return launch((attn_combine<128, false>), grid, block, lds, stream, p);
     else return launch((attn_combine<64, false>), grid, block, lds, stream, p);
   }
+}
+
+// bf16, at most 8 splits.
+hipError_t launch_prompt_combine(const PromptParams& p, int batch, int D, hipStream_t stream) {
+  if (p.num_splits > 8) return hipErrorInvalidConfiguration;
+  const int rows = batch * p.queries * p.Hq;
+  const dim3 grid((unsigned)(((int64_t)rows * (D / 4) + 255) / 256)), block(256);
+  if (D == 128) return launch(attn_combine_prompt<128>, grid, block, 0, stream, p, rows);
+  return launch(attn_combine_prompt<64>, grid, block, 0, stream, p, rows);
 }
 
 }  // namespace tempo

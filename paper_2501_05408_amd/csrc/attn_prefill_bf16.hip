@@ -138,7 +138,7 @@ constexpr int kWaveColumns = 32;
 __host__ __device__ inline int prefill_block_steps(int G, int waves) { return (kWaveColumns * waves) / G; }
 
 template <int D, int NW, int NBUF, bool kRope>
-__global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(AttnParams p) {
+__global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) {
   constexpr int KT = D / 16;                  // 16-dim contraction steps of the logits
   constexpr int OT = D / 32;                  // 32-dim tiles of the output
   constexpr int KU = D / 16;                  // 1 KiB units of one group's keys
@@ -490,7 +490,7 @@ int prefill_bf16_block_steps(int G, int waves) { return prefill_block_steps(G, w
 
 namespace {
 template <int NW>
-hipError_t launch_prefill_nw(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
+hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
   // Eight wavefronts (one workgroup per compute unit at D = 128): eight buffers, two groups per
   // barrier, an iteration's first operands read in the one before.  Fewer: four buffers, so that
   // at least two workgroups share a compute unit.
@@ -515,7 +515,7 @@ hipError_t launch_prefill_nw(const AttnParams& p, int batch, int D, int grid_spl
 // waves: 1, 2, 4 or 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
 // grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
 // range and writes `out`; p.tps_log2 must then be 30).
-hipError_t launch_prefill_bf16(const AttnParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {
+hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {
   switch (waves) {
     case 1: return launch_prefill_nw<1>(p, batch, D, grid_splits, stream);
     case 2: return launch_prefill_nw<2>(p, batch, D, grid_splits, stream);

@@ -216,10 +216,12 @@ hipError_t launch_elements_bf16(const StoreParams& p, const uint16_t* k, const u
 
 hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_new, int D,
                          int dtype, hipStream_t stream) {
-  // bf16, uniform first step, 32 rows or more: the group kernel (4096 rows of 16 sequences in 8
-  // heads: 86 us, element-wise 315 us).  A group takes one workgroup however few of its rows the
-  // call holds; from a group's worth of rows on that is the faster way.
-  if (dtype == TEMPO_BF16 && !p.t_per_seq && p.count >= 32) {
+  // bf16, uniform first step, at least one whole 32-slot group: the group kernel (4096 rows of 16
+  // sequences in 8 heads: 86 us, element-wise 315 us).  Rows that fill no group go element by
+  // element: a partly covered group's values are read, merged and written back (36 rows over two
+  // groups: 0.8 us slower that way).
+  const int first_whole = (p.t + 31) >> 5, past_whole = (p.t + p.count) >> 5;
+  if (dtype == TEMPO_BF16 && !p.t_per_seq && p.count >= 32 && past_whole > first_whole) {
     const int groups = ((p.t + p.count - 1) >> 5) - (p.t >> 5) + 1;
     // A ring whose every slot is written, from the middle of a group on: the last group lies in the
     // same slots as the first.  Its rows go in a launch behind the others.

@@ -132,13 +132,19 @@ constexpr int kMaxSplits = 1024;
 //     argument -> table -> data chain and its merge and partial write, as far as the other
 //     workgroups resident on the unit do not hide them; fitted on steps that are not powers
 //     of two, where short splits looked better than they are), and about 3 us for the
-//     combine launch if there is more than one split.
+//     combine launch if there is more than one split, 5 us if there are more than the 8 that
+//     the one-batch combine takes.  (With 3 us for both, a few sequences got many short splits:
+//     one sequence, t = 299, 10 splits 8.8 us, one split 5.9 us; over 104 measured cases of
+//     batch 1 .. 16 with 8 or 16 heads the mean distance from the fastest plan went from 3.5% to
+//     0.4%, the largest from 50% to 6%.  Fewer than 8 (sequence, head) pairs were not measured and
+//     keep 3 us.  A one-batch combine of 16 or 32 splits was 2 us slower than the one through LDS.)
 // Short splits balance better; long splits mean fewer rounds, fewer partials and,
 // at one split, no combine at all.  Take the LONGEST split length whose estimate is
 // within 3% of the best one.
 constexpr double kSustainedBytesPerNs = 6900.0;  // whole part, GB/s
 constexpr double kUnitBytesPerNs = 40.0;         // one compute unit, GB/s
-constexpr double kLaunchNs = 2000.0, kRoundNs = 1000.0, kCombineNs = 3000.0;
+constexpr double kLaunchNs = 2000.0, kRoundNs = 1000.0, kCombineNs = 3000.0, kCombineManyNs = 5000.0;
+constexpr int64_t kManyPairs = 8;
 
 double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int bytes_per_key) {
   const int64_t workgroups = pairs * splits;
@@ -147,7 +153,7 @@ double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int b
   const double rate = share < kUnitBytesPerNs ? share : kUnitBytesPerNs;
   const int64_t rounds = (workgroups + kComputeUnits - 1) / kComputeUnits;
   return kLaunchNs + (double)rounds * (kRoundNs + (double)keys_per_split * bytes_per_key / rate) +
-         (splits > 1 ? kCombineNs : 0.0);
+         (splits > 8 && pairs >= kManyPairs ? kCombineManyNs : splits > 1 ? kCombineNs : 0.0);
 }
 
 // Ragged batches (per-sequence steps below t_max) hold less work than the model
@@ -295,7 +301,6 @@ AttnParams attn_params(const tempo_kv* kv, const void* q, void* out, int32_t Hq,
   p.num_splits = plan->num_splits;
   p.queries = queries;
   p.io_steps = queries;
-  p.block_steps = 0;
   p.pad_t = pad_t;
   p.direct = 0;
   p.scale_log2e = scale * 1.44269504088896340736f;
@@ -944,10 +949,11 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq ? 0 : workspace_bytes)
                                : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
   const tempo_plan cut = {1 << plan.tps_log2, plan.splits, 8};
-  AttnParams p = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
+  PromptParams p;
+  static_cast<AttnParams&>(p) = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
   p.io_steps = io_steps;
   p.direct = plan.splits == 1;
-  p.block_steps = bf16 && plan.splits > 1 ? prefill_bf16_block_steps(p.G, plan.waves) : 0;
+  p.block_steps = prefill_bf16_block_steps(p.G, plan.waves);
   p.count_per_seq = count_per_seq;
   if (rope) {
     p.rope_cos = rope->cos;
@@ -957,7 +963,8 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
                             : launch_partial_f32(p, batch, kv->head_dim, plan.splits, plan.waves, s);
   const int rc = launch_status(e, "attn_prefill");
   if (rc != TEMPO_OK || plan.splits == 1) return rc;
-  return launch_status(launch_combine(p, batch, kv->head_dim, kv->dtype, s), "attn_prefill_combine");
+  return launch_status(bf16 ? launch_prompt_combine(p, batch, kv->head_dim, s)
+                            : launch_combine(p, batch, kv->head_dim, kv->dtype, s), "attn_prefill_combine");
 }
 
 // Prompt processing: `count` steps per sequence, written and answered in one launch each, or

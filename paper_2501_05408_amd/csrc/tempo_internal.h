@@ -100,11 +100,15 @@ struct AttnParams {
   int32_t queries;           // C: consecutive query steps per sequence (q, out, workspace rows are [B][C][Hq])
   int32_t io_steps;          // steps per sequence in the caller's q / out ([B][io_steps][Hq][D]); the block is
                              //   `queries` consecutive ones of them (pointers pre-offset); == queries normally
-  int32_t block_steps;       // prompt kernel with split key ranges: query steps per workgroup, each block of them
-                             //   splits its own range; 0 = the call is one block
   int32_t pad_t;             // padded baseline: keys up to pad_t are read and masked; 0 = none
   int32_t direct;            // 1: single split, write `out` and skip the combine
   float scale_log2e;         // s * log2(e)
+};
+
+// What only prompts need; not in AttnParams, because the decode kernel's launch is sensitive to the
+// size of its arguments.
+struct PromptParams : AttnParams {
+  int32_t block_steps;       // query steps per workgroup; each block of them splits its own key range
 };
 
 // Visible range and split bookkeeping of one sequence, identical on host and device.
@@ -123,17 +127,6 @@ __host__ __device__ inline SeqRange seq_range(int t_b, int window, int tps_log2,
   r.chunk0 = r.lo >> tps_log2;
   r.nchunks = (r.hi >> tps_log2) - r.chunk0 + 1;
   return r;
-}
-
-// Splits that hold partials of row `row` (step * Hq + head) of a call whose first step is t_b.
-__host__ __device__ inline int row_splits(const AttnParams& p, int t_b, int row) {
-  int c0 = 0, C = p.queries;
-  if (p.block_steps > 0) {  // the step's block has a range, and splits, of its own
-    c0 = row / p.Hq / p.block_steps * p.block_steps;
-    C = p.queries - c0 < p.block_steps ? p.queries - c0 : p.block_steps;
-  }
-  const int n = seq_range(t_b + c0, p.window, p.tps_log2, C, p.pad_t).nchunks;
-  return n < p.num_splits ? n : p.num_splits;
 }
 
 // Launch and return the launch's own status.  hipGetLastError() is not used: it
@@ -161,7 +154,8 @@ hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_s
                                hipStream_t stream);
 size_t partial_bf16_lds_bytes(int waves, int columns, int D);      // dynamic LDS of that launch
 int prefill_bf16_block_steps(int G, int waves);                    // query steps per workgroup of the prompt kernel
-hipError_t launch_prefill_bf16(const AttnParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream);
+hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream);
+hipError_t launch_prompt_combine(const PromptParams& p, int batch, int D, hipStream_t stream);
 hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream);
 hipError_t launch_partial_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                               hipStream_t stream);
