@@ -137,7 +137,7 @@ __device__ inline void mask_tile(int grp, int lo_col, int hi_col, int lane, f32x
 constexpr int kWaveColumns = 32;
 __host__ __device__ inline int prefill_block_steps(int G, int waves) { return (kWaveColumns * waves) / G; }
 
-template <int D, int NW, int NBUF, bool kRope>
+template <int D, int NW, int NBUF, bool kRope, bool kStaged>
 __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) {
   constexpr int KT = D / 16;                  // 16-dim contraction steps of the logits
   constexpr int OT = D / 32;                  // 32-dim tiles of the output
@@ -265,16 +265,32 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
     asm volatile("" : "+v"(tile_lo), "+v"(tile_hi));
   };
   load_tiles();
+  // A prompt on a ring store: the groups from its first step on lie, as one run per (sequence,
+  // head), in the staging area; the ring holds the history.
+  const int64_t stage_run = ((int64_t)b * p.Hkv + hkv) * p.stage_groups * (64 * D);
   const char* from_pool[PER_WAVE];                  // this wavefront's units in the pools' first group
+  const char* from_stage[PER_WAVE];                 // ... and in the staging area's
 #pragma unroll
   for (int i = 0; i < PER_WAVE; ++i) {
     const int u = wave + NW * i;                    // wave-uniform
     from_pool[i] = u < KU ? static_cast<const char*>(p.k_pool) + u * 1024
                           : static_cast<const char*>(p.v_pool) + (u - KU) * 1024;
+    if (kStaged)
+      from_stage[i] = stage_run + (u < KU ? static_cast<const char*>(p.k_stage) + u * 1024
+                                          : static_cast<const char*>(p.v_stage) + (u - KU) * 1024);
   }
   const uint32_t lane_bytes = 16u * (uint32_t)lane;
   auto issue = [&](int at, int g) {                 // `at`: the buffer's offset in LDS, in 16-byte pieces
     const int gc = g < g_last ? g : g_last;
+    if (kStaged && gc >= p.stage_first) {
+      const uint64_t from = (uint64_t)(gc - p.stage_first) * (64u * D);
+#pragma unroll
+      for (int i = 0; i < PER_WAVE; ++i) {
+        const auto unit = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(from_stage[i] + from), 0, 1024, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
+      }
+      return;
+    }
     const int tile = gc >> tile_groups;
     if (tile - tile_base >= 64) {
       tile_base = tile;
@@ -503,12 +519,17 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
   const dim3 grid((unsigned)(nblocks * grid_splits), p.Hkv, batch);
   const dim3 block(64 * NW);
   const size_t lds = NBUF * (size_t)(D / 8) * 1024;
-  if (p.rope_cos) {
-    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, true>), grid, block, lds, stream, p);
-    return launch((attn_prefill_bf16<64, NW, NBUF, true>), grid, block, lds, stream, p);
+  if (p.k_stage) {
+    if (p.rope_cos) return hipErrorInvalidConfiguration;  // a ring store takes no unrotated prompts
+    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false, true>), grid, block, lds, stream, p);
+    return launch((attn_prefill_bf16<64, NW, NBUF, false, true>), grid, block, lds, stream, p);
   }
-  if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false>), grid, block, lds, stream, p);
-  return launch((attn_prefill_bf16<64, NW, NBUF, false>), grid, block, lds, stream, p);
+  if (p.rope_cos) {
+    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, true, false>), grid, block, lds, stream, p);
+    return launch((attn_prefill_bf16<64, NW, NBUF, true, false>), grid, block, lds, stream, p);
+  }
+  if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false, false>), grid, block, lds, stream, p);
+  return launch((attn_prefill_bf16<64, NW, NBUF, false, false>), grid, block, lds, stream, p);
 }
 }  // namespace
 

@@ -71,7 +71,9 @@ __global__ __launch_bounds__(256) void kv_append_bf16(StoreParams p, const uint1
 // partly covered: their other slots keep what the pool holds (values are read, merged and
 // written back; no other workgroup of the launch touches the group, see launch_append), so
 // one launch writes a prompt that starts or ends anywhere (three launches before).
-template <int D>
+// kStage: the images go to the staging area of a prompt on a ring store, the call's first group
+// filled up with the history the pool holds.
+template <int D, bool kStage>
 __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const uint16_t* __restrict__ k_new,
                                                             const uint16_t* __restrict__ v_new) {
   constexpr int KS = D / 32, DT = D / 16, LD = D + 2;
@@ -89,6 +91,11 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
   const int phys = clamp_block(p.block_table[(int64_t)b * p.max_blocks_per_seq + ((t0 >> p.z_log2) & p.tile_mask)],
                                p.num_blocks);
   const int64_t base = (((int64_t)phys * p.Hkv + head) << p.z_log2) * D + (int64_t)(t0 & (Z - 1)) * D;
+  uint16_t* const k_from = static_cast<uint16_t*>(p.k_pool) + base;   // what the group's other slots hold
+  uint16_t* const v_from = static_cast<uint16_t*>(p.v_pool) + base;
+  const int64_t staged = (((int64_t)b * p.Hkv + head) * p.stage_groups + g) * 32 * D;
+  uint16_t* const k_to = kStage ? static_cast<uint16_t*>(p.k_stage) + staged : k_from;
+  uint16_t* const v_to = kStage ? static_cast<uint16_t*>(p.v_stage) + staged : v_from;
   const int64_t row0 = ((int64_t)b * p.src_steps + first_row) * p.Hkv + head;  // source row of slot 0 (rows are Hkv apart)
 
   // values -> LDS, 16 bytes per lane and load
@@ -103,7 +110,7 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
   // keys: lane (row + 16c) of unit (tile, s) = dims 32s + 8c .. +7 of slot 16*tile + row
   {
     const int row = lane & 15, c = lane >> 4;
-    u32x4* kp = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.k_pool) + base) + lane;
+    u32x4* kp = reinterpret_cast<u32x4*>(k_to) + lane;
 #pragma unroll
     for (int tl = 0; tl < 2; ++tl) {
 #pragma unroll
@@ -115,6 +122,10 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
           if (p.rope_cos) rotate_pieces(p.rope_cos, p.rope_sin, t0 + 16 * tl + row, D / 2, 32 * s + 8 * c, lo, hi);
           kp[(tl * KS + s) * 64] = lo;
           kp[(tl * KS + s + KS / 2) * 64] = hi;
+        } else if (kStage && 16 * tl + row < lo) {
+          const u32x4* old = reinterpret_cast<const u32x4*>(k_from) + lane;
+          kp[(tl * KS + s) * 64] = old[(tl * KS + s) * 64];
+          kp[(tl * KS + s + KS / 2) * 64] = old[(tl * KS + s + KS / 2) * 64];
         }
       }
     }
@@ -123,7 +134,7 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
   // values: lane (n + 16c) of unit dt = dim 16dt + n of slots {4c..4c+3, 16+4c..16+4c+3}
   {
     const int n = lane & 15, c = lane >> 4;
-    u32x4* vp = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.v_pool) + base) + lane;
+    u32x4* vp = reinterpret_cast<u32x4*>(v_to) + lane;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
       const uint16_t* col = tile + 16 * dt + n;
@@ -143,7 +154,7 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
           m[r] = (4 * c + r) >= lo && (4 * c + r) < hi ? 0xFFFFu : 0u;
           m[4 + r] = (16 + 4 * c + r) >= lo && (16 + 4 * c + r) < hi ? 0xFFFFu : 0u;
         }
-        const u32x4 old = vp[dt * 64];
+        const u32x4 old = reinterpret_cast<const u32x4*>(v_from)[lane + dt * 64];
         const uint32_t mx = m[0] | (m[1] << 16), my = m[2] | (m[3] << 16);
         const uint32_t mz = m[4] | (m[5] << 16), mw = m[6] | (m[7] << 16);
         o.x = (o.x & mx) | (old.x & ~mx); o.y = (o.y & my) | (old.y & ~my);
@@ -240,8 +251,8 @@ hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_
     const dim3 grid(groups, p.Hkv, p.batch);
     const uint16_t* k = static_cast<const uint16_t*>(k_new);
     const uint16_t* v = static_cast<const uint16_t*>(v_new);
-    if (D == 128) return launch(kv_append_groups_bf16<128>, grid, dim3(64), 0, stream, p, k, v);
-    return launch(kv_append_groups_bf16<64>, grid, dim3(64), 0, stream, p, k, v);
+    if (D == 128) return launch((kv_append_groups_bf16<128, false>), grid, dim3(64), 0, stream, p, k, v);
+    return launch((kv_append_groups_bf16<64, false>), grid, dim3(64), 0, stream, p, k, v);
   }
   if (dtype == TEMPO_BF16)
     return launch_elements_bf16(p, static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), D, stream);
@@ -252,6 +263,17 @@ hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_
   const float* v = static_cast<const float*>(v_new);
   if (D == 128) return launch(kv_append_f32<128>, grid, dim3(threads), 0, stream, p, k, v);
   return launch(kv_append_f32<64>, grid, dim3(threads), 0, stream, p, k, v);
+}
+
+// The rows' group images to p.k_stage / p.v_stage (p.stage_groups groups per sequence and head).
+hipError_t launch_stage(const StoreParams& p, const void* k_new, const void* v_new, int D, hipStream_t stream) {
+  const int groups = ((p.t + p.count - 1) >> 5) - (p.t >> 5) + 1;
+  if (groups != p.stage_groups || p.t_per_seq || p.rope_cos) return hipErrorInvalidConfiguration;
+  const dim3 grid(groups, p.Hkv, p.batch);
+  const uint16_t* k = static_cast<const uint16_t*>(k_new);
+  const uint16_t* v = static_cast<const uint16_t*>(v_new);
+  if (D == 128) return launch((kv_append_groups_bf16<128, true>), grid, dim3(64), 0, stream, p, k, v);
+  return launch((kv_append_groups_bf16<64, true>), grid, dim3(64), 0, stream, p, k, v);
 }
 
 hipError_t launch_gather(const StoreParams& p, void* k_out, void* v_out, int D, int dtype, int j0,

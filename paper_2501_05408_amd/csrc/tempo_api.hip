@@ -323,6 +323,9 @@ StoreParams store_params(const tempo_kv* kv, int32_t batch, int32_t t, const int
   p.batch = batch;
   p.count = count;
   p.src_steps = count;
+  p.k_stage = nullptr;
+  p.v_stage = nullptr;
+  p.stage_groups = 0;
   p.count_per_seq = nullptr;
   p.rope_cos = nullptr;
   p.rope_sin = nullptr;
@@ -943,10 +946,11 @@ int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, 
 // the store.  q, out: the caller's, `io_steps` steps per sequence.
 int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, int32_t Hq, int32_t t, int32_t count,
                   int32_t io_steps, const int32_t* count_per_seq, int32_t window, float scale, void* workspace,
-                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope) {
+                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope, const StoreParams* staged = nullptr) {
   const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
-  const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq ? 0 : workspace_bytes)
+  // (and staged keys/values lie where the partials of split ranges would)
+  const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
                                : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
   const tempo_plan cut = {1 << plan.tps_log2, plan.splits, 8};
   PromptParams p;
@@ -954,10 +958,18 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   p.io_steps = io_steps;
   p.direct = plan.splits == 1;
   p.block_steps = prefill_bf16_block_steps(p.G, plan.waves);
+  p.k_stage = p.v_stage = nullptr;
+  p.stage_first = p.stage_groups = 0;
   p.count_per_seq = count_per_seq;
   if (rope) {
     p.rope_cos = rope->cos;
     p.rope_sin = rope->sin;
+  }
+  if (staged) {
+    p.k_stage = staged->k_stage;
+    p.v_stage = staged->v_stage;
+    p.stage_first = t >> 5;
+    p.stage_groups = staged->stage_groups;
   }
   const hipError_t e = bf16 ? launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s)
                             : launch_partial_f32(p, batch, kv->head_dim, plan.splits, plan.waves, s);
@@ -965,6 +977,44 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   if (rc != TEMPO_OK || plan.splits == 1) return rc;
   return launch_status(bf16 ? launch_prompt_combine(p, batch, kv->head_dim, s)
                             : launch_combine(p, batch, kv->head_dim, kv->dtype, s), "attn_prefill_combine");
+}
+
+// A ring store holds little more than the window, so a prompt written into it has to be answered
+// in chunks, each too small to fill the part (2048 steps of 4 sequences, window 512, 4 blocks of
+// 256: 8 chunks, 253 us).  Instead the prompt's key/value groups are laid out in the workspace
+// first, one launch answers all steps from there (and from the ring, for the history), and the
+// steps the ring holds in the end are written last.  How many steps from t on the workspace has
+// room for, if any; less than `left` ends on a group.
+int32_t staged_steps(const tempo_kv* kv, int32_t batch, int32_t t, int32_t left, size_t workspace_bytes) {
+  if (kv->dtype != TEMPO_BF16 || kv->ring_blocks == 0) return 0;
+  const int64_t group_bytes = (int64_t)batch * kv->num_kv_heads * 2 * 32 * kv->head_dim * 2;  // keys and values of all sequences
+  const int64_t room = (int64_t)workspace_bytes / group_bytes, first = t >> 5;
+  const int64_t end = (first + room) << 5;                       // first step without room
+  return end >= (int64_t)t + left ? left : (end > t ? (int32_t)(end - t) : 0);
+}
+
+// Steps c0 .. c0+C-1 of the call, staged.
+int prefill_staged(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
+                   int32_t Hq, int32_t t, int32_t count, int32_t c0, int32_t C, int32_t window, float scale,
+                   void* workspace, hipStream_t s) {
+  const char* k = static_cast<const char*>(k_new);
+  const char* v = static_cast<const char*>(v_new);
+  const size_t row = (size_t)kv->num_kv_heads * kv->head_dim * 2, q_at = (size_t)c0 * Hq * kv->head_dim * 2;
+  StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
+  sp.src_steps = count;
+  sp.stage_groups = ((t + c0 + C - 1) >> 5) - ((t + c0) >> 5) + 1;
+  sp.k_stage = workspace;
+  sp.v_stage = static_cast<char*>(workspace) + (size_t)batch * kv->num_kv_heads * sp.stage_groups * 64 * kv->head_dim;
+  int rc = launch_status(launch_stage(sp, k + c0 * row, v + c0 * row, kv->head_dim, s), "kv_stage");
+  if (rc != TEMPO_OK) return rc;
+  rc = attend_prompt(kv, static_cast<const char*>(q) + q_at, static_cast<char*>(out) + q_at, batch, Hq, t + c0, C, count,
+                     nullptr, window, scale, workspace, 0, s, nullptr, &sp);
+  if (rc != TEMPO_OK) return rc;
+  const int64_t slots = (int64_t)kv->ring_blocks * kv->block_size;
+  const int32_t kept = C < slots ? C : (int32_t)slots, from = c0 + C - kept;
+  StoreParams last = store_params(kv, batch, t + from, nullptr, kept);
+  last.src_steps = count;
+  return launch_status(launch_append(last, k + from * row, v + from * row, kv->head_dim, kv->dtype, s), "kv_append_block");
 }
 
 // Prompt processing: `count` steps per sequence, written and answered in one launch each, or
@@ -1005,6 +1055,13 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   if (prompt_in_one_launch(kv, batch, Hq, count)) {
     for (int32_t c0 = 0; c0 < count;) {
       const int32_t C = ring_chunk(kv, t + c0, count - c0, window, block);
+      const int32_t S = C < count - c0 ? staged_steps(kv, batch, t + c0, count - c0, workspace_bytes) : 0;
+      if (S > C) {
+        rc = prefill_staged(kv, q, k_new, v_new, out, batch, Hq, t, count, c0, S, window, scale, workspace, s);
+        if (rc != TEMPO_OK) return rc;
+        c0 += S;
+        continue;
+      }
       const size_t kv_at = (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz, q_at = (size_t)c0 * Hq * kv->head_dim * esz;
       StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
       sp.src_steps = count;

@@ -63,6 +63,9 @@ struct StoreParams {
   int32_t num_blocks;
   int32_t Hkv;
   int32_t batch;
+  void* k_stage;             // non-null (bf16, group-wise append): the groups' images go here, [batch][Hkv][stage_groups]
+  void* v_stage;             //   groups from that of step t on, not into the pool, which is only read
+  int32_t stage_groups;
   int32_t count;             // append: consecutive steps per sequence, rows [B][count][Hkv][D]
   int32_t src_steps;         // steps per sequence in the caller's k_new / v_new (>= count; == count normally)
   const int32_t* count_per_seq;  // may be null; sequence b writes only its first count_per_seq[b] rows
@@ -109,6 +112,9 @@ struct AttnParams {
 // size of its arguments.
 struct PromptParams : AttnParams {
   int32_t block_steps;       // query steps per workgroup; each block of them splits its own key range
+  const void* k_stage;       // may be null; groups stage_first .. are read from here ([batch][Hkv][stage_groups]
+  const void* v_stage;       //   group images), earlier ones from the pool
+  int32_t stage_first, stage_groups;
 };
 
 // Visible range and split bookkeeping of one sequence, identical on host and device.
@@ -148,6 +154,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
 // ---- launchers (defined next to their kernels) -------------------------------
 hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_new, int D,
                          int dtype, hipStream_t stream);
+hipError_t launch_stage(const StoreParams& p, const void* k_new, const void* v_new, int D, hipStream_t stream);
 hipError_t launch_gather(const StoreParams& p, void* k_out, void* v_out, int D, int dtype, int j0,
                          int count, hipStream_t stream);
 hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_splits, int waves,

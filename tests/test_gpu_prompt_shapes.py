@@ -16,7 +16,7 @@ from test_gpu_parity import DEV, assert_close, dev, host_inputs, np64, random_ta
 pytestmark = pytest.mark.gpu
 
 
-def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70):
+def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70, least_workspace=False):
     Hq, steps = Hkv * G, t + count
     q, K, V = host_inputs(seed, B, steps, Hq, Hkv, D, dtype)
     if ring:
@@ -36,7 +36,17 @@ def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70):
         at += n
     qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
     out = torch.empty_like(qd)
-    st.prefill_attend(qd, Kd[:, t:].contiguous(), Vd[:, t:].contiguous(), out, t, count, window)
+    k_new, v_new = Kd[:, t:].contiguous(), Vd[:, t:].contiguous()
+    if least_workspace:                                  # what the blocks of 128 columns need, and no byte more
+        block = 128 // G
+        need = max(T.tempo_attn_plan_workspace_bytes(st.kv, B * min(block, count - c), Hq, T.tempo_attn_block_plan(
+            st.kv, B, Hq, min(block, count - c), t + c, window)) for c in range(0, count, block))
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device=DEV)   # NaN, should anything of it be read unwritten
+        T.tempo_prefill_window(st.kv, qd, k_new, v_new, out, B, Hq, t, count, None, window, st.scale, ws, need)
+    else:
+        st._prefill_ws = torch.full((T.tempo_prefill_workspace_bytes(
+            st.kv, B, Hq, ring_blocks * Z + 128 if ring else st.max_t),), 0xFF, dtype=torch.uint8, device=DEV)
+        st.prefill_attend(qd, k_new, v_new, out, t, count, window)
     got = np64(out)
     K64, V64 = K.astype(np.float64), V.astype(np.float64)
     picks = sorted({0, 1, count // 2, count - 2, count - 1} | set(range(0, count, max(1, count // 40))))
@@ -60,8 +70,11 @@ def test_prompt_shapes(B, Hkv, G, D, t, count, window):
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window", [
     (2, 2, 3, 128, 32, 0, 700, 100), (1, 4, 4, 64, 64, 0, 333, 33), (3, 1, 8, 128, 32, 77, 400, 64),
     (1, 2, 1, 64, 32, 1000, 129, 1), (1, 2, 3, 128, 256, 0, 900, 512), (2, 1, 3, 128, 256, 300, 513, 512)])
-def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window):
-    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16)
+@pytest.mark.parametrize("least_workspace", [False, True])
+def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window, least_workspace):
+    """With the workspace tempo_prefill_workspace_bytes asks for the prompt is staged there; with the
+    least that is accepted, answered in chunks the ring can hold."""
+    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace)
 
 
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
