@@ -533,12 +533,11 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
 }
 }  // namespace
 
-// waves: 1, 2, 4 or 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
+// waves: 2, 4 or 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
 // grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
 // range and writes `out`; p.tps_log2 must then be 30).
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {
   switch (waves) {
-    case 1: return launch_prefill_nw<1>(p, batch, D, grid_splits, stream);
     case 2: return launch_prefill_nw<2>(p, batch, D, grid_splits, stream);
     case 4: return launch_prefill_nw<4>(p, batch, D, grid_splits, stream);
     case 8: return launch_prefill_nw<8>(p, batch, D, grid_splits, stream);

@@ -850,12 +850,15 @@ struct PromptPlan {
 };
 
 // A time model of the launch, in nanoseconds, with constants measured on MI355X (D = 128, scaled
-// by the head dim).  A compute unit holds one workgroup of 8 wavefronts, or two of fewer (64 KiB
-// of LDS each); a workgroup spends about 5 us before its first and after its last group, and an
-// iteration over a 32-slot group takes 0.55 us with one wavefront on a SIMD and 0.78 us with two.
-// So wide workgroups win once they fill the part; narrow ones, and a key range cut into splits
-// (with a combine launch of about 5 us, and partials of (D + 2) * 4 bytes per column and
-// split), when the query columns alone do not.
+// by the head dim).  Two workgroups of 2 or 4 wavefronts share a compute unit (64 KiB of LDS each);
+// a workgroup spends about 5 us before its first and after its last group, and an iteration over a
+// 32-slot group takes 0.55 us with one wavefront on a SIMD and 0.78 us with two.  So 4 wavefronts
+// win once they fill the part; 2, and a key range cut into splits (with a combine launch of about
+// 5 us, and partials of (D + 2) * 4 bytes per column and split), when the query columns alone do
+// not (100 steps behind 1900 keys, one sequence: no splits 52 us, 8 splits 25 us).
+// 8 wavefronts in one workgroup read each key/value half as often, but nothing covers the
+// workgroup's beginning and end: the better shape only for long ranges at D = 128 (us with 4 / 8:
+// 16 x 200 steps 32.7 / 35.7, 16 x 1000 185 / 200, 4 x 4000 449 / 437; D = 64, 8 x 1500 125 / 147).
 bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
   const int32_t QB = prefill_bf16_block_steps(G, 4);
   return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
@@ -865,15 +868,19 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
                        size_t workspace_bytes) {
   const int G = Hq / kv->num_kv_heads;
   const double scale = kv->head_dim / 128.0;
-  PromptPlan best = {8, 30, 1};
+  PromptPlan best = {4, 30, 1};
   double best_ns = -1.0;
   const bool may_split = !prompt_fills_part(kv, batch, G, count);
-  for (int waves = 8; waves >= 1; waves /= 2) {
+  const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
+  const int32_t wide = prefill_bf16_block_steps(G, 8);
+  const int64_t mean_keys = window > 0 && window < t + count / 2 ? window : t + count / 2;
+  if (kv->head_dim == 128 && mean_keys >= 1800 && (count + wide - 1) / wide * pairs >= 4 * kComputeUnits) return {8, 30, 1};
+  for (int waves = 4; waves >= 2; waves /= 2) {
     const int32_t QB = prefill_bf16_block_steps(G, waves);
     if (QB < 1) break;
-    const int64_t blocks = (count + QB - 1) / QB, pairs = (int64_t)batch * kv->num_kv_heads;
+    const int64_t blocks = (count + QB - 1) / QB;
     const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
-    const int resident = waves == 8 ? 1 : 2;
+    const int resident = 2;
     for (int k = 30; k >= 7; k = k == 30 ? 13 : k - 1) {
       const int splits = k == 30 ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
       if (k != 30 && !may_split) break;
@@ -883,7 +890,7 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
       if (k != 30 && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
       const int64_t workgroups = blocks * pairs * splits;
       const int64_t rounds = (workgroups + resident * kComputeUnits - 1) / (resident * kComputeUnits);
-      const bool shared_simd = waves == 8 || (waves == 4 && workgroups > kComputeUnits);
+      const bool shared_simd = waves == 4 && workgroups > kComputeUnits;
       const int64_t span = k == 30 || keys < ((int64_t)1 << k) ? keys : (int64_t)1 << k;
       // a causal prompt's blocks are half the longest on average: beyond the first round that counts
       const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;

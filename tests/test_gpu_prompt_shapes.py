@@ -1,4 +1,4 @@
-"""GPU parity of prompts over the sizes at which the prompt kernel's launch changes shape (1, 2, 4 or 8
+"""GPU parity of prompts over the sizes at which the prompt kernel's launch changes shape (2, 4 or 8
 wavefronts of 32 columns per workgroup, split key ranges, ring stores answered in chunks), against the
 fp64 CPU oracle; and of block-store writes that begin or end inside a 32-slot group, bit for bit.
 Tolerances are those of test_gpu_parity.py.
