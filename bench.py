@@ -279,7 +279,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
 
         dt = gpu_timed(torch, block_step, 200, 20)["median"]
         plan = T.tempo_attn_block_plan(sts[0].kv, 16, Hq, C, 4096 - C, 0)
-        kernel = "attn_partial_bf16<128, false>" if C * (Hq // Hkv) <= 16 else "attn_prefill_bf16<128, NW, false, true>"
+        kernel = "attn_partial_bf16<128, false>" if C * (Hq // Hkv) <= 16 else "attn_block_bf16<128, NW, false, true>"
         out[f"block{C}_b16_t{4096 - C}"] = {"us_per_call": us(dt), "us_per_query_step": us(dt / C),
                                             "kv_gbs": round(block_bytes / dt / 1e9, 1),
                                             "splits": plan.num_splits, "tokens_per_split": plan.tokens_per_split,
@@ -297,7 +297,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
     tflops = 16 * pairs * 4 * D * Hq / dt / 1e12
     out["prompt_b16_t4096"] = {"ms": round(dt * 1e3, 3), "tokens_per_s": round(16 * P / dt, 1),
                                "tflops": round(tflops, 1),
-                               "roofline": {"kernel": "attn_prefill_bf16<128, 8, false, false>", "bound": "mfma",
+                               "roofline": {"kernel": "attn_prefill_bf16<128, 8, 8, false, false>", "bound": "mfma",
                                             "achieved": round(tflops, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
                                             "unit": "TFLOP/s", "frac": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4)},
                                "note": "one tempo_prefill_causal call (block-store write + prompt kernel); "
@@ -342,7 +342,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
 
     dt = gpu_timed(torch, rope_block, 200, 20)["median"]
     out[f"rope_block{C}_b16_t{4096 - C}"] = {"us_per_call": us(dt), "us_per_query_step": us(dt / C),
-                                             "roofline": hbm_roofline("attn_prefill_bf16<128, 4, true, true>", block_bytes, dt),
+                                             "roofline": hbm_roofline("attn_block_bf16<128, 4, true, true>", block_bytes, dt),
                                              "note": "rotating block write + block attention with unrotated queries"}
     del qc, kc, vc, oc
     del sts
@@ -438,7 +438,7 @@ def prompt_only(torch, T, BlockStore, synth, dev, repeats):
     flops = B * (P * (P + 1) // 2) * 4 * D * Hq
     return {"workload": "prompt of 4096 steps x 16 sequences, llama-3.2-3b attention shape, one tempo_prefill_causal call",
             "ms": round(dt * 1e3, 3), "tokens_per_s": round(B * P / dt, 1), "algorithmic_flops_per_call": flops,
-            "roofline": {"kernel": "attn_prefill_bf16<128, 8, false, false>", "bound": "mfma",
+            "roofline": {"kernel": "attn_prefill_bf16<128, 8, 8, false, false>", "bound": "mfma",
                          "achieved": round(flops / dt / 1e12, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(flops / dt / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)}}
 

@@ -437,17 +437,19 @@ int tempo_rope_attn_block_window(const tempo_kv* kv, const tempo_rope* rope, con
  * starts; Section 4.3: the temporal dimension evaluated in tiles): steps
  * t .. t+count-1 of every sequence in ONE call.  The keys/values of those steps are
  * written to the store and every step's query attends over its own range (keys
- * 0 .. t+c, or its window), exactly as `count` single decode steps would.  Work is
- * issued in blocks of 128 / (num_q_heads / num_kv_heads) steps: per block one
- * tempo_kv_append_block and one tempo_attn_block_* (all launches asynchronous on
- * `stream`, nothing allocated).
+ * 0 .. t+c, or its window), exactly as `count` single decode steps would.  One launch
+ * writes the store, one answers all steps (a third combines, if the columns are few and
+ * their key range was split).  On a ring store the keys/values are laid out in the
+ * workspace first and the steps the ring keeps are written last; a workspace without the
+ * room for that takes the prompt in chunks that the ring can hold.  (All launches
+ * asynchronous on `stream`, nothing allocated.)
  *   q, out        device, [batch][count][num_q_heads][head_dim]
  *   k_new, v_new  device, [batch][count][num_kv_heads][head_dim]
  *   count_per_seq device, int32 [batch], or NULL: sequence b has only count_per_seq[b]
  *                 (0 .. count) prompt steps; its later rows of q / k_new / v_new are not
  *                 read into the store, its later rows of out and its later slots in
  *                 the store are left as they are.  bf16 linear stores only
- *                 (TEMPO_ERR_SHAPE otherwise); always the prompt kernel.
+ *                 (TEMPO_ERR_SHAPE otherwise).
  *   workspace     device, 256-byte aligned, >= tempo_prefill_workspace_bytes(kv, batch,
  *                 num_q_heads, t + count - 1) bytes
  * All arguments are validated for every block before the first launch.
@@ -465,8 +467,8 @@ int tempo_prefill_window(const tempo_kv* kv, const void* q, const void* k_new, c
 /* tempo_prefill_* with the rotary producer fused in: q_raw and k_raw arrive
  * unrotated; keys are turned to their step's position on the way into the store
  * (the same bits tempo_rope_kv_append stores), queries when the prompt kernel loads
- * them.  bf16 linear stores only (TEMPO_ERR_SHAPE otherwise); always the prompt
- * kernel; rope->positions must exceed t + count - 1.  Other arguments as
+ * them.  bf16 linear stores only (TEMPO_ERR_SHAPE otherwise); rope->positions must
+ * exceed t + count - 1.  Other arguments as
  * tempo_prefill_causal / _window. */
 int tempo_rope_prefill_causal(const tempo_kv* kv, const tempo_rope* rope, const void* q_raw,
                               const void* k_raw, const void* v_new, void* out, int32_t batch,
@@ -482,9 +484,10 @@ int tempo_rope_prefill_window(const tempo_kv* kv, const tempo_rope* rope, const 
 
 /* How many launches a tempo_prefill_* call of `count` steps issues at most (host
  * only; 0 on unsupported arguments): 2 when the prompt's query blocks fill the part
- * (bf16, linear store: one block-store write, then one launch of the prompt kernel,
- * in which every workgroup walks the whole key range of its 128 (step, head)
- * columns through LDS and writes `out` directly), else 3 per block of steps. */
+ * (bf16, linear store: one block-store write, then one launch in which every workgroup
+ * walks the whole key range of its (step, head) columns through LDS and writes `out`
+ * directly), 3 on other linear stores, else 3 per block of
+ * 128 / (num_q_heads / num_kv_heads) steps. */
 int tempo_prefill_launches(const tempo_kv* kv, int32_t batch, int32_t num_q_heads, int32_t count);
 
 /* Workspace bound for tempo_prefill_* calls whose last step is at most max_t (host only). */
