@@ -507,7 +507,7 @@ int prefill_bf16_block_steps(int G, int waves) { return prefill_block_steps(G, w
 namespace {
 template <int NW>
 hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
-  // Eight wavefronts (one workgroup per compute unit at D = 128): eight buffers, two groups per
+  // Eight wavefronts (one workgroup per compute unit): eight buffers, two groups per
   // barrier, an iteration's first operands read in the one before.  Fewer: four buffers, so that
   // at least two workgroups share a compute unit.
   constexpr int NBUF = NW == 8 ? 8 : 4;
@@ -519,21 +519,23 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
   const dim3 grid((unsigned)(nblocks * grid_splits), p.Hkv, batch);
   const dim3 block(64 * NW);
   const size_t lds = NBUF * (size_t)(D / 8) * 1024;
-  if (p.k_stage) {
-    if (p.rope_cos) return hipErrorInvalidConfiguration;  // a ring store takes no unrotated prompts
-    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false, true>), grid, block, lds, stream, p);
-    return launch((attn_prefill_bf16<64, NW, NBUF, false, true>), grid, block, lds, stream, p);
+  if (p.k_stage && p.rope_cos) return hipErrorInvalidConfiguration;  // a ring store takes no unrotated prompts
+  if (D == 128) {
+    if (p.k_stage) return launch((attn_prefill_bf16<128, NW, NBUF, false, true>), grid, block, lds, stream, p);
+    if (p.rope_cos) return launch((attn_prefill_bf16<128, NW, NBUF, true, false>), grid, block, lds, stream, p);
+    return launch((attn_prefill_bf16<128, NW, NBUF, false, false>), grid, block, lds, stream, p);
   }
-  if (p.rope_cos) {
-    if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, true, false>), grid, block, lds, stream, p);
-    return launch((attn_prefill_bf16<64, NW, NBUF, true, false>), grid, block, lds, stream, p);
+  if constexpr (NW == 8) {
+    return hipErrorInvalidConfiguration;  // four wavefronts are always the better shape at D = 64
+  } else {
+    if (p.k_stage) return launch((attn_prefill_bf16<64, NW, NBUF, false, true>), grid, block, lds, stream, p);
+    if (p.rope_cos) return launch((attn_prefill_bf16<64, NW, NBUF, true, false>), grid, block, lds, stream, p);
+    return launch((attn_prefill_bf16<64, NW, NBUF, false, false>), grid, block, lds, stream, p);
   }
-  if (D == 128) return launch((attn_prefill_bf16<128, NW, NBUF, false, false>), grid, block, lds, stream, p);
-  return launch((attn_prefill_bf16<64, NW, NBUF, false, false>), grid, block, lds, stream, p);
 }
 }  // namespace
 
-// waves: 2, 4 or 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
+// waves: 2, 4 or (D = 128) 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
 // grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
 // range and writes `out`; p.tps_log2 must then be 30).
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {

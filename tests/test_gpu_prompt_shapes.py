@@ -77,6 +77,31 @@ def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window, least_workspace):
     run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace)
 
 
+@pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 37), (64, 2, 1021, 20)])
+def test_rope_prompt_with_split_ranges(D, G, t, count):
+    """Few unrotated columns behind a long history: the bits of rotating first."""
+    B, Hkv, Z, dtype = 1, 2, 32, T.TEMPO_BF16
+    q, K, V = host_inputs(74, B, t + count, Hkv * G, Hkv, D, dtype)
+    half = D // 2
+    angle = torch.arange(t + count, dtype=torch.float64)[:, None] * 500000.0 ** (-torch.arange(half, dtype=torch.float64) / half)
+    Kd, Vd = dev(K, dtype), dev(V, dtype)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
+    outs = []
+    for fused in (True, False):
+        st = BlockStore(B, Hkv * G, Hkv, D, Z, t + count - 1, dtype, fill="nan")
+        st.set_rope(torch.cos(angle).float().to(DEV), torch.sin(angle).float().to(DEV))
+        st.rope_append_block(Kd[:, :t].contiguous(), Vd[:, :t].contiguous(), 0, t)
+        qr, kr = qd.clone(), Kd[:, t:].contiguous()
+        if not fused:
+            for c in range(count):
+                qr[:, c] = st.rope_rotate(qr[:, c].contiguous(), torch.empty_like(qr[:, c]).contiguous(), t + c)
+                kr[:, c] = st.rope_rotate(kr[:, c].contiguous(), torch.empty_like(kr[:, c]).contiguous(), t + c)
+        out = torch.empty_like(qr)
+        st.prefill_attend(qr, kr, Vd[:, t:].contiguous(), out, t, count, rope=fused)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
     (1, 2, 4, 64, 64, 0, 300, 0, False), (2, 2, 3, 128, 4, 13, 70, 0, False), (1, 1, 1, 64, 8, 2500, 9, 0, False),
     (1, 1, 20, 128, 16, 37, 30, 33, False), (1, 1, 3, 128, 16, 3000, 5, 0, False), (2, 1, 3, 64, 8, 50, 260, 40, True)])
