@@ -307,15 +307,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
     }
   };
-  // Slots beyond the block's last step may be unwritten (NaN): the 0 mask under the
-  // sums is applied once, to the value units of the range's last group, in LDS, by the
-  // wavefront that copied the unit and after its copy has landed (the copy keeps the
-  // lane of every 16-byte piece, so a lane masks the slots its consumers will read from
-  // it).  Masked slots inside the range hold written data and weight 0.
-  const bool tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
-  auto mask_values = [&](int at) {  // the buffer of g_last, and tail
+  // Slots before the range's first key and beyond the block's last step may be unwritten
+  // (NaN): the 0 mask under the sums is applied once, to the value units of the range's first
+  // and last group, in LDS, by the wavefront that copied the unit and after its copy has landed
+  // (the copy keeps the lane of every 16-byte piece, so a lane masks the slots its consumers
+  // will read from it).  Masked slots inside the range hold written data and weight 0.
+  const bool head = (start & 31) != 0, tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
+  auto mask_values = [&](int g, int at) {  // the buffer of group g: the first, and head, or the last, and tail
     uint32_t keep[4];
-    value_masks(g_last, 0, t_last, lane, keep);
+    value_masks(g, start, t_last, lane, keep);
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
       const int u = wave + NW * i;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   auto finish = [&]() {
     if (kPair == 1 || ((grp - g_first) & 1)) {
       landed();
-      if (tail && g_last <= grp + kAhead && g_last > grp + kAhead - kPair) mask_values(next(g_last - grp));
+      if (tail && g_last <= grp + kAhead && g_last > grp + kAhead - kPair) mask_values(g_last, next(g_last - grp));
       meet();
     }
     at0 = next(1);
@@ -393,7 +393,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 #pragma unroll
   for (int i = 0; i < NBUF - kPair; ++i) issue(i * kBuf, g_first + i);
   landed();                                    // groups g_first .. g_first + kAhead - 1
-  if (tail && g_last - g_first < kAhead) mask_values((g_last - g_first) * kBuf);
+  if (head) mask_values(g_first, 0);
+  if (tail && g_last - g_first < kAhead) mask_values(g_last, (g_last - g_first) * kBuf);
   meet();
   for (; grp < own_first && grp <= g_last; finish()) copies();
   // operand i of an iteration: keys of group grp + 1, then values of group grp

@@ -161,3 +161,37 @@ def test_append_block_that_fills_a_ring_from_inside_a_group():
     st.append_block(Kd[:, t:].contiguous(), Vd[:, t:].contiguous(), t, count)
     kg, vg = st.gather(t, count)
     assert torch.equal(kg, Kd[:, t:]) and torch.equal(vg, Vd[:, t:])
+
+
+def run_from_first_visible_step(call, B, Hkv, G, D, Z, t, count, window, ring):
+    """`call` answers steps t .. t+count-1 on a poisoned store whose history begins at the first step
+    that step t sees; every step against the oracle."""
+    Hq, steps, dtype = Hkv * G, t + count, T.TEMPO_BF16
+    q, K, V = host_inputs(75, B, steps, Hq, Hkv, D, dtype)
+    ring_blocks = T.tempo_ring_blocks(window, Z, min(count, 128 // G)) if ring else 0
+    table, nb = random_table(75, B, ring_blocks if ring else (steps - 1) // Z + 1)
+    st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, dtype, num_blocks=nb, block_table=table, fill="nan", ring_blocks=ring_blocks)
+    Kd, Vd, first = dev(K, dtype), dev(V, dtype), t - window + 1
+    assert first > 0 and first % 32 != 0
+    if window > 1:
+        st.append_block(Kd[:, first:t].contiguous(), Vd[:, first:t].contiguous(), first, t - first)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
+    out = torch.empty_like(qd)
+    call(st, qd, Kd[:, t:].contiguous(), Vd[:, t:].contiguous(), out)
+    got = np64(out)
+    K64, V64 = K.astype(np.float64), V.astype(np.float64)
+    for c in range(count):
+        ref = oracle.attend(q[t + c].astype(np.float64), K64, V64, t + c, window, 1.0 / np.sqrt(D))
+        assert_close(got[:, c], ref, dtype, f"step {t + c} of {t}..{steps - 1} G={G} D={D} w={window} ring={ring}")
+
+
+FIRST_VISIBLE = [(1, 1, 3, 128, 32, 1000, 1, 64), (2, 2, 3, 128, 64, 1000, 5, 64), (1, 2, 3, 64, 32, 1000, 40, 64),
+                 (1, 1, 3, 128, 256, 998, 400, 200), (1, 1, 20, 64, 32, 300, 3, 290), (2, 1, 1, 128, 32, 70, 1, 1)]
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window", FIRST_VISIBLE)
+@pytest.mark.parametrize("ring", [False, True])
+def test_prompt_behind_a_history_that_begins_inside_a_group(B, Hkv, G, D, Z, t, count, window, ring):
+    """Slots of the first group before the window's start were never written and hold NaN."""
+    run_from_first_visible_step(lambda st, q, k, v, out: st.prefill_attend(q, k, v, out, t, count, window),
+                                B, Hkv, G, D, Z, t, count, window, ring)
