@@ -214,15 +214,15 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
                                          (lds_ptr)(lds_v + ((gv & 1) * DT + u) * 64), 16, 0, kCachePolicy);
     }
   };
-  // Slots beyond the block's last step may be unwritten (NaN): the 0 mask under the
-  // sums is applied once, to the value units of the range's last group, in LDS, by the
-  // wavefront that copied the unit and after its copy has landed (the copy keeps the
-  // lane of every 16-byte piece, so a lane masks the slots its consumers will read from
-  // it).  Masked slots inside the range hold written data and weight 0.
-  const bool tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
-  auto mask_values = [&](int gv) {  // gv == g_last, and tail
+  // Slots before the range's first key and beyond the block's last step may be unwritten
+  // (NaN): the 0 mask under the sums is applied once, to the value units of the range's first
+  // and last group, in LDS, by the wavefront that copied the unit and after its copy has landed
+  // (the copy keeps the lane of every 16-byte piece, so a lane masks the slots its consumers
+  // will read from it).  Masked slots inside the range hold written data and weight 0.
+  const bool head = (start & 31) != 0, tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
+  auto mask_values = [&](int gv) {  // gv == g_first, and head, or gv == g_last, and tail
     uint32_t keep[4];
-    value_masks(gv, 0, t_last, lane, keep);
+    value_masks(gv, start, t_last, lane, keep);
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int u = wave + NW * i - KU;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
     issue_values(g_first, off0);
   }
   landed();
-  if (tail && g_first == g_last) mask_values(g_first);
+  if (head || (tail && g_first == g_last)) mask_values(g_first);
   meet();
   float xc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // logits of the current group
   if (active(g_first)) logits(g_first, xc);

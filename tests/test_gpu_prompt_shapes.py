@@ -195,3 +195,14 @@ def test_prompt_behind_a_history_that_begins_inside_a_group(B, Hkv, G, D, Z, t, 
     """Slots of the first group before the window's start were never written and hold NaN."""
     run_from_first_visible_step(lambda st, q, k, v, out: st.prefill_attend(q, k, v, out, t, count, window),
                                 B, Hkv, G, D, Z, t, count, window, ring)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window", [
+    (1, 2, 20, 64, 32, 300, 1, 290), (1, 1, 3, 128, 32, 1000, 5, 64), (2, 2, 3, 128, 64, 1000, 10, 64),
+    (1, 1, 3, 128, 256, 998, 21, 200), (1, 1, 3, 64, 32, 1000, 42, 600), (1, 2, 1, 128, 32, 70, 20, 1)])
+@pytest.mark.parametrize("ring", [False, True])
+def test_block_behind_a_history_that_begins_inside_a_group(B, Hkv, G, D, Z, t, count, window, ring):
+    def call(st, q, k, v, out):
+        st.append_block(k, v, t, count)
+        st.attend_block(q, out, t, count, window)
+    run_from_first_visible_step(call, B, Hkv, G, D, Z, t, count, window, ring)
