@@ -119,13 +119,12 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
   t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
   const int t_first = t_base, t_last = t_first + C - 1;
   const int lo = (p.window > 0 && t_first - p.window + 1 > 0) ? t_first - p.window + 1 : 0;
-  // The split of the key range this workgroup walks (the whole range when not split:
-  // tps_log2 = 30), newest split first as in the decode kernel.
+  // The split of the key range this workgroup walks, newest split first as in the decode kernel.
   const int chunk0 = lo >> p.tps_log2;
   const int nchunks = (t_last >> p.tps_log2) - chunk0 + 1;
   if (zsplit >= nchunks) return;                                    // uniform over the workgroup
   const int split = nchunks - 1 - zsplit;
-  const int cs = (chunk0 + split) << p.tps_log2, ce = cs + ((1 << p.tps_log2) - 1);
+  const int cs = (chunk0 + split) << p.tps_log2, ce = split_end(chunk0 + split, p.tps_log2);
   const int start = lo > cs ? lo : cs;
   const int end = t_last < ce ? t_last : ce;
   const int g_first = start >> 5, g_last = end >> 5;

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
   // (A work list names the split itself.)
   const int split = kList ? zsplit : rg.nchunks - 1 - zsplit;
   const int chunk = rg.chunk0 + split;
-  const int cs = chunk << p.tps_log2, ce = ((chunk + 1) << p.tps_log2) - 1;
+  const int cs = chunk << p.tps_log2, ce = split_end(chunk, p.tps_log2);
   const int start = rg.lo > cs ? rg.lo : cs;
   const int end = rg.hi < ce ? rg.hi : ce;
   const int g_last = end >> 5;

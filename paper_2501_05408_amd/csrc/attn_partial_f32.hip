@@ -54,7 +54,7 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   if ((int)blockIdx.z >= rg.nchunks) return;  // uniform over the workgroup
   const int split = rg.nchunks - 1 - (int)blockIdx.z;  // newest split first, as in the bf16 kernel
   const int chunk = rg.chunk0 + split;
-  const int cs = chunk << p.tps_log2, ce = cs + ((1 << p.tps_log2) - 1);
+  const int cs = chunk << p.tps_log2, ce = split_end(chunk, p.tps_log2);
 
   // this tile's columns and the union of their ranges, cut to the split (empty if they do not meet)
   const int col0 = 16 * tile, ncols = all_cols - col0 < 16 ? all_cols - col0 : 16;

@@ -182,12 +182,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   const int t_first = t_base + c0, t_last = t_first + C - 1;
   const int lo = (p.window > 0 && t_first - p.window + 1 > 0) ? t_first - p.window + 1 : 0;
   // The split of the key range this workgroup walks (the whole range when not split:
-  // tps_log2 = 30), newest split first as in the decode kernel.
+  // kWholeRange), newest split first as in the decode kernel.
   const int chunk0 = lo >> p.tps_log2;
   const int nchunks = (t_last >> p.tps_log2) - chunk0 + 1;
   if (zsplit >= nchunks) return;                                    // uniform over the workgroup
   const int split = nchunks - 1 - zsplit;
-  const int cs = (chunk0 + split) << p.tps_log2, ce = cs + ((1 << p.tps_log2) - 1);
+  const int cs = (chunk0 + split) << p.tps_log2, ce = split_end(chunk0 + split, p.tps_log2);
   const int start = lo > cs ? lo : cs;
   const int end = t_last < ce ? t_last : ce;
   const int g_first = start >> 5, g_last = end >> 5;
@@ -538,7 +538,7 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
 
 // waves: 2, 4 or (D = 128) 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
 // grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
-// range and writes `out`; p.tps_log2 must then be 30).
+// range and writes `out`; p.tps_log2 must then be kWholeRange).
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {
   switch (waves) {
     case 2: return launch_prefill_nw<2>(p, batch, D, grid_splits, stream);

@@ -844,7 +844,7 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
 }
 
 // How the prompt kernel takes a prompt: wavefronts of 32 columns per workgroup, and splits of
-// a block's key range (tps_log2 = 30, splits = 1: none).
+// a block's key range (tps_log2 = kWholeRange, splits = 1: none).
 struct PromptPlan {
   int waves, tps_log2, splits;
 };
@@ -868,30 +868,30 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
                        size_t workspace_bytes) {
   const int G = Hq / kv->num_kv_heads;
   const double scale = kv->head_dim / 128.0;
-  PromptPlan best = {4, 30, 1};
+  PromptPlan best = {4, kWholeRange, 1};
   double best_ns = -1.0;
   const bool may_split = !prompt_fills_part(kv, batch, G, count);
   const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
   const int32_t wide = prefill_bf16_block_steps(G, 8);
   const int64_t mean_keys = window > 0 && window < t + count / 2 ? window : t + count / 2;
-  if (kv->head_dim == 128 && mean_keys >= 1800 && (count + wide - 1) / wide * pairs >= 4 * kComputeUnits) return {8, 30, 1};
+  if (kv->head_dim == 128 && mean_keys >= 1800 && (count + wide - 1) / wide * pairs >= 4 * kComputeUnits) return {8, kWholeRange, 1};
   for (int waves = 4; waves >= 2; waves /= 2) {
     const int32_t QB = prefill_bf16_block_steps(G, waves);
     if (QB < 1) break;
     const int64_t blocks = (count + QB - 1) / QB;
     const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
     const int resident = 2;
-    for (int k = 30; k >= 7; k = k == 30 ? 13 : k - 1) {
-      const int splits = k == 30 ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
-      if (k != 30 && !may_split) break;
-      if (k != 30 && splits == 1) continue;
+    for (int k = kWholeRange; k >= 7; k = k == kWholeRange ? 13 : k - 1) {
+      const int splits = k == kWholeRange ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
+      if (k != kWholeRange && !may_split) break;
+      if (k != kWholeRange && splits == 1) continue;
       if (splits > 8) break;  // the combine reads up to 8 splits in one batch
       const int64_t rows = (int64_t)batch * count * Hq;
-      if (k != 30 && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
+      if (k != kWholeRange && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
       const int64_t workgroups = blocks * pairs * splits;
       const int64_t rounds = (workgroups + resident * kComputeUnits - 1) / (resident * kComputeUnits);
       const bool shared_simd = waves == 4 && workgroups > kComputeUnits;
-      const int64_t span = k == 30 || keys < ((int64_t)1 << k) ? keys : (int64_t)1 << k;
+      const int64_t span = k == kWholeRange || keys < ((int64_t)1 << k) ? keys : (int64_t)1 << k;
       // a causal prompt's blocks are half the longest on average: beyond the first round that counts
       const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;
       double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (shared_simd ? 780.0 : 550.0) * scale);
@@ -919,7 +919,7 @@ PromptPlan plan_prompt_f32(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_
                            size_t workspace_bytes) {
   const int64_t columns = (int64_t)count * (Hq / kv->num_kv_heads);
   const int64_t tiles = (columns + 15) / 16 * kv->num_kv_heads * batch, rows = (int64_t)batch * count * Hq;
-  PromptPlan plan = {8, 30, 1};
+  PromptPlan plan = {8, kWholeRange, 1};
   const int64_t keys = window > 0 && window + count < (int64_t)t + count ? (int64_t)window + count : (int64_t)t + count;
   if (keys <= 256) plan.waves = 4;
   for (int k = 10; k <= 20 && tiles < kComputeUnits / 2; ++k) {
@@ -959,10 +959,11 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   // (and staged keys/values lie where the partials of split ranges would)
   const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
                                : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
-  const tempo_plan cut = {1 << plan.tps_log2, plan.splits, 8};
+  const tempo_plan cut = {32, plan.splits, plan.waves};  // (its split length is set below)
   PromptParams p;
   static_cast<AttnParams&>(p) = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
   p.io_steps = io_steps;
+  p.tps_log2 = plan.tps_log2;
   p.direct = plan.splits == 1;
   p.block_steps = prefill_bf16_block_steps(p.G, plan.waves);
   p.k_stage = p.v_stage = nullptr;

@@ -98,7 +98,7 @@ struct AttnParams {
   int32_t Hkv;
   int32_t Hq;
   int32_t G;                 // Hq / Hkv
-  int32_t tps_log2;          // log2(tokens per split)
+  int32_t tps_log2;          // log2(tokens per split); kWholeRange: not split
   int32_t num_splits;        // S: stride of the split axis in the workspace
   int32_t queries;           // C: consecutive query steps per sequence (q, out, workspace rows are [B][C][Hq])
   int32_t io_steps;          // steps per sequence in the caller's q / out ([B][io_steps][Hq][D]); the block is
@@ -116,6 +116,15 @@ struct PromptParams : AttnParams {
   const void* v_stage;       //   group images), earlier ones from the pool
   int32_t stage_first, stage_groups;
 };
+
+// tps_log2 of a key range that is not split: steps are below 2^31, so no range crosses a multiple of it
+// (one of 2^30 keys would be cut where it crosses step 2^30, which a ring store reaches).
+constexpr int kWholeRange = 31;
+
+// Last key of split `chunk`.
+__host__ __device__ inline int split_end(int chunk, int tps_log2) {
+  return (int)((((uint32_t)chunk + 1u) << tps_log2) - 1u);
+}
 
 // Visible range and split bookkeeping of one sequence, identical on host and device.
 // With a block of C queries (steps t_b .. t_b+C-1) the range is the union of the

@@ -206,3 +206,25 @@ def test_block_behind_a_history_that_begins_inside_a_group(B, Hkv, G, D, Z, t, c
         st.append_block(k, v, t, count)
         st.attend_block(q, out, t, count, window)
     run_from_first_visible_step(call, B, Hkv, G, D, Z, t, count, window, ring)
+
+
+@pytest.mark.parametrize("dtype,B,count", [(T.TEMPO_BF16, 1, 40), (T.TEMPO_BF16, 1, 300), (T.TEMPO_F32, 16, 40)])
+def test_ring_prompt_whose_range_crosses_two_to_the_thirty(dtype, B, count):
+    """A ring store answers any step; the oracle sees the same rows counted from the first visible step."""
+    Hkv, G, D, Z, window = 8, 3, 128, 32, 50
+    t = (1 << 30) - 20
+    first, n = t - window + 1, window - 1 + count
+    q, K, V = host_inputs(76, B, n, Hkv * G, Hkv, D, dtype)
+    ring_blocks = T.tempo_ring_blocks(window, Z, min(count, 128 // G))
+    st = BlockStore(B, Hkv * G, Hkv, D, Z, t + count - 1, dtype, fill="nan", ring_blocks=ring_blocks)
+    Kd, Vd = dev(K, dtype), dev(V, dtype)
+    st.append_block(Kd[:, :window - 1].contiguous(), Vd[:, :window - 1].contiguous(), first, window - 1)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, window - 1:]), dtype)
+    out = torch.empty_like(qd)
+    st.prefill_attend(qd, Kd[:, window - 1:].contiguous(), Vd[:, window - 1:].contiguous(), out, t, count, window)
+    got = np64(out)
+    K64, V64 = K.astype(np.float64), V.astype(np.float64)
+    for c in range(0, count, 3):
+        at = window - 1 + c
+        ref = oracle.attend(q[at].astype(np.float64), K64, V64, at, window, 1.0 / np.sqrt(D))
+        assert_close(got[:, c], ref, dtype, f"prompt step 2^30 {t + c - (1 << 30):+d}")

@@ -1,0 +1,84 @@
+"""What the host side of the library launches, with the launches recorded instead of made
+(host_launches.cpp): every visible key is in some launched split, and the route a call takes.
+No test here computes anything on a GPU."""
+import ctypes
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2501_05408_amd import tempo as T
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOMEWHERE = 1 << 20                       # pointers that are checked for NULL and alignment, never read
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return load(str(tmp_path_factory.mktemp("host") / "host_launches.so"))
+
+
+def load(path, *flags):
+    subprocess.check_call(
+        ["g++", "-std=c++17", "-O1", "-w", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-x", "c++",
+         os.path.join(ROOT, "tests", "host_launches.cpp"), "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+         "-I", os.path.join(ROOT, "paper_2501_05408_amd", "csrc"), "-o", path, *flags])
+    lib = ctypes.CDLL(path)
+    for name, (res, args) in T.SIGNATURES.items():
+        fn = getattr(lib, name)
+        fn.restype, fn.argtypes = res, args
+    lib.host_launches_take.restype = ctypes.c_char_p
+    return lib
+
+
+def store(dtype, Hkv, D, Z, columns, ring=0):
+    return T.make_kv(SOMEWHERE, SOMEWHERE, SOMEWHERE, 1 << 20, columns, Z, Hkv, D, dtype, ring)
+
+
+def taken(lib):
+    """The launches since the last call: (name, {field: number})."""
+    out = []
+    for line in lib.host_launches_take().decode().splitlines():
+        name, *fields = line.split()
+        out.append((name, {k: int(v) for k, v in (f.split("=") for f in fields)}))
+    return out
+
+
+def prefill(lib, kv, batch, Hq, t, count, window=0, workspace=1 << 50):
+    lib.host_launches_take()
+    args = (ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, batch, Hq, t, count, None)
+    if window:
+        rc = lib.tempo_prefill_window(*args, window, 0.125, SOMEWHERE, workspace, None)
+    else:
+        rc = lib.tempo_prefill_causal(*args, 0.125, SOMEWHERE, workspace, None)
+    assert rc == T.TEMPO_OK
+    return taken(lib)
+
+
+def assert_all_keys_launched(launches, G, t, count):
+    """Every step of the call is answered once, and the splits that are launched for the steps that
+    share a workgroup reach from the first key of the first of them to the last step."""
+    step = t
+    for name, f in launches:
+        if name not in ("prompt", "prompt_staged", "block_bf16", "partial_bf16", "partial_f32"):
+            continue
+        assert f["t"] == step
+        together = 32 * f["waves"] // G if name.startswith("prompt") else f["queries"]
+        for c in range(0, f["queries"], together):
+            last = step + min(c + together, f["queries"]) - 1
+            first = max(0, step + c - f["window"] + 1) if f["window"] else 0
+            assert (last >> f["tps_log2"]) - (first >> f["tps_log2"]) + 1 <= f["grid_splits"], (name, f, first, last)
+        step += f["queries"]
+    assert step == t + count
+
+
+@pytest.mark.parametrize("dtype,window,count", [(T.TEMPO_BF16, 40, 30), (T.TEMPO_BF16, 200, 1000), (T.TEMPO_F32, 40, 30),
+                                                (T.TEMPO_F32, 200, 1000)])
+@pytest.mark.parametrize("batch", [1, 64])
+def test_prompts_whose_range_crosses_two_to_the_thirty(lib, dtype, window, count, batch):
+    G, Z = 3, 32
+    ring = T.tempo_ring_blocks(window, Z, min(count, 128 // G))
+    t = (1 << 30) - 20
+    launches = prefill(lib, store(dtype, 2, 128, Z, ring, ring), batch, 2 * G, t, count, window)
+    assert_all_keys_launched(launches, G, t, count)
