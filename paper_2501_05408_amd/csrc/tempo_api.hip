@@ -159,8 +159,9 @@ double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int b
 // Ragged batches (per-sequence steps below t_max) hold less work than the model
 // assumes and it is unevenly spread, so their splits are capped at 1024 keys to
 // keep the long sequences from becoming single long-running workgroups.
+// max_splits: no more splits than this (unless even the longest splits of a ragged batch are more).
 void make_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t_max, int32_t window,
-               bool ragged, int32_t queries, tempo_plan* plan) {
+               bool ragged, int32_t queries, int64_t max_splits, tempo_plan* plan) {
   // one workgroup serves a query group; fp32 takes 16 (step, head) columns per workgroup
   const int64_t columns = (int64_t)queries * (Hq / kv->num_kv_heads);
   const int64_t pairs = (int64_t)batch * kv->num_kv_heads * (kv->dtype == TEMPO_F32 ? (columns + 15) / 16 : 1);
@@ -173,7 +174,7 @@ void make_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t_max, int
   for (int k = 5; k <= 30; ++k) costs[k - 5] = -1.0;
   for (int k = 5; k <= k_max; ++k) {
     const int64_t splits = splits_bound(t_max, window, k);
-    if (splits > kMaxSplits) continue;
+    if (splits > max_splits) continue;
     const int64_t tps = (int64_t)1 << k;
     const int64_t per_split = tps < len ? tps : len;  // a split never holds more than the range
     costs[k - 5] = plan_cost_ns(pairs, splits, per_split, bytes_per_key);
@@ -405,8 +406,8 @@ int do_combine(const tempo_kv* kv, void* out, int32_t batch, int32_t Hq, int32_t
 // cut down until the bf16 kernel's wave-merge area (one accumulator row per column
 // and wavefront) fits the LDS a workgroup may ask for.
 void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window,
-                     bool ragged, int32_t queries, tempo_plan* plan) {
-  make_plan(kv, batch, Hq, last_step(t, queries), union_window(window, queries), ragged, queries, plan);
+                     bool ragged, int32_t queries, tempo_plan* plan, int64_t max_splits = kMaxSplits) {
+  make_plan(kv, batch, Hq, last_step(t, queries), union_window(window, queries), ragged, queries, max_splits, plan);
   if (kv->dtype != TEMPO_BF16) return;
   const int columns = queries * (Hq / kv->num_kv_heads);
   if (columns > kNarrowColumns) {
@@ -437,7 +438,8 @@ void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, i
 int decode(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out,
            int32_t batch, int32_t Hq, int32_t t, const int32_t* t_per_seq, int32_t window, float scale,
            void* workspace, size_t workspace_bytes, void* stream, int32_t queries = 1,
-           const tempo_rope* rope = nullptr, int32_t pad_t = 0, const int32_t* worklist = nullptr) {
+           const tempo_rope* rope = nullptr, int32_t pad_t = 0, const int32_t* worklist = nullptr,
+           int64_t max_splits = kMaxSplits) {
   int rc = check_layout(kv);
   if (rc != TEMPO_OK) return rc;
   if (!q || !out) return TEMPO_ERR_NULL;
@@ -449,7 +451,7 @@ int decode(const tempo_kv* kv, const void* q, const void* k_new, const void* v_n
   if (pad_t < 0 || pad_t > INT32_MAX - 64) return TEMPO_ERR_RANGE;
   tempo_plan plan;
   // the padded baseline is planned as the step it pretends every step to be
-  make_block_plan(kv, batch, Hq, pad_t > t ? pad_t : t, window, t_per_seq != nullptr, queries, &plan);
+  make_block_plan(kv, batch, Hq, pad_t > t ? pad_t : t, window, t_per_seq != nullptr, queries, &plan, max_splits);
   if ((rc = check_attn(kv, batch, Hq, t, window, t_per_seq != nullptr, &plan, workspace, workspace_bytes, queries,
                        pad_t)) != TEMPO_OK)
     return rc;
@@ -719,9 +721,16 @@ int tempo_decode_step_causal_noalloc(const tempo_kv* kv, const void* q, const vo
   if ((rc = check_heads(kv, batch, num_q_heads)) != TEMPO_OK) return rc;
   if (t < 0 || t > INT32_MAX - 64) return TEMPO_ERR_RANGE;
   // the partials of this call's own plan must fit the static array
+  // (fp32 shares a key/value read among a group's query heads, so it wants more splits than fit there
+  // for many heads and long ranges: then the best plan that fits)
+  const int64_t rows = (int64_t)batch * num_q_heads;
+  int64_t max_splits = kMaxSplits;
+  if (kv->dtype == TEMPO_F32) {
+    while (max_splits > 1 && plan_bytes(kv, rows, (int32_t)max_splits) > kScratchBytes) --max_splits;
+  }
   tempo_plan plan;
-  make_block_plan(kv, batch, num_q_heads, t, 0, t_per_seq != nullptr, 1, &plan);
-  const size_t need = plan_bytes(kv, (int64_t)batch * num_q_heads, plan.num_splits);
+  make_block_plan(kv, batch, num_q_heads, t, 0, t_per_seq != nullptr, 1, &plan, max_splits);
+  const size_t need = plan_bytes(kv, rows, plan.num_splits);
   if (need > kScratchBytes) {
     fprintf(stderr, "libtempo: tempo_decode_step_causal_noalloc: this step needs %zu bytes of split partials, "
                     "the static array holds %zu; use tempo_decode_step_causal with a workspace\n", need, kScratchBytes);
@@ -729,7 +738,8 @@ int tempo_decode_step_causal_noalloc(const tempo_kv* kv, const void* q, const vo
   }
   void* ws = nullptr;
   if ((rc = scratch_on_current_device(&ws)) != TEMPO_OK) return rc;
-  return decode(kv, q, k_new, v_new, out, batch, num_q_heads, t, t_per_seq, 0, scale, ws, kScratchBytes, stream);
+  return decode(kv, q, k_new, v_new, out, batch, num_q_heads, t, t_per_seq, 0, scale, ws, kScratchBytes, stream, 1,
+                nullptr, 0, nullptr, max_splits);
 }
 
 // The work list of a ragged step is tied to the plan the step will use: both come from

@@ -2,7 +2,7 @@
 // launcher appends one line that says what it was asked for.  Built by test_host_launches.py with
 // the host compiler, signed overflow checked; no GPU and no HIP runtime is involved.
 #define __align__(n) __attribute__((aligned(n)))
-#define HIP_SYMBOL(x) (&(x))
+#define HIP_SYMBOL(x) x
 #include "tempo_api.hip"
 
 #include <stdarg.h>

@@ -82,3 +82,25 @@ def test_prompts_whose_range_crosses_two_to_the_thirty(lib, dtype, window, count
     t = (1 << 30) - 20
     launches = prefill(lib, store(dtype, 2, 128, Z, ring, ring), batch, 2 * G, t, count, window)
     assert_all_keys_launched(launches, G, t, count)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,batch,t,ragged", [(24, 8, 128, 48, 8192, False), (32, 8, 128, 16, 17378, False),
+                                                     (64, 1, 64, 16, 17378, True), (8, 2, 128, 64, 17378, False)])
+def test_no_alloc_f32_step_takes_a_plan_that_fits_the_array(lib, Hq, Hkv, D, batch, t, ragged):
+    kv = store(T.TEMPO_F32, Hkv, D, 64, t // 64 + 1)
+    lib.host_launches_take()
+    rc = lib.tempo_decode_step_causal_noalloc(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, batch, Hq, t,
+                                              SOMEWHERE if ragged else None, 0.125, None)
+    assert rc == T.TEMPO_OK
+    (name, f), *rest = taken(lib)
+    assert name == "partial_f32" and f["num_splits"] * batch * Hq * (D + 2) * 4 <= 8 << 20
+    assert f["grid_splits"] >= (t >> f["tps_log2"]) + 1
+    assert [n for n, _ in rest] == (["combine"] if f["num_splits"] > 1 else [])
+
+
+def test_no_alloc_bf16_step_that_does_not_fit_stays_refused(lib, capfd):
+    kv = store(T.TEMPO_BF16, 8, 128, 256, 32)
+    lib.host_launches_take()
+    rc = lib.tempo_decode_step_causal_noalloc(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, 64, 64, 8191,
+                                              SOMEWHERE, 0.125, None)
+    assert rc == T.TEMPO_ERR_WORKSPACE and not taken(lib)
