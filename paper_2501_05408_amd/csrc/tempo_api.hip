@@ -72,7 +72,10 @@ int check_scale(float scale) { return (scale > 0.0f && scale <= 3.0e38f) ? TEMPO
 // The steps a block of queries starting at t touches: the last step, and the
 // window measured from the last step that spans the union of the queries' ranges.
 int32_t last_step(int32_t t, int32_t queries) { return t + (queries - 1); }
-int32_t union_window(int32_t window, int32_t queries) { return window > 0 ? window + (queries - 1) : 0; }
+// (0, causal, if that is more than any step is far from step 0)
+int32_t union_window(int32_t window, int32_t queries) {
+  return window > 0 && window <= INT32_MAX - (queries - 1) ? window + (queries - 1) : 0;
+}
 
 // A linear store must have a table column for step t's tile; a ring store reuses
 // its columns, so any step can be written.
@@ -930,7 +933,7 @@ PromptPlan plan_prompt_f32(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_
   const int64_t columns = (int64_t)count * (Hq / kv->num_kv_heads);
   const int64_t tiles = (columns + 15) / 16 * kv->num_kv_heads * batch, rows = (int64_t)batch * count * Hq;
   PromptPlan plan = {8, kWholeRange, 1};
-  const int64_t keys = window > 0 && window + count < (int64_t)t + count ? (int64_t)window + count : (int64_t)t + count;
+  const int64_t keys = window > 0 && window < t ? (int64_t)window + count : (int64_t)t + count;
   if (keys <= 256) plan.waves = 4;
   for (int k = 10; k <= 20 && tiles < kComputeUnits / 2; ++k) {
     const int splits = splits_bound(t + count - 1, union_window(window, count), k);

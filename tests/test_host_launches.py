@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -19,17 +20,22 @@ def lib(tmp_path_factory):
     return load(str(tmp_path_factory.mktemp("host") / "host_launches.so"))
 
 
-def load(path, *flags):
-    subprocess.check_call(
-        ["g++", "-std=c++17", "-O1", "-w", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-x", "c++",
-         os.path.join(ROOT, "tests", "host_launches.cpp"), "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
-         "-I", os.path.join(ROOT, "paper_2501_05408_amd", "csrc"), "-o", path, *flags])
+def load(path, *flags, build=True):
+    if build:
+        compile_host(path, *flags)
     lib = ctypes.CDLL(path)
     for name, (res, args) in T.SIGNATURES.items():
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
     lib.host_launches_take.restype = ctypes.c_char_p
     return lib
+
+
+def compile_host(path, *flags):
+    subprocess.check_call(
+        ["g++", "-std=c++17", "-O1", "-w", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-x", "c++",
+         os.path.join(ROOT, "tests", "host_launches.cpp"), "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+         "-I", os.path.join(ROOT, "paper_2501_05408_amd", "csrc"), "-o", path, *flags])
 
 
 def store(dtype, Hkv, D, Z, columns, ring=0):
@@ -104,3 +110,19 @@ def test_no_alloc_bf16_step_that_does_not_fit_stays_refused(lib, capfd):
     rc = lib.tempo_decode_step_causal_noalloc(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, 64, 64, 8191,
                                               SOMEWHERE, 0.125, None)
     assert rc == T.TEMPO_ERR_WORKSPACE and not taken(lib)
+
+
+@pytest.mark.parametrize("call", [
+    "assert_all_keys_launched(prefill(lib, store(T.TEMPO_F32, 2, 64, 64, 100), 1, 8, 37, 300, (1 << 31) - 129), 4, 37, 300)",
+    "assert_all_keys_launched(prefill(lib, store(T.TEMPO_BF16, 8, 128, 64, 100), 1, 8, 37, 3000, (1 << 31) - 129), 1, 37, 3000)",
+    "lib.tempo_attn_block_plan(ctypes.byref(store(T.TEMPO_BF16, 8, 128, 64, 100)), 1, 8, 128, 37, (1 << 31) - 65, 0, "
+    "ctypes.byref(T.tempo_plan()))"])
+def test_windows_near_the_largest_integer_do_not_overflow(tmp_path, call):
+    """In a process of its own: signed overflow ends it."""
+    path = str(tmp_path / "checked.so")
+    load(path, "-fsanitize=signed-integer-overflow", "-fno-sanitize-recover=all", "-static-libubsan")
+    code = ("import ctypes, test_host_launches as H\nfrom test_host_launches import T, prefill, store, assert_all_keys_launched\n"
+            f"lib = H.load({path!r}, build=False)\n{call}")
+    run = subprocess.run([sys.executable, "-c", code], cwd=os.path.join(ROOT, "tests"),
+                         env={**os.environ, "PYTHONPATH": ROOT}, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr
