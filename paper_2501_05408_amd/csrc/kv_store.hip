@@ -68,9 +68,9 @@ __global__ __launch_bounds__(256) void kv_append_bf16(StoreParams p, const uint1
 // is a gather of 16-byte pieces.  Values: a 16-byte piece holds one dim of 8 slots, so the
 // 32 x D tile goes through LDS (row stride D + 2 elements, which spreads the four rows a
 // column tile's lanes read over different banks).  The call's first and last group may be
-// partly covered: their other slots keep what the pool holds (values are read, merged and
-// written back; no other workgroup of the launch touches the group, see launch_append), so
-// one launch writes a prompt that starts or ends anywhere (three launches before).
+// partly covered: their other slots are not written (their values go element by element), as
+// another launch may write them at the same time, so one launch writes a prompt that starts or
+// ends anywhere.
 // kStage: the images go to the staging area of a prompt on a ring store, the call's first group
 // filled up with the history the pool holds.
 template <int D, bool kStage>
@@ -147,12 +147,21 @@ __global__ __launch_bounds__(64) void kv_append_groups_bf16(StoreParams p, const
       u32x4 o;
       o.x = e[0] | (e[1] << 16); o.y = e[2] | (e[3] << 16);
       o.z = e[4] | (e[5] << 16); o.w = e[6] | (e[7] << 16);
-      if (lo > 0 || hi < 32) {  // partly covered: keep what the pool holds in the other slots
+      if (!kStage && (lo > 0 || hi < 32)) {  // partly covered: this call's slots only
+        uint16_t* at = reinterpret_cast<uint16_t*>(vp + dt * 64);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const int slot = r < 4 ? 4 * c + r : 16 + 4 * c + (r - 4);
+          if (slot >= lo && slot < hi) at[r] = (uint16_t)e[r];
+        }
+        continue;
+      }
+      if (kStage && lo > 0) {  // the history in the group's first slots (nothing is read beyond the call's last step)
         uint32_t m[8];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          m[r] = (4 * c + r) >= lo && (4 * c + r) < hi ? 0xFFFFu : 0u;
-          m[4 + r] = (16 + 4 * c + r) >= lo && (16 + 4 * c + r) < hi ? 0xFFFFu : 0u;
+          m[r] = 4 * c + r >= lo ? 0xFFFFu : 0u;
+          m[4 + r] = 16 + 4 * c + r >= lo ? 0xFFFFu : 0u;
         }
         const u32x4 old = reinterpret_cast<const u32x4*>(v_from)[lane + dt * 64];
         const uint32_t mx = m[0] | (m[1] << 16), my = m[2] | (m[3] << 16);
@@ -229,8 +238,7 @@ hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_
                          int dtype, hipStream_t stream) {
   // bf16, uniform first step, at least one whole 32-slot group: the group kernel (4096 rows of 16
   // sequences in 8 heads: 86 us, element-wise 315 us).  Rows that fill no group go element by
-  // element: a partly covered group's values are read, merged and written back (36 rows over two
-  // groups: 0.8 us slower that way).
+  // element, as the group kernel's work for a partly covered group is that of a whole one.
   const int first_whole = (p.t + 31) >> 5, past_whole = (p.t + p.count) >> 5;
   if (dtype == TEMPO_BF16 && !p.t_per_seq && p.count >= 32 && past_whole > first_whole) {
     const int groups = ((p.t + p.count - 1) >> 5) - (p.t >> 5) + 1;

@@ -228,3 +228,25 @@ def test_ring_prompt_whose_range_crosses_two_to_the_thirty(dtype, B, count):
         at = window - 1 + c
         ref = oracle.attend(q[at].astype(np.float64), K64, V64, at, window, 1.0 / np.sqrt(D))
         assert_close(got[:, c], ref, dtype, f"prompt step 2^30 {t + c - (1 << 30):+d}")
+
+
+def test_appends_to_the_same_groups_on_two_streams_keep_each_others_rows():
+    """Two calls that are not ordered write different slots of the same 32-slot groups: neither may
+    write a slot of the other's back as it was."""
+    B, Hkv, D, Z, steps = 16, 8, 128, 64, 128
+    _, K, V = host_inputs(77, B, steps, Hkv, Hkv, D, T.TEMPO_BF16)
+    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
+    st = BlockStore(B, Hkv, Hkv, D, Z, steps - 1, T.TEMPO_BF16)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for first in (33, 40, 47, 50, 62):
+        parts = [(0, first), (first, steps - first)]
+        rows = [(Kd[:, t:t + n].contiguous(), Vd[:, t:t + n].contiguous()) for t, n in parts]
+        for _ in range(10):
+            st.k_pool.zero_(), st.v_pool.zero_()
+            torch.cuda.synchronize()
+            for s, (t, n), (k, v) in zip(streams, parts, rows):
+                with torch.cuda.stream(s):
+                    st.append_block(k, v, t, n)
+            torch.cuda.synchronize()
+            kg, vg = st.gather(0, steps)
+            assert torch.equal(kg, Kd) and torch.equal(vg, Vd)
