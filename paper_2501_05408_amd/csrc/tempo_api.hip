@@ -327,9 +327,6 @@ StoreParams store_params(const tempo_kv* kv, int32_t batch, int32_t t, const int
   p.batch = batch;
   p.count = count;
   p.src_steps = count;
-  p.k_stage = nullptr;
-  p.v_stage = nullptr;
-  p.stage_groups = 0;
   p.count_per_seq = nullptr;
   p.rope_cos = nullptr;
   p.rope_sin = nullptr;
@@ -966,7 +963,7 @@ int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, 
 // the store.  q, out: the caller's, `io_steps` steps per sequence.
 int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, int32_t Hq, int32_t t, int32_t count,
                   int32_t io_steps, const int32_t* count_per_seq, int32_t window, float scale, void* workspace,
-                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope, const StoreParams* staged = nullptr) {
+                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope, const StageParams* staged = nullptr) {
   const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
   // (and staged keys/values lie where the partials of split ranges would)
@@ -1021,7 +1018,8 @@ int prefill_staged(const tempo_kv* kv, const void* q, const void* k_new, const v
   const char* k = static_cast<const char*>(k_new);
   const char* v = static_cast<const char*>(v_new);
   const size_t row = (size_t)kv->num_kv_heads * kv->head_dim * 2, q_at = (size_t)c0 * Hq * kv->head_dim * 2;
-  StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
+  StageParams sp;
+  static_cast<StoreParams&>(sp) = store_params(kv, batch, t + c0, nullptr, C);
   sp.src_steps = count;
   sp.stage_groups = ((t + c0 + C - 1) >> 5) - ((t + c0) >> 5) + 1;
   sp.k_stage = workspace;

@@ -63,14 +63,19 @@ struct StoreParams {
   int32_t num_blocks;
   int32_t Hkv;
   int32_t batch;
-  void* k_stage;             // non-null (bf16, group-wise append): the groups' images go here, [batch][Hkv][stage_groups]
-  void* v_stage;             //   groups from that of step t on, not into the pool, which is only read
-  int32_t stage_groups;
   int32_t count;             // append: consecutive steps per sequence, rows [B][count][Hkv][D]
   int32_t src_steps;         // steps per sequence in the caller's k_new / v_new (>= count; == count normally)
   const int32_t* count_per_seq;  // may be null; sequence b writes only its first count_per_seq[b] rows
   const float* rope_cos;     // bf16 append: non-null = keys arrive unrotated and are turned to their step's
   const float* rope_sin;     //   position on the way into the store ([positions][D/2] tables)
+};
+
+// What only the staging of a prompt on a ring store needs (bf16): the groups' images go here,
+// [batch][Hkv][stage_groups] groups from that of step t on, not into the pool, which is only read.
+struct StageParams : StoreParams {
+  void* k_stage;
+  void* v_stage;
+  int32_t stage_groups;
 };
 
 struct AttnParams {
@@ -163,7 +168,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
 // ---- launchers (defined next to their kernels) -------------------------------
 hipError_t launch_append(const StoreParams& p, const void* k_new, const void* v_new, int D,
                          int dtype, hipStream_t stream);
-hipError_t launch_stage(const StoreParams& p, const void* k_new, const void* v_new, int D, hipStream_t stream);
+hipError_t launch_stage(const StageParams& p, const void* k_new, const void* v_new, int D, hipStream_t stream);
 hipError_t launch_gather(const StoreParams& p, void* k_out, void* v_out, int D, int dtype, int j0,
                          int count, hipStream_t stream);
 hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_splits, int waves,

@@ -46,7 +46,7 @@ static hipError_t attend(const char* what, const AttnParams& p, int grid_splits,
 hipError_t launch_append(const StoreParams& p, const void*, const void*, int, int, hipStream_t) {
   return say("append t=%d count=%d", p.t, p.count);
 }
-hipError_t launch_stage(const StoreParams& p, const void*, const void*, int, hipStream_t) {
+hipError_t launch_stage(const StageParams& p, const void*, const void*, int, hipStream_t) {
   return say("stage t=%d count=%d groups=%d", p.t, p.count, p.stage_groups);
 }
 hipError_t launch_gather(const StoreParams&, void*, void*, int, int, int j0, int count, hipStream_t) {
