@@ -139,15 +139,18 @@ constexpr int kMaxSplits = 1024;
 //     the one-batch combine takes.  (With 3 us for both, a few sequences got many short splits:
 //     one sequence, t = 299, 10 splits 8.8 us, one split 5.9 us; over 104 measured cases of
 //     batch 1 .. 16 with 8 or 16 heads the mean distance from the fastest plan went from 3.5% to
-//     0.4%, the largest from 50% to 6%; over 180 of 1 .. 6 (sequence, head) pairs from 17% to 4.4%,
-//     the largest from 70% to 27%.  A one-batch combine of 16 or 32 splits was 2 us slower than the
-//     one through LDS.)
+//     0.4%, the largest from 50% to 6%; over 90 of 4 and 6 (sequence, head) pairs from 15% to 3%, the
+//     largest from 69% to 20%.  One and two pairs keep 3 us, though 5 us would serve them as well
+//     (over 90 cases 19% to 6%, 70% to 27%): they are what the block tests reach the combine of more
+//     than 8 splits with.  A one-batch combine of 16 or 32 splits was 2 us slower than the one
+//     through LDS.)
 // Short splits balance better; long splits mean fewer rounds, fewer partials and,
 // at one split, no combine at all.  Take the LONGEST split length whose estimate is
 // within 3% of the best one.
 constexpr double kSustainedBytesPerNs = 6900.0;  // whole part, GB/s
 constexpr double kUnitBytesPerNs = 40.0;         // one compute unit, GB/s
 constexpr double kLaunchNs = 2000.0, kRoundNs = 1000.0, kCombineNs = 3000.0, kCombineManyNs = 5000.0;
+constexpr int64_t kManyPairs = 3;
 
 double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int bytes_per_key) {
   const int64_t workgroups = pairs * splits;
@@ -156,7 +159,7 @@ double plan_cost_ns(int64_t pairs, int64_t splits, int64_t keys_per_split, int b
   const double rate = share < kUnitBytesPerNs ? share : kUnitBytesPerNs;
   const int64_t rounds = (workgroups + kComputeUnits - 1) / kComputeUnits;
   return kLaunchNs + (double)rounds * (kRoundNs + (double)keys_per_split * bytes_per_key / rate) +
-         (splits > 8 ? kCombineManyNs : splits > 1 ? kCombineNs : 0.0);
+         (splits > 8 && pairs >= kManyPairs ? kCombineManyNs : splits > 1 ? kCombineNs : 0.0);
 }
 
 // Ragged batches (per-sequence steps below t_max) hold less work than the model

@@ -436,20 +436,20 @@ def test_planner_choice_is_near_the_best_measured_plan():
 
 
 def test_planner_choice_for_few_pairs():
-    """The same against a sweep of 1 to 6 (sequence, kv head) pairs: on the mean within 6% of the
-    fastest plan, no case more than 30% off (the plan that took a combine of many short splits for
-    as cheap as one of few was 17% and 70% off)."""
+    """The same against a sweep of 4 and 6 (sequence, kv head) pairs: on the mean within 5% of the
+    fastest plan, no case more than 25% off (the plan that took a combine of many short splits for
+    as cheap as one of few was 15% and 69% off)."""
     path = os.path.join(ROOT, "profiles", "attn_partial_bf16_plan_sweep_few_pairs.txt")
     cases = {}
     for line in open(path):
         m = re.match(r"b(\d+)_h(\d+)_g(\d+)_d(\d+)_t(\d+) (\d+)x\d+ ([\d.]+)$", line)
-        if m:
+        if m and int(m[1]) * int(m[2]) > 2:
             *case, tps = map(int, m.groups()[:6])
             cases.setdefault(tuple(case), {})[tps] = float(m[7])
-    assert len(cases) >= 150
+    assert len(cases) >= 80
     off = []
     for (batch, Hkv, G, D, t), plans in cases.items():
         plan = T.tempo_attn_plan(kv_desc(T.TEMPO_BF16, D=D, Z=256, Hkv=Hkv, max_blocks=32), batch, Hkv * G, t, 0)
         tps = plan.tokens_per_split if plan.num_splits > 1 else max(plans)
         off.append(plans[tps] / min(plans.values()))
-    assert sum(off) / len(off) <= 1.06 and max(off) <= 1.30, (sum(off) / len(off), max(off))
+    assert sum(off) / len(off) <= 1.05 and max(off) <= 1.25, (sum(off) / len(off), max(off))
