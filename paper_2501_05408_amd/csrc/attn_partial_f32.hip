@@ -24,6 +24,8 @@
 // and values) took 117.6 us a step; this kernel 49 us.  A prompt of 512 steps, 8/2 heads of 64,
 // in blocks of 128 columns 203 us, as one launch of this kernel 17.5 us.  Blocks and prompts: 64 products of 32
 // cycles per group at D = 128, half of them padding when a tile holds few columns.
+#include <type_traits>
+
 #include "attn_bf16_common.h"
 
 namespace tempo {
@@ -302,31 +304,53 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   }
   __syncthreads();
 
-  for (int idx = threadIdx.x; idx < ncols * (D / 4); idx += blockDim.x) {
-    const int jcol = idx / (D / 4), d = 4 * (idx - jcol * (D / 4));
-    float M = -INFINITY;
-    for (int w = 0; w < nwaves; ++w) M = fmaxf(M, sm_m[w * 16 + jcol]);
-    f32x4 num = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-    for (int w = 0; w < nwaves; ++w) {
-      const float mw = sm_m[w * 16 + jcol];
-      if (mw == -INFINITY) continue;  // saw no key of this column (all wavefronts: the partial is (-inf, 0, 0))
-      const float wgt = exp2f(mw - M);
-      num += wgt * *reinterpret_cast<const f32x4*>(sm_acc + (w * ncols + jcol) * LD + d);
-      den += wgt * sm_l[w * 16 + jcol];
-    }
-    const int jc = (col0 + jcol) / p.G, jg = col0 + jcol - jc * p.G;
-    if (p.direct) {
-      const int64_t orow = ((int64_t)b * p.io_steps + jc) * p.Hq + (int64_t)hkv * p.G + jg;
-      *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + orow * D + d) = num / den;
-    } else {
-      const int64_t part = (((int64_t)b * p.queries + jc) * p.Hq + (int64_t)hkv * p.G + jg) * p.num_splits + split;
-      *reinterpret_cast<f32x4*>(p.ws_acc + part * D + d) = num;
-      if (d == 0) {
-        p.ws_ml[part * 2] = M;
-        p.ws_ml[part * 2 + 1] = den;
+  // All wavefronts' values of an element in one batch of reads: a loop over them is a chain of LDS
+  // round trips (24/8 heads of 128, 1 sequence, t = 150, 8 wavefronts: 10.0 us a step with the loop, 9.5 us; 1 head
+  // group of 16, t = 299: 11.4 us, 10.3 us).
+  auto merge = [&](auto waves) {
+    for (int idx = threadIdx.x; idx < ncols * (D / 4); idx += blockDim.x) {
+      const int jcol = idx / (D / 4), d = 4 * (idx - jcol * (D / 4));
+      constexpr int NW = decltype(waves)::value;
+      float mw[NW], lw[NW];
+      f32x4 aw[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        mw[w] = sm_m[w * 16 + jcol];
+        lw[w] = sm_l[w * 16 + jcol];
+        aw[w] = *reinterpret_cast<const f32x4*>(sm_acc + (w * ncols + jcol) * LD + d);
+      }
+      float M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
+      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        // saw no key of this column (all wavefronts: the partial is (-inf, 0, 0))
+        const bool none = mw[w] == -INFINITY;
+        const float wgt = none ? 0.f : exp2f(mw[w] - M);
+        num += wgt * (none ? f32x4{0.f, 0.f, 0.f, 0.f} : aw[w]);
+        den += wgt * (none ? 0.f : lw[w]);
+      }
+      const int jc = (col0 + jcol) / p.G, jg = col0 + jcol - jc * p.G;
+      if (p.direct) {
+        const int64_t orow = ((int64_t)b * p.io_steps + jc) * p.Hq + (int64_t)hkv * p.G + jg;
+        *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + orow * D + d) = num / den;
+      } else {
+        const int64_t part = (((int64_t)b * p.queries + jc) * p.Hq + (int64_t)hkv * p.G + jg) * p.num_splits + split;
+        *reinterpret_cast<f32x4*>(p.ws_acc + part * D + d) = num;
+        if (d == 0) {
+          p.ws_ml[part * 2] = M;
+          p.ws_ml[part * 2 + 1] = den;
+        }
       }
     }
+  };
+  switch (nwaves) {
+    case 1: merge(std::integral_constant<int, 1>{}); break;
+    case 2: merge(std::integral_constant<int, 2>{}); break;
+    case 4: merge(std::integral_constant<int, 4>{}); break;
+    default: merge(std::integral_constant<int, 8>{});
   }
 }
 
