@@ -118,7 +118,9 @@ typedef struct tempo_kv {
 /* How a step's visible range is cut into independent partial-attention work
  * items ("splits"), each a run of tokens_per_split consecutive key positions
  * aligned to a multiple of tokens_per_split; one workgroup of `waves` 64-lane
- * wavefronts handles the query group of one (sequence, kv head, split). */
+ * wavefronts handles the query group of one (sequence, kv head, split).  (fp32: of one
+ * query head over short ranges, and with twice the wavefronts where a split is planned
+ * with one for each 32 of its at most 64 keys.) */
 typedef struct tempo_plan {
   int32_t tokens_per_split;   /* power of two, >= 32 */
   int32_t num_splits;         /* splits launched per (sequence, kv head) for the longest range */

@@ -123,6 +123,24 @@ int32_t splits_bound(int32_t t, int32_t window, int tps_log2) {
 constexpr int kComputeUnits = 256;
 constexpr int kMaxSplits = 1024;
 
+// Does the vector kernel (one workgroup per query head) take an fp32 step instead of the matrix-core
+// one (a query group and 16 columns per workgroup)?  Over short ranges, while the heads' separate
+// reads of a group's keys and values (through different dies' caches, so not shared unless the group
+// is wide) stay cheap: us a call, vector / matrix, at D = 128:
+//   1 sequence, 24/8 heads, 81 keys 6.7 / 7.7, 151 keys 8.3 / 9.4, 200 keys 9.1 / 9.2
+//   16 sequences, 24/8 heads, 48 keys 6.5 / 7.1 (18k key rows read), 81 keys 9.1 / 8.3 (31k)
+//   16 sequences, 16/1 heads, 200 keys 9.5 / 11.3 (51k), 256 keys 12.6 / 11.6 (66k)
+// and always where no head shares a read (16 sequences of 8/8 heads, 1501 keys 34.5 / 44.1).  At D = 64
+// the matrix-core kernel has half the products: 1 sequence, 8/2 heads, 8 keys 3.4 / 3.9, 64 keys 6.0 / 5.2.
+bool f32_step_on_vector_alu(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window, int32_t queries) {
+  if (kv->dtype != TEMPO_F32 || queries != 1) return false;
+  const int64_t keys = window > 0 && window < (int64_t)t + 1 ? window : (int64_t)t + 1;
+  const int32_t G = Hq / kv->num_kv_heads;
+  if (kv->head_dim == 128 && G == 1) return true;
+  const int64_t shared = G < 8 ? 8 : (G > 32 ? 32 : G);
+  return keys <= (kv->head_dim == 128 ? 192 : 24) && batch * keys * Hq <= 3200 * shared;
+}
+
 // Split planning: a small time model of the launch, in nanoseconds, with constants
 // measured on MI355X.
 //   - Workgroups are handed to compute units round-robin, so the busiest unit gets
@@ -170,7 +188,9 @@ void make_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t_max, int
                bool ragged, int32_t queries, int64_t max_splits, tempo_plan* plan) {
   // one workgroup serves a query group; fp32 takes 16 (step, head) columns per workgroup
   const int64_t columns = (int64_t)queries * (Hq / kv->num_kv_heads);
-  const int64_t pairs = (int64_t)batch * kv->num_kv_heads * (kv->dtype == TEMPO_F32 ? (columns + 15) / 16 : 1);
+  const int64_t pairs = f32_step_on_vector_alu(kv, batch, Hq, t_max, window, queries)
+                            ? (int64_t)batch * Hq
+                            : (int64_t)batch * kv->num_kv_heads * (kv->dtype == TEMPO_F32 ? (columns + 15) / 16 : 1);
   const int64_t len = (window > 0 && window < (int64_t)t_max + 1) ? window : (int64_t)t_max + 1;
   const int bytes_per_key = 2 * kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);  // K and V of one head
   const int k_max = ragged ? 10 : 30;
@@ -368,6 +388,14 @@ int check_attn(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t
   return TEMPO_OK;
 }
 
+// Wavefronts of the fp32 matrix-core kernel, whose groups have 16 keys where a plan's have 32: a split of
+// 32 or 64 keys that is planned with a wavefront for every 32 gets one for every 16, because a wavefront's
+// second group costs such a split about as much as its first (24/8 heads of 128, 1 sequence: splits of 32
+// keys at t = 700 11.1 us with 1 wavefront, 9.3 us with 2; one split at t = 63 7.2 us with 2, 6.3 us with 4).
+int f32_waves(const tempo_plan& plan) {
+  return plan.waves <= 2 && plan.waves * 32 == plan.tokens_per_split ? 2 * plan.waves : plan.waves;
+}
+
 // out != nullptr and a single split: the launch writes `out` itself; otherwise it
 // writes partials and the caller launches the combine.
 // k_new/v_new != nullptr: step t's key/value are appended inside the same launch.
@@ -391,7 +419,9 @@ int do_partial(const tempo_kv* kv, const void* q, const void* k_new, const void*
     return launch_status(launch_block_bf16(p, batch, kv->head_dim, gs, stream), "attn_block_partial");
   const hipError_t e = kv->dtype == TEMPO_BF16
                            ? launch_partial_bf16(p, batch, kv->head_dim, gs, plan->waves, stream)
-                           : launch_partial_f32(p, batch, kv->head_dim, gs, plan->waves, stream);
+                       : f32_step_on_vector_alu(kv, batch, Hq, t, window, queries)
+                           ? launch_step_f32(p, batch, kv->head_dim, gs, plan->waves, stream)
+                           : launch_partial_f32(p, batch, kv->head_dim, gs, f32_waves(*plan), stream);
   return launch_status(e, "attn_decode_partial");
 }
 

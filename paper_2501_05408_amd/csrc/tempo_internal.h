@@ -181,6 +181,8 @@ hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_spl
 hipError_t launch_partial_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                               hipStream_t stream);
 
+hipError_t launch_step_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves, hipStream_t stream);
+
 hipError_t launch_rope_rotate(const float* rope_cos, const float* rope_sin, const void* x, void* y,
                               int dtype, int batch, int heads, int D, int t, const int32_t* t_per_seq,
                               hipStream_t stream);

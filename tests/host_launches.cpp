@@ -69,6 +69,9 @@ hipError_t launch_block_bf16(const AttnParams& p, int, int, int grid_splits, hip
 hipError_t launch_partial_f32(const AttnParams& p, int, int, int grid_splits, int waves, hipStream_t) {
   return attend("partial_f32", p, grid_splits, waves);
 }
+hipError_t launch_step_f32(const AttnParams& p, int, int, int grid_splits, int waves, hipStream_t) {
+  return attend("step_f32", p, grid_splits, waves);
+}
 hipError_t launch_rope_rotate(const float*, const float*, const void*, void*, int, int, int, int, int t, const int32_t*,
                               hipStream_t) {
   return say("rope_rotate t=%d", t);

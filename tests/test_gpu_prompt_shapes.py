@@ -250,3 +250,44 @@ def test_appends_to_the_same_groups_on_two_streams_keep_each_others_rows():
             torch.cuda.synchronize()
             kg, vg = st.gather(0, steps)
             assert torch.equal(kg, Kd) and torch.equal(vg, Vd)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,Z,steps,window", [(1, 2, 3, 128, 16, 200, 0), (2, 1, 1, 128, 64, 420, 0), (3, 2, 4, 64, 8, 40, 0),
+                                                      (1, 1, 17, 128, 4, 210, 0), (2, 2, 3, 128, 32, 260, 70), (16, 2, 8, 128, 64, 110, 0)])
+@pytest.mark.parametrize("rope", [False, True])
+def test_f32_steps_where_the_kernel_changes(B, Hkv, G, D, Z, steps, window, rope):
+    """Every step of sequences that grow past the ranges the vector kernel takes (24 keys at D = 64,
+    192 at D = 128 or fewer for many heads, all where no head shares a read), with the write fused in."""
+    Hq, dtype = Hkv * G, T.TEMPO_F32
+    q, K, V = host_inputs(78, B, steps, Hq, Hkv, D, dtype)
+    table, nb = random_table(78, B, (steps - 1) // Z + 1)
+    st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, dtype, num_blocks=nb, block_table=table, fill="nan")
+    qd, Kd, Vd = dev(q, dtype), dev(K, dtype), dev(V, dtype)
+    half = D // 2
+    angle = np.arange(steps)[:, None] * 500000.0 ** (-np.arange(half) / half)
+    if rope:
+        st.set_rope(torch.from_numpy(np.cos(angle)).float().to(DEV), torch.from_numpy(np.sin(angle)).float().to(DEV))
+    out = torch.empty((steps, B, Hq, D), dtype=torch.float32, device=DEV)
+    for t in range(steps):
+        k_t, v_t = Kd[:, t].contiguous(), Vd[:, t].contiguous()
+        if rope:
+            st.rope_step(qd[t], k_t, v_t, out[t], t, window)
+        elif window:
+            st.step_window(qd[t], k_t, v_t, out[t], t, window)
+        else:
+            st.step_causal(qd[t], k_t, v_t, out[t], t)
+    got = np64(out)
+
+    def turned(x, at):                                   # [..., D] rows of steps `at`, in 64 bits
+        c, s = np.cos(angle).astype(np.float32).astype(np.float64)[at], np.sin(angle).astype(np.float32).astype(np.float64)[at]
+        lo, hi = x[..., :half], x[..., half:]
+        return np.concatenate([lo * c - hi * s, hi * c + lo * s], axis=-1)
+
+    q64, K64, V64 = q.astype(np.float64), K.astype(np.float64), V.astype(np.float64)
+    if rope:
+        q64 = np.stack([turned(q64[t], t) for t in range(steps)])
+        K64 = np.stack([turned(K64[:, t], t) for t in range(steps)], axis=1)
+    for t in range(0, steps, 3):
+        assert_close(got[t], oracle.attend(q64[t], K64, V64, t, window, 1.0 / np.sqrt(D)), dtype, f"fp32 step {t} w={window} rope={rope}")
+    kg, vg = st.gather(0, steps)
+    assert torch.equal(vg, Vd) and (rope or torch.equal(kg, Kd))

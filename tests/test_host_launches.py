@@ -67,7 +67,7 @@ def assert_all_keys_launched(launches, G, t, count):
     share a workgroup reach from the first key of the first of them to the last step."""
     step = t
     for name, f in launches:
-        if name not in ("prompt", "prompt_staged", "block_bf16", "partial_bf16", "partial_f32"):
+        if name not in ("prompt", "prompt_staged", "block_bf16", "partial_bf16", "partial_f32", "step_f32"):
             continue
         assert f["t"] == step
         together = 32 * f["waves"] // G if name.startswith("prompt") else f["queries"]
@@ -126,3 +126,21 @@ def test_windows_near_the_largest_integer_do_not_overflow(tmp_path, call):
     run = subprocess.run([sys.executable, "-c", code], cwd=os.path.join(ROOT, "tests"),
                          env={**os.environ, "PYTHONPATH": ROOT}, capture_output=True, text=True)
     assert run.returncode == 0, run.stderr
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,batch,keys,kernel", [
+    (24, 8, 128, 1, 192, "step_f32"), (24, 8, 128, 1, 193, "partial_f32"), (24, 8, 128, 16, 66, "step_f32"),
+    (24, 8, 128, 16, 67, "partial_f32"), (8, 2, 64, 1, 24, "step_f32"), (8, 2, 64, 1, 25, "partial_f32"),
+    (8, 8, 128, 16, 5000, "step_f32"), (16, 1, 128, 16, 192, "step_f32"), (8, 8, 64, 16, 5000, "partial_f32")])
+@pytest.mark.parametrize("windowed", [False, True])
+def test_kernel_of_an_f32_step(lib, Hq, Hkv, D, batch, keys, kernel, windowed):
+    t = 20000 if windowed else keys - 1
+    kv = store(T.TEMPO_F32, Hkv, D, 64, t // 64 + 1)
+    lib.host_launches_take()
+    rc = lib.tempo_attn_decode_window(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, batch, Hq, t, None, keys, 0.125, SOMEWHERE,
+                                      1 << 50, None)
+    assert rc == T.TEMPO_OK
+    (name, f), *_ = taken(lib)
+    lo = t - keys + 1
+    assert name == kernel and f["grid_splits"] >= (t >> f["tps_log2"]) - (lo >> f["tps_log2"]) + 1
+    assert f["waves"] in (1, 2, 4, 8)
