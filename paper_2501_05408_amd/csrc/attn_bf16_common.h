@@ -158,6 +158,128 @@ __device__ inline void value_masks(int grp, int v_lo, int v_hi, int lane, uint32
   }
 }
 
+// ---- what a workgroup of the block and prompt kernels does -----------------------------
+// Shared by attn_block_bf16.hip (16 columns per wavefront) and attn_prefill_bf16.hip (32): the
+// (step, head) columns of a block of query steps, column = c*G + g, against one split of the
+// block's key range.
+
+// Steps per workgroup of `columns` columns for a query group of G heads.
+__host__ __device__ inline int block_steps_of(int G, int columns) { return columns / G; }
+
+struct BlockWork {
+  int b, hkv;            // sequence, kv head
+  int c0, steps, ncols;  // first step of the block within the call, its steps and columns
+  int t_first, t_last;   // its first and last step
+  int split;             // of the block's key range
+  int start, end;        // keys of that range in the split ...
+  int g_first, g_last;   // ... and the 32-slot groups they lie in
+  bool any;              // uniform over the workgroup; false: nothing to do
+};
+
+// Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by
+// linear index; the blocks of one (sequence, head) read the same keys/values, so each die is given
+// a contiguous run of the work list instead: workgroup L takes item (L mod 8) * (n / 8) + L / 8
+// (remainder items spread over the first dies), and the blocks that run together on a die share
+// its L2.  Blocks come longest range first, splits newest first as in the decode kernel.
+// kBlocks: the call's steps are cut into blocks of `columns` columns; else they are one block.
+template <bool kBlocks>
+__device__ inline BlockWork block_work(const AttnParams& p, int columns) {
+  BlockWork w;
+  const unsigned nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
+  const unsigned linear = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
+  const unsigned die = linear & 7u, share = total >> 3, extra = total & 7u;
+  const unsigned item = die * share + (die < extra ? die : extra) + (linear >> 3);
+  const unsigned ix = item % nx, iyz = item / nx;
+  w.hkv = (int)(iyz % ny);
+  w.b = (int)(iyz / ny);
+  int zsplit = (int)ix;                                       // 0 unless the key range is split
+  w.c0 = 0;
+  w.steps = p.queries;
+  w.any = true;
+  if (kBlocks) {
+    const int QB = block_steps_of(p.G, columns);
+    const int nblocks = (p.queries + QB - 1) / QB;
+    zsplit = (int)(ix / nblocks);
+    w.c0 = (nblocks - 1 - (int)(ix % nblocks)) * QB;
+    // steps of this sequence in the call: all of them, or its own count
+    int steps_b = p.queries;
+    if (p.count_per_seq) {
+      const int n = ((const_i32_ptr)p.count_per_seq)[w.b];
+      steps_b = n < 0 ? 0 : (n < p.queries ? n : p.queries);
+    }
+    w.any = w.c0 < steps_b;
+    w.steps = steps_b - w.c0 < QB ? steps_b - w.c0 : QB;
+  }
+  w.ncols = w.steps * p.G;
+  int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[w.b] : p.t; // first step of the call for this sequence
+  t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
+  w.t_first = t_base + w.c0;
+  w.t_last = w.t_first + w.steps - 1;
+  const int lo = (p.window > 0 && w.t_first - p.window + 1 > 0) ? w.t_first - p.window + 1 : 0;
+  const int chunk0 = lo >> p.tps_log2;                        // (kWholeRange when not split)
+  const int nchunks = (w.t_last >> p.tps_log2) - chunk0 + 1;
+  w.any = w.any && zsplit < nchunks;
+  w.split = nchunks - 1 - zsplit;
+  const int cs = (chunk0 + w.split) << p.tps_log2, ce = split_end(chunk0 + w.split, p.tps_log2);
+  w.start = lo > cs ? lo : cs;
+  w.end = w.t_last < ce ? w.t_last : ce;
+  w.g_first = w.start >> 5;
+  w.g_last = w.end >> 5;
+  return w;
+}
+
+// Wavefront-uniform bounds over one wavefront's columns, cut to the split.
+struct WaveBounds {
+  bool idle;             // a wavefront beyond the block's columns
+  int hi, hi_min;        // newest key any / all of its columns see
+  int lo_first, lo_last; // first key any / all of them see
+};
+__device__ inline WaveBounds wave_bounds(const AttnParams& p, const BlockWork& w, int first_col, int columns) {
+  WaveBounds o;
+  const int last_col = (first_col + columns - 1) < w.ncols - 1 ? (first_col + columns - 1) : w.ncols - 1;
+  o.idle = first_col >= w.ncols;
+  const int own_hi = w.t_first + (o.idle ? 0 : last_col / p.G);
+  const int own_hi_min = w.t_first + (o.idle ? 0 : first_col / p.G);
+  const int own_lo_first = (p.window > 0 && own_hi_min - p.window + 1 > 0) ? own_hi_min - p.window + 1 : 0;
+  const int own_lo_last = (p.window > 0 && own_hi - p.window + 1 > 0) ? own_hi - p.window + 1 : 0;
+  o.hi = own_hi < w.end ? own_hi : w.end;
+  o.hi_min = own_hi_min < w.end ? own_hi_min : w.end;
+  o.lo_first = own_lo_first > w.start ? own_lo_first : w.start;
+  o.lo_last = own_lo_last > w.start ? own_lo_last : w.start;
+  return o;
+}
+
+// One lane's column (unused columns behave like the block's last step with q = 0).
+struct LaneColumn {
+  int cq, gq;            // step within the block, head within the group
+  int step;              // the column's own step: its newest key and its position
+  int lo, hi;            // its keys in the split
+};
+__device__ inline LaneColumn lane_column(const AttnParams& p, const BlockWork& w, int col) {
+  LaneColumn o;
+  o.cq = col < w.ncols ? col / p.G : w.steps - 1;
+  o.gq = col < w.ncols ? col - o.cq * p.G : 0;
+  o.step = w.t_first + o.cq;
+  o.hi = o.step < w.end ? o.step : w.end;
+  const int lo_own = (p.window > 0 && o.step - p.window + 1 > 0) ? o.step - p.window + 1 : 0;
+  o.lo = lo_own > w.start ? lo_own : w.start;
+  return o;
+}
+
+// Slots before the range's first key and beyond the block's last step may be unwritten (NaN): the
+// 0 mask under the sums is applied once, to the value units of the range's first and last group,
+// in LDS, by the wavefront that copied the unit and after its copy has landed (the copy keeps the
+// lane of every 16-byte piece, so a lane masks the slots its consumers will read from it).  Masked
+// slots inside the range hold written data and weight 0.  cut_head: the first group needs it,
+// cut_tail: the last one (uniform over the workgroup).
+__device__ inline bool cut_head(const BlockWork& w) { return (w.start & 31) != 0; }
+__device__ inline bool cut_tail(const BlockWork& w) { return (w.g_last << 5) + 31 > w.t_last; }
+__device__ inline void mask_piece(u32x4* piece, const uint32_t* keep) {
+  u32x4 v = *piece;
+  v.x &= keep[0]; v.y &= keep[1]; v.z &= keep[2]; v.w &= keep[3];
+  *piece = v;
+}
+
 // Maximum over the four lanes {l, l^16, l^32, l^48} that hold one column's logits,
 // left in all four.  Two lane-swap instructions of gfx950 instead of two trips
 // through the LDS permute unit: v_permlane16_swap exchanges the odd 16-lane rows of

@@ -78,6 +78,8 @@ __device__ inline bf16x8 softmax_weights(const float* x, float scale, float ref)
   return pa;
 }
 
+constexpr int kWaveColumns = 16;
+
 // NW wavefronts per workgroup, 16 columns per wavefront.
 //
 // The loop is software-pipelined by one group: iteration n computes the logits of group
@@ -102,68 +104,30 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
   u32x4* const lds_v = lds + 2 * KU * 64;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // Which (split, kv head, sequence) this workgroup takes.  Workgroups are handed to the 8
-  // accelerator dies (XCDs, each with its own L2) round-robin by linear index; each die is
-  // given a contiguous run of the work list instead: workgroup L takes item
-  // (L mod 8) * (n / 8) + L / 8 (remainder items spread over the first dies).
-  const unsigned nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
-  const unsigned linear = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
-  const unsigned die = linear & 7u, share = total >> 3, extra = total & 7u;
-  const unsigned item = die * share + (die < extra ? die : extra) + (linear >> 3);
-  const unsigned iyz = item / nx;
-  const int zsplit = (int)(item % nx);
-  const int hkv = (int)(iyz % ny), b = (int)(iyz / ny);
-  const int C = p.queries;                                          // steps in the block
-  const int ncols = C * p.G;
-  int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[b] : p.t; // first step of the block for this sequence
-  t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
-  const int t_first = t_base, t_last = t_first + C - 1;
-  const int lo = (p.window > 0 && t_first - p.window + 1 > 0) ? t_first - p.window + 1 : 0;
-  // The split of the key range this workgroup walks, newest split first as in the decode kernel.
-  const int chunk0 = lo >> p.tps_log2;
-  const int nchunks = (t_last >> p.tps_log2) - chunk0 + 1;
-  if (zsplit >= nchunks) return;                                    // uniform over the workgroup
-  const int split = nchunks - 1 - zsplit;
-  const int cs = (chunk0 + split) << p.tps_log2, ce = split_end(chunk0 + split, p.tps_log2);
-  const int start = lo > cs ? lo : cs;
-  const int end = t_last < ce ? t_last : ce;
-  const int g_first = start >> 5, g_last = end >> 5;
-
-  // wavefront-uniform bounds over this wavefront's 16 columns, cut to the split:
-  // the groups it has any work in, and those no column cuts
-  const int first_col = 16 * wave;
-  const int last_col = (first_col + 15) < ncols - 1 ? (first_col + 15) : ncols - 1;
-  const bool idle = first_col >= ncols;                             // a wavefront beyond the block's columns
-  const int own_hi = t_first + (idle ? 0 : last_col / p.G);         // newest key any of its columns sees
-  const int own_hi_min = t_first + (idle ? 0 : first_col / p.G);    // newest key ALL of its columns see
-  const int own_lo_first = (p.window > 0 && own_hi_min - p.window + 1 > 0) ? own_hi_min - p.window + 1 : 0;
-  const int own_lo_last = (p.window > 0 && own_hi - p.window + 1 > 0) ? own_hi - p.window + 1 : 0;
-  const int w_hi = own_hi < end ? own_hi : end, w_hi_min = own_hi_min < end ? own_hi_min : end;
-  const int w_lo_first = own_lo_first > start ? own_lo_first : start;
-  const int w_lo_last = own_lo_last > start ? own_lo_last : start;
+  const BlockWork work = block_work<false>(p, kWaveColumns * NW);
+  if (!work.any) return;                       // uniform over the workgroup, before any barrier
+  const int b = work.b, hkv = work.hkv, c0 = work.c0, ncols = work.ncols, split = work.split;
+  const int t_last = work.t_last, start = work.start, g_first = work.g_first, g_last = work.g_last;
+  const int first_col = kWaveColumns * wave;
+  const WaveBounds own = wave_bounds(p, work, first_col, kWaveColumns);
   // has this wavefront any work in group g / does some column's range cut group g?  (wave-uniform)
-  auto active = [&](int g) { return !idle && (g << 5) <= w_hi && (g << 5) + 31 >= w_lo_first; };
-  auto is_cut = [&](int g) { return (g << 5) < w_lo_last || (g << 5) + 31 > w_hi_min; };
+  auto active = [&](int g) { return !own.idle && (g << 5) <= own.hi && (g << 5) + 31 >= own.lo_first; };
+  auto is_cut = [&](int g) { return (g << 5) < own.lo_last || (g << 5) + 31 > own.hi_min; };
 
-  // This lane's column (unused columns behave like the block's last step with q = 0),
-  // its range, its query operand, its softmax state.
-  const int col = first_col + (lane & 15);
-  const int cq = col < ncols ? col / p.G : C - 1;
-  const int gq = col < ncols ? col - cq * p.G : 0;
-  const int step = t_first + cq;               // the column's own step: its newest key and its position
-  const int hi_col = step < end ? step : end;
-  const int lo_own = (p.window > 0 && step - p.window + 1 > 0) ? step - p.window + 1 : 0;
-  const int lo_col = lo_own > start ? lo_own : start;
+  // This lane's column, its query operand, its softmax state.
+  const LaneColumn mine = lane_column(p, work, first_col + (lane & 15));
+  const int cq = mine.cq, gq = mine.gq, step = mine.step, lo_col = mine.lo, hi_col = mine.hi;
+  const bool used = first_col + (lane & 15) < ncols;
   u32x4 qreg[KS];
   {
     const int c = lane >> 4;
     const uint16_t* qp = static_cast<const uint16_t*>(p.q) +
-                         (((int64_t)b * p.io_steps + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 8 * c;
+                         (((int64_t)b * p.io_steps + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 8 * c;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const u32x4 zero = {0u, 0u, 0u, 0u};
       const u32x4 v = *reinterpret_cast<const u32x4*>(qp + 32 * s);
-      qreg[s] = col < ncols ? v : zero;
+      qreg[s] = used ? v : zero;
     }
     if (kRope) rotate_query<D>(p, step, lane, qreg);  // queries arrive unrotated
   }
@@ -213,23 +177,14 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
                                          (lds_ptr)(lds_v + ((gv & 1) * DT + u) * 64), 16, 0, kCachePolicy);
     }
   };
-  // Slots before the range's first key and beyond the block's last step may be unwritten
-  // (NaN): the 0 mask under the sums is applied once, to the value units of the range's first
-  // and last group, in LDS, by the wavefront that copied the unit and after its copy has landed
-  // (the copy keeps the lane of every 16-byte piece, so a lane masks the slots its consumers
-  // will read from it).  Masked slots inside the range hold written data and weight 0.
-  const bool head = (start & 31) != 0, tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
+  const bool head = cut_head(work), tail = cut_tail(work);
   auto mask_values = [&](int gv) {  // gv == g_first, and head, or gv == g_last, and tail
     uint32_t keep[4];
     value_masks(gv, start, t_last, lane, keep);
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int u = wave + NW * i - KU;
-      if (u < 0 || u >= DT) continue;
-      u32x4* at = lds_v + ((gv & 1) * DT + u) * 64 + lane;
-      u32x4 v = *at;
-      v.x &= keep[0]; v.y &= keep[1]; v.z &= keep[2]; v.w &= keep[3];
-      *at = v;
+      if (u >= 0 && u < DT) mask_piece(lds_v + ((gv & 1) * DT + u) * 64 + lane, keep);
     }
   };
   // End of an iteration: wait until this wavefront's copies have landed, fix up what it
@@ -316,12 +271,12 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
       const int jc = j / p.G, jg = j - jc * p.G;
       if (p.direct) {
         __bf16* orow = static_cast<__bf16*>(p.out) +
-                       (((int64_t)b * p.io_steps + jc) * p.Hq + (int64_t)hkv * p.G + jg) * D;
+                       (((int64_t)b * p.io_steps + c0 + jc) * p.Hq + (int64_t)hkv * p.G + jg) * D;
         const float inv = 1.0f / l_j;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) orow[16 * dt + n] = (__bf16)(acc[dt][r] * inv);
       } else {
-        const int64_t row = ((int64_t)b * p.queries + jc) * p.Hq + (int64_t)hkv * p.G + jg;
+        const int64_t row = ((int64_t)b * p.queries + c0 + jc) * p.Hq + (int64_t)hkv * p.G + jg;
         const int64_t part = row * p.num_splits + split;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) p.ws_acc[part * D + 16 * dt + n] = acc[dt][r];

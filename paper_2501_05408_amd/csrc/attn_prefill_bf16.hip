@@ -133,9 +133,7 @@ __device__ inline void mask_tile(int grp, int lo_col, int hi_col, int lane, f32x
   }
 }
 
-// Columns per wavefront, and steps per workgroup for a query group of G heads.
 constexpr int kWaveColumns = 32;
-__host__ __device__ inline int prefill_block_steps(int G, int waves) { return (kWaveColumns * waves) / G; }
 
 template <int D, int NW, int NBUF, bool kRope, bool kStaged>
 __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) {
@@ -151,70 +149,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   extern __shared__ u32x4 lds[];              // [NBUF][UNITS][64] x 16 bytes: a group's keys, then its values
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int QB = prefill_block_steps(p.G, NW);
-  const int nblocks = (p.queries + QB - 1) / QB;
-  // Which (block, split, kv head, sequence) this workgroup takes.  Workgroups are handed
-  // to the 8 accelerator dies (XCDs, each with its own L2) round-robin by linear index;
-  // the blocks of one (sequence, head) read the same keys/values, so each die is given a
-  // contiguous run of the work list instead: workgroup L takes item (L mod 8) * (n / 8)
-  // + L / 8 (remainder items spread over the first dies), and the blocks that run
-  // together on a die share its L2.
-  const unsigned nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
-  const unsigned linear = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
-  const unsigned die = linear & 7u, share = total >> 3, extra = total & 7u;
-  const unsigned item = die * share + (die < extra ? die : extra) + (linear >> 3);
-  const unsigned ix = item % nx, iyz = item / nx;
-  const int qb = nblocks - 1 - (int)(ix % nblocks);           // longest range first
-  const int zsplit = (int)(ix / nblocks);                     // 0 unless the key range is split
-  const int hkv = (int)(iyz % ny), b = (int)(iyz / ny);
-  const int c0 = qb * QB;                                           // first step of the block within the call
-  // steps of this sequence in the call: all of them, or its own count
-  int steps_b = p.queries;
-  if (p.count_per_seq) {
-    const int n = ((const_i32_ptr)p.count_per_seq)[b];
-    steps_b = n < 0 ? 0 : (n < p.queries ? n : p.queries);
-  }
-  if (c0 >= steps_b) return;                                        // uniform over the workgroup, before any barrier
-  const int C = steps_b - c0 < QB ? steps_b - c0 : QB;             // steps in this block
-  const int ncols = C * p.G;
-  int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[b] : p.t; // first step of the call for this sequence
-  t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
-  const int t_first = t_base + c0, t_last = t_first + C - 1;
-  const int lo = (p.window > 0 && t_first - p.window + 1 > 0) ? t_first - p.window + 1 : 0;
-  // The split of the key range this workgroup walks (the whole range when not split:
-  // kWholeRange), newest split first as in the decode kernel.
-  const int chunk0 = lo >> p.tps_log2;
-  const int nchunks = (t_last >> p.tps_log2) - chunk0 + 1;
-  if (zsplit >= nchunks) return;                                    // uniform over the workgroup
-  const int split = nchunks - 1 - zsplit;
-  const int cs = (chunk0 + split) << p.tps_log2, ce = split_end(chunk0 + split, p.tps_log2);
-  const int start = lo > cs ? lo : cs;
-  const int end = t_last < ce ? t_last : ce;
-  const int g_first = start >> 5, g_last = end >> 5;
-
-  // wavefront-uniform bounds over this wavefront's columns, cut to the split:
-  // the groups it has any work in, and those no column cuts
+  const BlockWork work = block_work<true>(p, kWaveColumns * NW);
+  if (!work.any) return;                       // uniform over the workgroup, before any barrier
+  const int b = work.b, hkv = work.hkv, c0 = work.c0, ncols = work.ncols, split = work.split;
+  const int t_last = work.t_last, start = work.start, g_first = work.g_first, g_last = work.g_last;
   const int first_col = kWaveColumns * wave;
-  const int last_col = (first_col + kWaveColumns - 1) < ncols - 1 ? (first_col + kWaveColumns - 1) : ncols - 1;
-  const bool idle = first_col >= ncols;                             // a wavefront beyond the block's columns
-  const int own_hi = t_first + (idle ? 0 : last_col / p.G);         // newest key any of its columns sees
-  const int own_hi_min = t_first + (idle ? 0 : first_col / p.G);    // newest key ALL of its columns see
-  const int own_lo_first = (p.window > 0 && own_hi_min - p.window + 1 > 0) ? own_hi_min - p.window + 1 : 0;
-  const int own_lo_last = (p.window > 0 && own_hi - p.window + 1 > 0) ? own_hi - p.window + 1 : 0;
-  const int w_hi = own_hi < end ? own_hi : end, w_hi_min = own_hi_min < end ? own_hi_min : end;
-  const int w_lo_first = own_lo_first > start ? own_lo_first : start;
-  const int w_lo_last = own_lo_last > start ? own_lo_last : start;
+  const WaveBounds own = wave_bounds(p, work, first_col, kWaveColumns);
 
-  // This lane's column (unused columns behave like the block's last step with q = 0),
-  // its range, its query operand (lane half h: dims 16 s + 8 h .. +7), its softmax state.
+  // This lane's column, its query operand (lane half h: dims 16 s + 8 h .. +7), its softmax state.
   const int half = lane >> 5;
   const int col = first_col + (lane & 31);
-  const int cq = col < ncols ? col / p.G : C - 1;
-  const int gq = col < ncols ? col - cq * p.G : 0;
-  const int step = t_first + cq;               // the column's own step: its newest key and its position
-  const int hi_col = step < end ? step : end;
-  const int lo_own = (p.window > 0 && step - p.window + 1 > 0) ? step - p.window + 1 : 0;
-  const int lo_col = lo_own > start ? lo_own : start;
+  const LaneColumn mine = lane_column(p, work, col);
+  const int cq = mine.cq, gq = mine.gq, step = mine.step, lo_col = mine.lo, hi_col = mine.hi;
   u32x4 qreg[KT];
   {
     const uint16_t* qp = static_cast<const uint16_t*>(p.q) +
@@ -307,23 +253,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
     }
   };
-  // Slots before the range's first key and beyond the block's last step may be unwritten
-  // (NaN): the 0 mask under the sums is applied once, to the value units of the range's first
-  // and last group, in LDS, by the wavefront that copied the unit and after its copy has landed
-  // (the copy keeps the lane of every 16-byte piece, so a lane masks the slots its consumers
-  // will read from it).  Masked slots inside the range hold written data and weight 0.
-  const bool head = (start & 31) != 0, tail = (g_last << 5) + 31 > t_last;  // uniform over the workgroup
+  const bool head = cut_head(work), tail = cut_tail(work);
   auto mask_values = [&](int g, int at) {  // the buffer of group g: the first, and head, or the last, and tail
     uint32_t keep[4];
     value_masks(g, start, t_last, lane, keep);
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
       const int u = wave + NW * i;
-      if (u < KU) continue;
-      u32x4* piece = lds + at + u * 64 + lane;
-      u32x4 v = *piece;
-      v.x &= keep[0]; v.y &= keep[1]; v.z &= keep[2]; v.w &= keep[3];
-      *piece = v;
+      if (u >= KU) mask_piece(lds + at + u * 64 + lane, keep);
     }
   };
   // Waits and barriers are written out instead of __syncthreads() so that they are the ones
@@ -356,8 +293,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 
   // The groups this wavefront has work in: own_first .. own_last.  The others it only helps
   // to copy: loops of their own, so that no path around the arithmetic carries the accumulators.
-  const int own_first = idle ? g_last + 1 : (w_lo_first > (g_first << 5) ? w_lo_first >> 5 : g_first);
-  const int own_last = idle ? g_last : w_hi >> 5;
+  const int own_first = own.idle ? g_last + 1 : (own.lo_first > (g_first << 5) ? own.lo_first >> 5 : g_first);
+  const int own_last = own.idle ? g_last : own.hi >> 5;
 
   int grp = g_first;
   // LDS offset of the buffer of group grp + ahead (NBUF is a power of two)
@@ -367,7 +304,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // Into the buffer of group grp - kPair, which everybody finished before the last barrier.
   auto copies = [&]() { issue(next(NBUF - kPair), grp + NBUF - kPair); };
   // The groups no column's range cuts: first_whole .. last_whole.
-  const int first_whole = (w_lo_last + 31) >> 5, last_whole = ((w_hi_min + 1) >> 5) - 1;
+  const int first_whole = (own.lo_last + 31) >> 5, last_whole = ((own.hi_min + 1) >> 5) - 1;
   float base = 0.f;                            // m_run, or 0 while the column has seen no key
   // mask and reference of group g, whose logits are in x
   auto enter = [&](int g, f32x16& x, float mx) {
@@ -503,7 +440,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 
 }  // namespace
 
-int prefill_bf16_block_steps(int G, int waves) { return prefill_block_steps(G, waves); }
+int prefill_bf16_block_steps(int G, int waves) { return block_steps_of(G, kWaveColumns * waves); }
 
 namespace {
 template <int NW>
@@ -512,7 +449,7 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
   // barrier, an iteration's first operands read in the one before.  Fewer: four buffers, so that
   // at least two workgroups share a compute unit.
   constexpr int NBUF = NW == 8 ? 8 : 4;
-  const int QB = prefill_block_steps(p.G, NW);
+  const int QB = prefill_bf16_block_steps(p.G, NW);
   if (QB < 1) return hipErrorInvalidConfiguration;
   const int64_t nblocks = (p.queries + QB - 1) / QB;
   // the kernel renumbers its workgroups with 32-bit arithmetic on the linear index
