@@ -15,6 +15,10 @@
 // (attn_prefill_bf16.hip: 32 columns per wavefront, deeper buffers of 64 KiB) is the faster one
 // for whole prompts and the slower one here: 21 steps of 3 heads, 16 sequences, t = 4075:
 // 60.3 us per call with this kernel, 62.6 us with that one.
+//
+// Prompts over a short range come here too (kBlocks; a block of 128 columns per workgroup, no split):
+// twice the wavefronts per compute unit cover a workgroup's beginning and end, which are most of it
+// then.  Which prompts: short_prompt() in tempo_api.hip.
 #include "attn_bf16_common.h"
 
 
@@ -88,7 +92,8 @@ constexpr int kWaveColumns = 16;
 // independent inside an iteration, so they overlap instead of alternating.  Keys
 // therefore run one group ahead of values through LDS: two key buffers (groups n + 1,
 // n + 2) and two value buffers (groups n, n + 1).
-template <int D, int NW, bool kRope, bool kStream>
+// kBlocks: a prompt over a short range, cut into blocks of all 16 * NW columns.
+template <int D, int NW, bool kRope, bool kStream, bool kBlocks = false>
 __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
   u32x4* const lds_v = lds + 2 * KU * 64;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const BlockWork work = block_work<false>(p, kWaveColumns * NW);
+  const BlockWork work = block_work<kBlocks>(p, kWaveColumns * NW);
   if (!work.any) return;                       // uniform over the workgroup, before any barrier
   const int b = work.b, hkv = work.hkv, c0 = work.c0, ncols = work.ncols, split = work.split;
   const int t_last = work.t_last, start = work.start, g_first = work.g_first, g_last = work.g_last;
@@ -314,6 +319,20 @@ hipError_t launch_block_nw(const AttnParams& p, int batch, int D, int grid_split
 }
 
 }  // namespace
+
+// A prompt: blocks of 128 columns, each over its whole range (p.direct, p.tps_log2 = kWholeRange).
+hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipStream_t stream) {
+  constexpr int NW = 8;
+  if (D != 128 || !p.direct) return hipErrorInvalidConfiguration;
+  const int QB = block_steps_of(p.G, kWaveColumns * NW);
+  if (QB < 1) return hipErrorInvalidConfiguration;
+  const int64_t nblocks = (p.queries + QB - 1) / QB;
+  if (nblocks * p.Hkv * batch > INT32_MAX) return hipErrorInvalidConfiguration;  // 32-bit work items
+  const dim3 grid((unsigned)nblocks, p.Hkv, batch);
+  const size_t lds = 2 * (size_t)(2 * (D / 32) + D / 16) * 1024;
+  if (p.rope_cos) return launch((attn_block_bf16<128, NW, true, false, true>), grid, dim3(64 * NW), lds, stream, p);
+  return launch((attn_block_bf16<128, NW, false, false, true>), grid, dim3(64 * NW), lds, stream, p);
+}
 
 // A block of few columns gets a workgroup of just enough wavefronts (2, 4 or 8), so that
 // several workgroups share a compute unit and the kernel stays bound by HBM.

@@ -955,6 +955,17 @@ bool prompt_in_one_launch(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t
   return (int64_t)batch * count * heads * kv->head_dim <= INT32_MAX;
 }
 
+// Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
+// than 64, and at most 128 keys for the longest block of 128 columns (us, block kernel / prompt kernel, 24/8
+// heads: 16 sequences of 64 steps 12.2 / 13.5, 128 steps 22.8 / 24.0, 200 steps 35.3 / 35.9, 300 steps behind
+// a history with window 64 41.3 / 45.1, 1 sequence of 42 steps 11.5 / 12.2).  At D = 64 the prompt kernel is
+// the faster one throughout (8 sequences, 32/8 heads, 128 steps 12.7 / 11.9).
+bool short_prompt(const tempo_kv* kv, int32_t Hq, int32_t t, int32_t count, int32_t window) {
+  const int32_t G = Hq / kv->num_kv_heads, QB = kMaxColumns / G;
+  const int64_t all = (int64_t)t + count, most = (int64_t)window + QB - 1;
+  return kv->head_dim == 128 && (int64_t)count * G > 64 && (window > 0 && most < all ? most : all) <= 128;
+}
+
 // fp32: tiles of 16 (step, head) columns, the keys of a tile spread over 8 wavefronts.  A tile's
 // group of 16 keys costs about 1 us at D = 128; the key range is split (and combined, 5 us) only
 // if the tiles leave most of the part idle and a wavefront would walk more than 8 groups.
@@ -1000,8 +1011,10 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
   // (and staged keys/values lie where the partials of split ranges would)
-  const PromptPlan plan = bf16 ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
-                               : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
+  const bool is_short = bf16 && !staged && short_prompt(kv, Hq, t, count, window);
+  const PromptPlan plan = is_short ? PromptPlan{8, kWholeRange, 1}
+                          : bf16   ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
+                                   : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
   const tempo_plan cut = {32, plan.splits, plan.waves};  // (its split length is set below)
   PromptParams p;
   static_cast<AttnParams&>(p) = attn_params(kv, q, out, Hq, t, nullptr, window, scale, &cut, workspace, batch, count);
@@ -1022,8 +1035,9 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
     p.stage_first = t >> 5;
     p.stage_groups = staged->stage_groups;
   }
-  const hipError_t e = bf16 ? launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s)
-                            : launch_partial_f32(p, batch, kv->head_dim, plan.splits, plan.waves, s);
+  const hipError_t e = is_short ? launch_short_prompt_bf16(p, batch, kv->head_dim, s)
+                       : bf16   ? launch_prefill_bf16(p, batch, kv->head_dim, plan.waves, plan.splits, s)
+                                : launch_partial_f32(p, batch, kv->head_dim, plan.splits, plan.waves, s);
   const int rc = launch_status(e, "attn_prefill");
   if (rc != TEMPO_OK || plan.splits == 1) return rc;
   return launch_status(bf16 ? launch_prompt_combine(p, batch, kv->head_dim, s)

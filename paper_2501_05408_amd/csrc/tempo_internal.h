@@ -177,6 +177,7 @@ size_t partial_bf16_lds_bytes(int waves, int columns, int D);      // dynamic LD
 int prefill_bf16_block_steps(int G, int waves);                    // query steps per workgroup of the prompt kernel
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream);
 hipError_t launch_prompt_combine(const PromptParams& p, int batch, int D, hipStream_t stream);
+hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipStream_t stream);
 hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream);
 hipError_t launch_partial_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                               hipStream_t stream);

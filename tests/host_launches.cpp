@@ -63,6 +63,7 @@ hipError_t launch_prefill_bf16(const PromptParams& p, int, int, int waves, int g
   return attend(p.k_stage ? "prompt_staged" : "prompt", p, grid_splits, waves);
 }
 hipError_t launch_prompt_combine(const PromptParams& p, int, int, hipStream_t) { return attend("prompt_combine", p, 0, 0); }
+hipError_t launch_short_prompt_bf16(const AttnParams& p, int, int, hipStream_t) { return attend("short_prompt", p, 1, 0); }
 hipError_t launch_block_bf16(const AttnParams& p, int, int, int grid_splits, hipStream_t) {
   return attend("block_bf16", p, grid_splits, 0);
 }

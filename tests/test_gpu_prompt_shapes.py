@@ -291,3 +291,27 @@ def test_f32_steps_where_the_kernel_changes(B, Hkv, G, D, Z, steps, window, rope
         assert_close(got[t], oracle.attend(q64[t], K64, V64, t, window, 1.0 / np.sqrt(D)), dtype, f"fp32 step {t} w={window} rope={rope}")
     kg, vg = st.gather(0, steps)
     assert torch.equal(vg, Vd) and (rope or torch.equal(kg, Kd))
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,t,count,window", [
+    (16, 8, 3, 128, 0, 64, 0), (2, 2, 3, 128, 60, 43, 0), (1, 1, 3, 128, 0, 128, 0), (2, 1, 3, 128, 900, 300, 64),
+    (1, 2, 128, 128, 31, 5, 0), (3, 1, 20, 128, 7, 33, 1), (1, 1, 1, 128, 0, 128, 0), (1, 1, 1, 128, 33, 400, 1)])
+def test_prompts_over_short_ranges(B, Hkv, G, D, t, count, window):
+    run_prompt(B, Hkv, G, D, 32, t, count, window, False, T.TEMPO_BF16)
+
+
+def test_prompts_over_short_ranges_rotated_and_of_different_lengths():
+    test_rope_prompt_with_split_ranges(128, 3, 20, 70)
+    B, Hkv, G, D, count = 4, 2, 3, 128, 100
+    q, K, V = host_inputs(79, B, count, Hkv * G, Hkv, D, T.TEMPO_BF16)
+    st = BlockStore(B, Hkv * G, Hkv, D, 32, count - 1, T.TEMPO_BF16, fill="nan")
+    lengths = torch.tensor([0, 1, 43, 100], dtype=torch.int32, device=DEV)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))), T.TEMPO_BF16)
+    out = torch.full_like(qd, 7.0)
+    st.prefill_attend(qd, dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16), out, 0, count, count_per_seq=lengths)
+    got = np64(out)
+    for b, n in enumerate(lengths.tolist()):
+        assert (got[b, n:] == 7.0).all()
+        for c in range(0, n, 6):
+            ref = oracle.attend(q[c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), c, 0, 1.0 / np.sqrt(D))
+            assert_close(got[b, c], ref[b], T.TEMPO_BF16, f"sequence {b} of {n} steps, step {c}")

@@ -67,10 +67,11 @@ def assert_all_keys_launched(launches, G, t, count):
     share a workgroup reach from the first key of the first of them to the last step."""
     step = t
     for name, f in launches:
-        if name not in ("prompt", "prompt_staged", "block_bf16", "partial_bf16", "partial_f32", "step_f32"):
+        if name not in ("prompt", "prompt_staged", "short_prompt", "block_bf16", "partial_bf16", "partial_f32", "step_f32"):
             continue
         assert f["t"] == step
-        together = 32 * f["waves"] // G if name.startswith("prompt") else f["queries"]
+        together = {"prompt": 32 * f["waves"] // G, "prompt_staged": 32 * f["waves"] // G,
+                    "short_prompt": 128 // G}.get(name, f["queries"])
         for c in range(0, f["queries"], together):
             last = step + min(c + together, f["queries"]) - 1
             first = max(0, step + c - f["window"] + 1) if f["window"] else 0
@@ -144,3 +145,13 @@ def test_kernel_of_an_f32_step(lib, Hq, Hkv, D, batch, keys, kernel, windowed):
     lo = t - keys + 1
     assert name == kernel and f["grid_splits"] >= (t >> f["tps_log2"]) - (lo >> f["tps_log2"]) + 1
     assert f["waves"] in (1, 2, 4, 8)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,t,count,window,kernel", [
+    (24, 8, 128, 0, 128, 0, "short_prompt"), (24, 8, 128, 0, 129, 0, "prompt"), (24, 8, 128, 86, 42, 0, "short_prompt"),
+    (24, 8, 128, 500, 900, 87, "short_prompt"), (24, 8, 128, 500, 900, 88, "prompt"), (24, 8, 128, 0, 21, 0, "prompt"),
+    (24, 8, 128, 0, 22, 0, "short_prompt"), (8, 2, 64, 0, 100, 0, "prompt"), (256, 2, 128, 0, 5, 0, "short_prompt")])
+def test_kernel_of_a_bf16_prompt_over_a_short_range(lib, Hq, Hkv, D, t, count, window, kernel):
+    launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, 100), 2, Hq, t, count, window)
+    assert [n for n, _ in launches][:2] == ["append", kernel]
+    assert_all_keys_launched(launches, Hq // Hkv, t, count)
