@@ -892,13 +892,15 @@ struct PromptPlan {
   int waves, tps_log2, splits;
 };
 
-// A time model of the launch, in nanoseconds, with constants measured on MI355X (D = 128, scaled
-// by the head dim).  Two workgroups of 2 or 4 wavefronts share a compute unit (64 KiB of LDS each);
-// a workgroup spends about 5 us before its first and after its last group, and an iteration over a
-// 32-slot group takes 0.55 us with one wavefront on a SIMD and 0.78 us with two.  So 4 wavefronts
-// win once they fill the part; 2, and a key range cut into splits (with a combine launch of about
-// 5 us, and partials of (D + 2) * 4 bytes per column and split), when the query columns alone do
-// not (100 steps behind 1900 keys, one sequence: no splits 52 us, 8 splits 25 us).
+// A time model of the launch, in nanoseconds, with constants measured on MI355X at D = 128 (at D = 64
+// an iteration takes 0.68 of it: 128 groups per workgroup 48 us against 68 us).  Two workgroups of 2 or
+// 4 wavefronts share a compute unit (at D = 128 by their 64 KiB of LDS each); a workgroup spends about
+// 5 us before its first and after its last group, and an iteration over a 32-slot group takes 0.55 us
+// with one wavefront on a SIMD, 0.78 us with two, and 0.64 us with one where two workgroups of 2 copy
+// each their own keys/values.  So 4 wavefronts win once they fill the part; 2, and a key range cut into
+// splits (with a combine launch of about 5 us, and partials of (D + 2) * 4 bytes per column and split),
+// when the query columns alone do not (100 steps behind 1900 keys, one sequence: no splits 52 us, 8
+// splits 25 us).
 // 8 wavefronts in one workgroup read each key/value half as often, but nothing covers the
 // workgroup's beginning and end: the better shape only for long ranges at D = 128 (us with 4 / 8:
 // 16 x 200 steps 32.7 / 35.7, 16 x 1000 185 / 200, 4 x 4000 449 / 437; D = 64, 8 x 1500 125 / 147).
@@ -910,7 +912,7 @@ bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t cou
 PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
                        size_t workspace_bytes) {
   const int G = Hq / kv->num_kv_heads;
-  const double scale = kv->head_dim / 128.0;
+  const double scale = kv->head_dim == 128 ? 1.0 : 0.68;
   PromptPlan best = {4, kWholeRange, 1};
   double best_ns = -1.0;
   const bool may_split = !prompt_fills_part(kv, batch, G, count);
@@ -933,11 +935,11 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
       if (k != kWholeRange && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
       const int64_t workgroups = blocks * pairs * splits;
       const int64_t rounds = (workgroups + resident * kComputeUnits - 1) / (resident * kComputeUnits);
-      const bool shared_simd = waves == 4 && workgroups > kComputeUnits;
+      const bool shared = workgroups > kComputeUnits;  // two workgroups on some compute unit
       const int64_t span = k == kWholeRange || keys < ((int64_t)1 << k) ? keys : (int64_t)1 << k;
       // a causal prompt's blocks are half the longest on average: beyond the first round that counts
       const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;
-      double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (shared_simd ? 780.0 : 550.0) * scale);
+      double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (!shared ? 550.0 : waves == 4 ? 780.0 : 640.0) * scale);
       if (splits > 1) ns += 5000.0 + 2.0 * (double)rows * splits * kv->head_dim * 4 / 4000.0;
       if (best_ns < 0.0 || ns < 0.97 * best_ns) {  // the wider workgroup and the fewer splits unless clearly slower
         best_ns = ns;
