@@ -1,8 +1,8 @@
-// One fp32 decode step over a short range, on the vector ALU.
+// One or a few fp32 decode steps over a short range, on the vector ALU.
 //
 // Same quantities as attn_partial_f32.hip (running max m, running sum l and accumulator acc in
 // fp32, base-2 units; Section 2, Eq. 1 over one split; Section 4.3 masks).  One workgroup = one
-// (sequence, QUERY head, split).  A wavefront looks at 4 key positions at a time: 16 lanes per
+// (sequence, step, QUERY head, split).  A wavefront looks at 4 key positions at a time: 16 lanes per
 // position, each lane holding D/16 consecutive dims.  The dot product is a 16-lane butterfly (DPP
 // row operations); each 16-lane row keeps its own (m, l, acc) and the rows and wavefronts are
 // merged once, through LDS, at the end.
@@ -11,7 +11,7 @@
 // D = 128 however few of its 16 columns are used, and wavefronts that share a SIMD wait for each
 // other's; here a key costs D/16 fused multiply-adds and a butterfly, and every head has a compute
 // unit.  Over long ranges it is the slower one, as every head of a group reads the group's keys and
-// values.  Which steps come here, and what both take: f32_step_on_vector_alu() in tempo_api.hip.
+// values.  Which calls come here, and what both take: f32_on_vector_alu() in tempo_api.hip.
 #include "tempo_internal.h"
 
 namespace tempo {
@@ -24,17 +24,20 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int nwaves = blockDim.x >> 6;
-  const int hq = blockIdx.x, b = blockIdx.y;
+  const int cq = blockIdx.x / p.Hq, hq = blockIdx.x - cq * p.Hq, b = blockIdx.y;  // cq < p.queries
   const int hkv = hq / p.G;
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
-  const SeqRange rg = seq_range(t_b, p.window, p.tps_log2);
+  const SeqRange rg = seq_range(t_b, p.window, p.tps_log2, p.queries);
   if ((int)blockIdx.z >= rg.nchunks) return;
   const int split = rg.nchunks - 1 - (int)blockIdx.z;  // newest split first, as in the other kernels
   const int chunk = rg.chunk0 + split;
   const int cs = chunk << p.tps_log2, ce = split_end(chunk, p.tps_log2);
-  const int start = rg.lo > cs ? rg.lo : cs;
-  const int end = t_b < ce ? t_b : ce;
+  // this step's own range, cut to the split (empty if they do not meet)
+  const int t_q = t_b + cq;
+  const int lo_q = (p.window > 0 && t_q - p.window + 1 > 0) ? t_q - p.window + 1 : 0;
+  const int start = lo_q > cs ? lo_q : cs;
+  const int end = t_q < ce ? t_q : ce;
 
   const int row = lane >> 4, col = lane & 15;
   const int Z = 1 << p.z_log2;
@@ -47,22 +50,22 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
 
   float qv[E];
   {
-    const float* qp = static_cast<const float*>(p.q) + ((int64_t)b * p.io_steps * p.Hq + hq) * D + col * E;
+    const float* qp = static_cast<const float*>(p.q) + (((int64_t)b * p.io_steps + cq) * p.Hq + hq) * D + col * E;
 #pragma unroll
     for (int e = 0; e < E; ++e) qv[e] = qp[e];
   }
   // Rotary embedding: dims col*E .. +E-1 pair with those of lane col ^ 8 of the same 16-lane row;
   // table entry (position, i) with i = (col & 7) * E + e.
-  auto rotate = [&](float* x) {
-    const float* cs_t = p.rope_cos + (int64_t)t_b * (D / 2) + (col & 7) * E;
-    const float* sn_t = p.rope_sin + (int64_t)t_b * (D / 2) + (col & 7) * E;
+  auto rotate = [&](float* x, int pos) {
+    const float* cs_t = p.rope_cos + (int64_t)pos * (D / 2) + (col & 7) * E;
+    const float* sn_t = p.rope_sin + (int64_t)pos * (D / 2) + (col & 7) * E;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const float other = __shfl_xor(x[e], 8);
       x[e] = col < 8 ? rope_lo(x[e], other, cs_t[e], sn_t[e]) : rope_hi(other, x[e], cs_t[e], sn_t[e]);
     }
   };
-  if (p.rope_cos) rotate(qv);
+  if (p.rope_cos) rotate(qv, t_q);
   float m = -INFINITY, l = 0.f, acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
       vx[e] = v4.x; vx[e + 1] = v4.y; vx[e + 2] = v4.z; vx[e + 3] = v4.w;
     }
     if (fresh) {  // all 16 lanes of the row take this branch together
-      if (p.rope_cos) rotate(kx);  // the new key arrives unrotated
+      if (p.rope_cos) rotate(kx, t_b);  // the new key arrives unrotated
       if (hq == hkv * p.G) {
 #pragma unroll
         for (int e = 0; e < E; e += 4) {
@@ -140,9 +143,9 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
     }
     const float num = (nums[0] + nums[1]) + (nums[2] + nums[3]), den = (dens[0] + dens[1]) + (dens[2] + dens[3]);
     if (p.direct) {
-      static_cast<float*>(p.out)[((int64_t)b * p.io_steps * p.Hq + hq) * D + d] = num / den;
+      static_cast<float*>(p.out)[(((int64_t)b * p.io_steps + cq) * p.Hq + hq) * D + d] = num / den;
     } else {
-      const int64_t part = ((int64_t)b * p.Hq + hq) * p.num_splits + split;
+      const int64_t part = (((int64_t)b * p.queries + cq) * p.Hq + hq) * p.num_splits + split;
       p.ws_acc[part * D + d] = num;
       if (d == 0) {
         p.ws_ml[part * 2] = M;
@@ -154,10 +157,10 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
 
 }  // namespace
 
-// One query step, no padding bound.
+// No padding bound; p.k_new (the fused write) with one query step only.
 hipError_t launch_step_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves, hipStream_t stream) {
-  if (p.queries != 1 || p.pad_t != 0 || batch > 65535 || grid_splits > 65535) return hipErrorInvalidConfiguration;
-  const dim3 grid(p.Hq, batch, grid_splits);
+  if ((p.k_new && p.queries != 1) || p.pad_t != 0 || batch > 65535 || grid_splits > 65535) return hipErrorInvalidConfiguration;
+  const dim3 grid(p.Hq * p.queries, batch, grid_splits);
   const dim3 block(64 * waves);
   const size_t lds = (size_t)waves * 4 * (2 + (size_t)D) * sizeof(float);
   if (D == 128) return launch(attn_step_f32<128>, grid, block, lds, stream, p);

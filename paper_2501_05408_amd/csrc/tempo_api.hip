@@ -123,22 +123,26 @@ int32_t splits_bound(int32_t t, int32_t window, int tps_log2) {
 constexpr int kComputeUnits = 256;
 constexpr int kMaxSplits = 1024;
 
-// Does the vector kernel (one workgroup per query head) take an fp32 step instead of the matrix-core
-// one (a query group and 16 columns per workgroup)?  Over short ranges, while the heads' separate
+// Does the vector kernel (one workgroup per step and query head) take an fp32 step or block of steps
+// instead of the matrix-core one (16 columns of a query group and its steps per workgroup)?  Over short ranges, while the heads' separate
 // reads of a group's keys and values (through different dies' caches, so not shared unless the group
 // is wide) stay cheap: us a call, vector / matrix, at D = 128:
 //   1 sequence, 24/8 heads, 81 keys 6.7 / 7.7, 151 keys 8.3 / 9.4, 200 keys 9.1 / 9.2
 //   16 sequences, 24/8 heads, 48 keys 6.5 / 7.1 (18k key rows read), 81 keys 9.1 / 8.3 (31k)
 //   16 sequences, 16/1 heads, 200 keys 9.5 / 11.3 (51k), 256 keys 12.6 / 11.6 (66k)
-// and always where no head shares a read (16 sequences of 8/8 heads, 1501 keys 34.5 / 44.1).  At D = 64
+//   blocks of 1 sequence, 24/8 heads: 4 steps, 4 keys 6.3 / 7.9, 32 steps, 32 keys (25k) 10.3 / 9.6; 8/8 heads:
+//   32 steps, 32 keys 10.1 / 9.0, 132 keys (34k) 11.1 / 12.9, 64 steps, 164 keys (84k) 15.0 / 12.3
+// and always where no head or step shares a read (16 sequences of 8/8 heads, 1501 keys 34.5 / 44.1).  At D = 64
 // the matrix-core kernel has half the products: 1 sequence, 8/2 heads, 8 keys 3.4 / 3.9, 64 keys 6.0 / 5.2.
-bool f32_step_on_vector_alu(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window, int32_t queries) {
-  if (kv->dtype != TEMPO_F32 || queries != 1) return false;
-  const int64_t keys = window > 0 && window < (int64_t)t + 1 ? window : (int64_t)t + 1;
+bool f32_on_vector_alu(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window, int32_t queries) {
+  if (kv->dtype != TEMPO_F32) return false;
+  const int64_t keys = window > 0 && window < (int64_t)t + 1 ? window : (int64_t)t + 1;  // of the last step
   const int32_t G = Hq / kv->num_kv_heads;
-  if (kv->head_dim == 128 && G == 1) return true;
-  const int64_t shared = G < 8 ? 8 : (G > 32 ? 32 : G);
-  return keys <= (kv->head_dim == 128 ? 192 : 24) && batch * keys * Hq <= 3200 * shared;
+  if (kv->head_dim == 128 && G == 1 && queries == 1) return true;
+  if (keys > (kv->head_dim == 128 ? 192 : 24)) return false;
+  const int64_t rows = batch * keys * Hq * queries, shared = G < 8 ? 8 : (G > 32 ? 32 : G);
+  if (queries == 1) return rows <= 3200 * shared;
+  return keys > 96 ? rows <= 36000 : queries <= (kv->head_dim == 128 ? 16 : 8) && rows <= 12000;
 }
 
 // Split planning: a small time model of the launch, in nanoseconds, with constants
@@ -188,7 +192,7 @@ void make_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t_max, int
                bool ragged, int32_t queries, int64_t max_splits, tempo_plan* plan) {
   // one workgroup serves a query group; fp32 takes 16 (step, head) columns per workgroup
   const int64_t columns = (int64_t)queries * (Hq / kv->num_kv_heads);
-  const int64_t pairs = f32_step_on_vector_alu(kv, batch, Hq, t_max, window, queries)
+  const int64_t pairs = f32_on_vector_alu(kv, batch, Hq, t_max, window, queries)
                             ? (int64_t)batch * Hq
                             : (int64_t)batch * kv->num_kv_heads * (kv->dtype == TEMPO_F32 ? (columns + 15) / 16 : 1);
   const int64_t len = (window > 0 && window < (int64_t)t_max + 1) ? window : (int64_t)t_max + 1;
@@ -419,7 +423,7 @@ int do_partial(const tempo_kv* kv, const void* q, const void* k_new, const void*
     return launch_status(launch_block_bf16(p, batch, kv->head_dim, gs, stream), "attn_block_partial");
   const hipError_t e = kv->dtype == TEMPO_BF16
                            ? launch_partial_bf16(p, batch, kv->head_dim, gs, plan->waves, stream)
-                       : f32_step_on_vector_alu(kv, batch, Hq, t, window, queries)
+                       : f32_on_vector_alu(kv, batch, Hq, last_step(t, queries), union_window(window, queries), queries)
                            ? launch_step_f32(p, batch, kv->head_dim, gs, plan->waves, stream)
                            : launch_partial_f32(p, batch, kv->head_dim, gs, f32_waves(*plan), stream);
   return launch_status(e, "attn_decode_partial");

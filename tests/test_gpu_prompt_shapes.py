@@ -315,3 +315,28 @@ def test_prompts_over_short_ranges_rotated_and_of_different_lengths():
         for c in range(0, n, 6):
             ref = oracle.attend(q[c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), c, 0, 1.0 / np.sqrt(D))
             assert_close(got[b, c], ref[b], T.TEMPO_BF16, f"sequence {b} of {n} steps, step {c}")
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,t,count,window", [
+    (1, 8, 3, 128, 0, 4, 0), (1, 1, 16, 128, 100, 4, 0), (2, 2, 1, 128, 100, 16, 0), (1, 2, 3, 128, 900, 5, 70),
+    (1, 2, 4, 64, 0, 4, 0), (1, 2, 4, 64, 20, 4, 0), (1, 2, 4, 64, 22, 4, 0), (1, 1, 1, 128, 33, 9, 1)])
+def test_f32_blocks_where_the_kernel_changes(B, Hkv, G, D, t, count, window):
+    """Small blocks over short ranges (vector kernel) and just past them, unrotated and with rotated queries."""
+    dtype = T.TEMPO_F32
+    q, K, V = host_inputs(80, B, t + count, Hkv * G, Hkv, D, dtype)
+    st = BlockStore(B, Hkv * G, Hkv, D, 16, t + count - 1, dtype, fill="nan")
+    first = max(0, t - window + 1) if window else 0
+    Kd, Vd = dev(K, dtype), dev(V, dtype)
+    st.append_block(Kd[:, first:].contiguous(), Vd[:, first:].contiguous(), first, t + count - first)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
+    out = st.attend_block(qd, torch.empty_like(qd), t, count, window)
+    for c in range(count):
+        ref = oracle.attend(q[t + c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), t + c, window, 1.0 / np.sqrt(D))
+        assert_close(np64(out)[:, c], ref, dtype, f"fp32 block step {t + c} w={window}")
+    half = D // 2
+    angle = torch.arange(t + count, dtype=torch.float64)[:, None] * 500000.0 ** (-torch.arange(half, dtype=torch.float64) / half)
+    st.set_rope(torch.cos(angle).float().to(DEV), torch.sin(angle).float().to(DEV))
+    turned = torch.stack([st.rope_rotate(qd[:, c].contiguous(), torch.empty_like(qd[:, c]).contiguous(), t + c)
+                          for c in range(count)], dim=1)
+    got = st.attend_block(qd, torch.empty_like(qd), t, count, window, rope=True)
+    assert torch.equal(got, st.attend_block(turned, torch.empty_like(qd), t, count, window))
