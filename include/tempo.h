@@ -443,7 +443,9 @@ int tempo_rope_attn_block_window(const tempo_kv* kv, const tempo_rope* rope, con
  * written to the store and every step's query attends over its own range (keys
  * 0 .. t+c, or its window), exactly as `count` single decode steps would.  One launch
  * writes the store, one answers all steps (a third combines, if the columns are few and
- * their key range was split).  On a ring store the keys/values are laid out in the
+ * their key range was split); few steps behind a long history are answered in blocks of
+ * 128 / (num_q_heads / num_kv_heads) steps, each by tempo_kv_append_block and one
+ * tempo_attn_block_*.  On a ring store the keys/values are laid out in the
  * workspace first and the steps the ring keeps are written last; a workspace without the
  * room for that takes the prompt in chunks that the ring can hold.  (All launches
  * asynchronous on `stream`, nothing allocated.)
@@ -490,7 +492,7 @@ int tempo_rope_prefill_window(const tempo_kv* kv, const tempo_rope* rope, const 
  * only; 0 on unsupported arguments): 2 when the prompt's query blocks fill the part
  * (bf16, linear store: one block-store write, then one launch in which every workgroup
  * walks the whole key range of its (step, head) columns through LDS and writes `out`
- * directly), 3 on other linear stores, else 3 per block of
+ * directly), 3 on fp32 linear stores, else 3 per block of
  * 128 / (num_q_heads / num_kv_heads) steps. */
 int tempo_prefill_launches(const tempo_kv* kv, int32_t batch, int32_t num_q_heads, int32_t count);
 

@@ -890,6 +890,59 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
                 workspace_bytes, stream, 1, rope);
 }
 
+// Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
+// than 64, and at most 128 keys for the longest block of 128 columns (us, block kernel / prompt kernel, 24/8
+// heads: 16 sequences of 64 steps 12.2 / 13.5, 128 steps 22.8 / 24.0, 200 steps 35.3 / 35.9, 300 steps behind
+// a history with window 64 41.3 / 45.1, 1 sequence of 42 steps 11.5 / 12.2).  At D = 64 the prompt kernel is
+// the faster one throughout (8 sequences, 32/8 heads, 128 steps 12.7 / 11.9).
+bool short_prompt(const tempo_kv* kv, int32_t Hq, int32_t t, int32_t count, int32_t window) {
+  const int32_t G = Hq / kv->num_kv_heads, QB = kMaxColumns / G;
+  const int64_t all = (int64_t)t + count, most = (int64_t)window + QB - 1;
+  return kv->head_dim == 128 && (int64_t)count * G > 64 && (window > 0 && most < all ? most : all) <= 128;
+}
+
+// Do a prompt's blocks of 128 columns alone give every compute unit one?
+bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
+  const int32_t QB = prefill_bf16_block_steps(G, 4);
+  return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
+}
+
+// Is a prompt answered block by block (blocks of 128 columns, each written, attended with split key ranges and
+// combined) rather than in one launch?  The one launch cuts key ranges into at most 8 splits and its kernels
+// are made for many columns; a block's attention spreads a long range over the whole part.
+//   fp32: one block does, always (1 sequence, 24/8 heads, 1 step behind 2000 keys 12.6 us, in one launch 37;
+//   behind 30000 49, 128).  More do not (2 blocks behind 2000 keys 62, 51).
+//   bf16, at most 16 columns, which the single-step kernel takes: always (24/8 heads, 1 step, 1 sequence behind
+//   8000 keys 14, 27; 16 sequences behind 300 keys 10, 12), but for one or two (sequence, head) pairs with a
+//   few columns behind a short range, whose many splits cost more to combine (1 sequence, 8/1 heads, 2 steps
+//   behind 1000 keys 14.0, 11.1).
+//   bf16, more columns: by two estimates in us, fitted to 1050 measured prompts of 1 to 128 pairs (on the mean
+//   0.2% from the better of the two), unless their blocks fill the part.  A block takes 15 and 1.05 to 1.5 times its keys' stream from HBM; one
+//   launch 8 and the longer of a workgroup's walk through an eighth of the keys and 1.2 times the stream
+//   (1 sequence, 24/8 heads, 21 steps behind 4000 keys 21, 20, behind 8000 24, 30, behind 32000 48, 85).
+bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window) {
+  const int32_t G = Hq / kv->num_kv_heads, block = kMaxColumns / G;
+  if (kv->dtype != TEMPO_BF16) return count <= block;
+  if (prompt_fills_part(kv, batch, G, count)) return false;
+  const int64_t pairs = (int64_t)batch * kv->num_kv_heads, columns = (int64_t)count * G;
+  const int64_t keys = window > 0 && window <= t ? (int64_t)window + count - 1 : (int64_t)t + count;
+  if (columns <= kNarrowColumns) {
+    tempo_plan plan;
+    make_block_plan(kv, batch, Hq, t, window, false, count, &plan);
+    return !(pairs < kManyPairs && plan.num_splits > 8 && columns >= 8 && count > 1 && keys <= 2200);
+  }
+  if (short_prompt(kv, Hq, t, count, window)) return false;
+  const bool narrow = kv->head_dim == 64;
+  const double stream = (double)pairs * keys * kv->head_dim * 4 / (kSustainedBytesPerNs * 1000.0);
+  const int64_t blocks = (count + block - 1) / block, widest = columns < kMaxColumns ? columns : kMaxColumns;
+  const double by_blocks = (double)blocks * ((narrow ? 14.0 : 15.0) +
+                                             (widest <= 32 ? 1.05 : widest <= 64 ? 1.1 : 1.5) * (narrow ? 1.4 : 1.0) * stream);
+  const int64_t workgroups = 8 * pairs * blocks, rounds = (workgroups + 2 * kComputeUnits - 1) / (2 * kComputeUnits);
+  const double walk = (workgroups <= kComputeUnits ? 0.55 : 0.78) * (narrow ? 0.68 : 1.0) * (columns > 64 ? 1.1 : 1.0) * rounds * (double)keys / 256.0;
+  const double one_launch = 8.0 + (walk > 1.2 * stream ? walk : 1.2 * stream);
+  return by_blocks < one_launch;
+}
+
 // How the prompt kernel takes a prompt: wavefronts of 32 columns per workgroup, and splits of
 // a block's key range (tps_log2 = kWholeRange, splits = 1: none).
 struct PromptPlan {
@@ -908,11 +961,6 @@ struct PromptPlan {
 // 8 wavefronts in one workgroup read each key/value half as often, but nothing covers the
 // workgroup's beginning and end: the better shape only for long ranges at D = 128 (us with 4 / 8:
 // 16 x 200 steps 32.7 / 35.7, 16 x 1000 185 / 200, 4 x 4000 449 / 437; D = 64, 8 x 1500 125 / 147).
-bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
-  const int32_t QB = prefill_bf16_block_steps(G, 4);
-  return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
-}
-
 PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
                        size_t workspace_bytes) {
   const int G = Hq / kv->num_kv_heads;
@@ -959,17 +1007,6 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
 bool prompt_in_one_launch(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t count) {
   const int32_t heads = kv->dtype == TEMPO_BF16 ? kv->num_kv_heads : Hq;
   return (int64_t)batch * count * heads * kv->head_dim <= INT32_MAX;
-}
-
-// Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
-// than 64, and at most 128 keys for the longest block of 128 columns (us, block kernel / prompt kernel, 24/8
-// heads: 16 sequences of 64 steps 12.2 / 13.5, 128 steps 22.8 / 24.0, 200 steps 35.3 / 35.9, 300 steps behind
-// a history with window 64 41.3 / 45.1, 1 sequence of 42 steps 11.5 / 12.2).  At D = 64 the prompt kernel is
-// the faster one throughout (8 sequences, 32/8 heads, 128 steps 12.7 / 11.9).
-bool short_prompt(const tempo_kv* kv, int32_t Hq, int32_t t, int32_t count, int32_t window) {
-  const int32_t G = Hq / kv->num_kv_heads, QB = kMaxColumns / G;
-  const int64_t all = (int64_t)t + count, most = (int64_t)window + QB - 1;
-  return kv->head_dim == 128 && (int64_t)count * G > 64 && (window > 0 && most < all ? most : all) <= 128;
 }
 
 // fp32: tiles of 16 (step, head) columns, the keys of a tile spread over 8 wavefronts.  A tile's
@@ -1089,6 +1126,34 @@ int prefill_staged(const tempo_kv* kv, const void* q, const void* k_new, const v
   return launch_status(launch_append(last, k + from * row, v + from * row, kv->head_dim, kv->dtype, s), "kv_append_block");
 }
 
+// `count` steps from t on, in blocks of 128 columns: write, attend, combine.
+int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
+                      int32_t Hq, int32_t t, int32_t count, int32_t window, float scale, void* workspace, hipStream_t s) {
+  const size_t esz = kv->dtype == TEMPO_BF16 ? 2 : 4;
+  const int32_t block = kMaxColumns / (Hq / kv->num_kv_heads);
+  for (int32_t c0 = 0; c0 < count; c0 += block) {
+    const int32_t C = count - c0 < block ? count - c0 : block;
+    tempo_plan plan;
+    make_block_plan(kv, batch, Hq, t + c0, window, false, C, &plan);
+    const char* kc = static_cast<const char*>(k_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
+    const char* vc = static_cast<const char*>(v_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
+    const char* qc = static_cast<const char*>(q) + (size_t)c0 * Hq * kv->head_dim * esz;
+    char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
+    StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
+    sp.src_steps = count;
+    int rc = launch_status(launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s), "kv_append_block");
+    if (rc != TEMPO_OK) return rc;
+    rc = do_partial(kv, qc, nullptr, nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, nullptr,
+                    0, count);
+    if (rc != TEMPO_OK) return rc;
+    if (plan.num_splits > 1) {
+      rc = do_combine(kv, oc, batch, Hq, t + c0, nullptr, window, &plan, workspace, s, C, 0, count);
+      if (rc != TEMPO_OK) return rc;
+    }
+  }
+  return TEMPO_OK;
+}
+
 // Prompt processing: `count` steps per sequence, written and answered in one launch each, or
 // in blocks of as many steps as the column tiles hold.
 static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
@@ -1107,7 +1172,6 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   if ((int64_t)batch * block * Hq * kv->head_dim > INT32_MAX) return TEMPO_ERR_SHAPE;
   const size_t esz = kv->dtype == TEMPO_BF16 ? 2 : 4;
   const bool ragged = false;  // every sequence starts at step t
-  const int32_t* t_per_seq = nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // validate every block before the first launch, so that an error leaves the store untouched
   for (int32_t c0 = 0; c0 < count; c0 += block) {
@@ -1123,6 +1187,8 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
     return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
+  if (!count_per_seq && !rope && prompt_by_blocks(kv, batch, Hq, t, count, window))
+    return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
   if (prompt_in_one_launch(kv, batch, Hq, count)) {
     for (int32_t c0 = 0; c0 < count;) {
@@ -1153,28 +1219,8 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     return TEMPO_OK;
   }
 
-  // A call beyond that range goes block by block.
-  for (int32_t c0 = 0; c0 < count; c0 += block) {
-    const int32_t C = count - c0 < block ? count - c0 : block;
-    tempo_plan plan;
-    make_block_plan(kv, batch, Hq, t + c0, window, ragged, C, &plan);
-    const char* kc = static_cast<const char*>(k_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
-    const char* vc = static_cast<const char*>(v_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
-    const char* qc = static_cast<const char*>(q) + (size_t)c0 * Hq * kv->head_dim * esz;
-    char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
-    StoreParams sp = store_params(kv, batch, t + c0, t_per_seq, C);
-    sp.src_steps = count;
-    hipError_t e = launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s);
-    if ((rc = launch_status(e, "kv_append_block")) != TEMPO_OK) return rc;
-    rc = do_partial(kv, qc, nullptr, nullptr, oc, batch, Hq, t + c0, t_per_seq, window, scale, &plan, workspace, s,
-                    C, nullptr, 0, count);
-    if (rc != TEMPO_OK) return rc;
-    if (plan.num_splits > 1) {
-      rc = do_combine(kv, oc, batch, Hq, t + c0, t_per_seq, window, &plan, workspace, s, C, 0, count);
-      if (rc != TEMPO_OK) return rc;
-    }
-  }
-  return TEMPO_OK;
+  // A call beyond the index range of one launch goes block by block too.
+  return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s);
 }
 
 int tempo_prefill_causal(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out,
@@ -1216,8 +1262,10 @@ int tempo_rope_prefill_window(const tempo_kv* kv, const tempo_rope* rope, const 
 int tempo_prefill_launches(const tempo_kv* kv, int32_t batch, int32_t num_q_heads, int32_t count) {
   if (check_layout(kv) != TEMPO_OK || check_heads(kv, batch, num_q_heads) != TEMPO_OK || count < 1) return 0;
   const int32_t G = num_q_heads / kv->num_kv_heads, block = kMaxColumns / G;
-  if (kv->ring_blocks == 0 && prompt_in_one_launch(kv, batch, num_q_heads, count))
-    return kv->dtype == TEMPO_BF16 && prompt_fills_part(kv, batch, G, count) ? 2 : 3;  // then no key range is split
+  if (kv->ring_blocks == 0 && prompt_in_one_launch(kv, batch, num_q_heads, count)) {
+    if (kv->dtype != TEMPO_BF16) return 3;
+    if (prompt_fills_part(kv, batch, G, count)) return 2;  // one launch, and no key range is split
+  }
   return 3 * ((count + block - 1) / block);
 }
 

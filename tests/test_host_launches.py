@@ -155,3 +155,31 @@ def test_kernel_of_a_bf16_prompt_over_a_short_range(lib, Hq, Hkv, D, t, count, w
     launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, 100), 2, Hq, t, count, window)
     assert [n for n, _ in launches][:2] == ["append", kernel]
     assert_all_keys_launched(launches, Hq // Hkv, t, count)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,t,count,window,blocks", [
+    (T.TEMPO_BF16, 24, 8, 128, 1, 8000, 1, 0, 1), (T.TEMPO_BF16, 24, 8, 128, 16, 300, 5, 0, 1),    # the single-step kernel's
+    (T.TEMPO_BF16, 24, 8, 128, 1, 32000, 21, 0, 1), (T.TEMPO_BF16, 24, 8, 128, 1, 2000, 21, 0, 0),  # long and short histories
+    (T.TEMPO_BF16, 8, 1, 128, 1, 32000, 42, 0, 3), (T.TEMPO_BF16, 8, 2, 64, 1, 30000, 40, 0, 2),
+    (T.TEMPO_BF16, 8, 1, 128, 1, 1000, 2, 0, 0), (T.TEMPO_BF16, 24, 8, 128, 64, 8000, 3, 0, 0),     # fills the part
+    (T.TEMPO_BF16, 24, 8, 128, 1, 3000, 5, 64, 1), (T.TEMPO_BF16, 24, 8, 128, 4, 30000, 42, 64, 0),
+    (T.TEMPO_F32, 24, 8, 128, 1, 2000, 16, 0, 1), (T.TEMPO_F32, 24, 8, 128, 1, 2000, 64, 0, 0)])
+def test_prompts_behind_long_histories_go_block_by_block(lib, dtype, Hq, Hkv, D, batch, t, count, window, blocks):
+    for ring in (False, True) if window else (False,):
+        check_route(lib, dtype, Hq, Hkv, D, batch, t, count, window, blocks, ring)
+
+
+def check_route(lib, dtype, Hq, Hkv, D, batch, t, count, window, blocks, ring):
+    G, Z = Hq // Hkv, 64
+    R = T.tempo_ring_blocks(window, Z, min(count, 128 // G)) if ring else 0
+    launches = prefill(lib, store(dtype, Hkv, D, Z, R or (t + count) // Z + 1, R), batch, Hq, t, count, window)
+    assert_all_keys_launched(launches, G, t, count)
+    names = [n for n, _ in launches]
+    answers = [f for n, f in launches if n in ("partial_bf16", "block_bf16", "partial_f32", "step_f32") and f["queries"] <= 128 // G]
+    if blocks:
+        assert len(answers) == blocks and names.count("append") == blocks
+        assert [(f["t"], f["queries"]) for f in answers] == [(t + c, min(128 // G, count - c)) for c in range(0, count, 128 // G)]
+    else:
+        assert names[1] in ("prompt", "prompt_staged", "short_prompt", "partial_f32")
+    bound = lib.tempo_prefill_launches(ctypes.byref(store(dtype, Hkv, D, Z, R or (t + count) // Z + 1, R)), batch, Hq, count)
+    assert len(launches) <= bound
