@@ -142,7 +142,7 @@ bool f32_on_vector_alu(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
   if (keys > (kv->head_dim == 128 ? 192 : 24)) return false;
   const int64_t rows = batch * keys * Hq * queries, shared = G < 8 ? 8 : (G > 32 ? 32 : G);
   if (queries == 1) return rows <= 3200 * shared;
-  return keys > 96 ? rows <= 36000 : queries <= (kv->head_dim == 128 ? 16 : 8) && rows <= 12000;
+  return keys > 64 ? rows <= 36000 : queries <= (kv->head_dim == 128 ? 16 : 8) && rows <= 12000;
 }
 
 // Split planning: a small time model of the launch, in nanoseconds, with constants
@@ -1010,16 +1010,19 @@ bool prompt_in_one_launch(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t
 }
 
 // fp32: tiles of 16 (step, head) columns, the keys of a tile spread over 8 wavefronts.  A tile's
-// group of 16 keys costs about 1 us at D = 128; the key range is split (and combined, 5 us) only
-// if the tiles leave most of the part idle and a wavefront would walk more than 8 groups.
+// group of 16 keys costs about 2 us at D = 128; the key range is split (and combined, 5 us) only
+// if the tiles leave most of the part idle and a wavefront would walk more than 6 groups (1 sequence,
+// 16/1 heads, 16 steps behind 1000 keys: one split 33.6 us, 4 splits 22; 64 steps of 24/8 heads behind
+// 500: 25.0, 3 splits 26.4).
 PromptPlan plan_prompt_f32(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
                            size_t workspace_bytes) {
   const int64_t columns = (int64_t)count * (Hq / kv->num_kv_heads);
   const int64_t tiles = (columns + 15) / 16 * kv->num_kv_heads * batch, rows = (int64_t)batch * count * Hq;
   PromptPlan plan = {8, kWholeRange, 1};
-  const int64_t keys = window > 0 && window < t ? (int64_t)window + count : (int64_t)t + count;
+  const int64_t steps = 16 / (columns / count) + 1;  // of a tile
+  const int64_t keys = window > 0 && window + steps < (int64_t)t + count ? window + steps : (int64_t)t + count;
   if (keys <= 256) plan.waves = 4;
-  for (int k = 10; k <= 20 && tiles < kComputeUnits / 2; ++k) {
+  for (int k = 8; k <= 20 && keys >= 768 && tiles < kComputeUnits / 2; ++k) {
     const int splits = splits_bound(t + count - 1, union_window(window, count), k);
     if (splits == 1) break;
     if (splits > 8 || tiles * splits > 2 * kComputeUnits || plan_bytes(kv, rows, splits) > workspace_bytes) continue;
