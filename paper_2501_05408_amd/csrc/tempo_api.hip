@@ -890,21 +890,23 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
                 workspace_bytes, stream, 1, rope);
 }
 
-// Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
-// than 64, and at most 128 keys for the longest block of 128 columns (us, block kernel / prompt kernel, 24/8
-// heads: 16 sequences of 64 steps 12.2 / 13.5, 128 steps 22.8 / 24.0, 200 steps 35.3 / 35.9, 300 steps behind
-// a history with window 64 41.3 / 45.1, 1 sequence of 42 steps 11.5 / 12.2).  At D = 64 the prompt kernel is
-// the faster one throughout (8 sequences, 32/8 heads, 128 steps 12.7 / 11.9).
-bool short_prompt(const tempo_kv* kv, int32_t Hq, int32_t t, int32_t count, int32_t window) {
-  const int32_t G = Hq / kv->num_kv_heads, QB = kMaxColumns / G;
-  const int64_t all = (int64_t)t + count, most = (int64_t)window + QB - 1;
-  return kv->head_dim == 128 && (int64_t)count * G > 64 && (window > 0 && most < all ? most : all) <= 128;
-}
-
 // Do a prompt's blocks of 128 columns alone give every compute unit one?
 bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
   const int32_t QB = prefill_bf16_block_steps(G, 4);
   return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
+}
+
+// Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
+// than 64, and at most 128 keys for the longest block of 128 columns (us, block kernel / prompt kernel, 24/8
+// heads: 16 sequences of 64 steps 12.2 / 13.5, 128 steps 22.8 / 24.0, 200 steps 35.3 / 35.9, 300 steps behind
+// a history with window 64 41.3 / 45.1, 1 sequence of 42 steps 11.5 / 12.2; windows only if the blocks fill the
+// part: 1 sequence of 42 steps behind a history 14.3 / 13.3).  At D = 64 the prompt kernel is
+// the faster one throughout (8 sequences, 32/8 heads, 128 steps 12.7 / 11.9).
+bool short_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window) {
+  const int32_t G = Hq / kv->num_kv_heads, QB = kMaxColumns / G;
+  const int64_t all = (int64_t)t + count, most = (int64_t)window + QB - 1;
+  if (kv->head_dim != 128 || (int64_t)count * G <= 64) return false;
+  return all <= 128 || (window > 0 && most <= 128 && prompt_fills_part(kv, batch, G, count));
 }
 
 // Is a prompt answered block by block (blocks of 128 columns, each written, attended with split key ranges and
@@ -931,7 +933,7 @@ bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, 
     make_block_plan(kv, batch, Hq, t, window, false, count, &plan);
     return !(pairs < kManyPairs && plan.num_splits > 8 && columns >= 8 && count > 1 && keys <= 2200);
   }
-  if (short_prompt(kv, Hq, t, count, window)) return false;
+  if (short_prompt(kv, batch, Hq, t, count, window)) return false;
   const bool narrow = kv->head_dim == 64;
   const double stream = (double)pairs * keys * kv->head_dim * 4 / (kSustainedBytesPerNs * 1000.0);
   const int64_t blocks = (count + block - 1) / block, widest = columns < kMaxColumns ? columns : kMaxColumns;
@@ -1057,7 +1059,7 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
   // (and staged keys/values lie where the partials of split ranges would)
-  const bool is_short = bf16 && !staged && short_prompt(kv, Hq, t, count, window);
+  const bool is_short = bf16 && !staged && short_prompt(kv, batch, Hq, t, count, window);
   const PromptPlan plan = is_short ? PromptPlan{8, kWholeRange, 1}
                           : bf16   ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
                                    : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
