@@ -73,7 +73,8 @@ def test_prompt_shapes(B, Hkv, G, D, t, count, window):
 @pytest.mark.parametrize("least_workspace", [False, True])
 def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window, least_workspace):
     """With the workspace tempo_prefill_workspace_bytes asks for the prompt is staged there; with the
-    least that is accepted, answered in chunks the ring can hold."""
+    least that is accepted, the first three in several staged pieces.  (The last three fit the ring as
+    one chunk either way; several chunks: test_ring_prompts_in_chunks.)"""
     run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace)
 
 
@@ -340,3 +341,12 @@ def test_f32_blocks_where_the_kernel_changes(B, Hkv, G, D, t, count, window):
                           for c in range(count)], dim=1)
     got = st.attend_block(qd, torch.empty_like(qd), t, count, window, rope=True)
     assert torch.equal(got, st.attend_block(turned, torch.empty_like(qd), t, count, window))
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window", [
+    (16, 32, 1, 64, 256, 0, 700, 100), (16, 32, 1, 64, 256, 77, 500, 100), (8, 64, 2, 64, 64, 13, 330, 40),
+    (64, 8, 3, 128, 256, 0, 1100, 300)])
+def test_ring_prompts_in_chunks(B, Hkv, G, D, Z, t, count, window):
+    """Shapes whose least workspace has no room to stage the prompt (test_host_launches.py checks that
+    they take this path): each chunk written into the ring and answered from it."""
+    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=True)

@@ -183,3 +183,44 @@ def check_route(lib, dtype, Hq, Hkv, D, batch, t, count, window, blocks, ring):
         assert names[1] in ("prompt", "prompt_staged", "short_prompt", "partial_f32")
     bound = lib.tempo_prefill_launches(ctypes.byref(store(dtype, Hkv, D, Z, R or (t + count) // Z + 1, R)), batch, Hq, count)
     assert len(launches) <= bound
+
+
+def least_prompt_workspace(lib, kv, batch, Hq, t, count, window):
+    """What the blocks of 128 columns need, and no byte more: the least a prompt is accepted with."""
+    block, need = 128 // (Hq // kv.num_kv_heads), 0
+    for c in range(0, count, block):
+        n, plan = min(block, count - c), T.tempo_plan()
+        assert lib.tempo_attn_block_plan(ctypes.byref(kv), batch, Hq, n, t + c, window, 0, ctypes.byref(plan)) == T.TEMPO_OK
+        need = max(need, lib.tempo_attn_plan_workspace_bytes(ctypes.byref(kv), batch * n, Hq, ctypes.byref(plan)))
+    return need
+
+
+# (B, Hkv, G, D, Z, t, count, window) whose least workspace has no room to stage more than a chunk, and ...
+CHUNKED = [(16, 32, 1, 64, 256, 0, 700, 100), (16, 32, 1, 64, 256, 77, 500, 100), (8, 64, 2, 64, 64, 13, 330, 40),
+           (64, 8, 3, 128, 256, 0, 1100, 300)]
+# ... some that has
+STAGED = [(2, 2, 3, 128, 32, 0, 700, 100), (1, 4, 4, 64, 64, 0, 333, 33), (3, 1, 8, 128, 32, 77, 400, 64)]
+
+
+@pytest.mark.parametrize("shape", CHUNKED + STAGED)
+def test_ring_prompts_with_the_least_workspace(lib, shape):
+    B, Hkv, G, D, Z, t, count, window = shape
+    ring = T.tempo_ring_blocks(window, Z, min(count, 128 // G))
+    kv = store(T.TEMPO_BF16, Hkv, D, Z, ring, ring)
+    need = least_prompt_workspace(lib, kv, B, Hkv * G, t, count, window)
+    launches = prefill(lib, kv, B, Hkv * G, t, count, window, need)
+    assert_all_keys_launched(launches, G, t, count)
+    names = [n for n, _ in launches]
+    if shape in STAGED:
+        assert names.count("stage") >= 1 and "prompt_staged" in names
+    else:
+        assert "stage" not in names and names.count("append") >= 3
+        at = t
+        for (name, f), (_, answer) in zip(launches[::2], launches[1::2]):   # written, then answered, chunk by chunk
+            assert name == "append" and (f["t"], f["count"]) == (answer["t"], answer["queries"]) == (at, f["count"])
+            at += f["count"]
+            # all that the chunk's steps see is still in the ring when it has been written
+            oldest = max(0, f["t"] - window + 1)
+            assert (at - 1) // Z - oldest // Z < ring
+    assert lib.tempo_prefill_window(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, B, Hkv * G, t, count, None,
+                                    window, 0.125, SOMEWHERE, need - 256, None) == T.TEMPO_ERR_WORKSPACE
