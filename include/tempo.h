@@ -34,8 +34,11 @@
  *    negative tempo_status before launching anything if they are bad.  Block
  *    ids read from the table on the device are clamped into [0, num_blocks),
  *    so a corrupt table gives wrong numbers, not a memory fault.
- *  - The result never depends on pool contents outside the visible range:
- *    masking is by index (the paper's -inf mask under max, 0 mask under sums).
+ *  - The result never depends on pool contents outside the visible range (of a call
+ *    that answers several steps: outside the union of their ranges): masking is by
+ *    index (the paper's -inf mask under max, 0 mask under sums).  Inside that union a
+ *    bf16 value that a step does not see is multiplied by a weight of 0, so one that is
+ *    not finite may show in steps of the call that do not see it (fp32: it does not).
  *
  * Supported shapes: head_dim in {64, 128}; block_size a power of two, >= 32
  * for bf16 and >= 4 for f32; num_q_heads a multiple of num_kv_heads with a

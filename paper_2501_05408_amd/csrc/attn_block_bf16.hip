@@ -10,17 +10,16 @@
 // the range).  The key/value image of a 32-slot group (16 KiB at D = 128) is the same for
 // all wavefronts: the workgroup copies it once from the pool into LDS (it is already in
 // MFMA operand order there, 1 KiB units) and every wavefront reads its operands from LDS.
-// Two key and two value buffers (32 KiB): four or five workgroups share a compute unit, and
-// it is their number that hides the latency of the stream.  The prompt kernel
-// (attn_prefill_bf16.hip: 32 columns per wavefront, deeper buffers of 64 KiB) is the faster one
-// for whole prompts and the slower one here: 21 steps of 3 heads, 16 sequences, t = 4075:
-// 60.3 us per call with this kernel, 62.6 us with that one.
+// Two key and two value buffers (32 KiB at D = 128, 16 at D = 64): at D = 128 five workgroups of 2
+// wavefronts (LDS), three of 4 or two of 8 (registers) fit a compute unit, and it is their number that
+// hides the latency of the stream.  The prompt kernel (attn_prefill_bf16.hip: 32 columns per
+// wavefront, deeper buffers of 64 KiB) is the faster one for whole prompts and the slower one here:
+// 21 steps of 3 heads, 16 sequences, t = 4075: 60.3 us per call with this kernel, 62.6 us with that one.
 //
 // Prompts over a short range come here too (kBlocks; a block of 128 columns per workgroup, no split):
 // twice the wavefronts per compute unit cover a workgroup's beginning and end, which are most of it
 // then.  Which prompts: short_prompt() in tempo_api.hip.
 #include "attn_bf16_common.h"
-
 
 namespace tempo {
 namespace {

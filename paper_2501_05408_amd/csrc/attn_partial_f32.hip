@@ -22,8 +22,9 @@
 // What bounds it.  A step: HBM.  16 sequences, 24/8 heads of 128, t = 2047 (269 MB): one
 // workgroup per query head and 16 lanes per key (shuffles, each head reading the group's keys
 // and values) took 117.6 us a step; this kernel 49 us.  A prompt of 512 steps, 8/2 heads of 64,
-// in blocks of 128 columns 203 us, as one launch of this kernel 17.5 us.  Blocks and prompts: 64 products of 32
-// cycles per group at D = 128, half of them padding when a tile holds few columns.
+// in blocks of 128 columns 203 us, as one launch of this kernel 16.9 us.  Blocks and prompts: 64 products
+// of 32 cycles per group at D = 128, most of them padding when a tile holds few columns: steps and small
+// blocks over short ranges go to attn_step_f32.hip.
 #include <type_traits>
 
 #include "attn_bf16_common.h"
@@ -305,8 +306,8 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   __syncthreads();
 
   // All wavefronts' values of an element in one batch of reads: a loop over them is a chain of LDS
-  // round trips (24/8 heads of 128, 1 sequence, t = 150, 8 wavefronts: 10.0 us a step with the loop, 9.5 us; 1 head
-  // group of 16, t = 299: 11.4 us, 10.3 us).
+  // round trips (24/8 heads of 128, 1 sequence, t = 150, 8 wavefronts: 10.0 us a step with the loop, 9.5 us; a
+  // group of 16 heads, t = 15: 7.4 us, 6.2 us).
   auto merge = [&](auto waves) {
     for (int idx = threadIdx.x; idx < ncols * (D / 4); idx += blockDim.x) {
       const int jcol = idx / (D / 4), d = 4 * (idx - jcol * (D / 4));

@@ -297,6 +297,8 @@ size_t plan_bytes(const tempo_kv* kv, int64_t rows, int32_t S) {
   return ml_bytes(rows, S) + align_up((size_t)rows * S * kv->head_dim * sizeof(float), 256);
 }
 
+// The decode kernel's wave-merge area: a limit of its launch.  (The fp32 kernel asks for up to 68,608
+// bytes, the prompt kernel for up to 128 KiB, of the 160 KiB a compute unit has.)
 constexpr size_t kMaxLds = 64 * 1024;
 
 AttnParams attn_params(const tempo_kv* kv, const void* q, void* out, int32_t Hq, int32_t t,
@@ -919,8 +921,8 @@ bool short_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int3
 //   few columns behind a short range, whose many splits cost more to combine (1 sequence, 8/1 heads, 2 steps
 //   behind 1000 keys 14.0, 11.1).
 //   bf16, more columns: by two estimates in us, fitted to 1050 measured prompts of 1 to 128 pairs (on the mean
-//   0.2% from the better of the two), unless their blocks fill the part.  A block takes 15 and 1.05 to 1.5 times its keys' stream from HBM; one
-//   launch 8 and the longer of a workgroup's walk through an eighth of the keys and 1.2 times the stream
+//   0.2% from the better of the two), unless their blocks fill the part.  A block takes 15 and 1.05 to
+//   1.5 times its keys' stream from HBM; one launch 8 and the longer of a workgroup's walk through an eighth of the keys and 1.2 times the stream
 //   (1 sequence, 24/8 heads, 21 steps behind 4000 keys 21, 20, behind 8000 24, 30, behind 32000 48, 85).
 bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window) {
   const int32_t G = Hq / kv->num_kv_heads, block = kMaxColumns / G;
@@ -979,7 +981,7 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
     if (QB < 1) break;
     const int64_t blocks = (count + QB - 1) / QB;
     const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
-    const int resident = 2;
+    const int resident = 2;  // (at D = 64 more would fit; the constants were fitted with 2 there too)
     for (int k = kWholeRange; k >= 7; k = k == kWholeRange ? 13 : k - 1) {
       const int splits = k == kWholeRange ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
       if (k != kWholeRange && !may_split) break;
