@@ -959,9 +959,11 @@ struct PromptPlan {
 // 5 us before its first and after its last group, and an iteration over a 32-slot group takes 0.55 us
 // with one wavefront on a SIMD, 0.78 us with two, and 0.64 us with one where two workgroups of 2 copy
 // each their own keys/values.  So 4 wavefronts win once they fill the part; 2, and a key range cut into
-// splits (with a combine launch of about 5 us, and partials of (D + 2) * 4 bytes per column and split),
-// when the query columns alone do not (100 steps behind 1900 keys, one sequence: no splits 52 us, 8
-// splits 25 us).
+// splits (a combine launch, and partials of (D + 2) * 4 bytes per column and split), when the query
+// columns alone do not (100 steps behind 1900 keys, one sequence: no splits 52 us, 8 splits 25 us).
+// The combine is priced at 1.5 us beside the rest of the model: over 1496 measured prompts that fits
+// best (0.4% off the fastest of 1.5, 2.5, 3.5 and 5 us on the mean, 9% at most; 5 us 3.1% and 51%: 4
+// sequences of 21 steps, 24/8 heads, window 512: 19.6 us unsplit, 14.8; 1 and 2 us like 1.5).
 // 8 wavefronts in one workgroup read each key/value half as often, but nothing covers the
 // workgroup's beginning and end: the better shape only for long ranges at D = 128 (us with 4 / 8:
 // 16 x 200 steps 32.7 / 35.7, 16 x 1000 185 / 200, 4 x 4000 449 / 437; D = 64, 8 x 1500 125 / 147).
@@ -996,7 +998,7 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
       // a causal prompt's blocks are half the longest on average: beyond the first round that counts
       const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;
       double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (!shared ? 550.0 : waves == 4 ? 780.0 : 640.0) * scale);
-      if (splits > 1) ns += 5000.0 + 2.0 * (double)rows * splits * kv->head_dim * 4 / 4000.0;
+      if (splits > 1) ns += 1500.0 + 2.0 * (double)rows * splits * kv->head_dim * 4 / 4000.0;
       if (best_ns < 0.0 || ns < 0.97 * best_ns) {  // the wider workgroup and the fewer splits unless clearly slower
         best_ns = ns;
         best = {waves, k, splits};

@@ -185,6 +185,17 @@ def check_route(lib, dtype, Hq, Hkv, D, batch, t, count, window, blocks, ring):
     assert len(launches) <= bound
 
 
+@pytest.mark.parametrize("Hq, Hkv, D, batch, t, count, window, split", [
+    (24, 8, 128, 4, 3000, 21, 512, True), (24, 8, 128, 2, 4000, 42, 512, True), (32, 8, 64, 2, 3000, 21, 512, True),
+    (8, 2, 64, 1, 1000, 64, 512, True), (1, 1, 128, 1, 4000, 42, 300, True), (24, 8, 128, 4, 3000, 21, 64, False)])
+def test_key_ranges_of_windowed_prompts_are_split_where_that_is_faster(lib, Hq, Hkv, D, batch, t, count, window, split):
+    for ring in (0, T.tempo_ring_blocks(window, 64, count)):
+        launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, ring or (t + count) // 64 + 1, ring), batch, Hq, t, count, window)
+        assert_all_keys_launched(launches, Hq // Hkv, t, count)
+        assert [n for n, _ in launches] == ["append", "prompt"] + (["prompt_combine"] if split else [])
+        assert (launches[1][1]["grid_splits"] > 1) == split
+
+
 def least_prompt_workspace(lib, kv, batch, Hq, t, count, window):
     """What the blocks of 128 columns need, and no byte more: the least a prompt is accepted with."""
     block, need = 128 // (Hq // kv.num_kv_heads), 0
