@@ -29,9 +29,11 @@
 // back-to-back products; separate product and softmax phases of the two wavefronts, with a
 // barrier between, were slower than this order for that reason).  Measured on 16 prompts of
 // 4096 steps, 24 query heads in 8 groups, D = 128 (1.65 Tflop): 16-column kernel 2082 us a
-// call, this one 1877 us (back to back; 1750 us in short runs, before the clock drops);
-// 1750 cycles per group and pair of wavefronts (1020 of them
-// products), 9900 before the first and 4100 after the last group of a workgroup.
+// call, this one 1800 us (back to back, the clock at 1.8 GHz); 1700 cycles per group and pair of
+// wavefronts (1020 of them products), 11000 before the first and 4400 after the last group of a
+// workgroup.  Every vector instruction of the loop counts: without the eight moves of the next
+// group's logits and with one comparison for a reference that stays, 1859 -> 1800 us; 499 steps of
+// one sequence, 32/8 heads of 64, 15.2 -> 14.7; 4 x 2048 with window 512 105 -> 102.8.
 //
 // Workgroups of one (sequence, head) are adjacent in the work list and run together on
 // one die, so the pool is streamed from HBM about once per (sequence, head) and the
@@ -74,24 +76,28 @@ __device__ inline float half_sum(float v) {
 // maximum.  The result acc / sum does not depend on ref.
 constexpr float kSlack = 8.0f;
 
-// Maximum of the group's logits over the column, in log2 units.  x holds the RAW dot
-// products (masked ones are -inf); `scale` > 0 is s * log2(e).
-__device__ inline float tile_max(const f32x16& x, float scale) {
+// Maximum of this lane's sixteen logits.  x holds the RAW dot products (masked ones are -inf).
+__device__ inline float tile_max(const f32x16& x) {
   const float a = max3(x[0], x[1], x[2]), b = max3(x[3], x[4], x[5]), c = max3(x[6], x[7], x[8]);
   const float d = max3(x[9], x[10], x[11]), e = max3(x[12], x[13], x[14]);
-  return half_max(max3(max3(a, b, c), max3(d, e, x[15]), x[15])) * scale;
+  return max3(max3(a, b, c), max3(d, e, x[15]), x[15]);
 }
 
 // First half: move the reference if this group's maximum calls for it.  A lane's
 // sixteen logits, its accumulators and its share of the sum all belong to ONE column,
-// so the rescale factor needs no exchange.
+// so the rescale factor needs no exchange.  Most groups move nothing, so that case is one
+// comparison: of the lane's own raw maximum (the lanes of a column meet only behind the branch)
+// with `limit`, the raw dot product from which on the reference has to move.
 template <int D>
-__device__ inline void softmax_reference(float mx, float& ref, float& base, f32x16* acc, float& sum) {
-  // ref = -inf until the column sees its first key; -inf + kSlack = -inf, so any finite mx moves it
-  const bool move = mx > ref + kSlack;
-  if (__any(move)) {
+__device__ inline void softmax_reference(float lane_max, float scale, float& limit, float& ref, float& base, f32x16* acc,
+                                         float& sum) {
+  if (__any(lane_max > limit)) {
+    const float mx = half_max(lane_max) * scale;  // `scale` > 0 is s * log2(e)
+    // ref = -inf until the column sees its first key; -inf + kSlack = -inf, so any finite mx moves it
+    const bool move = mx > ref + kSlack;
     const float alpha = move ? fast_exp2(ref - mx) : 1.0f;  // exp2(-inf) = 0 on the first key
     ref = move ? mx : ref;
+    limit = (ref + kSlack) / scale;
     base = ref == -INFINITY ? 0.f : ref;  // a column that has seen no key yet: weights exp2(-inf - 0) = 0
     sum *= alpha;
 #pragma unroll
@@ -306,13 +312,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // The groups no column's range cuts: first_whole .. last_whole.
   const int first_whole = (own.lo_last + 31) >> 5, last_whole = ((own.hi_min + 1) >> 5) - 1;
   float base = 0.f;                            // m_run, or 0 while the column has seen no key
-  // mask and reference of group g, whose logits are in x
+  float limit = -INFINITY;                     // raw dot product from which on m_run has to move
+  // mask and reference of group g, whose logits are in x, their maximum in this lane mx
   auto enter = [&](int g, f32x16& x, float mx) {
     if (g < first_whole || g > last_whole) {
       mask_tile(g, lo_col, hi_col, lane, x);
-      mx = tile_max(x, p.scale_log2e);
+      mx = tile_max(x);
     }
-    softmax_reference<D>(mx, m_run, base, acc, l_run);
+    softmax_reference<D>(mx, p.scale_log2e, limit, m_run, base, acc, l_run);
   };
   // End of an iteration.  After a barrier the next kPair groups, the group behind them (its
   // logits are computed one group ahead) and, with early operand reads, one more are in LDS.
@@ -340,27 +347,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   auto read_operand = [&](int i) {
     op[i] = i < KT ? key_operand(next(1), i) : value_operand(at0, (i - KT) / OT, (i - KT) % OT);
   };
-  f32x16 xc;                                   // logits of group grp, masked, its reference already moved
+  f32x16 xa, xb;                               // logits of group grp, masked, its reference already moved: in turn
   if (grp <= own_last) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) xc[r] = 0.f;
+    for (int r = 0; r < 16; ++r) xa[r] = 0.f;
 #pragma unroll
     for (int s = 0; s < KT; ++s)
-      xc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(key_operand(at0, s), as_bf16x8(qreg[s]), xc, 0, 0, 0);
-    enter(grp, xc, tile_max(xc, p.scale_log2e));
+      xa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(key_operand(at0, s), as_bf16x8(qreg[s]), xa, 0, 0, 0);
+    enter(grp, xa, tile_max(xa));
     if (kEarly) {
 #pragma unroll
       for (int i = 0; i < kRead; ++i) read_operand(i);
     }
   }
-  for (; grp <= own_last; finish()) {
+  // Group grp, logits in xc; those of group grp + 1 to xn.
+  auto iterate = [&](const f32x16& xc, f32x16& xn) {
     if (!kEarly) {
 #pragma unroll
       for (int i = 0; i < kRead; ++i) read_operand(i);
     }
     u32x4 pa[2];
     float even, mx[5];
-    f32x16 xn;
 #pragma unroll
     for (int r = 0; r < 16; ++r) xn[r] = 0.f;
     __builtin_amdgcn_sched_barrier(0);
@@ -391,8 +398,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
       asm volatile("" : "+v"(l_run));
       __builtin_amdgcn_sched_barrier(0);
     }
-    xc = xn;
-    enter(grp + 1, xc, half_max(max3(max3(mx[0], mx[1], mx[2]), max3(mx[3], mx[4], xn[15]), xn[15])) * p.scale_log2e);
+    enter(grp + 1, xn, max3(max3(mx[0], mx[1], mx[2]), max3(mx[3], mx[4], xn[15]), xn[15]));
+    finish();
+  };
+  // Two groups a turn: with one, the logits move to other registers at its end.
+  while (grp <= own_last) {
+    iterate(xa, xb);
+    if (grp > own_last) break;
+    iterate(xb, xa);
   }
   for (; grp <= g_last; finish()) copies();
   // the copies issued last may still be in flight: they must land before the LDS is given up
