@@ -159,6 +159,26 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   if (!work.any) return;                       // uniform over the workgroup, before any barrier
   const int b = work.b, hkv = work.hkv, c0 = work.c0, ncols = work.ncols, split = work.split;
   const int t_last = work.t_last, start = work.start, g_first = work.g_first, g_last = work.g_last;
+  // The block-table entries of the range's first 64 tiles, one per lane, are asked for before anything
+  // else: the first copies wait for them and for nothing else.
+  const int32_t* table = p.block_table + (int64_t)b * p.max_blocks_per_seq;
+  const int tile_groups = p.z_log2 - 5;             // log2(groups per tile)
+  const int tile_last = g_last >> tile_groups;
+  int tile_base = g_first >> tile_groups;           // lane i holds the byte offset, in either pool, of tile tile_base + i
+  uint32_t tile_lo, tile_hi;
+  auto fetch_entry = [&]() {
+    const int tile = tile_base + lane < tile_last ? tile_base + lane : tile_last;  // never past the range's last tile
+    return table[tile & p.tile_mask];
+  };
+  auto place_tiles = [&](int found) {
+    const uint64_t at = ((uint64_t)((int64_t)clamp_block(found, p.num_blocks) * p.Hkv + hkv) << p.z_log2) * (D * 2);
+    tile_lo = (uint32_t)at;
+    tile_hi = (uint32_t)(at >> 32);
+    // waited for here: the use in the loop must not become a wait for the copies in flight
+    asm volatile("" : "+v"(tile_lo), "+v"(tile_hi));
+  };
+  const int entry = fetch_entry();
+
   const int first_col = kWaveColumns * wave;
   const WaveBounds own = wave_bounds(p, work, first_col, kWaveColumns);
 
@@ -172,17 +192,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
     const uint16_t* qp = static_cast<const uint16_t*>(p.q) +
                          (((int64_t)b * p.io_steps + c0 + cq) * p.Hq + (int64_t)hkv * p.G + gq) * D + 8 * half;
 #pragma unroll
-    for (int s = 0; s < KT; ++s) {
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      const u32x4 v = *reinterpret_cast<const u32x4*>(qp + 16 * s);
-      qreg[s] = col < ncols ? v : zero;
-    }
-    if (kRope) {  // queries arrive unrotated; a dim's partner D/2 further sits in the same lane
-#pragma unroll
-      for (int s = 0; s < KT / 2; ++s)
-        rotate_pieces(p.rope_cos, p.rope_sin, step, D / 2, 16 * s + 8 * half, qreg[s], qreg[s + KT / 2]);
-    }
+    for (int s = 0; s < KT; ++s) qreg[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s);
   }
+  __builtin_amdgcn_sched_barrier(0);           // ... on their way before the first copies are, and used behind them
   float m_run = -INFINITY;                     // softmax reference of this lane's column (log2 units)
   float l_run = 0.f;                           // running sum over this lane's slots
   f32x16 acc[OT];                              // dims 32 ot + 8 (r / 4) + 4 h + (r mod 4) of this lane's column
@@ -202,21 +214,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // two kinds return out of order every wait for an operand would become a wait for all.  Beyond the range's last group the last one is
   // copied again (into a buffer nobody reads any more): every iteration then issues the
   // same number of copies, and "the group before the newest has landed" is one counted wait.
-  const int32_t* table = p.block_table + (int64_t)b * p.max_blocks_per_seq;
-  const int tile_groups = p.z_log2 - 5;             // log2(groups per tile)
-  const int tile_last = g_last >> tile_groups;
-  int tile_base = g_first >> tile_groups;           // lane i holds the byte offset, in either pool, of tile tile_base + i
-  uint32_t tile_lo, tile_hi;
-  auto load_tiles = [&]() {
-    const int tile = tile_base + lane < tile_last ? tile_base + lane : tile_last;  // never past the range's last tile
-    const int phys = clamp_block(table[tile & p.tile_mask], p.num_blocks);
-    const uint64_t at = ((uint64_t)((int64_t)phys * p.Hkv + hkv) << p.z_log2) * (D * 2);
-    tile_lo = (uint32_t)at;
-    tile_hi = (uint32_t)(at >> 32);
-    // waited for here: the use in the loop must not become a wait for the copies in flight
-    asm volatile("" : "+v"(tile_lo), "+v"(tile_hi));
-  };
-  load_tiles();
+  place_tiles(entry);
   // A prompt on a ring store: the groups from its first step on lie, as one run per (sequence,
   // head), in the staging area; the ring holds the history.
   const int64_t stage_run = ((int64_t)b * p.Hkv + hkv) * p.stage_groups * (64 * D);
@@ -246,7 +244,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
     const int tile = gc >> tile_groups;
     if (tile - tile_base >= 64) {
       tile_base = tile;
-      load_tiles();
+      place_tiles(fetch_entry());
     }
     const uint32_t lo = __builtin_amdgcn_readlane(tile_lo, tile - tile_base);
     const uint32_t hi = __builtin_amdgcn_readlane(tile_hi, tile - tile_base);
@@ -336,6 +334,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 
 #pragma unroll
   for (int i = 0; i < NBUF - kPair; ++i) issue(i * kBuf, g_first + i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < KT; ++s) {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    qreg[s] = col < ncols ? qreg[s] : zero;
+  }
+  if (kRope) {  // queries arrive unrotated; a dim's partner D/2 further sits in the same lane
+#pragma unroll
+    for (int s = 0; s < KT / 2; ++s)
+      rotate_pieces(p.rope_cos, p.rope_sin, step, D / 2, 16 * s + 8 * half, qreg[s], qreg[s + KT / 2]);
+  }
   landed();                                    // groups g_first .. g_first + kAhead - 1
   if (head) mask_values(g_first, 0);
   if (tail && g_last - g_first < kAhead) mask_values(g_last, (g_last - g_first) * kBuf);
