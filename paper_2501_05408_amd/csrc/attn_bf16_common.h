@@ -159,16 +159,13 @@ __device__ inline void value_masks(int grp, int v_lo, int v_hi, int lane, uint32
 }
 
 // ---- what a workgroup of the block and prompt kernels does -----------------------------
-// Shared by attn_block_bf16.hip (16 columns per wavefront) and attn_prefill_bf16.hip (32): the
-// (step, head) columns of a block of query steps, column = c*G + g, against one split of the
-// block's key range.
-
-// Steps per workgroup of `columns` columns for a query group of G heads.
-__host__ __device__ inline int block_steps_of(int G, int columns) { return columns / G; }
+// Shared by attn_block_bf16.hip (16 columns per wavefront) and attn_prefill_bf16.hip (32): a block of
+// the call's (step, head) columns, column = c*G + g, against one split of the block's key range.
 
 struct BlockWork {
   int b, hkv;            // sequence, kv head
-  int c0, steps, ncols;  // first step of the block within the call, its steps and columns
+  int c0, steps, ncols;  // first step of the block within the call, the steps it touches, its columns
+  int skip;              // heads of step c0 that belong to the block before
   int t_first, t_last;   // its first and last step
   int split;             // of the block's key range
   int start, end;        // keys of that range in the split ...
@@ -181,7 +178,10 @@ struct BlockWork {
 // a contiguous run of the work list instead: workgroup L takes item (L mod 8) * (n / 8) + L / 8
 // (remainder items spread over the first dies), and the blocks that run together on a die share
 // its L2.  Blocks come longest range first, splits newest first as in the decode kernel.
-// kBlocks: the call's steps are cut into blocks of `columns` columns; else they are one block.
+// kBlocks: the call's columns are cut into blocks of `columns`; else they are one block.  A block may
+// begin and end between the heads of a step: with whole steps, 3 heads leave 2 of 128 columns empty (4 x
+// 2048 steps, window 512, 8 groups of 3 heads: 1568 workgroups, 32 more than three rounds of 512 hold, and
+// 101.2 us a call, 100.0 now).
 template <bool kBlocks>
 __device__ inline BlockWork block_work(const AttnParams& p, int columns) {
   BlockWork w;
@@ -194,23 +194,28 @@ __device__ inline BlockWork block_work(const AttnParams& p, int columns) {
   w.b = (int)(iyz / ny);
   int zsplit = (int)ix;                                       // 0 unless the key range is split
   w.c0 = 0;
+  w.skip = 0;
   w.steps = p.queries;
   w.any = true;
   if (kBlocks) {
-    const int QB = block_steps_of(p.G, columns);
-    const int nblocks = (p.queries + QB - 1) / QB;
+    const unsigned G = (unsigned)p.G, nblocks = prompt_blocks(p.queries, p.G, columns);
     zsplit = (int)(ix / nblocks);
-    w.c0 = (nblocks - 1 - (int)(ix % nblocks)) * QB;
+    const unsigned first = (nblocks - 1 - ix % nblocks) * (unsigned)columns;  // of the call's columns: below 2^32
     // steps of this sequence in the call: all of them, or its own count
     int steps_b = p.queries;
     if (p.count_per_seq) {
       const int n = ((const_i32_ptr)p.count_per_seq)[w.b];
       steps_b = n < 0 ? 0 : (n < p.queries ? n : p.queries);
     }
-    w.any = w.c0 < steps_b;
-    w.steps = steps_b - w.c0 < QB ? steps_b - w.c0 : QB;
+    const unsigned all = (unsigned)steps_b * G;
+    w.any = first < all;
+    w.ncols = (int)(all - first < (unsigned)columns ? all - first : (unsigned)columns);
+    w.c0 = (int)(first / G);
+    w.skip = (int)(first - (unsigned)w.c0 * G);
+    w.steps = (w.skip + w.ncols - 1) / p.G + 1;
+  } else {
+    w.ncols = w.steps * p.G;
   }
-  w.ncols = w.steps * p.G;
   int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[w.b] : p.t; // first step of the call for this sequence
   t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
   w.t_first = t_base + w.c0;
@@ -238,8 +243,8 @@ __device__ inline WaveBounds wave_bounds(const AttnParams& p, const BlockWork& w
   WaveBounds o;
   const int last_col = (first_col + columns - 1) < w.ncols - 1 ? (first_col + columns - 1) : w.ncols - 1;
   o.idle = first_col >= w.ncols;
-  const int own_hi = w.t_first + (o.idle ? 0 : last_col / p.G);
-  const int own_hi_min = w.t_first + (o.idle ? 0 : first_col / p.G);
+  const int own_hi = w.t_first + (o.idle ? 0 : (w.skip + last_col) / p.G);
+  const int own_hi_min = w.t_first + (o.idle ? 0 : (w.skip + first_col) / p.G);
   const int own_lo_first = (p.window > 0 && own_hi_min - p.window + 1 > 0) ? own_hi_min - p.window + 1 : 0;
   const int own_lo_last = (p.window > 0 && own_hi - p.window + 1 > 0) ? own_hi - p.window + 1 : 0;
   o.hi = own_hi < w.end ? own_hi : w.end;
@@ -257,8 +262,8 @@ struct LaneColumn {
 };
 __device__ inline LaneColumn lane_column(const AttnParams& p, const BlockWork& w, int col) {
   LaneColumn o;
-  o.cq = col < w.ncols ? col / p.G : w.steps - 1;
-  o.gq = col < w.ncols ? col - o.cq * p.G : 0;
+  o.cq = col < w.ncols ? (w.skip + col) / p.G : w.steps - 1;
+  o.gq = col < w.ncols ? w.skip + col - o.cq * p.G : 0;
   o.step = w.t_first + o.cq;
   o.hi = o.step < w.end ? o.step : w.end;
   const int lo_own = (p.window > 0 && o.step - p.window + 1 > 0) ? o.step - p.window + 1 : 0;

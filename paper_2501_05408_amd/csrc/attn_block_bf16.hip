@@ -272,7 +272,7 @@ __global__ __launch_bounds__(64 * NW) void attn_block_bf16(AttnParams p) {
     const float l_j = acc_l[r];
     const float ref_j = __shfl(m_run, 4 * c + r);  // the reference lives in lane (column & 15)
     if (j < ncols) {
-      const int jc = j / p.G, jg = j - jc * p.G;
+      const int jc = (work.skip + j) / p.G, jg = work.skip + j - jc * p.G;
       if (p.direct) {
         __bf16* orow = static_cast<__bf16*>(p.out) +
                        (((int64_t)b * p.io_steps + c0 + jc) * p.Hq + (int64_t)hkv * p.G + jg) * D;
@@ -323,9 +323,8 @@ hipError_t launch_block_nw(const AttnParams& p, int batch, int D, int grid_split
 hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipStream_t stream) {
   constexpr int NW = 8;
   if (D != 128 || !p.direct) return hipErrorInvalidConfiguration;
-  const int QB = block_steps_of(p.G, kWaveColumns * NW);
-  if (QB < 1) return hipErrorInvalidConfiguration;
-  const int64_t nblocks = (p.queries + QB - 1) / QB;
+  if (p.G > kWaveColumns * NW) return hipErrorInvalidConfiguration;
+  const int64_t nblocks = prompt_blocks(p.queries, p.G, kWaveColumns * NW);
   if (nblocks * p.Hkv * batch > INT32_MAX) return hipErrorInvalidConfiguration;  // 32-bit work items
   const dim3 grid((unsigned)nblocks, p.Hkv, batch);
   const size_t lds = 2 * (size_t)(2 * (D / 32) + D / 16) * 1024;

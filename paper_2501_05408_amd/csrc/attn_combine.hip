@@ -27,9 +27,9 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
                                  p.num_splits, n, 1, static_cast<char*>(p.out) + orow * D * esz, smem);
 }
 
-// One float4 column of a row per thread; block_steps > 0: ranges by blocks of steps.
+// One float4 column of a row per thread; block_columns > 0: ranges by blocks of a prompt's columns.
 template <int D, bool kBf16>
-__device__ __forceinline__ void combine_few(const AttnParams& p, int rows, int block_steps) {
+__device__ __forceinline__ void combine_few(const AttnParams& p, int rows, int block_columns) {
   constexpr int C4 = D / 4;
   constexpr int U = 8;
   const int idx = blockIdx.x * 256 + threadIdx.x;
@@ -40,10 +40,13 @@ __device__ __forceinline__ void combine_few(const AttnParams& p, int rows, int b
   int t_b = p.t_per_seq ? p.t_per_seq[b] : p.t;
   t_b = t_b > p.t ? p.t : (t_b < 0 ? 0 : t_b);
   int t_first = t_b, steps = p.queries;
-  if (block_steps > 0) {
-    const int c0 = (row / p.Hq - b * p.queries) / block_steps * block_steps;
-    t_first += c0;
-    steps = steps - c0 < block_steps ? steps - c0 : block_steps;
+  if (block_columns > 0) {
+    const unsigned at = (unsigned)(row - b * (p.Hq * p.queries)), G = (unsigned)p.G, all = (unsigned)p.queries * G;
+    const unsigned column = at / (unsigned)p.Hq * G + at % (unsigned)p.Hq % G;
+    const unsigned first = column / (unsigned)block_columns * (unsigned)block_columns;
+    const unsigned past = all - first < (unsigned)block_columns ? all : first + (unsigned)block_columns;
+    t_first += (int)(first / G);
+    steps = (int)((past - 1) / G - first / G) + 1;
   }
   const SeqRange rg = seq_range(t_first, p.window, p.tps_log2, steps, p.pad_t);
   const int n = rg.nchunks < p.num_splits ? rg.nchunks : p.num_splits;  // 1..8
@@ -91,10 +94,10 @@ __global__ __launch_bounds__(256) void attn_combine_few(AttnParams p, int rows) 
   combine_few<D, kBf16>(p, rows, 0);
 }
 
-// A prompt: every block of p.block_steps steps has split its own key range.
+// A prompt: every block of p.block_columns columns has split its own key range.
 template <int D>
 __global__ __launch_bounds__(256) void attn_combine_prompt(PromptParams p, int rows) {
-  combine_few<D, true>(p, rows, p.block_steps);
+  combine_few<D, true>(p, rows, p.block_columns);
 }
 }  // namespace
 

@@ -6,9 +6,9 @@
 // decode kernel computes for each of those steps, one after the other.  With many
 // steps per key the products dominate the reads.
 //
-// Mapping.  One workgroup = one (sequence, kv head, block of QB query steps, split of the
-// block's key range; normally one split); its columns are the block's (step, head) pairs,
-// 32 per wavefront (column = c*G + g), as the columns of 32x32x16 products:
+// Mapping.  One workgroup = one (sequence, kv head, block of (step, head) columns, split of the
+// block's key range; normally one split); column = c*G + g, 32 per wavefront, as the columns of
+// 32x32x16 products:
 //   logits tile  = K (32 slots x 16 dims) * Q^T (16 dims x 32 columns)   D/16 steps
 //   output tiles = V^T (32 dims x 16 slots) * P^T (16 slots x 32 columns)  D/32 tiles x 2 steps
 // A lane then holds logits, weights, sum and output of ONE column: no exchange but one lane
@@ -462,8 +462,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 
 }  // namespace
 
-int prefill_bf16_block_steps(int G, int waves) { return block_steps_of(G, kWaveColumns * waves); }
-
 namespace {
 template <int NW>
 hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
@@ -471,9 +469,8 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
   // barrier, an iteration's first operands read in the one before.  Fewer: four buffers, so that
   // at least two workgroups share a compute unit.
   constexpr int NBUF = NW == 8 ? 8 : 4;
-  const int QB = prefill_bf16_block_steps(p.G, NW);
-  if (QB < 1) return hipErrorInvalidConfiguration;
-  const int64_t nblocks = (p.queries + QB - 1) / QB;
+  if (p.G > kWaveColumns * NW || p.block_columns != kWaveColumns * NW) return hipErrorInvalidConfiguration;
+  const int64_t nblocks = prompt_blocks(p.queries, p.G, kWaveColumns * NW);
   // the kernel renumbers its workgroups with 32-bit arithmetic on the linear index
   if (nblocks * grid_splits * p.Hkv * batch > INT32_MAX) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)(nblocks * grid_splits), p.Hkv, batch);
@@ -495,7 +492,7 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
 }
 }  // namespace
 
-// waves: 2, 4 or (D = 128) 8 wavefronts of 32 columns per workgroup; p.block_steps is set to match.
+// waves: 2, 4 or (D = 128) 8 wavefronts of 32 columns per workgroup; p.block_columns is set to match.
 // grid_splits: splits of a block's key range (1 = every workgroup walks its block's whole
 // range and writes `out`; p.tps_log2 must then be kWholeRange).
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream) {

@@ -894,8 +894,7 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
 
 // Do a prompt's blocks of 128 columns alone give every compute unit one?
 bool prompt_fills_part(const tempo_kv* kv, int32_t batch, int32_t G, int32_t count) {
-  const int32_t QB = prefill_bf16_block_steps(G, 4);
-  return (int64_t)((count + QB - 1) / QB) * kv->num_kv_heads * batch >= kComputeUnits;
+  return (int64_t)prompt_blocks(count, G, kMaxColumns) * kv->num_kv_heads * batch >= kComputeUnits;
 }
 
 // Does a bf16 prompt go to the block kernel's form for prompts over short ranges?  At D = 128, more columns
@@ -947,6 +946,8 @@ bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, 
   return by_blocks < one_launch;
 }
 
+constexpr int kWaveColumns = 32;  // of the prompt kernel
+
 // How the prompt kernel takes a prompt: wavefronts of 32 columns per workgroup, and splits of
 // a block's key range (tps_log2 = kWholeRange, splits = 1: none).
 struct PromptPlan {
@@ -975,13 +976,12 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
   double best_ns = -1.0;
   const bool may_split = !prompt_fills_part(kv, batch, G, count);
   const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
-  const int32_t wide = prefill_bf16_block_steps(G, 8);
   const int64_t mean_keys = window > 0 && window < t + count / 2 ? window : t + count / 2;
-  if (kv->head_dim == 128 && mean_keys >= 1800 && (count + wide - 1) / wide * pairs >= 4 * kComputeUnits) return {8, kWholeRange, 1};
+  if (kv->head_dim == 128 && mean_keys >= 1800 && prompt_blocks(count, G, 8 * kWaveColumns) * pairs >= 4 * kComputeUnits) return {8, kWholeRange, 1};
   for (int waves = 4; waves >= 2; waves /= 2) {
-    const int32_t QB = prefill_bf16_block_steps(G, waves);
-    if (QB < 1) break;
-    const int64_t blocks = (count + QB - 1) / QB;
+    if (G > waves * kWaveColumns) break;
+    const int32_t QB = prompt_block_span(G, waves * kWaveColumns);
+    const int64_t blocks = prompt_blocks(count, G, waves * kWaveColumns);
     const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
     const int resident = 2;  // (at D = 64 more would fit; the constants were fitted with 2 there too)
     for (int k = kWholeRange; k >= 7; k = k == kWholeRange ? 13 : k - 1) {
@@ -1073,7 +1073,7 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   p.io_steps = io_steps;
   p.tps_log2 = plan.tps_log2;
   p.direct = plan.splits == 1;
-  p.block_steps = prefill_bf16_block_steps(p.G, plan.waves);
+  p.block_columns = plan.waves * kWaveColumns;
   p.k_stage = p.v_stage = nullptr;
   p.stage_first = p.stage_groups = 0;
   p.count_per_seq = count_per_seq;

@@ -116,7 +116,7 @@ struct AttnParams {
 // What only prompts need; not in AttnParams, because the decode kernel's launch is sensitive to the
 // size of its arguments.
 struct PromptParams : AttnParams {
-  int32_t block_steps;       // query steps per workgroup; each block of them splits its own key range
+  int32_t block_columns;     // (step, head) columns per workgroup; each block of them splits its own key range
   const void* k_stage;       // may be null; groups stage_first .. are read from here ([batch][Hkv][stage_groups]
   const void* v_stage;       //   group images), earlier ones from the pool
   int32_t stage_first, stage_groups;
@@ -129,6 +129,15 @@ constexpr int kWholeRange = 31;
 // Last key of split `chunk`.
 __host__ __device__ inline int split_end(int chunk, int tps_log2) {
   return (int)((((uint32_t)chunk + 1u) << tps_log2) - 1u);
+}
+
+// A prompt's (step, head) columns, step by step, are cut into blocks of `columns` (at least G): how many ...
+__host__ __device__ inline uint32_t prompt_blocks(int queries, int G, int columns) {
+  return ((uint32_t)queries * (uint32_t)G + (uint32_t)columns - 1u) / (uint32_t)columns;  // queries <= 2^24, G <= 128
+}
+// ... and the most steps one of them touches (a block may begin and end inside a step).
+__host__ __device__ inline int prompt_block_span(int G, int columns) {
+  return columns % G == 0 ? columns / G : (columns + G - 2) / G + 1;
 }
 
 // Visible range and split bookkeeping of one sequence, identical on host and device.
@@ -174,7 +183,6 @@ hipError_t launch_gather(const StoreParams& p, void* k_out, void* v_out, int D, 
 hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                                hipStream_t stream);
 size_t partial_bf16_lds_bytes(int waves, int columns, int D);      // dynamic LDS of that launch
-int prefill_bf16_block_steps(int G, int waves);                    // query steps per workgroup of the prompt kernel
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream);
 hipError_t launch_prompt_combine(const PromptParams& p, int batch, int D, hipStream_t stream);
 hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipStream_t stream);

@@ -350,3 +350,10 @@ def test_ring_prompts_in_chunks(B, Hkv, G, D, Z, t, count, window):
     """Shapes whose least workspace has no room to stage the prompt (test_host_launches.py checks that
     they take this path): each chunk written into the ring and answered from it."""
     run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=True)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,t,count,window", [
+    (1, 2, 3, 128, 1500, 130, 0), (1, 1, 5, 64, 2900, 70, 300), (2, 1, 40, 64, 1023, 11, 129), (1, 8, 3, 128, 0, 1100, 0),
+    (2, 2, 3, 128, 0, 43, 0), (2, 1, 23, 128, 0, 90, 40), (1, 1, 127, 64, 3, 5, 0)])
+def test_blocks_that_begin_between_the_heads_of_a_step(B, Hkv, G, D, t, count, window):
+    run_prompt(B, Hkv, G, D, 64, t, count, window, False, T.TEMPO_BF16)

@@ -235,3 +235,17 @@ def test_ring_prompts_with_the_least_workspace(lib, shape):
             assert (at - 1) // Z - oldest // Z < ring
     assert lib.tempo_prefill_window(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, B, Hkv * G, t, count, None,
                                     window, 0.125, SOMEWHERE, need - 256, None) == T.TEMPO_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,batch,t,count,window", [
+    (24, 8, 128, 1, 1500, 100, 0), (24, 8, 128, 2, 4000, 42, 512), (5, 1, 64, 1, 2900, 70, 300), (40, 1, 64, 1, 1023, 11, 900)])
+def test_splits_reach_over_blocks_that_begin_between_the_heads_of_a_step(lib, Hq, Hkv, D, batch, t, count, window):
+    """A block is a run of (step, head) columns: all splits of the steps it touches are launched."""
+    G = Hq // Hkv
+    launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, 100), batch, Hq, t, count, window)
+    (_, f), = [l for l in launches if l[0] == "prompt"]
+    assert f["grid_splits"] > 1
+    for k in range(0, count * G, 32 * f["waves"]):
+        first, last = t + k // G, t + (min(k + 32 * f["waves"], count * G) - 1) // G
+        lo = max(0, first - window + 1) if window else 0
+        assert (last >> f["tps_log2"]) - (lo >> f["tps_log2"]) + 1 <= f["grid_splits"]
