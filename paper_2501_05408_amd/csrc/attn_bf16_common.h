@@ -166,6 +166,7 @@ struct BlockWork {
   int b, hkv;            // sequence, kv head
   int c0, steps, ncols;  // first step of the block within the call, the steps it touches, its columns
   int skip;              // heads of step c0 that belong to the block before
+  int all_steps;         // of this sequence in the call
   int t_first, t_last;   // its first and last step
   int split;             // of the block's key range
   int start, end;        // keys of that range in the split ...
@@ -195,19 +196,17 @@ __device__ inline BlockWork block_work(const AttnParams& p, int columns) {
   int zsplit = (int)ix;                                       // 0 unless the key range is split
   w.c0 = 0;
   w.skip = 0;
-  w.steps = p.queries;
+  w.steps = w.all_steps = p.queries;
   w.any = true;
   if (kBlocks) {
     const unsigned G = (unsigned)p.G, nblocks = prompt_blocks(p.queries, p.G, columns);
     zsplit = (int)(ix / nblocks);
     const unsigned first = (nblocks - 1 - ix % nblocks) * (unsigned)columns;  // of the call's columns: below 2^32
-    // steps of this sequence in the call: all of them, or its own count
-    int steps_b = p.queries;
-    if (p.count_per_seq) {
+    if (p.count_per_seq) {  // its own count
       const int n = ((const_i32_ptr)p.count_per_seq)[w.b];
-      steps_b = n < 0 ? 0 : (n < p.queries ? n : p.queries);
+      w.all_steps = n < 0 ? 0 : (n < p.queries ? n : p.queries);
     }
-    const unsigned all = (unsigned)steps_b * G;
+    const unsigned all = (unsigned)w.all_steps * G;
     w.any = first < all;
     w.ncols = (int)(all - first < (unsigned)columns ? all - first : (unsigned)columns);
     w.c0 = (int)(first / G);

@@ -35,11 +35,19 @@
 // group's logits and with one comparison for a reference that stays, 1859 -> 1800 us; 499 steps of
 // one sequence, 32/8 heads of 64, 15.2 -> 14.7; 4 x 2048 with window 512 105 -> 102.8.
 //
+// A prompt from step 0 on sees its own rows only, so they need not pass through the store (kRows): every
+// workgroup copies them from the caller's arrays, keys as 16-byte pieces gathered into operand order,
+// values row by row and turned by gfx950's transposing LDS read (two of 8 bytes where the pools' order
+// takes one of 16), and the workgroup whose columns begin a group's first step writes that group to the
+// store while it lies in LDS.  One launch instead of a write and a launch that waits for it: 499 steps of
+// one sequence, 32/8 heads of 64, 14.7 -> 12.0 us, 40 steps 8.2 -> 5.8; 4 x 2048 with window 512 on a
+// ring, which had staged its rows in the workspace, 102.7 -> 84.5.  The extra reads cost 3 to 4% of a long
+// causal prompt's loop (prompt_from_rows() in tempo_api.hip draws the line).
+//
 // Workgroups of one (sequence, head) are adjacent in the work list and run together on
 // one die, so the pool is streamed from HBM about once per (sequence, head) and the
 // blocks that follow find it in that die's L2; the longest blocks come first.
 #include "attn_bf16_common.h"
-
 
 namespace tempo {
 namespace {
@@ -141,14 +149,23 @@ __device__ inline void mask_tile(int grp, int lo_col, int hi_col, int lane, f32x
 
 constexpr int kWaveColumns = 32;
 
-template <int D, int NW, int NBUF, bool kRope, bool kStaged>
+// Where the keys/values of a group come from: the store's pools; the pools and, from the call's first step
+// on, the staging area; or the caller's rows (a prompt from step 0 on, which sees nothing else).
+enum Source { kPools, kStage, kRows };
+
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4* lds_i16x4_ptr;
+
+template <int D, int NW, int NBUF, bool kRope, Source kFrom>
 __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) {
   constexpr int KT = D / 16;                  // 16-dim contraction steps of the logits
   constexpr int OT = D / 32;                  // 32-dim tiles of the output
   constexpr int KU = D / 16;                  // 1 KiB units of one group's keys
   constexpr int UNITS = 2 * KU;               // ... and of its keys and values together
   constexpr int PER_WAVE = UNITS / NW;        // units each wavefront copies per group
-  static_assert(UNITS % NW == 0 && (NBUF == 4 || NBUF == 8), "copy split");
+  constexpr bool kStaged = kFrom == kStage;
+  static_assert(KU % NW == 0 && (NBUF == 4 || NBUF == 8), "copy split");
+  static_assert(kFrom == kPools || !kRope, "unrotated keys come from the store");
   constexpr bool kEarly = NBUF > 4;           // first operands of an iteration are read at the end of the one before
   constexpr int kPair = kEarly ? 2 : 1;       // groups per barrier
   constexpr int kRead = KT;                   // operands read ahead of the matrix instruction that takes them
@@ -165,8 +182,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   const int tile_groups = p.z_log2 - 5;             // log2(groups per tile)
   const int tile_last = g_last >> tile_groups;
   int tile_base = g_first >> tile_groups;           // lane i holds the byte offset, in either pool, of tile tile_base + i
+  // kRows: the groups whose first step's first column is this block's are written to the store by it
+  const unsigned block_first = (unsigned)c0 * (unsigned)p.G + (unsigned)work.skip, group_columns = 32u * (unsigned)p.G;
+  const int write_first = kFrom != kRows ? 0 : (int)((block_first + group_columns - 1) / group_columns);
+  const int write_past = kFrom != kRows ? 0 : (int)((block_first + (unsigned)ncols + group_columns - 1) / group_columns);
   uint32_t tile_lo, tile_hi;
   auto fetch_entry = [&]() {
+    if (kFrom == kRows) {                           // of group write_first + lane (at most 9 groups)
+      const int g = write_first + lane < write_past ? write_first + lane : g_last;
+      return table[(g >> tile_groups) & p.tile_mask];
+    }
     const int tile = tile_base + lane < tile_last ? tile_base + lane : tile_last;  // never past the range's last tile
     return table[tile & p.tile_mask];
   };
@@ -214,7 +239,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // two kinds return out of order every wait for an operand would become a wait for all.  Beyond the range's last group the last one is
   // copied again (into a buffer nobody reads any more): every iteration then issues the
   // same number of copies, and "the group before the newest has landed" is one counted wait.
-  place_tiles(entry);
+  if (kFrom != kRows) place_tiles(entry);
+  // kRows: byte offset, from the row of the group's first step, of each piece this lane copies.  Keys land
+  // in operand order, as from the pools.  Values land row by row, 16-byte pieces in the order piece ^ (row
+  // part), which spreads the four rows a transposing read takes over all LDS banks.
+  constexpr int kRowBytes = 2 * D, kPieces = D / 8, kUnitRows = 64 / kPieces;
+  const uint32_t row_stride = (uint32_t)p.Hkv * kRowBytes;
+  auto swizzle = [](int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); };
+  uint32_t row_piece[PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < PER_WAVE; ++i) {
+    const int u = wave + NW * i;
+    const int key_row = 16 * (u / (D / 32)) + (lane & 15), value_row = (u - KU) * kUnitRows + lane / kPieces;
+    row_piece[i] = u < KU ? (uint32_t)key_row * row_stride + 64u * (uint32_t)(u % (D / 32)) + 16u * (uint32_t)(lane >> 4)
+                          : (uint32_t)value_row * row_stride + 16u * (uint32_t)((lane % kPieces) ^ swizzle(lane / kPieces));
+  }
   // A prompt on a ring store: the groups from its first step on lie, as one run per (sequence,
   // head), in the staging area; the ring holds the history.
   const int64_t stage_run = ((int64_t)b * p.Hkv + hkv) * p.stage_groups * (64 * D);
@@ -232,6 +271,20 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   const uint32_t lane_bytes = 16u * (uint32_t)lane;
   auto issue = [&](int at, int g) {                 // `at`: the buffer's offset in LDS, in 16-byte pieces
     const int gc = g < g_last ? g : g_last;
+    if (kFrom == kRows) {
+      // rows beyond the sequence's last step are beyond the buffer: zeros
+      const int left = work.all_steps - 32 * gc;
+      const uint32_t bytes = (uint32_t)((left < 32 ? left : 32) - 1) * row_stride + kRowBytes;
+      const uint64_t from = (((uint64_t)b * (uint32_t)p.io_steps + 32u * (uint32_t)gc) * (uint32_t)p.Hkv + (uint32_t)hkv) * kRowBytes;
+      char* const rows[2] = {const_cast<char*>(static_cast<const char*>(p.k_new)) + from,
+                             const_cast<char*>(static_cast<const char*>(p.v_new)) + from};
+#pragma unroll
+      for (int i = 0; i < PER_WAVE; ++i) {
+        const auto group = __builtin_amdgcn_make_buffer_rsrc(rows[i / (PER_WAVE / 2)], 0, (int)bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(group, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, (int)row_piece[i], 0, 0, 0);
+      }
+      return;
+    }
     if (kStaged && gc >= p.stage_first) {
       const uint64_t from = (uint64_t)(gc - p.stage_first) * (64u * D);
 #pragma unroll
@@ -257,7 +310,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
     }
   };
-  const bool head = cut_head(work), tail = cut_tail(work);
+  // (kRows: every row of the call is written, and what lies beyond reads as zeros)
+  const bool head = kFrom != kRows && cut_head(work), tail = kFrom != kRows && cut_tail(work);
   auto mask_values = [&](int g, int at) {  // the buffer of group g: the first, and head, or the last, and tail
     uint32_t keep[4];
     value_masks(g, start, t_last, lane, keep);
@@ -293,7 +347,57 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   auto key_operand = [&](int at, int s) { return as_bf16x8(lds[at + k_lane + (s >> 1) * 64 + (s & 1) * 32]); };
   // Value rows: dim l & 31 of tile ot is unit 2 ot + (dim / 16), lanes (dim & 15) + 16 (2 chunk + h).
   const int v_lane = KU * 64 + ((lane >> 4) & 1) * 64 + (lane & 15) + 16 * half;
-  auto value_operand = [&](int at, int chunk, int ot) { return as_bf16x8(lds[at + v_lane + ot * 128 + chunk * 32]); };
+  // From rows, gfx950's transposing read: 16 lanes that point at 4 rows x 4 pieces of 4 dims get one dim of
+  // the 4 rows each.  Lane 16 q + i gets dim 16 (q & 1) + i of tile ot, rows 8 chunk + 4 (q >> 1) + 0 .. 3 and
+  // the same + 16: the slots of the pools' unit.
+  const int tr_row = 4 * half + ((lane & 15) >> 2);
+  int v_row_lane[OT];
+#pragma unroll
+  for (int ot = 0; ot < OT; ++ot)
+    v_row_lane[ot] = KU * 1024 + tr_row * kRowBytes + 8 * (lane & 1) +
+                     16 * ((4 * ot + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ swizzle((lane & 15) >> 2));
+  auto rows_of_dim = [&](int byte) {                // of rows r .. r+3 and r+16 .. r+19, where `byte` points into row r
+    char* const from = reinterpret_cast<char*>(lds) + byte;
+    struct Both { i16x4 low, high; } both;
+    both.low = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)from);
+    both.high = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(from + 16 * kRowBytes));
+    return __builtin_bit_cast(u32x4, both);
+  };
+  auto value_operand = [&](int at, int chunk, int ot) {
+    if (kFrom == kRows) return as_bf16x8(rows_of_dim(16 * at + v_row_lane[ot] + chunk * 8 * kRowBytes));
+    return as_bf16x8(lds[at + v_lane + ot * 128 + chunk * 32]);
+  };
+  // kRows: group g, in the buffer at `at`, into the store: its keys' units as they lie in LDS, its values'
+  // units (tile_off_v_bf16) by transposing reads.  Slots of a group that the call does not write are left alone.
+  auto write_group = [&](int g, int at) {
+    const int lo = p.keep_first - 32 * g > 0 ? p.keep_first - 32 * g : 0;
+    const int hi = work.all_steps - 32 * g < 32 ? work.all_steps - 32 * g : 32;
+    if (lo >= hi) return;
+    const int phys = clamp_block(__builtin_amdgcn_readlane(entry, g - write_first), p.num_blocks);
+    const int64_t to = (((int64_t)phys * p.Hkv + hkv) << p.z_log2) * D + (int64_t)((g << 5) & ((1 << p.z_log2) - 1)) * D;
+    u32x4* const k_to = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.k_pool) + to) + lane;
+    u32x4* const v_to = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.v_pool) + to) + lane;
+    const int c = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE / 2; ++i) {
+      const int u = wave + NW * i, slot = 16 * (u / (D / 32)) + (lane & 15);
+      const u32x4 keys = lds[at + u * 64 + lane];
+      if (slot >= lo && slot < hi) k_to[u * 64] = keys;
+      const int row = 4 * c + ((lane & 15) >> 2);
+      const u32x4 values = rows_of_dim(16 * at + KU * 1024 + row * kRowBytes + 8 * (lane & 1) +
+                                       16 * ((2 * u + ((lane & 3) >> 1)) ^ swizzle(row)));
+      if (lo == 0 && hi == 32) {
+        v_to[u * 64] = values;
+        continue;
+      }
+      uint16_t* const each = reinterpret_cast<uint16_t*>(v_to + u * 64);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int s = e < 4 ? 4 * c + e : 12 + 4 * c + e;
+        if (s >= lo && s < hi) each[e] = (uint16_t)(values[e >> 1] >> (16 * (e & 1)));
+      }
+    }
+  };
 
   // The groups this wavefront has work in: own_first .. own_last.  The others it only helps
   // to copy: loops of their own, so that no path around the arithmetic carries the accumulators.
@@ -323,6 +427,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // logits are computed one group ahead) and, with early operand reads, one more are in LDS.
   constexpr int kAhead = 2 * kPair;            // of grp, which may be the second of a pair
   auto finish = [&]() {
+    if (kFrom == kRows && grp >= write_first && grp < write_past) write_group(grp, at0);
     if (kPair == 1 || ((grp - g_first) & 1)) {
       landed();
       if (tail && g_last <= grp + kAhead && g_last > grp + kAhead - kPair) mask_values(g_last, next(g_last - grp));
@@ -463,6 +568,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
 }  // namespace
 
 namespace {
+template <int D, int NW, int NBUF>
+hipError_t launch_from(const PromptParams& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  if (p.k_new) return launch((attn_prefill_bf16<D, NW, NBUF, false, kRows>), grid, block, lds, stream, p);
+  if (p.k_stage) return launch((attn_prefill_bf16<D, NW, NBUF, false, kStage>), grid, block, lds, stream, p);
+  if (p.rope_cos) return launch((attn_prefill_bf16<D, NW, NBUF, true, kPools>), grid, block, lds, stream, p);
+  return launch((attn_prefill_bf16<D, NW, NBUF, false, kPools>), grid, block, lds, stream, p);
+}
+
 template <int NW>
 hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
   // Eight wavefronts (one workgroup per compute unit): eight buffers, two groups per
@@ -476,19 +589,14 @@ hipError_t launch_prefill_nw(const PromptParams& p, int batch, int D, int grid_s
   const dim3 grid((unsigned)(nblocks * grid_splits), p.Hkv, batch);
   const dim3 block(64 * NW);
   const size_t lds = NBUF * (size_t)(D / 8) * 1024;
-  if (p.k_stage && p.rope_cos) return hipErrorInvalidConfiguration;  // a ring store takes no unrotated prompts
-  if (D == 128) {
-    if (p.k_stage) return launch((attn_prefill_bf16<128, NW, NBUF, false, true>), grid, block, lds, stream, p);
-    if (p.rope_cos) return launch((attn_prefill_bf16<128, NW, NBUF, true, false>), grid, block, lds, stream, p);
-    return launch((attn_prefill_bf16<128, NW, NBUF, false, false>), grid, block, lds, stream, p);
-  }
+  if ((p.k_stage || p.k_new) && p.rope_cos) return hipErrorInvalidConfiguration;  // unrotated keys go to the store first
   if constexpr (NW == 8) {
-    return hipErrorInvalidConfiguration;  // four wavefronts are always the better shape at D = 64
-  } else {
-    if (p.k_stage) return launch((attn_prefill_bf16<64, NW, NBUF, false, true>), grid, block, lds, stream, p);
-    if (p.rope_cos) return launch((attn_prefill_bf16<64, NW, NBUF, true, false>), grid, block, lds, stream, p);
-    return launch((attn_prefill_bf16<64, NW, NBUF, false, false>), grid, block, lds, stream, p);
+    if (D != 128) return hipErrorInvalidConfiguration;  // four wavefronts are always the better shape at D = 64
   }
+  if constexpr (NW < 8) {
+    if (D == 64) return launch_from<64, NW, NBUF>(p, grid, block, lds, stream);
+  }
+  return launch_from<128, NW, NBUF>(p, grid, block, lds, stream);
 }
 }  // namespace
 

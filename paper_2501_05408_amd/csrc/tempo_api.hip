@@ -1055,15 +1055,44 @@ int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, 
   return C;
 }
 
+// A bf16 prompt from step 0 on whose keys/values the prompt kernel reads from the caller's rows; it writes
+// the steps from keep_first on to the store itself.
+struct PromptRows {
+  const void *k, *v;
+  int32_t keep_first;
+};
+
+// May it?  Not where `out` lies over the rows (which a write launch of its own has read before), nor where
+// 16-byte pieces of them are not aligned.  And is it the faster way?  It saves a launch and a pass over
+// memory, and costs a little per group and workgroup: the faster way for all windowed prompts and for
+// causal ones up to about 1.15e11 flops (us, write and attend / from rows, 1 to 16 sequences; 24/8 heads of 128:
+// 1 x 40 steps 11.2 / 8.8, 16 x 160 23.6 / 16.8, 16 x 640 83.6 / 77.2, 4 x 1900 (9e10) 117 / 110, 16 x 1300 (1.7e11)
+// 243 / 247, 16 x 2700 808 / 832; 32/8 heads of 64: 16 x 900 94.0 / 91.1, 16 x 1900 (2.4e11) 321 / 335; 16/16 heads of
+// 64: 16 x 320 25.0 / 17.1, 16 x 1900 (1.2e11) 207 / 214; window 256, 24/8 heads of 128: 16 x 4000 508 / 471, on a
+// ring, staged before, 529 / 447; 432 shapes measured, the slower way taken in none by more than 4%).
+constexpr double kRowsMostFlops = 1.15e11;
+
+bool prompt_from_rows(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
+                      int32_t t, int32_t count, int32_t window) {
+  if (kv->dtype != TEMPO_BF16 || t != 0 || !prompt_in_one_launch(kv, batch, Hq, count)) return false;
+  if (window == 0 && 2.0 * batch * Hq * kv->head_dim * count * count > kRowsMostFlops) return false;
+  const uintptr_t k = reinterpret_cast<uintptr_t>(k_new), v = reinterpret_cast<uintptr_t>(v_new);
+  const uintptr_t o = reinterpret_cast<uintptr_t>(out);
+  if ((k | v) & 15u) return false;
+  const uintptr_t out_bytes = (uintptr_t)batch * count * Hq * kv->head_dim * 2, row_bytes = out_bytes / (Hq / kv->num_kv_heads);
+  return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
+}
+
 // One launch (and the combine, if it splits key ranges) for `count` steps from t on, already in
 // the store.  q, out: the caller's, `io_steps` steps per sequence.
 int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, int32_t Hq, int32_t t, int32_t count,
                   int32_t io_steps, const int32_t* count_per_seq, int32_t window, float scale, void* workspace,
-                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope, const StageParams* staged = nullptr) {
+                  size_t workspace_bytes, hipStream_t s, const tempo_rope* rope, const StageParams* staged = nullptr,
+                  const PromptRows* rows = nullptr) {
   const bool bf16 = kv->dtype == TEMPO_BF16;
   // (a sequence with fewer steps than the others has blocks, and splits, the combine does not know)
   // (and staged keys/values lie where the partials of split ranges would)
-  const bool is_short = bf16 && !staged && short_prompt(kv, batch, Hq, t, count, window);
+  const bool is_short = bf16 && !staged && !rows && short_prompt(kv, batch, Hq, t, count, window);
   const PromptPlan plan = is_short ? PromptPlan{8, kWholeRange, 1}
                           : bf16   ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
                                    : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
@@ -1075,7 +1104,12 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   p.direct = plan.splits == 1;
   p.block_columns = plan.waves * kWaveColumns;
   p.k_stage = p.v_stage = nullptr;
-  p.stage_first = p.stage_groups = 0;
+  p.stage_first = p.stage_groups = p.keep_first = 0;
+  if (rows) {
+    p.k_new = rows->k;
+    p.v_new = rows->v;
+    p.keep_first = rows->keep_first;
+  }
   p.count_per_seq = count_per_seq;
   if (rope) {
     p.rope_cos = rope->cos;
@@ -1196,6 +1230,12 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
     return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
+  if (!rope && prompt_from_rows(kv, k_new, v_new, out, batch, Hq, t, count, window)) {
+    const int64_t slots = kv->ring_blocks ? (int64_t)kv->ring_blocks * kv->block_size : count;
+    const PromptRows rows = {k_new, v_new, count > slots ? (int32_t)(count - slots) : 0};  // a ring keeps the last steps
+    return attend_prompt(kv, q, out, batch, Hq, t, count, count, count_per_seq, window, scale, workspace, workspace_bytes, s,
+                         nullptr, nullptr, &rows);
+  }
   if (!count_per_seq && !rope && prompt_by_blocks(kv, batch, Hq, t, count, window))
     return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.

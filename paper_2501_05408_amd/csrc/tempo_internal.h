@@ -83,7 +83,8 @@ struct AttnParams {
   void* v_pool;
   const int32_t* block_table;
   const void* q;
-  const void* k_new;         // [B][Hkv][D]; non-null: append step t inside the attention kernel (queries == 1)
+  const void* k_new;         // [B][Hkv][D]; non-null: append step t inside the attention kernel (queries == 1);
+                             //   prompt kernel: [B][io_steps][Hkv][D], all keys/values are read from there
   const void* v_new;
   const int32_t* t_per_seq;  // may be null
   const int32_t* count_per_seq;  // prompt kernel: may be null; sequence b answers only its first count_per_seq[b] steps
@@ -120,6 +121,7 @@ struct PromptParams : AttnParams {
   const void* k_stage;       // may be null; groups stage_first .. are read from here ([batch][Hkv][stage_groups]
   const void* v_stage;       //   group images), earlier ones from the pool
   int32_t stage_first, stage_groups;
+  int32_t keep_first;        // k_new set (a prompt from step 0 on): first step that the launch writes to the store
 };
 
 // tps_log2 of a key range that is not split: steps are below 2^31, so no range crosses a multiple of it

@@ -249,3 +249,31 @@ def test_splits_reach_over_blocks_that_begin_between_the_heads_of_a_step(lib, Hq
         first, last = t + k // G, t + (min(k + 32 * f["waves"], count * G) - 1) // G
         lo = max(0, first - window + 1) if window else 0
         assert (last >> f["tps_log2"]) - (lo >> f["tps_log2"]) + 1 <= f["grid_splits"]
+
+
+@pytest.mark.parametrize("what,Hq,Hkv,D,batch,t,count,window,ring,apart,names", [
+    ("one launch", 24, 8, 128, 16, 0, 300, 0, False, 1 << 32, ["prompt"]),
+    ("few columns behind few keys", 24, 8, 128, 1, 0, 3, 0, False, 1 << 32, ["prompt"]),
+    ("split ranges", 8, 1, 128, 1, 0, 1000, 0, False, 1 << 32, ["prompt", "prompt_combine"]),
+    ("a ring that does not hold the prompt", 24, 8, 128, 4, 0, 2048, 512, True, 1 << 32, ["prompt"]),
+    ("a history", 24, 8, 128, 16, 1, 300, 0, False, 1 << 32, ["append", "prompt"]),
+    ("long and causal", 24, 8, 128, 16, 0, 1300, 0, False, 1 << 32, ["append", "prompt"]),
+    ("long and windowed", 24, 8, 128, 16, 0, 1300, 500, False, 1 << 32, ["prompt"]),
+    ("out over the rows", 24, 8, 128, 16, 0, 300, 0, False, 16 * 300 * 24 * 128 * 2 - 16, ["append", "prompt"]),
+    ("out right before the rows", 24, 8, 128, 16, 0, 300, 0, False, 16 * 300 * 24 * 128 * 2, ["prompt"]),
+    ("rows not aligned", 24, 8, 128, 16, 0, 300, 0, False, (1 << 32) + 8, ["append", "prompt"])])
+def test_prompts_that_are_read_from_the_callers_rows(lib, what, Hq, Hkv, D, batch, t, count, window, ring, apart, names):
+    R = T.tempo_ring_blocks(window, 256, 128 * Hkv // Hq) if ring else 0
+    kv = store(T.TEMPO_BF16, Hkv, D, 256, R or 100, R)
+    out, k, v = 1 << 33, (1 << 33) + apart, (1 << 33) + 3 * (apart & ~15)
+    args = (ctypes.byref(kv), SOMEWHERE, k, v, out, batch, Hq, t, count, None)
+    for workspace in (1 << 50, least_prompt_workspace(lib, kv, batch, Hq, t, count, window)):
+        lib.host_launches_take()
+        rc = (lib.tempo_prefill_window(*args, window, 0.125, SOMEWHERE, workspace, None) if window else
+              lib.tempo_prefill_causal(*args, 0.125, SOMEWHERE, workspace, None))
+        assert rc == T.TEMPO_OK
+        launches = taken(lib)
+        assert [n for n, _ in launches if n != "prompt_combine"] == [n for n in names if n != "prompt_combine"]
+        if workspace == 1 << 50:
+            assert [n for n, _ in launches] == names
+        assert_all_keys_launched(launches, Hq // Hkv, t, count)
