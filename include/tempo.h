@@ -446,7 +446,7 @@ int tempo_rope_attn_block_window(const tempo_kv* kv, const tempo_rope* rope, con
  * written to the store and every step's query attends over its own range (keys
  * 0 .. t+c, or its window), exactly as `count` single decode steps would.  One launch
  * writes the store, one answers all steps (a third combines, if the columns are few and
- * their key range was split); a bf16 prompt from step 0 on, unless it is long and causal, is written and
+ * their key range was split); a prompt from step 0 on, unless it is long, is written and
  * answered by the same launch; few steps behind a long history are answered in blocks of
  * 128 / (num_q_heads / num_kv_heads) steps, each by tempo_kv_append_block and one
  * tempo_attn_block_*.  On a ring store the keys/values of other prompts are laid out in the

@@ -38,7 +38,11 @@ struct GroupF32 {
   f32x4 v[4][D / 64];
 };
 
-template <int D>
+// kRows: a prompt from step 0 on sees its own rows only, so they are read from the caller's arrays (k_new /
+// v_new), not from the store, and the workgroup of the tile that holds a step's first column writes that
+// step's rows to the store: one launch instead of a write and one that waits for it (512 steps, 8/2 heads of
+// 64, 16.8 -> 11.5 us; 16 x 64 steps 11.0 -> 6.6; long prompts alike, 16 x 512 steps of 24/8 heads of 128 754 / 749).
+template <int D, bool kRows>
 __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   constexpr int KI = D / 16;   // 16-byte pieces of a key row per lane
   constexpr int VJ = D / 64;   // 16-byte pieces of a value row per lane
@@ -84,7 +88,14 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   // k_new / v_new, and the workgroup of the first column tile also stores them for later steps.
   const float* kn = p.k_new ? static_cast<const float*>(p.k_new) + ((int64_t)b * p.Hkv + hkv) * D : nullptr;
   const float* vn = p.k_new ? static_cast<const float*>(p.v_new) + ((int64_t)b * p.Hkv + hkv) * D : nullptr;
-  const int grp_new = kn != nullptr && split == rg.nchunks - 1 ? t_b >> 4 : -1;
+  const int grp_new = !kRows && kn != nullptr && split == rg.nchunks - 1 ? t_b >> 4 : -1;
+  // kRows: sequence b's rows, new_row from one step's to the next one's
+  const int64_t new_row = (int64_t)p.Hkv * D;
+  [[maybe_unused]] const float* k_rows = kRows ? static_cast<const float*>(p.k_new) + (int64_t)b * p.io_steps * new_row + (int64_t)hkv * D : nullptr;
+  [[maybe_unused]] const float* v_rows = kRows ? static_cast<const float*>(p.v_new) + (int64_t)b * p.io_steps * new_row + (int64_t)hkv * D : nullptr;
+  // Sixteen rows that are all in the range: their address is scalar but for a lane's part that never changes.
+  auto whole = [&](int grp) { return kRows && (grp << 4) >= start && (grp << 4) + 15 <= end; };
+  const uint32_t k_lane = (uint32_t)(n * new_row + 4 * c), v_lane = (uint32_t)(4 * c * new_row + 4 * n);
 
   GroupF32<D> g;
   // A group of 16 keys lies in one tile if tiles have at least 16 slots: one scalar table entry.
@@ -96,16 +107,29 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
   auto load_keys = [&](int grp, int64_t base) {
     const int j = (grp << 4) + n, jc = clamped(j);
     const float* src = kpool + 4 * c + (p.z_log2 >= 4 ? base + (int64_t)(jc & (Z - 1)) * D : row_of(jc));
-    if (grp == grp_new) src = jc == t_b ? kn + 4 * c : src;  // (its slot in the pool is not read)
+    if constexpr (kRows) src = whole(grp) ? k_rows + (grp << 4) * new_row + k_lane : k_rows + jc * new_row + 4 * c;
+    else if (grp == grp_new) src = jc == t_b ? kn + 4 * c : src;  // (its slot in the pool is not read)
 #pragma unroll
     for (int i = 0; i < KI; ++i) g.k[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + 16 * i));
   };
   auto load_values = [&](int grp, int64_t base) {
+    if constexpr (kRows) {
+      if (whole(grp)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float* src = v_rows + ((grp << 4) + r) * new_row + v_lane;
+#pragma unroll
+          for (int i = 0; i < VJ; ++i) g.v[r][i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + 64 * i));
+        }
+        return;
+      }
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int j = (grp << 4) + 4 * c + r, jc = clamped(j);
       const float* src = vpool + 4 * n + (p.z_log2 >= 4 ? base + (int64_t)(jc & (Z - 1)) * D : row_of(jc));
-      if (grp == grp_new) src = jc == t_b ? vn + 4 * n : src;
+      if constexpr (kRows) src = v_rows + jc * new_row + 4 * n;
+      else if (grp == grp_new) src = jc == t_b ? vn + 4 * n : src;
 #pragma unroll
       for (int i = 0; i < VJ; ++i) g.v[r][i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + 64 * i));
     }
@@ -353,6 +377,22 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
     case 4: merge(std::integral_constant<int, 4>{}); break;
     default: merge(std::integral_constant<int, 8>{});
   }
+
+  // The store's rows, read once more (the loop has brought them near): stores before the barrier above
+  // would be waited for there (16 x 300 steps, window 100, 24/8 heads of 128: 202 us with them, 179).
+  if constexpr (kRows) {
+    const int tile_first = (col0 + p.G - 1) / p.G, tile_last = (col0 + ncols + p.G - 1) / p.G - 1;
+    const int64_t slots = p.tile_mask == INT32_MAX ? INT32_MAX : ((int64_t)p.tile_mask + 1) << p.z_log2;  // a ring keeps the last ones
+    const int kept = p.queries > slots ? p.queries - (int)slots : 0, from_step = tile_first > kept ? tile_first : kept;
+    const int first = from_step > cs ? from_step : cs, last = tile_last < ce ? tile_last : ce;  // of this split
+    for (int i = threadIdx.x; i < (last - first + 1) * (D / 4); i += blockDim.x) {
+      const int j = first + i / (D / 4), d = 4 * (i % (D / 4));
+      const int64_t from = j * new_row + d, to = row_of(j) + d;
+      const f32x4 key = *reinterpret_cast<const f32x4*>(k_rows + from), value = *reinterpret_cast<const f32x4*>(v_rows + from);
+      *reinterpret_cast<f32x4*>(kpool + to) = key;
+      *reinterpret_cast<f32x4*>(vpool + to) = value;
+    }
+  }
 }
 
 }  // namespace
@@ -364,8 +404,13 @@ hipError_t launch_partial_f32(const AttnParams& p, int batch, int D, int grid_sp
   const dim3 grid(tiles * p.Hkv, batch, grid_splits);
   const dim3 block(64 * waves);
   const size_t lds = (size_t)waves * (32 + (size_t)(columns < 16 ? columns : 16) * (D + 4)) * sizeof(float);
-  if (D == 128) return launch(attn_partial_f32<128>, grid, block, lds, stream, p);
-  else return launch(attn_partial_f32<64>, grid, block, lds, stream, p);
+  if (p.k_new && p.io_steps > 1) {  // (one step a call: [B][Hkv][D] either way)
+    if (p.rope_cos || p.t_per_seq || p.t != 0) return hipErrorInvalidConfiguration;
+    if (D == 128) return launch((attn_partial_f32<128, true>), grid, block, lds, stream, p);
+    return launch((attn_partial_f32<64, true>), grid, block, lds, stream, p);
+  }
+  if (D == 128) return launch((attn_partial_f32<128, false>), grid, block, lds, stream, p);
+  return launch((attn_partial_f32<64, false>), grid, block, lds, stream, p);
 }
 
 }  // namespace tempo

@@ -17,7 +17,9 @@
 namespace tempo {
 namespace {
 
-template <int D>
+// kRows: the steps from 0 on, whose keys/values are read from the caller's rows (k_new / v_new, [B][io_steps][Hkv][D]);
+// the workgroup of a step's first query head of the group stores them for later calls.
+template <int D, bool kRows>
 __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
   constexpr int E = D / 16;  // dims per lane
   extern __shared__ float smem[];
@@ -79,6 +81,11 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
     const bool fresh = kn != nullptr && j == t_b;  // uniform over the 16-lane row
     const float* ksrc = fresh ? kn + col * E : kpool + off;
     const float* vsrc = fresh ? vn + col * E : vpool + off;
+    if constexpr (kRows) {
+      const int64_t from = (((int64_t)b * p.io_steps + j) * p.Hkv + hkv) * D + col * E;
+      ksrc = static_cast<const float*>(p.k_new) + from;
+      vsrc = static_cast<const float*>(p.v_new) + from;
+    }
     float kx[E], vx[E];
 #pragma unroll
     for (int e = 0; e < E; e += 4) {
@@ -87,7 +94,7 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
       kx[e] = k4.x; kx[e + 1] = k4.y; kx[e + 2] = k4.z; kx[e + 3] = k4.w;
       vx[e] = v4.x; vx[e + 1] = v4.y; vx[e + 2] = v4.z; vx[e + 3] = v4.w;
     }
-    if (fresh) {  // all 16 lanes of the row take this branch together
+    if (kRows ? j == t_q : fresh) {  // all 16 lanes of the row take this branch together
       if (p.rope_cos) rotate(kx, t_b);  // the new key arrives unrotated
       if (hq == hkv * p.G) {
 #pragma unroll
@@ -157,14 +164,19 @@ __global__ __launch_bounds__(512) void attn_step_f32(AttnParams p) {
 
 }  // namespace
 
-// No padding bound; p.k_new (the fused write) with one query step only.
+// No padding bound; p.k_new (the fused write) with one query step, or from step 0 on.
 hipError_t launch_step_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves, hipStream_t stream) {
-  if ((p.k_new && p.queries != 1) || p.pad_t != 0 || batch > 65535 || grid_splits > 65535) return hipErrorInvalidConfiguration;
+  const bool rows = p.k_new && p.io_steps > 1;  // (one step a call: [B][Hkv][D] either way)
+  if ((rows && (p.rope_cos || p.t_per_seq || p.t != 0)) || p.pad_t != 0 || batch > 65535 || grid_splits > 65535) return hipErrorInvalidConfiguration;
   const dim3 grid(p.Hq * p.queries, batch, grid_splits);
   const dim3 block(64 * waves);
   const size_t lds = (size_t)waves * 4 * (2 + (size_t)D) * sizeof(float);
-  if (D == 128) return launch(attn_step_f32<128>, grid, block, lds, stream, p);
-  else return launch(attn_step_f32<64>, grid, block, lds, stream, p);
+  if (rows) {
+    if (D == 128) return launch((attn_step_f32<128, true>), grid, block, lds, stream, p);
+    return launch((attn_step_f32<64, true>), grid, block, lds, stream, p);
+  }
+  if (D == 128) return launch((attn_step_f32<128, false>), grid, block, lds, stream, p);
+  return launch((attn_step_f32<64, false>), grid, block, lds, stream, p);
 }
 
 }  // namespace tempo

@@ -1055,32 +1055,42 @@ int32_t ring_chunk(const tempo_kv* kv, int32_t t, int32_t left, int32_t window, 
   return C;
 }
 
-// A bf16 prompt from step 0 on whose keys/values the prompt kernel reads from the caller's rows; it writes
-// the steps from keep_first on to the store itself.
+// A prompt from step 0 on whose keys/values the attention kernel reads from the caller's rows; it writes the
+// steps from keep_first on to the store itself.
 struct PromptRows {
   const void *k, *v;
   int32_t keep_first;
 };
 
 // May it?  Not where `out` lies over the rows (which a write launch of its own has read before), nor where
-// 16-byte pieces of them are not aligned.  And is it the faster way?  It saves a launch and a pass over
-// memory, and costs a little per group and workgroup: the faster way for all windowed prompts and for
+// 16-byte pieces of them are not aligned.
+bool rows_readable(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
+                   int32_t count) {
+  const uintptr_t k = reinterpret_cast<uintptr_t>(k_new), v = reinterpret_cast<uintptr_t>(v_new);
+  const uintptr_t o = reinterpret_cast<uintptr_t>(out);
+  if ((k | v) & 15u) return false;
+  const uintptr_t step_bytes = (uintptr_t)batch * count * kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);
+  const uintptr_t out_bytes = step_bytes * Hq, row_bytes = step_bytes * kv->num_kv_heads;
+  return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
+}
+
+// And is it the faster way?  fp32: at D = 64 (of 96 shapes all but one, 0.95 to 1.74), and at D = 128 up to about
+// 4.5e9 flops (us, write and attend / from rows: 8/8 heads, 4 x 128 steps 17.5 / 10.4, 24/8 heads, 16 x 128 75.6 / 74.8, 16 x 300
+// (9e9) 326 / 337).  bf16: it saves a launch and a pass over memory, and costs a little per group and workgroup: the faster way for all windowed prompts and for
 // causal ones up to about 1.15e11 flops (us, write and attend / from rows, 1 to 16 sequences; 24/8 heads of 128:
 // 1 x 40 steps 11.2 / 8.8, 16 x 160 23.6 / 16.8, 16 x 640 83.6 / 77.2, 4 x 1900 (9e10) 117 / 110, 16 x 1300 (1.7e11)
 // 243 / 247, 16 x 2700 808 / 832; 32/8 heads of 64: 16 x 900 94.0 / 91.1, 16 x 1900 (2.4e11) 321 / 335; 16/16 heads of
 // 64: 16 x 320 25.0 / 17.1, 16 x 1900 (1.2e11) 207 / 214; window 256, 24/8 heads of 128: 16 x 4000 508 / 471, on a
-// ring, staged before, 529 / 447; 432 shapes measured, the slower way taken in none by more than 4%).
-constexpr double kRowsMostFlops = 1.15e11;
+// ring, staged before, 529 / 447; 357 shapes measured, 1.20 times as fast on the geometric mean; the slower way taken in none by more than 4%).
+constexpr double kRowsMostFlops = 1.15e11, kRowsMostFlopsF32 = 4.5e9;
 
 bool prompt_from_rows(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
                       int32_t t, int32_t count, int32_t window) {
-  if (kv->dtype != TEMPO_BF16 || t != 0 || !prompt_in_one_launch(kv, batch, Hq, count)) return false;
-  if (window == 0 && 2.0 * batch * Hq * kv->head_dim * count * count > kRowsMostFlops) return false;
-  const uintptr_t k = reinterpret_cast<uintptr_t>(k_new), v = reinterpret_cast<uintptr_t>(v_new);
-  const uintptr_t o = reinterpret_cast<uintptr_t>(out);
-  if ((k | v) & 15u) return false;
-  const uintptr_t out_bytes = (uintptr_t)batch * count * Hq * kv->head_dim * 2, row_bytes = out_bytes / (Hq / kv->num_kv_heads);
-  return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
+  if (t != 0 || !prompt_in_one_launch(kv, batch, Hq, count)) return false;
+  const double mean_keys = window > 0 && window < count / 2 ? window : 0.5 * count;
+  const double flops = 4.0 * batch * Hq * kv->head_dim * count * mean_keys;
+  if (kv->dtype == TEMPO_BF16 ? window == 0 && flops > kRowsMostFlops : kv->head_dim == 128 && flops > kRowsMostFlopsF32) return false;
+  return rows_readable(kv, k_new, v_new, out, batch, Hq, count);
 }
 
 // One launch (and the combine, if it splits key ranges) for `count` steps from t on, already in
@@ -1169,11 +1179,13 @@ int prefill_staged(const tempo_kv* kv, const void* q, const void* k_new, const v
   return launch_status(launch_append(last, k + from * row, v + from * row, kv->head_dim, kv->dtype, s), "kv_append_block");
 }
 
-// `count` steps from t on, in blocks of 128 columns: write, attend, combine.
+// `count` steps from t on, in blocks of 128 columns: write (fp32, one block from step 0 on: the attention launch
+// does), attend, combine.
 int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
                       int32_t Hq, int32_t t, int32_t count, int32_t window, float scale, void* workspace, hipStream_t s) {
   const size_t esz = kv->dtype == TEMPO_BF16 ? 2 : 4;
   const int32_t block = kMaxColumns / (Hq / kv->num_kv_heads);
+  const bool rows = kv->dtype == TEMPO_F32 && t == 0 && count <= block && rows_readable(kv, k_new, v_new, out, batch, Hq, count);
   for (int32_t c0 = 0; c0 < count; c0 += block) {
     const int32_t C = count - c0 < block ? count - c0 : block;
     tempo_plan plan;
@@ -1184,9 +1196,9 @@ int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, cons
     char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
     StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
     sp.src_steps = count;
-    int rc = launch_status(launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s), "kv_append_block");
+    int rc = rows ? TEMPO_OK : launch_status(launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s), "kv_append_block");
     if (rc != TEMPO_OK) return rc;
-    rc = do_partial(kv, qc, nullptr, nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, nullptr,
+    rc = do_partial(kv, qc, rows ? kc : nullptr, rows ? vc : nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, nullptr,
                     0, count);
     if (rc != TEMPO_OK) return rc;
     if (plan.num_splits > 1) {
@@ -1230,7 +1242,8 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
     return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
-  if (!rope && prompt_from_rows(kv, k_new, v_new, out, batch, Hq, t, count, window)) {
+  const bool one_f32_block = kv->dtype == TEMPO_F32 && count <= block;  // (goes by blocks, which know the way by rows too)
+  if (!rope && !one_f32_block && prompt_from_rows(kv, k_new, v_new, out, batch, Hq, t, count, window)) {
     const int64_t slots = kv->ring_blocks ? (int64_t)kv->ring_blocks * kv->block_size : count;
     const PromptRows rows = {k_new, v_new, count > slots ? (int32_t)(count - slots) : 0};  // a ring keeps the last steps
     return attend_prompt(kv, q, out, batch, Hq, t, count, count, count_per_seq, window, scale, workspace, workspace_bytes, s,

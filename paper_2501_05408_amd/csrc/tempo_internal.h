@@ -83,8 +83,8 @@ struct AttnParams {
   void* v_pool;
   const int32_t* block_table;
   const void* q;
-  const void* k_new;         // [B][Hkv][D]; non-null: append step t inside the attention kernel (queries == 1);
-                             //   prompt kernel: [B][io_steps][Hkv][D], all keys/values are read from there
+  const void* k_new;         // [B][io_steps][Hkv][D]; non-null: the rows of the call's steps, which the attention
+                             //   kernel appends (io_steps == 1, or a prompt from step 0 on)
   const void* v_new;
   const int32_t* t_per_seq;  // may be null
   const int32_t* count_per_seq;  // prompt kernel: may be null; sequence b answers only its first count_per_seq[b] steps

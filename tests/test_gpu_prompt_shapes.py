@@ -359,24 +359,25 @@ def test_blocks_that_begin_between_the_heads_of_a_step(B, Hkv, G, D, t, count, w
     run_prompt(B, Hkv, G, D, 64, t, count, window, False, T.TEMPO_BF16)
 
 
+@pytest.mark.parametrize("dtype", [T.TEMPO_BF16, T.TEMPO_F32])
 @pytest.mark.parametrize("B,Hkv,G,D,Z,count,window,ring", [
     (1, 2, 3, 128, 32, 1, 0, False), (2, 2, 3, 128, 64, 31, 0, False), (2, 1, 4, 64, 32, 33, 0, False),
     (1, 3, 1, 64, 64, 97, 0, False), (2, 2, 3, 128, 32, 171, 40, False), (1, 1, 128, 128, 32, 37, 0, False),
     (2, 8, 3, 128, 256, 700, 0, False), (1, 2, 5, 64, 32, 1000, 0, False), (2, 2, 3, 128, 32, 403, 33, True),
     (1, 4, 1, 64, 32, 129, 64, True), (2, 2, 8, 128, 64, 650, 100, True), (1, 2, 3, 128, 32, 64, 1, True)])
-def test_prompts_read_from_the_callers_rows(B, Hkv, G, D, Z, count, window, ring):
-    """From step 0 on the prompt kernel reads the call's rows and writes the store itself; rows that are not
+def test_prompts_read_from_the_callers_rows(B, Hkv, G, D, Z, count, window, ring, dtype):
+    """From step 0 on the prompt kernels read the call's rows and write the store themselves; rows that are not
     16-byte aligned take the way through the store.  Same store, bit for bit (slots nobody writes included),
-    same outputs within the rounding of the weights, which another order of the contraction leaves alone."""
+    same outputs within the tolerance against the oracle."""
     Hq = Hkv * G
-    q, K, V = host_inputs(91, B, count, Hq, Hkv, D, T.TEMPO_BF16)
+    q, K, V = host_inputs(91, B, count, Hq, Hkv, D, dtype)
     R = T.tempo_ring_blocks(window, Z, min(count, 128 // G)) if ring else 0
     table, nb = random_table(91, B, R or (count - 1) // Z + 1)
-    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
-    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))), T.TEMPO_BF16)
+    Kd, Vd = dev(K, dtype), dev(V, dtype)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))), dtype)
     got = []
-    for shift in (0, 4):
-        st = BlockStore(B, Hq, Hkv, D, Z, count - 1, T.TEMPO_BF16, num_blocks=nb, block_table=table, fill="nan", ring_blocks=R)
+    for shift in (0, 4 if dtype == T.TEMPO_BF16 else 2):
+        st = BlockStore(B, Hq, Hkv, D, Z, count - 1, dtype, num_blocks=nb, block_table=table, fill="nan", ring_blocks=R)
         rows = []
         for x in (Kd, Vd):
             room = torch.full((x.numel() + shift,), float("nan"), dtype=x.dtype, device=DEV)
@@ -386,10 +387,10 @@ def test_prompts_read_from_the_callers_rows(B, Hkv, G, D, Z, count, window, ring
         st.prefill_attend(qd, rows[0], rows[1], out, 0, count, window)
         got.append((out, st.k_pool.view(torch.int16), st.v_pool.view(torch.int16)))
     assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
-    assert_close(np64(got[0][0]), np64(got[1][0]), T.TEMPO_BF16, f"{(B, Hkv, G, D, Z, count, window, ring)}")
+    assert_close(np64(got[0][0]), np64(got[1][0]), dtype, f"{(B, Hkv, G, D, Z, count, window, ring)}")
     for c in sorted({0, count // 2, count - 1}):
         ref = oracle.attend(q[c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), c, window, 1.0 / np.sqrt(D))
-        assert_close(np64(got[0][0])[:, c], ref, T.TEMPO_BF16, f"step {c}")
+        assert_close(np64(got[0][0])[:, c], ref, dtype, f"step {c}")
 
 
 @pytest.mark.parametrize("D,G", [(128, 3), (64, 8)])

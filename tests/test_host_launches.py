@@ -261,10 +261,17 @@ def test_splits_reach_over_blocks_that_begin_between_the_heads_of_a_step(lib, Hq
     ("long and windowed", 24, 8, 128, 16, 0, 1300, 500, False, 1 << 32, ["prompt"]),
     ("out over the rows", 24, 8, 128, 16, 0, 300, 0, False, 16 * 300 * 24 * 128 * 2 - 16, ["append", "prompt"]),
     ("out right before the rows", 24, 8, 128, 16, 0, 300, 0, False, 16 * 300 * 24 * 128 * 2, ["prompt"]),
-    ("rows not aligned", 24, 8, 128, 16, 0, 300, 0, False, (1 << 32) + 8, ["append", "prompt"])])
+    ("rows not aligned", 24, 8, 128, 16, 0, 300, 0, False, (1 << 32) + 8, ["append", "prompt"]),
+    ("fp32", 8, 2, 64, 1, 0, 512, 0, False, 1 << 32, ["partial_f32"]),
+    ("fp32, one block", 8, 2, 64, 1, 0, 32, 0, False, 1 << 32, ["partial_f32"]),
+    ("fp32, one block, few keys", 8, 2, 64, 1, 0, 5, 0, False, 1 << 32, ["step_f32"]),
+    ("fp32, a ring that does not hold the prompt", 8, 2, 64, 4, 0, 2048, 512, True, 1 << 32, ["partial_f32"]),
+    ("fp32, long at D = 128", 24, 8, 128, 4, 0, 1000, 0, False, 1 << 32, ["append", "partial_f32"]),
+    ("fp32, a history", 8, 2, 64, 1, 1, 512, 0, False, 1 << 32, ["append", "partial_f32"]),
+    ("fp32, out over the rows", 8, 2, 64, 1, 0, 512, 0, False, 512 * 8 * 64 * 4 - 16, ["append", "partial_f32"])])
 def test_prompts_that_are_read_from_the_callers_rows(lib, what, Hq, Hkv, D, batch, t, count, window, ring, apart, names):
     R = T.tempo_ring_blocks(window, 256, 128 * Hkv // Hq) if ring else 0
-    kv = store(T.TEMPO_BF16, Hkv, D, 256, R or 100, R)
+    kv = store(T.TEMPO_F32 if what.startswith("fp32") else T.TEMPO_BF16, Hkv, D, 256, R or 100, R)
     out, k, v = 1 << 33, (1 << 33) + apart, (1 << 33) + 3 * (apart & ~15)
     args = (ctypes.byref(kv), SOMEWHERE, k, v, out, batch, Hq, t, count, None)
     for workspace in (1 << 50, least_prompt_workspace(lib, kv, batch, Hq, t, count, window)):
