@@ -127,23 +127,30 @@ __device__ __forceinline__ void append_values(const AttnParams& p, int64_t base,
 
 // ---- rotary embedding of the fetched key row ---------------------------------------
 // The row pair fetch_new_row returned: lanes 0..D/8-1 hold the key row (lane l:
-// dims 8l .. 8l+7), whose partner dims sit in lane l ^ (D/16).  All lanes call this.
+// dims 8l .. 8l+7), whose partner dims sit in lane l ^ (D/16).  All lanes call this, with the angles of
+// dims 8 (l mod D/16) .. +7, which are loaded apart (a round trip of their own otherwise).
+struct Angles {
+  float cs[8], sn[8];
+};
 template <int D>
-__device__ inline u32x4 rotate_fetched_key(const AttnParams& p, int pos, int lane, u32x4 fetched) {
+__device__ inline void fetch_angles(const AttnParams& p, int pos, int lane, Angles& a) {
+  load_angles(p.rope_cos, pos, D / 2, 8 * (lane % (D / 16)), a.cs);
+  load_angles(p.rope_sin, pos, D / 2, 8 * (lane % (D / 16)), a.sn);
+}
+template <int D>
+__device__ inline u32x4 rotate_fetched_key(const Angles& a, int lane, u32x4 fetched) {
   constexpr int UNITS = D / 8;
   u32x4 other;
 #pragma unroll
   for (int w = 0; w < 4; ++w) other[w] = __shfl_xor(fetched[w], UNITS / 2);
   if (lane < UNITS) {
-    float cs[8], sn[8], x[8], o[8], y[8];
-    load_angles(p.rope_cos, pos, D / 2, 8 * (lane % (UNITS / 2)), cs);
-    load_angles(p.rope_sin, pos, D / 2, 8 * (lane % (UNITS / 2)), sn);
+    float x[8], o[8], y[8];
     unpack8(fetched, x);
     unpack8(other, o);
     const bool first = lane < UNITS / 2;  // dims below D/2: y = x cos - partner sin
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-      y[e] = first ? rope_lo(x[e], o[e], cs[e], sn[e]) : rope_hi(o[e], x[e], cs[e], sn[e]);
+      y[e] = first ? rope_lo(x[e], o[e], a.cs[e], a.sn[e]) : rope_hi(o[e], x[e], a.cs[e], a.sn[e]);
     fetched = pack8(y);
   }
   return fetched;
@@ -197,7 +204,8 @@ __device__ __forceinline__ void merge_waves(const AttnParams& p, const float* sm
   }
 }
 
-template <int D, bool kRope, bool kList>
+// kPeel: the last group has a copy of the loop's body for itself, see there.
+template <int D, bool kRope, bool kList, bool kPeel>
 __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
@@ -253,10 +261,11 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
   int grp_new = -1;
   uint16_t* stage = reinterpret_cast<uint16_t*>(smem + nwaves * (32 + ncols * D));
   u32x4 fetched = {0u, 0u, 0u, 0u};
+  Angles angles = {};
   if (p.k_new && split == rg.nchunks - 1 && ((t_b >> 5) - grp) % nwaves == 0 && (t_b >> 5) >= grp) {
     grp_new = t_b >> 5;
     fetched = fetch_new_row<D>(p, b, hkv, lane);
-    if (kRope) fetched = rotate_fetched_key<D>(p, t_b, lane, fetched);
+    if (kRope) fetch_angles<D>(p, t_b, lane, angles);
   }
 
   // The bounds that decide whether a group is cut by any column (a group inside
@@ -290,6 +299,7 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
     }
   }
   if (kRope) rotate_query<D>(p, t_b + cq, lane, qreg);
+  if (kRope && grp_new >= 0) fetched = rotate_fetched_key<D>(angles, lane, fetched);
 
   WaveState<D> st;
   st.m = -INFINITY;
@@ -297,9 +307,13 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) st.acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  while (grp <= g_last) {
-    const int nxt = grp + nwaves;
-    const bool more = nxt <= g_last;
+  // In one body the requests for the next group stand behind a condition each, and the compiler has to allow for
+  // keys that were requested and values that were not: a wait for keys becomes one for the values as well, and
+  // nothing is in flight while a wavefront computes.  With the last group apart (kPeel) the waits are for what
+  // is needed (us a step, one body / two; 24/8 heads of 128: window 512, 16 sequences 9.62 / 9.31, t = 4095 45.2 / 44.7,
+  // 1 sequence, t = 65535 45.7 / 45.1).
+  // Group grp; `more`: and request group nxt.
+  auto group = [&](int nxt, bool more) __attribute__((always_inline)) {
     const int64_t base_nxt = more ? group_base<D>(p, b, hkv, nxt) : 0;  // scalar loads, off the vector path
     if (grp == grp_new) append_keys<D>(p, base, t_b, lane, fetched, stage, g);
 
@@ -327,8 +341,23 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
     }
     if (more) load_values<D>(p, base_nxt, lane, g);  // the value registers are free again
 
-    grp = nxt;
     base = base_nxt;
+  };
+  // In one body the requests for the next group stand behind a condition each, and the compiler has to allow for
+  // keys that were requested and values that were not: a wait for keys becomes one for the values as well, and
+  // nothing is in flight while a wavefront computes.  With the last group apart the waits are for what is needed (us
+  // a step, one body / two, 24/8 heads of 128: window 512, 16 sequences 9.62 / 9.28, t = 4095 45.2 / 44.7, 1 sequence,
+  // t = 65535 45.7 / 45.1, rotary, t = 299 6.15 / 5.94).
+  if constexpr (kPeel) {
+    for (; grp + nwaves <= g_last; grp += nwaves) group(grp + nwaves, true);
+    if (grp <= g_last) group(grp + nwaves, false);
+  } else {
+    while (grp <= g_last) {
+      const int nxt = grp + nwaves;
+      const bool more = nxt <= g_last;
+      group(nxt, more);
+      grp = nxt;
+    }
   }
 
   // Wave result -> LDS.  Columns live in lane&15 for (m, l) and in (4c + r) for acc.
@@ -377,17 +406,29 @@ hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_s
   if (grid.y > 65535u) return hipErrorInvalidConfiguration;
   const dim3 block(64 * waves);
   const size_t lds = partial_bf16_lds_bytes(waves, p.queries * p.G, D);
+  // The last group apart (kPeel) pays between these lines (us a step, one body / two): below, where a wavefront has
+  // one group, the two bodies only lie further apart (32/4 heads of 128, window 64 5.17 / 5.41); beyond, at D = 64, where
+  // 16 wavefronts share a compute unit, more bytes in flight slow the stream down (32/8 heads, 1 sequence, 600
+  // keys 6.1 / 5.6, 16 sequences of 4096 25.5 / 26.9).
+  const int64_t last = (int64_t)p.t + p.queries, keys = p.window > 0 && p.window < last ? p.window : last;
+  const bool peel = keys > 96 && (D == 128 || keys <= 1536);
   if (p.worklist) {
     if (p.rope_cos) return hipErrorInvalidConfiguration;  // no caller combines the two
-    if (D == 128) return launch((attn_partial_bf16<128, false, true>), grid, block, lds, stream, p);
-    return launch((attn_partial_bf16<64, false, true>), grid, block, lds, stream, p);
+    if (D == 128) return launch((attn_partial_bf16<128, false, true, true>), grid, block, lds, stream, p);
+    return launch((attn_partial_bf16<64, false, true, false>), grid, block, lds, stream, p);
+  }
+  if (D == 128) {
+    if (p.rope_cos && peel) return launch((attn_partial_bf16<128, true, false, true>), grid, block, lds, stream, p);
+    if (p.rope_cos) return launch((attn_partial_bf16<128, true, false, false>), grid, block, lds, stream, p);
+    if (peel) return launch((attn_partial_bf16<128, false, false, true>), grid, block, lds, stream, p);
+    return launch((attn_partial_bf16<128, false, false, false>), grid, block, lds, stream, p);
   }
   if (p.rope_cos) {
-    if (D == 128) return launch((attn_partial_bf16<128, true, false>), grid, block, lds, stream, p);
-    return launch((attn_partial_bf16<64, true, false>), grid, block, lds, stream, p);
+    if (peel) return launch((attn_partial_bf16<64, true, false, true>), grid, block, lds, stream, p);
+    return launch((attn_partial_bf16<64, true, false, false>), grid, block, lds, stream, p);
   }
-  if (D == 128) return launch((attn_partial_bf16<128, false, false>), grid, block, lds, stream, p);
-  return launch((attn_partial_bf16<64, false, false>), grid, block, lds, stream, p);
+  if (peel) return launch((attn_partial_bf16<64, false, false, true>), grid, block, lds, stream, p);
+  return launch((attn_partial_bf16<64, false, false, false>), grid, block, lds, stream, p);
 }
 
 }  // namespace tempo
