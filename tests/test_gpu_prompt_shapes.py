@@ -412,3 +412,39 @@ def test_rows_beyond_a_sequences_own_count_are_not_read(D, G):
         for c in sorted({0, n // 2, n - 1} & set(range(n))):
             ref = oracle.attend(q[c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), c, 0, 1.0 / np.sqrt(D))
             assert_close(np64(out)[b:b + 1, c], ref[b:b + 1], T.TEMPO_BF16, f"sequence {b} step {c}")
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,first,steps,window", [
+    (2, 2, 3, 128, 60, 75, 0), (1, 1, 8, 128, 700, 34, 97), (3, 2, 4, 64, 90, 12, 0), (1, 1, 16, 64, 1530, 12, 0),
+    (2, 1, 1, 64, 1700, 5, 1536), (1, 2, 3, 128, 250, 60, 0)])
+@pytest.mark.parametrize("rope", [False, True])
+def test_steps_around_the_ranges_whose_last_group_stands_apart(B, Hkv, G, D, first, steps, window, rope):
+    """bf16 steps first .. first + steps - 1 (96 keys; 1536 at D = 64), the write fused in."""
+    Hq, dtype, T_ = Hkv * G, T.TEMPO_BF16, first + steps
+    q, K, V = host_inputs(93, B, T_, Hq, Hkv, D, dtype)
+    table, nb = random_table(93, B, (T_ - 1) // 32 + 1)
+    st = BlockStore(B, Hq, Hkv, D, 32, T_ - 1, dtype, num_blocks=nb, block_table=table, fill="nan")
+    angle = np.arange(T_)[:, None] * 500000.0 ** (-np.arange(D // 2) / (D // 2))
+    st.set_rope(torch.from_numpy(np.cos(angle)).float().to(DEV), torch.from_numpy(np.sin(angle)).float().to(DEV))
+    qd, Kd, Vd = dev(q, dtype), dev(K, dtype), dev(V, dtype)
+    write = st.rope_append_block if rope else st.append_block
+    write(Kd[:, :first].contiguous(), Vd[:, :first].contiguous(), 0, first)
+    out = torch.empty((steps, B, Hq, D), dtype=torch.bfloat16, device=DEV)
+    for i in range(steps):
+        t = first + i
+        row = (qd[t], Kd[:, t].contiguous(), Vd[:, t].contiguous(), out[i], t)
+        if rope:
+            st.rope_step(*row, window)
+        elif window:
+            st.step_window(*row, window)
+        else:
+            st.step_causal(*row)
+    kg, vg = st.gather(0, T_)                            # (rotated keys: as stored, which the rotary tests pin)
+    assert torch.equal(vg, Vd) and (rope or torch.equal(kg, Kd))
+    K64, V64, got = np64(kg), V.astype(np.float64), np64(out)
+    for i in range(steps):
+        qt = qd[first + i]
+        if rope:
+            qt = st.rope_rotate(qt, torch.empty_like(qt), first + i)
+        ref = oracle.attend(np64(qt), K64, V64, first + i, window, 1.0 / np.sqrt(D))
+        assert_close(got[i], ref, dtype, f"step {first + i} w={window} rope={rope}")
