@@ -21,8 +21,8 @@
 //
 // What bounds it.  A step: HBM.  16 sequences, 24/8 heads of 128, t = 2047 (269 MB): one
 // workgroup per query head and 16 lanes per key (shuffles, each head reading the group's keys
-// and values) took 117.6 us a step; this kernel 49 us.  A prompt of 512 steps, 8/2 heads of 64,
-// in blocks of 128 columns 203 us, as one launch of this kernel 16.9 us.  Blocks and prompts: 64 products
+// and values) took 117.6 us a step; this kernel 46.8 us.  A prompt of 512 steps, 8/2 heads of 64,
+// in blocks of 128 columns 203 us, as one launch of this kernel 11.2 us.  Blocks and prompts: 64 products
 // of 32 cycles per group at D = 128, most of them padding when a tile holds few columns: steps and small
 // blocks over short ranges go to attn_step_f32.hip.
 #include <type_traits>
@@ -177,9 +177,7 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
     for (int e = 0; e < 4; ++e) acc[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  while (any && grp <= g_last) {
-    const int nxt = grp + nwaves;
-    const bool more = nxt <= g_last;
+  auto group = [&](int nxt, bool more) __attribute__((always_inline)) {  // group grp; `more`: and request group nxt
     const int64_t base_nxt = more && p.z_log2 >= 4 ? group_base(nxt) : 0;
     const int j0 = grp << 4;
     if (grp == grp_new) {  // uniform: the group with step t_b's own key, fetched from k_new / v_new
@@ -305,8 +303,14 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
       }
     }
     if (more) load_values(nxt, base_nxt);
-    grp = nxt;
     base = base_nxt;
+  };
+  // The last group apart, so that a wait for keys is not one for the values requested behind them (see the bf16
+  // decode kernel; 16 sequences, 24/8 heads of 128, t = 2047, 48.3 -> 46.8 us a step, 9000 keys at D = 64 3 to 7%; ranges of
+  // 256 and 2048 keys at D = 64 up to 2% slower).
+  if (any) {
+    for (; grp + nwaves <= g_last; grp += nwaves) group(grp + nwaves, true);
+    if (grp <= g_last) group(grp + nwaves, false);
   }
 
   // wavefronts -> LDS, then one merge
