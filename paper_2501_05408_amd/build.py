@@ -21,9 +21,10 @@ OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["tempo_api.hip", "kv_store.hip", "attn_partial_bf16.hip", "attn_partial_f32.hip", "attn_step_f32.hip",
            "attn_combine.hip", "stream_read.hip", "rope.hip", "attn_prefill_bf16.hip", "attn_block_bf16.hip",
+           "attn_stream_bf16.hip",
            "worklist.hip", "discounted_sum.hip"]
 HEADERS = [os.path.join(CSRC, "tempo_internal.h"), os.path.join(CSRC, "attn_bf16_common.h"),
-           os.path.join(CSRC, "attn_combine.h"), os.path.join(ROOT, "include", "tempo.h")]
+           os.path.join(CSRC, "attn_bf16_columns32.h"), os.path.join(CSRC, "attn_combine.h"), os.path.join(ROOT, "include", "tempo.h")]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Rpass-analysis=kernel-resource-usage",
@@ -68,6 +69,7 @@ def _drop_remarks(lines):
 MIN_OCCUPANCY = [
     ("attn_partial_bf16ILi128E", 3),           # decode kernel, D = 128: <= 170 VGPRs
     ("attn_block_bf16ILi128ELi8E", 4),         # LDS-staged block kernel, D = 128: two workgroups of 8 per compute unit
+    ("attn_stream_bf16ILi128E", 2),            # stream kernel, D = 128: one workgroup of 8 wavefronts per compute unit
     ("attn_prefill_bf16ILi128E", 2),           # prompt kernel, D = 128: two wavefronts of 32 columns per SIMD
 ]
 

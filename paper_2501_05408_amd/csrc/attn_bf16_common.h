@@ -174,6 +174,24 @@ struct BlockWork {
   bool any;              // uniform over the workgroup; false: nothing to do
 };
 
+// The steps of w's columns (w.c0, w.steps set), their key range and the zsplit-th newest split of it.
+__device__ inline void cut_range(const AttnParams& p, BlockWork& w, int zsplit) {
+  int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[w.b] : p.t; // first step of the call for this sequence
+  t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
+  w.t_first = t_base + w.c0;
+  w.t_last = w.t_first + w.steps - 1;
+  const int lo = (p.window > 0 && w.t_first - p.window + 1 > 0) ? w.t_first - p.window + 1 : 0;
+  const int chunk0 = lo >> p.tps_log2;                        // (kWholeRange when not split)
+  const int nchunks = (w.t_last >> p.tps_log2) - chunk0 + 1;
+  w.any = w.any && zsplit < nchunks;
+  w.split = nchunks - 1 - zsplit;
+  const int cs = (chunk0 + w.split) << p.tps_log2, ce = split_end(chunk0 + w.split, p.tps_log2);
+  w.start = lo > cs ? lo : cs;
+  w.end = w.t_last < ce ? w.t_last : ce;
+  w.g_first = w.start >> 5;
+  w.g_last = w.end >> 5;
+}
+
 // Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by
 // linear index; the blocks of one (sequence, head) read the same keys/values, so each die is given
 // a contiguous run of the work list instead: workgroup L takes item (L mod 8) * (n / 8) + L / 8
@@ -215,20 +233,7 @@ __device__ inline BlockWork block_work(const AttnParams& p, int columns) {
   } else {
     w.ncols = w.steps * p.G;
   }
-  int t_base = p.t_per_seq ? ((const_i32_ptr)p.t_per_seq)[w.b] : p.t; // first step of the call for this sequence
-  t_base = t_base > p.t ? p.t : (t_base < 0 ? 0 : t_base);
-  w.t_first = t_base + w.c0;
-  w.t_last = w.t_first + w.steps - 1;
-  const int lo = (p.window > 0 && w.t_first - p.window + 1 > 0) ? w.t_first - p.window + 1 : 0;
-  const int chunk0 = lo >> p.tps_log2;                        // (kWholeRange when not split)
-  const int nchunks = (w.t_last >> p.tps_log2) - chunk0 + 1;
-  w.any = w.any && zsplit < nchunks;
-  w.split = nchunks - 1 - zsplit;
-  const int cs = (chunk0 + w.split) << p.tps_log2, ce = split_end(chunk0 + w.split, p.tps_log2);
-  w.start = lo > cs ? lo : cs;
-  w.end = w.t_last < ce ? w.t_last : ce;
-  w.g_first = w.start >> 5;
-  w.g_last = w.end >> 5;
+  cut_range(p, w, zsplit);
   return w;
 }
 

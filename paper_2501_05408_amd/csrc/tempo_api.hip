@@ -441,6 +441,45 @@ int do_combine(const tempo_kv* kv, void* out, int32_t batch, int32_t Hq, int32_t
   return launch_status(e, "attn_decode_combine");
 }
 
+// Splits of a block that the stream kernel takes: a time model as make_plan()'s, in nanoseconds, fitted to 228 blocks
+// of 18 to 124 columns behind 150 to 8000 keys at 7 split lengths each (the plans it takes are 0.5% off the fastest on
+// the mean, 16% at most).  One workgroup of 8 wavefronts per compute unit: about 3.4 us before its first group and
+// after its last one (at D = 64 three quarters of it), then its share of the stream or, if that takes longer, its
+// wavefronts' arithmetic, 1 us a group and tile of 32 columns; the combine reads and writes a partial per
+// column and split.
+void make_stream_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window, bool ragged,
+                      int32_t queries, tempo_plan* plan) {
+  constexpr double kFixedNs = 3400.0, kGroupNs = 1000.0, kFewNs = 5000.0, kManyNs = 8000.0, kPartialBytesPerNs = 4800.0;
+  const int D = kv->head_dim, columns = queries * (Hq / kv->num_kv_heads);
+  const int tiles = columns <= 32 ? 1 : columns <= 64 ? 2 : 4;
+  const int64_t pairs = (int64_t)batch * kv->num_kv_heads, keys = block_keys(t, queries, window);
+  const int32_t t_eff = last_step(t, queries), w_eff = union_window(window, queries);
+  const double wide = D / 128.0;
+  double costs[31], best = -1.0;
+  const int k_max = ragged ? 10 : 30;  // (ragged batches: as in make_plan)
+  int last = 7;
+  for (int k = 7; k <= k_max; ++k) {
+    const int64_t splits = splits_bound(t_eff, w_eff, k), workgroups = pairs * splits;
+    const int64_t rounds = (workgroups + kComputeUnits - 1) / kComputeUnits, busy = workgroups < kComputeUnits ? workgroups : kComputeUnits;
+    const int64_t per_split = ((int64_t)1 << k) < keys ? (int64_t)1 << k : keys;
+    const double share = kSustainedBytesPerNs / (double)busy, rate = share < kUnitBytesPerNs ? share : kUnitBytesPerNs;
+    const double stream = (double)per_split * D * 4 / rate, work = (double)((per_split + 255) / 256) * kGroupNs * tiles * wide;
+    costs[k] = (double)rounds * (kFixedNs * (D == 128 ? 1.0 : 0.75) + (stream > work ? stream : work));
+    if (splits > 1) costs[k] += (splits > 8 ? kManyNs : kFewNs) + 2.0 * batch * queries * Hq * (double)splits * D * 4 / kPartialBytesPerNs;
+    if (splits <= kMaxSplits && (best < 0.0 || costs[k] < best)) best = costs[k];
+    last = k;
+    if (splits == 1) break;
+  }
+  int chosen = last;
+  while (splits_bound(t_eff, w_eff, chosen) > kMaxSplits) ++chosen;
+  for (int k = 7; k <= last; ++k) {  // the longest within 2% of the best
+    if (splits_bound(t_eff, w_eff, k) <= kMaxSplits && costs[k] <= best * 1.02) chosen = k;
+  }
+  plan->tokens_per_split = 1 << chosen;
+  plan->num_splits = splits_bound(t_eff, w_eff, chosen);
+  plan->waves = 8;  // (always)
+}
+
 // Plan of a block of queries: the plan of the union range, with the wavefront count
 // cut down until the bf16 kernel's wave-merge area (one accumulator row per column
 // and wavefront) fits the LDS a workgroup may ask for.
@@ -449,17 +488,19 @@ void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, i
   make_plan(kv, batch, Hq, last_step(t, queries), union_window(window, queries), ragged, queries, max_splits, plan);
   if (kv->dtype != TEMPO_BF16) return;
   const int columns = queries * (Hq / kv->num_kv_heads);
+  if (columns > kNarrowColumns && block_streams(kv->head_dim, columns, (int64_t)batch * kv->num_kv_heads, block_keys(t, queries, window))) {
+    make_stream_plan(kv, batch, Hq, t, window, ragged, queries, plan);
+    return;
+  }
   if (columns > kNarrowColumns) {
     // The LDS-staged kernel: its workgroups do more arithmetic per key than the decode
     // kernel's, so two per compute unit are wanted (measured at batch 16 x 8 heads,
     // t = 4095: 4 splits of 1024 keys 59-68 us for 63-126 columns, 2 splits 82-83 us,
     // 8 splits 68-81 us).
     // Longest split length of at least 256 keys that gives >= 512 workgroups, else 256.
-    // Up to 32 columns a workgroup has only two wavefronts: twice as many workgroups
-    // (measured there: 8 splits of 512 keys 52.8-53.8 us, 4 splits of 1024 keys 55.5-56.1 us).
     const int32_t t_eff = last_step(t, queries), w_eff = union_window(window, queries);
     const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
-    const int64_t want = (columns <= 32 ? 4 : 2) * (int64_t)kComputeUnits;
+    const int64_t want = 2 * (int64_t)kComputeUnits;
     int k = 8;
     for (int cand = 30; cand >= 8; --cand) {
       if (pairs * splits_bound(t_eff, w_eff, cand) >= want) { k = cand; break; }
@@ -468,7 +509,7 @@ void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, i
     if (ragged && k > 10 && splits_bound(t_eff, w_eff, 10) <= kMaxSplits) k = 10;  // as for single steps
     plan->tokens_per_split = 1 << k;
     plan->num_splits = splits_bound(t_eff, w_eff, k);
-    plan->waves = 8;  // ignored: the launch picks 2, 4 or 8 wavefronts by the column count
+    plan->waves = 8;  // ignored: the launch picks 4 or 8 wavefronts by the column count
     return;
   }
   while (plan->waves > 1 && partial_bf16_lds_bytes(plan->waves, columns, kv->head_dim) > kMaxLds) plan->waves /= 2;

@@ -142,6 +142,22 @@ __host__ __device__ inline int prompt_block_span(int G, int columns) {
   return columns % G == 0 ? columns / G : (columns + G - 2) / G + 1;
 }
 
+// Keys that some step of a block of query steps sees.
+inline int64_t block_keys(int t, int queries, int window) {
+  const int64_t all = (int64_t)t + queries, windowed = (int64_t)window + queries - 1;
+  return window > 0 && windowed < all ? windowed : all;
+}
+// Does the stream kernel (attn_stream_bf16.hip) take a bf16 block of more than 16 columns, or the one that shares
+// each group among its wavefronts through LDS (attn_block_bf16.hip)?  Us a call, LDS / stream, each with its fastest
+// plan: D = 128, 24/8 heads, 18 columns, 1 sequence, 150 keys 10.0 / 6.0, 16 of 4075 51.6 / 46.9; 63 columns, 16 of 150
+// 11.3 / 12.1, 16 of 500 22.8 / 15.7, 16 of 4075 56.8 / 53.1.  Beyond 64 columns registers do not hold a wavefront's
+// accumulators.  D = 64, 32/8 heads, 60 columns, 1 sequence, 150 keys 8.3 / 7.1; four tiles cost four merges: 124
+// columns, 1 sequence, 150 keys 8.5 / 12.3, 8000 keys 20.4 / 21.7, 16 of 500 16.8 / 15.9, 4 of 4075 32.8 / 24.8.
+inline bool block_streams(int D, int columns, int64_t pairs, int64_t keys) {
+  if (D == 128) return columns <= 32 || (columns <= 64 && keys > 192);
+  return columns <= 64 || pairs * keys >= 65536;
+}
+
 // Visible range and split bookkeeping of one sequence, identical on host and device.
 // With a block of C queries (steps t_b .. t_b+C-1) the range is the union of the
 // queries' ranges: from the first query's lo to the last query's step.  The padded
@@ -188,6 +204,7 @@ size_t partial_bf16_lds_bytes(int waves, int columns, int D);      // dynamic LD
 hipError_t launch_prefill_bf16(const PromptParams& p, int batch, int D, int waves, int grid_splits, hipStream_t stream);
 hipError_t launch_prompt_combine(const PromptParams& p, int batch, int D, hipStream_t stream);
 hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipStream_t stream);
+hipError_t launch_stream_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream);
 hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream);
 hipError_t launch_partial_f32(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                               hipStream_t stream);

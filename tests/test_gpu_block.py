@@ -357,3 +357,36 @@ def test_llama_shape_prefill_bf16_full_size():
     for t in sample:
         ref = oracle.attend(np64(q[:, t]), K64[:, :t + 1], V64[:, :t + 1], t, 0, 1.0 / np.sqrt(D))
         assert_close(out[:, t], ref, dtype, f"llama prefill step {t}")
+
+
+@pytest.mark.parametrize("G,C,D,B,steps,window,k", [
+    (17, 1, 128, 2, 300, 0, 0), (11, 3, 128, 1, 260, 0, 5), (3, 11, 128, 3, 197, 0, 0), (3, 11, 128, 3, 210, 185, 0),
+    (16, 4, 128, 1, 700, 0, 7), (8, 8, 128, 2, 1030, 500, 0), (1, 64, 64, 2, 330, 0, 0), (13, 5, 64, 1, 2100, 0, 0),
+    (4, 31, 64, 16, 540, 0, 0), (4, 32, 64, 2, 400, 90, 8), (3, 21, 128, 2, 900, 0, 10), (33, 1, 128, 2, 200, 0, 0)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_wide_blocks_where_the_kernel_and_its_tiles_change(G, C, D, B, steps, window, k, ragged):
+    """17 to 128 columns at the lines between the stream kernel's tiles of 32 and the kernel that shares groups
+    through LDS, in a store that holds NaN wherever it was not written; k: splits of 2^k keys instead of the plan's."""
+    Hkv, Hq, Z = 2, 2 * G, 32
+    q, K, V = host_inputs(57, B, steps, Hq, Hkv, D, T.TEMPO_BF16)
+    table, nb = random_table(57, B, (steps - 1) // Z + 1)
+    st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, T.TEMPO_BF16, num_blocks=nb, block_table=table, fill="nan")
+    lowest = max(0, steps - C - window + 1) if window and not ragged else 0
+    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
+    st.append_block(Kd[:, lowest:].contiguous(), Vd[:, lowest:].contiguous(), lowest, steps - lowest)
+    t0 = steps - C
+    first = [t0 - 37 * b % (t0 + 1) for b in range(B)] if ragged else [t0] * B
+    tps = torch.tensor(first, dtype=torch.int32, device=DEV) if ragged else None
+    rows = np.stack([np.stack([q[first[b] + c][b] for c in range(C)]) for b in range(B)])
+    qd = dev(np.ascontiguousarray(rows), T.TEMPO_BF16)
+    out = torch.full_like(qd, float("nan"))
+    if k:
+        plan = T.tempo_plan()
+        plan.tokens_per_split, plan.num_splits, plan.waves = 1 << k, ((steps - 1) >> k) + 1, 8
+        nbytes = T.tempo_attn_plan_workspace_bytes(st.kv, B * C, Hq, plan)
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+        T.tempo_attn_block_with_plan(st.kv, qd, out, B, Hq, C, t0, tps, window, st.scale, plan, ws, nbytes)
+    else:
+        st.attend_block(qd, out, t0, C, window, tps)
+    ref = oracle_block(q, K.astype(np.float64), V.astype(np.float64), t0, C, window, D, first if ragged else None)
+    assert_close(np64(out), ref, T.TEMPO_BF16, f"{(G, C, D, B, steps, window, k, ragged)}")
