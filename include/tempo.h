@@ -476,7 +476,7 @@ int tempo_prefill_window(const tempo_kv* kv, const void* q, const void* k_new, c
 
 /* tempo_prefill_* with the rotary producer fused in: q_raw and k_raw arrive
  * unrotated; keys are turned to their step's position on the way into the store
- * (the same bits tempo_rope_kv_append stores), queries when the prompt kernel loads
+ * (the same bits tempo_rope_kv_append stores), queries when the attention kernel loads
  * them.  bf16 linear stores only (TEMPO_ERR_SHAPE otherwise); rope->positions must
  * exceed t + count - 1.  Other arguments as
  * tempo_prefill_causal / _window. */

@@ -960,10 +960,13 @@ bool short_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int3
 //   8000 keys 14, 27; 16 sequences behind 300 keys 10, 12), but for one or two (sequence, head) pairs with a
 //   few columns behind a short range, whose many splits cost more to combine (1 sequence, 8/1 heads, 2 steps
 //   behind 1000 keys 14.0, 11.1).
-//   bf16, more columns: by two estimates in us, fitted to 1050 measured prompts of 1 to 128 pairs (on the mean
-//   0.2% from the better of the two), unless their blocks fill the part.  A block takes 15 and 1.05 to
-//   1.5 times its keys' stream from HBM; one launch 8 and the longer of a workgroup's walk through an eighth of the keys and 1.2 times the stream
-//   (1 sequence, 24/8 heads, 21 steps behind 4000 keys 21, 20, behind 8000 24, 30, behind 32000 48, 85).
+//   bf16, more columns: by two estimates in us, fitted to 884 measured prompts of 1 to 128 pairs (on the mean
+//   0.2% from the better of the two), unless their blocks fill the part.  A block takes a time of its own and a
+//   share of its keys' stream from HBM, both by the kernel its columns go to (33 to 64 columns: 12.5 at the least with
+//   D = 128; with D = 64, 2 more where splits are combined); one launch 8 and the longer of a workgroup's walk through
+//   an eighth of the keys and 1.2 times the stream (33 to 64 columns, D = 64: 0.06 a step for the rows it writes) (us, by blocks / in one launch: 2 sequences,
+//   32/8 heads of 64, 5 steps behind 8000 keys 13.3 / 22.3, 1 sequence, 16/16 heads of 64, 48 steps behind 8000 17.0 / 24.4,
+//   4 sequences, 24/8 heads of 128, 21 steps behind 8000 35.6 / 31.5).
 bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window) {
   const int32_t G = Hq / kv->num_kv_heads, block = kMaxColumns / G;
   if (kv->dtype != TEMPO_BF16) return count <= block;
@@ -979,11 +982,15 @@ bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, 
   const bool narrow = kv->head_dim == 64;
   const double stream = (double)pairs * keys * kv->head_dim * 4 / (kSustainedBytesPerNs * 1000.0);
   const int64_t blocks = (count + block - 1) / block, widest = columns < kMaxColumns ? columns : kMaxColumns;
-  const double by_blocks = (double)blocks * ((narrow ? 14.0 : 15.0) +
-                                             (widest <= 32 ? 1.05 : widest <= 64 ? 1.1 : 1.5) * (narrow ? 1.4 : 1.0) * stream);
+  const int size = widest <= 32 ? 0 : widest <= 64 ? 1 : 2;
+  constexpr double kOwn[2][3] = {{8.0, 5.6, 14.1}, {5.7, 8.4, 14.6}}, kShare[2][3] = {{0.6, 1.8, 1.46}, {0.9, 0.8, 1.0}};
+  double block_time = kOwn[narrow][size] + kShare[narrow][size] * stream;
+  if (!narrow && size == 1 && block_time < 12.5) block_time = 12.5;
+  if (narrow && size == 1 && keys > 512) block_time += 2.0;
+  const double by_blocks = (double)blocks * block_time;
   const int64_t workgroups = 8 * pairs * blocks, rounds = (workgroups + 2 * kComputeUnits - 1) / (2 * kComputeUnits);
   const double walk = (workgroups <= kComputeUnits ? 0.55 : 0.78) * (narrow ? 0.68 : 1.0) * (columns > 64 ? 1.1 : 1.0) * rounds * (double)keys / 256.0;
-  const double one_launch = 8.0 + (walk > 1.2 * stream ? walk : 1.2 * stream);
+  const double one_launch = 8.0 + (walk > 1.2 * stream ? walk : 1.2 * stream) + (narrow && size == 1 ? 0.06 * count : 0.0);
   return by_blocks < one_launch;
 }
 
@@ -1223,7 +1230,8 @@ int prefill_staged(const tempo_kv* kv, const void* q, const void* k_new, const v
 // `count` steps from t on, in blocks of 128 columns: write (fp32, one block from step 0 on: the attention launch
 // does), attend, combine.
 int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, const void* v_new, void* out, int32_t batch,
-                      int32_t Hq, int32_t t, int32_t count, int32_t window, float scale, void* workspace, hipStream_t s) {
+                      int32_t Hq, int32_t t, int32_t count, int32_t window, float scale, void* workspace, hipStream_t s,
+                      const tempo_rope* rope = nullptr) {
   const size_t esz = kv->dtype == TEMPO_BF16 ? 2 : 4;
   const int32_t block = kMaxColumns / (Hq / kv->num_kv_heads);
   const bool rows = kv->dtype == TEMPO_F32 && t == 0 && count <= block && rows_readable(kv, k_new, v_new, out, batch, Hq, count);
@@ -1237,9 +1245,13 @@ int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, cons
     char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
     StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
     sp.src_steps = count;
+    if (rope) {
+      sp.rope_cos = rope->cos;
+      sp.rope_sin = rope->sin;
+    }
     int rc = rows ? TEMPO_OK : launch_status(launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s), "kv_append_block");
     if (rc != TEMPO_OK) return rc;
-    rc = do_partial(kv, qc, rows ? kc : nullptr, rows ? vc : nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, nullptr,
+    rc = do_partial(kv, qc, rows ? kc : nullptr, rows ? vc : nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, rope,
                     0, count);
     if (rc != TEMPO_OK) return rc;
     if (plan.num_splits > 1) {
@@ -1279,7 +1291,7 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     if (kv->ring_blocks && (int64_t)C > (int64_t)kv->ring_blocks * kv->block_size) return TEMPO_ERR_RANGE;
   }
 
-  // per-sequence prompt lengths and the rotary producer exist in the prompt kernel only
+  // per-sequence prompt lengths exist in the prompt kernel only; the rotary producer is refused where that could not take the prompt
   if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
     return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
@@ -1290,8 +1302,8 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     return attend_prompt(kv, q, out, batch, Hq, t, count, count, count_per_seq, window, scale, workspace, workspace_bytes, s,
                          nullptr, nullptr, &rows);
   }
-  if (!count_per_seq && !rope && prompt_by_blocks(kv, batch, Hq, t, count, window))
-    return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s);
+  if (!count_per_seq && prompt_by_blocks(kv, batch, Hq, t, count, window))
+    return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s, rope);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
   if (prompt_in_one_launch(kv, batch, Hq, count)) {
     for (int32_t c0 = 0; c0 < count;) {

@@ -103,6 +103,13 @@ def test_rope_prompt_with_split_ranges(D, G, t, count):
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 1), (128, 3, 1500, 5), (128, 4, 3000, 8), (64, 4, 3000, 12),
+                                         (64, 3, 9000, 70), (128, 20, 4000, 3)])
+def test_rope_prompt_by_blocks(D, G, t, count):
+    """Those that go in blocks of columns: each size of kernel, two blocks, and groups wider than the single-step kernel."""
+    test_rope_prompt_with_split_ranges(D, G, t, count)
+
+
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
     (1, 2, 4, 64, 64, 0, 300, 0, False), (2, 2, 3, 128, 4, 13, 70, 0, False), (1, 1, 1, 64, 8, 2500, 9, 0, False),
     (1, 1, 20, 128, 16, 37, 30, 33, False), (1, 1, 3, 128, 16, 3000, 5, 0, False), (2, 1, 3, 64, 8, 50, 260, 40, True)])
