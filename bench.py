@@ -154,7 +154,7 @@ def launch_bound_legs(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
                      "graph_min_us": us(graph["min"]), "ideal_us": us(nbytes / (HBM_PEAK_GBS * 1e9)),
                      "kv_bytes_per_step": nbytes, "splits": plan.num_splits,
                      "tokens_per_split": plan.tokens_per_split, "waves": plan.waves,
-                     "roofline": hbm_roofline("attn_partial_bf16<128, false>", nbytes, best,
+                     "roofline": hbm_roofline("attn_partial_bf16<128>", nbytes, best,
                                               "whole step, the faster of eager and graph replay")}
 
     sts = layers(16, 4095)
@@ -178,7 +178,7 @@ def launch_bound_legs(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
     for t in (4095, 8191):
         leg(f"head_dim64_hq32_b16_t{t}", lambda i: sts64[i % R].step_causal(q64, k64, v64, o64, t),
             16 * (t + 1) * 2 * 8 * 64 * 2, T.tempo_attn_plan(sts64[0].kv, 16, 32, t, 0))
-        out[f"head_dim64_hq32_b16_t{t}"]["roofline"]["kernel"] = "attn_partial_bf16<64, false>"
+        out[f"head_dim64_hq32_b16_t{t}"]["roofline"]["kernel"] = "attn_partial_bf16<64>"
     del sts64
     torch.cuda.empty_cache()
     sts = layers(16, 16383)
@@ -264,7 +264,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
 
     # blocks of query steps over the headline shape: append C steps, then one attention call answers
     # steps 4096-C .. 4095.  5 steps (15 of the 16 tile columns) ride in the single-step kernel;
-    # 10, 21 and 42 steps (30, 63 and 126 columns) go through the LDS-staged kernel.
+    # 10 and 21 steps (30 and 63 columns) go through the stream kernel, 42 (126 columns) through the LDS-staged one.
     sts = layers(8, 16, 4095)
     block_bytes = 16 * 4096 * kv_bytes_per_token
     for C in (5, 10, 21, 42):
@@ -279,7 +279,8 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
 
         dt = gpu_timed(torch, block_step, 200, 20)["median"]
         plan = T.tempo_attn_block_plan(sts[0].kv, 16, Hq, C, 4096 - C, 0)
-        kernel = "attn_partial_bf16<128, false>" if C * (Hq // Hkv) <= 16 else "attn_block_bf16<128, NW, false, true>"
+        kernel = ("attn_partial_bf16<128>" if C * (Hq // Hkv) <= 16 else
+                  "attn_stream_bf16<128>" if C * (Hq // Hkv) <= 64 else "attn_block_bf16<128, 8, false, true>")
         out[f"block{C}_b16_t{4096 - C}"] = {"us_per_call": us(dt), "us_per_query_step": us(dt / C),
                                             "kv_gbs": round(block_bytes / dt / 1e9, 1),
                                             "splits": plan.num_splits, "tokens_per_split": plan.tokens_per_split,
@@ -327,7 +328,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
     dt3 = gpu_timed(torch, rope_separate, 200, 20)["median"]
     out["rope_step_b16_t4095"] = {"us_per_step": us(dt), "kv_gbs": round(block_bytes / dt / 1e9, 1),
                                   "separate_launches_us": us(dt3),
-                                  "roofline": hbm_roofline("attn_partial_bf16<128, true>", block_bytes, dt),
+                                  "roofline": hbm_roofline("attn_partial_bf16<128, true, false, true>", block_bytes, dt),
                                   "note": "fused: rotate q,k + append + attend in 2 launches; separate: 4 launches"}
     # the same for a block of 21 steps: one rotating block write + one block call with raw queries
     C = 21
@@ -418,7 +419,7 @@ def ragged_step_bench(torch, T, BlockStore, synth, dev, kv_bytes_per_token, repe
             "kv_gbs": round(step_bytes / dt / 1e9, 1), "kv_bytes_per_step": step_bytes,
             "pool_gib": round(2 * k_pool.numel() * 2 / 2**30, 1),
             "splits": plan.num_splits, "tokens_per_split": plan.tokens_per_split, "waves": plan.waves,
-            "roofline": hbm_roofline("attn_partial_bf16<128, false>", step_bytes, min(dt, gdt),
+            "roofline": hbm_roofline("attn_partial_bf16<128, false, true, true>", step_bytes, min(dt, gdt),
                                      "all 28 layers (block-store write, attention, combine each, plus one work-list "
                                      "launch per step when listed); the fastest of dense grid, work list and one "
                                      "graph of the 28 dense layers"),
@@ -444,7 +445,7 @@ def prompt_only(torch, T, BlockStore, synth, dev, repeats):
 
 
 def block_only(torch, T, BlockStore, synth, dev, C, repeats):
-    """One block workload alone (for profiling the split path of the LDS-staged kernel): C query
+    """One block workload alone (for profiling the kernels of wide blocks): C query
     steps of 16 sequences of the headline shape in front of 4096 - C stored steps, one block-store
     write and one tempo_attn_block_causal call per repeat, 8 layer pools rotated."""
     B, Hq, Hkv, D, Z = 16, 24, 8, 128, 256
@@ -862,7 +863,7 @@ def main() -> int:
                            "launches": "tempo_kv_append + tempo_attn_decode_causal"},
         "steps_per_s": round(1.0 / sec_per_step, 1),
         "roofline": {
-            "kernel": "attn_partial_bf16<128, false>",
+            "kernel": "attn_partial_bf16<128, false, false, true>",
             "bound": "hbm",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,

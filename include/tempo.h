@@ -44,7 +44,7 @@
  * for bf16 and >= 4 for f32; num_q_heads a multiple of num_kv_heads with a
  * group of at most 128 query heads per key/value head (bf16: a group of up to
  * 16 heads is served by the single-step kernel, which can write the step's
- * key/value itself; a larger group by the LDS-staged kernel of the block entry
+ * key/value itself; a larger group by the kernels for wide blocks of the block entry
  * points, with the store written by a launch of its own first).
  */
 #ifndef TEMPO_H
@@ -408,8 +408,8 @@ int tempo_rope_decode_step_window(const tempo_kv* kv, const tempo_rope* rope, co
  *            the per-sequence first steps t_per_seq[b]
  * Limits: queries >= 1 and queries * (num_q_heads / num_kv_heads) <= 128
  * (TEMPO_ERR_SHAPE otherwise): up to 16 such (step, head) columns ride in the
- * padding of the single-step kernel's tiles, 17..128 use the LDS-staged kernel
- * (eight wavefronts of 16 columns share one copy of every key/value group).  workspace: device, 256-byte aligned, at least
+ * padding of the single-step kernel's tiles, 17..128 use kernels
+ * of their own (every key/value is still read once for all columns).  workspace: device, 256-byte aligned, at least
  * tempo_attn_block_workspace_bytes(kv, batch, num_q_heads, queries, t) bytes.
  * Other arguments, launches and errors as tempo_attn_decode_causal / _window.
  */

@@ -32,7 +32,7 @@
 // the G heads (column = c*G + g, C*G <= 16): step t+c sees keys up to t+c (and
 // from its own window start), which is one more per-lane bound in the index mask.
 // The keys and values are still read once, now for C steps.  Blocks of more than
-// 16 columns are served by the LDS-staged kernel of attn_prefill_bf16.hip.
+// 16 columns are served by attn_stream_bf16.hip and attn_block_bf16.hip.
 //
 // Rotary embedding (kRope instantiations).  q, and the k_new of a fused append,
 // arrive unrotated; the kernel turns them to their step's position with fp32
@@ -397,7 +397,7 @@ size_t partial_bf16_lds_bytes(int waves, int columns, int D) {
   return (size_t)waves * (32 + (size_t)columns * D) * sizeof(float) + 2 * (size_t)D * sizeof(uint16_t);
 }
 
-// Up to 16 (step, head) columns; wider blocks use the LDS-staged kernel.
+// Up to 16 (step, head) columns; wider blocks use the kernels of launch_block_bf16().
 hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_splits, int waves,
                                hipStream_t stream) {
   if (p.queries * p.G > 16) return hipErrorInvalidConfiguration;

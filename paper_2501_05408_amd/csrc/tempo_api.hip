@@ -44,8 +44,8 @@ int check_store(const tempo_kv* kv) {
 }
 
 // A block of C consecutive query steps: its C * (Hq / Hkv) (step, head) columns
-// either ride in the 16-column tile of the decode kernel or, up to 128, are spread
-// over the eight wavefronts of the LDS-staged kernel (the same limit for fp32).
+// either ride in the 16-column tile of the decode kernel or, up to 128, go to
+// the kernels for wide blocks (launch_block_bf16(); the same limit for fp32).
 // A single step of a group of more than 16 query heads is such a block of one step.
 constexpr int kMaxColumns = 128;
 // Up to this many columns the single-step kernel (one 16-column tile) serves the call.
@@ -386,7 +386,7 @@ int check_attn(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t
   if ((rc = check_plan(plan, t, window, ragged, queries, pad_t)) != TEMPO_OK) return rc;
   if (kv->dtype == TEMPO_BF16) {
     const int columns = queries * (Hq / kv->num_kv_heads);
-    // more than 16 columns go to the LDS-staged kernel, whose launch shape is fixed
+    // more than 16 columns go to the kernels for wide blocks, whose launch shapes are fixed
     if (columns <= kNarrowColumns && partial_bf16_lds_bytes(plan->waves, columns, kv->head_dim) > kMaxLds) return TEMPO_ERR_SHAPE;
   }
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return TEMPO_ERR_WORKSPACE;
@@ -421,7 +421,7 @@ int do_partial(const tempo_kv* kv, const void* q, const void* k_new, const void*
     p.rope_sin = rope->sin;
   }
   const int32_t gs = grid_splits(plan, t, t_per_seq, window, queries, pad_t);
-  if (kv->dtype == TEMPO_BF16 && queries * p.G > kNarrowColumns)  // a wide block: the LDS-staged kernel, key range split as planned
+  if (kv->dtype == TEMPO_BF16 && queries * p.G > kNarrowColumns)  // a wide block: kernels of their own, key range split as planned
     return launch_status(launch_block_bf16(p, batch, kv->head_dim, gs, stream), "attn_block_partial");
   const hipError_t e = kv->dtype == TEMPO_BF16
                            ? launch_partial_bf16(p, batch, kv->head_dim, gs, plan->waves, stream)
@@ -539,9 +539,9 @@ int decode(const tempo_kv* kv, const void* q, const void* k_new, const void* v_n
   // With more (sequence, head) pairs than compute units the in-kernel block-store write
   // costs more than a launch of its own (measured at 512 pairs: +7.5 us inside the
   // attention kernel, +4 us as a separate launch; at 128 pairs +1 us inside): write first.
-  // A group of more than 16 query heads runs in the LDS-staged kernel, which reads the
+  // A group of more than 16 query heads runs in the kernels for wide blocks, which read the
   // store only: the write (rotating the key when tables are given) goes first there too,
-  // and the kernel rotates the queries.
+  // and they rotate the queries.
   const bool wide = kv->dtype == TEMPO_BF16 && queries * (Hq / kv->num_kv_heads) > kNarrowColumns;
   if (k_new && kv->dtype == TEMPO_BF16 && (wide || (!rope && (int64_t)batch * kv->num_kv_heads > kComputeUnits))) {
     const StoreParams sp = store_params(kv, batch, t, t_per_seq);
@@ -877,8 +877,8 @@ int tempo_attn_decode_padded_causal(const tempo_kv* kv, const void* q, void* out
                                     int32_t t_pad, float scale, void* workspace, size_t workspace_bytes,
                                     void* stream) {
   if (kv && kv->dtype == TEMPO_F32) return TEMPO_ERR_DTYPE;  // the baseline exists for the bf16 kernel only
-  // ... and in the single-step kernel only: the LDS-staged kernel that serves larger query
-  // groups walks the step's own range and knows no padding bound
+  // ... and in the single-step kernel only: the kernels that serve larger query
+  // groups walk the step's own range and know no padding bound
   if (kv && kv->num_kv_heads > 0 && num_q_heads / kv->num_kv_heads > kNarrowColumns) return TEMPO_ERR_SHAPE;
   if (t_pad < t) return TEMPO_ERR_RANGE;
   return decode(kv, q, nullptr, nullptr, out, batch, num_q_heads, t, t_per_seq, 0, scale, workspace,
