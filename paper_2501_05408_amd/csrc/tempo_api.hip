@@ -1110,16 +1110,22 @@ struct PromptRows {
   int32_t keep_first;
 };
 
+// Is `out` clear of the rows?
+bool rows_apart(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
+                int32_t count) {
+  const uintptr_t k = reinterpret_cast<uintptr_t>(k_new), v = reinterpret_cast<uintptr_t>(v_new);
+  const uintptr_t o = reinterpret_cast<uintptr_t>(out);
+  const uintptr_t step_bytes = (uintptr_t)batch * count * kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);
+  const uintptr_t out_bytes = step_bytes * Hq, row_bytes = step_bytes * kv->num_kv_heads;
+  return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
+}
+
 // May it?  Not where `out` lies over the rows (which a write launch of its own has read before), nor where
 // 16-byte pieces of them are not aligned.
 bool rows_readable(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
                    int32_t count) {
-  const uintptr_t k = reinterpret_cast<uintptr_t>(k_new), v = reinterpret_cast<uintptr_t>(v_new);
-  const uintptr_t o = reinterpret_cast<uintptr_t>(out);
-  if ((k | v) & 15u) return false;
-  const uintptr_t step_bytes = (uintptr_t)batch * count * kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);
-  const uintptr_t out_bytes = step_bytes * Hq, row_bytes = step_bytes * kv->num_kv_heads;
-  return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
+  return ((reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new)) & 15u) == 0 &&
+         rows_apart(kv, k_new, v_new, out, batch, Hq, count);
 }
 
 // And is it the faster way?  fp32: at D = 64 (of 96 shapes all but one, 0.95 to 1.74), and at D = 128 up to about
@@ -1235,23 +1241,32 @@ int prefill_by_blocks(const tempo_kv* kv, const void* q, const void* k_new, cons
   const size_t esz = kv->dtype == TEMPO_BF16 ? 2 : 4;
   const int32_t block = kMaxColumns / (Hq / kv->num_kv_heads);
   const bool rows = kv->dtype == TEMPO_F32 && t == 0 && count <= block && rows_readable(kv, k_new, v_new, out, batch, Hq, count);
-  for (int32_t c0 = 0; c0 < count; c0 += block) {
-    const int32_t C = count - c0 < block ? count - c0 : block;
-    tempo_plan plan;
-    make_block_plan(kv, batch, Hq, t + c0, window, false, C, &plan);
-    const char* kc = static_cast<const char*>(k_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
-    const char* vc = static_cast<const char*>(v_new) + (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
-    const char* qc = static_cast<const char*>(q) + (size_t)c0 * Hq * kv->head_dim * esz;
-    char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
+  // `out` over the rows: a block's answers would stand where the next one's rows are read, so all are written first
+  const bool write_first = !kv->ring_blocks && count > block && !rows_apart(kv, k_new, v_new, out, batch, Hq, count);
+  const auto write = [&](int32_t c0, int32_t C) {
+    const size_t at = (size_t)c0 * kv->num_kv_heads * kv->head_dim * esz;
     StoreParams sp = store_params(kv, batch, t + c0, nullptr, C);
     sp.src_steps = count;
     if (rope) {
       sp.rope_cos = rope->cos;
       sp.rope_sin = rope->sin;
     }
-    int rc = rows ? TEMPO_OK : launch_status(launch_append(sp, kc, vc, kv->head_dim, kv->dtype, s), "kv_append_block");
+    return launch_status(launch_append(sp, static_cast<const char*>(k_new) + at, static_cast<const char*>(v_new) + at, kv->head_dim, kv->dtype, s),
+                         "kv_append_block");
+  };
+  for (int32_t c0 = 0; write_first && c0 < count; c0 += block) {
+    const int rc = write(c0, count - c0 < block ? count - c0 : block);
     if (rc != TEMPO_OK) return rc;
-    rc = do_partial(kv, qc, rows ? kc : nullptr, rows ? vc : nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, rope,
+  }
+  for (int32_t c0 = 0; c0 < count; c0 += block) {
+    const int32_t C = count - c0 < block ? count - c0 : block;
+    tempo_plan plan;
+    make_block_plan(kv, batch, Hq, t + c0, window, false, C, &plan);
+    const char* qc = static_cast<const char*>(q) + (size_t)c0 * Hq * kv->head_dim * esz;
+    char* oc = static_cast<char*>(out) + (size_t)c0 * Hq * kv->head_dim * esz;
+    int rc = rows || write_first ? TEMPO_OK : write(c0, C);
+    if (rc != TEMPO_OK) return rc;
+    rc = do_partial(kv, qc, rows ? k_new : nullptr, rows ? v_new : nullptr, oc, batch, Hq, t + c0, nullptr, window, scale, &plan, workspace, s, C, rope,
                     0, count);
     if (rc != TEMPO_OK) return rc;
     if (plan.num_splits > 1) {
@@ -1302,7 +1317,9 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     return attend_prompt(kv, q, out, batch, Hq, t, count, count, count_per_seq, window, scale, workspace, workspace_bytes, s,
                          nullptr, nullptr, &rows);
   }
-  if (!count_per_seq && prompt_by_blocks(kv, batch, Hq, t, count, window))
+  // (a ring that several blocks go through can't be written ahead of them: not where `out` lies over the rows)
+  const bool blocks_stand = !kv->ring_blocks || count <= block || rows_apart(kv, k_new, v_new, out, batch, Hq, count);
+  if (!count_per_seq && blocks_stand && prompt_by_blocks(kv, batch, Hq, t, count, window))
     return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s, rope);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
   if (prompt_in_one_launch(kv, batch, Hq, count)) {

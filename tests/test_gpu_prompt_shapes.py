@@ -110,6 +110,31 @@ def test_rope_prompt_by_blocks(D, G, t, count):
     test_rope_prompt_with_split_ranges(D, G, t, count)
 
 
+@pytest.mark.parametrize("Hkv,D,t,count,dtype", [(2, 64, 9000, 300, T.TEMPO_BF16), (2, 128, 9000, 140, T.TEMPO_BF16),
+                                                 (2, 64, 0, 300, T.TEMPO_BF16), (2, 64, 0, 300, T.TEMPO_F32)])
+def test_prompt_answered_over_its_rows(Hkv, D, t, count, dtype):
+    """out may be the memory of k_new or v_new (several blocks, and one launch): the same answers, and the same store."""
+    torch.manual_seed(5)
+    ty = torch.bfloat16 if dtype == T.TEMPO_BF16 else torch.float32
+    q, k, v = (torch.randn(1, count, Hkv, D, device=DEV).to(ty) for _ in range(3))
+    K, V = (torch.randn(1, max(t, 1), Hkv, D, device=DEV).to(ty) for _ in range(2))
+    got = []
+    for over in (None, "k", "v"):
+        st = BlockStore(1, Hkv, Hkv, D, 64, t + count - 1, dtype, fill="nan")
+        if t:
+            st.append_block(K, V, 0, t)
+        kn, vn = k.clone(), v.clone()
+        out = {"k": kn, "v": vn}.get(over, torch.empty_like(q))
+        st.prefill_attend(q, kn, vn, out, t, count)
+        got.append((out.float().cpu(), st.k_pool.cpu(), st.v_pool.cpu()))
+    scale = got[0][0].abs().max()
+    for out, kp, vp in got[1:]:
+        # another route may answer: weights rounded to bf16 against another reference, 2^-8 each way
+        assert (out - got[0][0]).abs().max() <= 2 ** -7 * scale
+        assert torch.equal(kp.nan_to_num(7), got[0][1].nan_to_num(7))
+        assert torch.equal(vp.nan_to_num(7), got[0][2].nan_to_num(7))
+
+
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
     (1, 2, 4, 64, 64, 0, 300, 0, False), (2, 2, 3, 128, 4, 13, 70, 0, False), (1, 1, 1, 64, 8, 2500, 9, 0, False),
     (1, 1, 20, 128, 16, 37, 30, 33, False), (1, 1, 3, 128, 16, 3000, 5, 0, False), (2, 1, 3, 64, 8, 50, 260, 40, True)])
