@@ -84,7 +84,7 @@ __device__ inline void combine_heads(const float* ml, const float* acc, int S, i
       float4 A = {0.f, 0.f, 0.f, 0.f};
       for (int i = 0; i < R; ++i) {
         const float* slot = smem + (i * cols + col) * 6;
-        if (slot[0] == -INFINITY) continue;  // a lane that had no split
+        if (slot[1] == 0.f) continue;  // a lane that had no split, or none with a key of this row
         const float w = exp2f(slot[0] - M);
         L = fmaf(w, slot[1], L);
         A.x = fmaf(w, slot[2], A.x); A.y = fmaf(w, slot[3], A.y);

@@ -206,7 +206,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_stream_bf16(AttnParams p) {
       float den = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
-        const bool none = mw[w] == -INFINITY;  // saw no key of this column
+        // saw no key of this column (by the sum: a group with a logit that is NaN leaves the reference at -inf too)
+        const bool none = lw[w] == 0.f;
         const float wgt = none ? 0.f : fast_exp2(mw[w] - M);
         num += wgt * (none ? f32x4{0.f, 0.f, 0.f, 0.f} : aw[w]);
         den += none ? 0.f : wgt * lw[w];

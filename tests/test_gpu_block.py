@@ -390,3 +390,30 @@ def test_wide_blocks_where_the_kernel_and_its_tiles_change(G, C, D, B, steps, wi
         st.attend_block(qd, out, t0, C, window, tps)
     ref = oracle_block(q, K.astype(np.float64), V.astype(np.float64), t0, C, window, D, first if ragged else None)
     assert_close(np64(out), ref, T.TEMPO_BF16, f"{(G, C, D, B, steps, window, k, ragged)}")
+
+
+@pytest.mark.parametrize("G,C,D,steps,k", [(3, 7, 128, 150, 0), (3, 21, 128, 700, 0), (3, 21, 128, 1500, 7), (20, 1, 128, 200, 0),
+                                           (4, 5, 64, 150, 0), (4, 16, 64, 400, 0), (4, 16, 64, 400, 5), (4, 31, 64, 3000, 9),
+                                           (3, 40, 128, 500, 0)])
+def test_a_key_that_is_not_a_number_shows_in_every_step_that_sees_it(G, C, D, steps, k):
+    """One such key, alone in a wavefront's or a split's share of the range or among others; in no other step's outputs."""
+    B, Hkv, Z, Hq, t0 = 1, 2, 32, 2 * G, steps - C
+    q, K, V = host_inputs(58, B, steps, Hq, Hkv, D, T.TEMPO_BF16)
+    st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, T.TEMPO_BF16, fill="nan")
+    Kd, Vd = dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16)
+    qd = dev(block_of(q, t0, C), T.TEMPO_BF16)
+    plan = T.tempo_attn_block_plan(st.kv, B, Hq, C, t0, 0)
+    if k:
+        plan.tokens_per_split, plan.num_splits = 1 << k, ((steps - 1) >> k) + 1
+    nbytes = T.tempo_attn_plan_workspace_bytes(st.kv, B * C, Hq, plan)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+    for j in sorted({3, 70, steps // 2, t0, steps - 1}):
+        Kx = Kd.clone()
+        Kx[:, j, 1] = float("nan")
+        st.append_block(Kx, Vd, 0, steps)
+        out = torch.zeros_like(qd)
+        T.tempo_attn_block_with_plan(st.kv, qd, out, B, Hq, C, t0, None, 0, st.scale, plan, ws, nbytes)
+        bad = torch.isnan(out)
+        assert not bad[:, :, :G].any(), j                # the other kv head's
+        for c in range(C):
+            assert bad[:, c, G:].all() if j <= t0 + c else not bad[:, c].any(), (j, c)
