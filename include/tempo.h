@@ -28,7 +28,7 @@
  *    nothing, never synchronises, keeps no state between calls (one exception:
  *    tempo_decode_step_causal_noalloc, see there), and every launch is
  *    asynchronous on `stream`; calls may be captured in a HIP graph.
- *  - `out` must not alias q, the pools or the workspace.
+ *  - `out` must not alias q, the pools or the workspace.  (It may lie over k_new and v_new.)
  *  - Results are deterministic: same inputs and same arguments, same bits.
  *  - Every entry point validates its arguments on the host and returns a
  *    negative tempo_status before launching anything if they are bad.  Block
@@ -453,6 +453,11 @@ int tempo_rope_attn_block_window(const tempo_kv* kv, const tempo_rope* rope, con
  * workspace first and the steps the ring keeps are written last; a workspace without the
  * room for that takes the prompt in chunks that the ring can hold.  (All launches
  * asynchronous on `stream`, nothing allocated.)
+ * `out` may lie over k_new and v_new: rows are then read before answers are written over
+ * them.  On a ring store that takes the prompt in several chunks this needs a copy of the
+ * rows, in the last 2 * batch * count * num_kv_heads * head_dim elements of the workspace
+ * (two launches more); without room for it beside the partials such a call is
+ * TEMPO_ERR_WORKSPACE, unless no answer stands over a later chunk's rows.
  *   q, out        device, [batch][count][num_q_heads][head_dim]
  *   k_new, v_new  device, [batch][count][num_kv_heads][head_dim]
  *   count_per_seq device, int32 [batch], or NULL: sequence b has only count_per_seq[b]

@@ -1120,6 +1120,20 @@ bool rows_apart(const tempo_kv* kv, const void* k_new, const void* v_new, const 
   return (o + out_bytes <= k || k + row_bytes <= o) && (o + out_bytes <= v || v + row_bytes <= o);
 }
 
+// Do answers of steps before the call's step c lie over rows (its k_new or v_new) of steps from c on?
+bool answers_over_later_rows(const tempo_kv* kv, const void* rows, const void* out, int32_t batch, int32_t Hq,
+                             int32_t count, int32_t c) {
+  const int64_t step_bytes = (int64_t)kv->head_dim * (kv->dtype == TEMPO_BF16 ? 2 : 4);
+  const int64_t row = step_bytes * kv->num_kv_heads, answer = step_bytes * Hq;
+  const int64_t apart = (int64_t)(reinterpret_cast<uintptr_t>(out) - reinterpret_cast<uintptr_t>(rows));
+  for (int32_t b = 0; b < batch; ++b) {
+    const int64_t from = apart + b * count * answer, to = from + c * answer;  // sequence b's answers, from the first row
+    const int64_t other = from > 0 ? from / (count * row) : 0;                // the first sequence whose rows end behind `from`
+    if (other < batch && (other * count + c) * row < to) return true;
+  }
+  return false;
+}
+
 // May it?  Not where `out` lies over the rows (which a write launch of its own has read before), nor where
 // 16-byte pieces of them are not aligned.
 bool rows_readable(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
@@ -1297,6 +1311,7 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   const bool ragged = false;  // every sequence starts at step t
   hipStream_t s = static_cast<hipStream_t>(stream);
   // validate every block before the first launch, so that an error leaves the store untouched
+  size_t need = 0;  // of the workspace, for the partials of any block
   for (int32_t c0 = 0; c0 < count; c0 += block) {
     const int32_t C = count - c0 < block ? count - c0 : block;
     tempo_plan plan;
@@ -1304,12 +1319,45 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     if ((rc = check_attn(kv, batch, Hq, t + c0, window, ragged, &plan, workspace, workspace_bytes, C)) != TEMPO_OK)
       return rc;
     if (kv->ring_blocks && (int64_t)C > (int64_t)kv->ring_blocks * kv->block_size) return TEMPO_ERR_RANGE;
+    const size_t partials = plan_bytes(kv, (int64_t)batch * C * Hq, plan.num_splits);
+    need = partials > need ? partials : need;
   }
 
+  const bool one_launch = prompt_in_one_launch(kv, batch, Hq, count);
   // per-sequence prompt lengths exist in the prompt kernel only; the rotary producer is refused where that could not take the prompt
-  if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !prompt_in_one_launch(kv, batch, Hq, count)))
+  if ((count_per_seq || rope) && (kv->dtype != TEMPO_BF16 || kv->ring_blocks != 0 || !one_launch))
     return TEMPO_ERR_SHAPE;
   if (rope && (rc = check_rope(rope, kv->head_dim, t + count - 1)) != TEMPO_OK) return rc;
+  // A ring store keeps little more than its window, so it can't be written ahead of the answers.  Where the prompt
+  // takes several chunks and answers stand over rows that are still to be read (by a later chunk; if it is staged, by the
+  // last write), the call reads a copy of the rows, at the workspace's end.
+  bool may_stage = true;
+  if (kv->ring_blocks && !rows_apart(kv, k_new, v_new, out, batch, Hq, count)) {
+    bool chunks = false, over = false;
+    for (int32_t c = 0;;) {
+      c += one_launch ? ring_chunk(kv, t + c, count - c, window, block) : (count - c < block ? count - c : block);
+      if (c >= count) break;
+      chunks = true;
+      over = over || answers_over_later_rows(kv, k_new, out, batch, Hq, count, c) ||
+             answers_over_later_rows(kv, v_new, out, batch, Hq, count, c);
+    }
+    if (chunks && (over || kv->dtype == TEMPO_BF16)) {  // (fp32 is not staged)
+      const size_t bytes = (size_t)batch * count * kv->num_kv_heads * kv->head_dim * esz;
+      if (workspace_bytes >= 2 * bytes && ((workspace_bytes - 2 * bytes) & ~(size_t)255) >= need) {
+        workspace_bytes = (workspace_bytes - 2 * bytes) & ~(size_t)255;
+        char* const copy = static_cast<char*>(workspace) + workspace_bytes;
+        const int workgroups = bytes < ((size_t)64 << 20) ? (int)((bytes + 16383) / 16384) : 4096;
+        if ((rc = launch_status(launch_stream_copy(k_new, copy, bytes, workgroups, s), "rows_copy")) != TEMPO_OK) return rc;
+        if ((rc = launch_status(launch_stream_copy(v_new, copy + bytes, bytes, workgroups, s), "rows_copy")) != TEMPO_OK) return rc;
+        k_new = copy;
+        v_new = copy + bytes;
+      } else if (over) {
+        return TEMPO_ERR_WORKSPACE;
+      } else {
+        may_stage = false;  // every chunk's answers stand clear of later rows
+      }
+    }
+  }
   const bool one_f32_block = kv->dtype == TEMPO_F32 && count <= block;  // (goes by blocks, which know the way by rows too)
   if (!rope && !one_f32_block && prompt_from_rows(kv, k_new, v_new, out, batch, Hq, t, count, window)) {
     const int64_t slots = kv->ring_blocks ? (int64_t)kv->ring_blocks * kv->block_size : count;
@@ -1317,15 +1365,15 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
     return attend_prompt(kv, q, out, batch, Hq, t, count, count, count_per_seq, window, scale, workspace, workspace_bytes, s,
                          nullptr, nullptr, &rows);
   }
-  // (a ring that several blocks go through can't be written ahead of them: not where `out` lies over the rows)
+  // (several blocks on a ring, answers over rows: the chunks looked at above, not the blocks)
   const bool blocks_stand = !kv->ring_blocks || count <= block || rows_apart(kv, k_new, v_new, out, batch, Hq, count);
   if (!count_per_seq && blocks_stand && prompt_by_blocks(kv, batch, Hq, t, count, window))
     return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s, rope);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
-  if (prompt_in_one_launch(kv, batch, Hq, count)) {
+  if (one_launch) {
     for (int32_t c0 = 0; c0 < count;) {
       const int32_t C = ring_chunk(kv, t + c0, count - c0, window, block);
-      const int32_t S = C < count - c0 ? staged_steps(kv, batch, t + c0, count - c0, workspace_bytes) : 0;
+      const int32_t S = may_stage && C < count - c0 ? staged_steps(kv, batch, t + c0, count - c0, workspace_bytes) : 0;
       if (S > C) {
         rc = prefill_staged(kv, q, k_new, v_new, out, batch, Hq, t, count, c0, S, window, scale, workspace, s);
         if (rc != TEMPO_OK) return rc;

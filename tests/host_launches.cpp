@@ -40,14 +40,15 @@ const char* host_launches_take() {
 
 namespace tempo {
 static hipError_t attend(const char* what, const AttnParams& p, int grid_splits, int waves) {
-  return say("%s t=%d queries=%d window=%d tps_log2=%d num_splits=%d grid_splits=%d direct=%d waves=%d", what, p.t,
-             p.queries, p.window, p.tps_log2, p.num_splits, grid_splits, p.direct, waves);
+  return say("%s t=%d queries=%d window=%d tps_log2=%d num_splits=%d grid_splits=%d direct=%d waves=%d out=%zu steps=%d k=%zu v=%zu",
+             what, p.t, p.queries, p.window, p.tps_log2, p.num_splits, grid_splits, p.direct, waves, (size_t)p.out, p.io_steps,
+             (size_t)p.k_new, (size_t)p.v_new);
 }
-hipError_t launch_append(const StoreParams& p, const void*, const void*, int, int, hipStream_t) {
-  return say("append t=%d count=%d", p.t, p.count);
+hipError_t launch_append(const StoreParams& p, const void* k, const void* v, int, int, hipStream_t) {
+  return say("append t=%d count=%d steps=%d k=%zu v=%zu", p.t, p.count, p.src_steps, (size_t)k, (size_t)v);
 }
-hipError_t launch_stage(const StageParams& p, const void*, const void*, int, hipStream_t) {
-  return say("stage t=%d count=%d groups=%d", p.t, p.count, p.stage_groups);
+hipError_t launch_stage(const StageParams& p, const void* k, const void* v, int, hipStream_t) {
+  return say("stage t=%d count=%d groups=%d steps=%d k=%zu v=%zu", p.t, p.count, p.stage_groups, p.src_steps, (size_t)k, (size_t)v);
 }
 hipError_t launch_gather(const StoreParams&, void*, void*, int, int, int j0, int count, hipStream_t) {
   return say("gather t=%d count=%d", j0, count);
@@ -88,5 +89,7 @@ hipError_t launch_worklist_build(const int32_t*, int, int t_max, int, int, int, 
 hipError_t launch_discounted_sum(const float*, float*, int, int T, int, float, hipStream_t) { return say("discounted T=%d", T); }
 int discounted_sum_max_window() { return 1024; }
 hipError_t launch_stream_read(const void*, size_t, void*, int, hipStream_t) { return say("stream_read"); }
-hipError_t launch_stream_copy(const void*, void*, size_t, int, hipStream_t) { return say("stream_copy"); }
+hipError_t launch_stream_copy(const void* from, void* to, size_t bytes, int, hipStream_t) {
+  return say("stream_copy from=%zu to=%zu bytes=%zu", (size_t)from, (size_t)to, bytes);
+}
 }  // namespace tempo

@@ -16,7 +16,7 @@ from test_gpu_parity import DEV, assert_close, dev, host_inputs, np64, random_ta
 pytestmark = pytest.mark.gpu
 
 
-def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70, least_workspace=False):
+def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70, least_workspace=False, aligned=True):
     Hq, steps = Hkv * G, t + count
     q, K, V = host_inputs(seed, B, steps, Hq, Hkv, D, dtype)
     if ring:
@@ -37,6 +37,8 @@ def run_prompt(B, Hkv, G, D, Z, t, count, window, ring, dtype, seed=70, least_wo
     qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))[:, t:]), dtype)
     out = torch.empty_like(qd)
     k_new, v_new = Kd[:, t:].contiguous(), Vd[:, t:].contiguous()
+    if not aligned:                                      # to 16 bytes: not answered from the rows themselves
+        k_new, v_new = (torch.cat([x.new_zeros(4), x.reshape(-1)])[4:].view(x.shape) for x in (k_new, v_new))
     if least_workspace:                                  # what the blocks of 128 columns need, and no byte more
         block = 128 // G
         need = max(T.tempo_attn_plan_workspace_bytes(st.kv, B * min(block, count - c), Hq, T.tempo_attn_block_plan(
@@ -75,7 +77,7 @@ def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window, least_workspace):
     """With the workspace tempo_prefill_workspace_bytes asks for the prompt is staged there; with the
     least that is accepted, the first three in several staged pieces.  (The last three fit the ring as
     one chunk either way; several chunks: test_ring_prompts_in_chunks.)"""
-    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace)
+    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace, aligned=False)
 
 
 @pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 37), (64, 2, 1021, 20)])
@@ -110,29 +112,41 @@ def test_rope_prompt_by_blocks(D, G, t, count):
     test_rope_prompt_with_split_ranges(D, G, t, count)
 
 
-@pytest.mark.parametrize("Hkv,D,t,count,dtype", [(2, 64, 9000, 300, T.TEMPO_BF16), (2, 128, 9000, 140, T.TEMPO_BF16),
-                                                 (2, 64, 0, 300, T.TEMPO_BF16), (2, 64, 0, 300, T.TEMPO_F32)])
-def test_prompt_answered_over_its_rows(Hkv, D, t, count, dtype):
-    """out may be the memory of k_new or v_new (several blocks, and one launch): the same answers, and the same store."""
+@pytest.mark.parametrize("dtype,B,Hkv,G,D,t,count,window,ring", [
+    (T.TEMPO_BF16, 1, 1, 3, 64, 16000, 70, 0, False), (T.TEMPO_BF16, 1, 1, 8, 128, 32000, 42, 0, False),   # several blocks
+    (T.TEMPO_BF16, 2, 2, 3, 128, 0, 90, 0, False), (T.TEMPO_F32, 2, 2, 3, 64, 0, 90, 0, False),            # one launch
+    (T.TEMPO_BF16, 1, 2, 3, 128, 0, 900, 100, True), (T.TEMPO_BF16, 2, 2, 1, 64, 0, 700, 100, True),       # chunks of a ring
+    (T.TEMPO_BF16, 2, 1, 3, 64, 77, 500, 64, True), (T.TEMPO_F32, 2, 2, 3, 64, 0, 400, 50, True),
+    (T.TEMPO_F32, 2, 2, 1, 64, 100, 500, 50, True)])
+@pytest.mark.parametrize("where", ["k", "v", "k's second half", "before k"])
+def test_prompt_answered_over_its_rows(dtype, B, Hkv, G, D, t, count, window, ring, where):
+    """out may lie over k_new and v_new: the answers and the store of a call whose buffers are apart.  (By which
+    launches: test_host_launches.py.)"""
     torch.manual_seed(5)
-    ty = torch.bfloat16 if dtype == T.TEMPO_BF16 else torch.float32
-    q, k, v = (torch.randn(1, count, Hkv, D, device=DEV).to(ty) for _ in range(3))
-    K, V = (torch.randn(1, max(t, 1), Hkv, D, device=DEV).to(ty) for _ in range(2))
+    ty, n = (torch.bfloat16 if dtype == T.TEMPO_BF16 else torch.float32), B * count * Hkv * D
+    q = torch.randn(B, count, Hkv * G, D, device=DEV).to(ty)
+    k, v = (torch.randn(n, device=DEV).to(ty) for _ in range(2))
+    R = T.tempo_ring_blocks(window, 64, min(count, 128 // G)) if ring else 0
+    past = min(t, window) if ring else t
+    K, V = (torch.randn(B, past, Hkv, D, device=DEV).to(ty) for _ in range(2))
+    k_at = n * G                                         # in a buffer of k, v and `out` over them
+    v_at = k_at + n + 64
+    out_at = {"k": k_at, "v": v_at, "k's second half": k_at + n // 2 // 64 * 64, "before k": k_at - n // 3 // 64 * 64}[where]
     got = []
-    for over in (None, "k", "v"):
-        st = BlockStore(1, Hkv, Hkv, D, 64, t + count - 1, dtype, fill="nan")
+    for over in (False, True):
+        st = BlockStore(B, Hkv * G, Hkv, D, 64, t + count - 1, dtype, fill="nan", ring_blocks=R)
         if t:
-            st.append_block(K, V, 0, t)
-        kn, vn = k.clone(), v.clone()
-        out = {"k": kn, "v": vn}.get(over, torch.empty_like(q))
-        st.prefill_attend(q, kn, vn, out, t, count)
+            st.append_block(K, V, t - past, past)
+        room = torch.zeros(n * (2 * G + 3) + 64, dtype=ty, device=DEV)
+        room[k_at:k_at + n], room[v_at:v_at + n] = k, v
+        rows = [room[at:at + n].view(B, count, Hkv, D) for at in (k_at, v_at)]
+        out = room[out_at:out_at + n * G].view(B, count, Hkv * G, D) if over else torch.empty_like(q)
+        st.prefill_attend(q, *rows, out, t, count, window)
         got.append((out.float().cpu(), st.k_pool.cpu(), st.v_pool.cpu()))
-    scale = got[0][0].abs().max()
-    for out, kp, vp in got[1:]:
-        # another route may answer: weights rounded to bf16 against another reference, 2^-8 each way
-        assert (out - got[0][0]).abs().max() <= 2 ** -7 * scale
-        assert torch.equal(kp.nan_to_num(7), got[0][1].nan_to_num(7))
-        assert torch.equal(vp.nan_to_num(7), got[0][2].nan_to_num(7))
+    # another route may answer: weights rounded to bf16 against another reference, 2^-8 each way
+    assert (got[1][0] - got[0][0]).abs().max() <= 2 ** -7 * got[0][0].abs().max()
+    assert torch.equal(got[1][1].nan_to_num(7), got[0][1].nan_to_num(7))
+    assert torch.equal(got[1][2].nan_to_num(7), got[0][2].nan_to_num(7))
 
 
 @pytest.mark.parametrize("B,Hkv,G,D,Z,t,count,window,ring", [
@@ -381,7 +395,7 @@ def test_f32_blocks_where_the_kernel_changes(B, Hkv, G, D, t, count, window):
 def test_ring_prompts_in_chunks(B, Hkv, G, D, Z, t, count, window):
     """Shapes whose least workspace has no room to stage the prompt (test_host_launches.py checks that
     they take this path): each chunk written into the ring and answered from it."""
-    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=True)
+    run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=True, aligned=False)
 
 
 @pytest.mark.parametrize("B,Hkv,G,D,t,count,window", [

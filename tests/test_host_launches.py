@@ -7,6 +7,7 @@ import re
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 from paper_2501_05408_amd import tempo as T
@@ -51,9 +52,9 @@ def taken(lib):
     return out
 
 
-def prefill(lib, kv, batch, Hq, t, count, window=0, workspace=1 << 50):
+def prefill(lib, kv, batch, Hq, t, count, window=0, workspace=1 << 50, rows=SOMEWHERE, out=SOMEWHERE):
     lib.host_launches_take()
-    args = (ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, batch, Hq, t, count, None)
+    args = (ctypes.byref(kv), SOMEWHERE, rows, rows, out, batch, Hq, t, count, None)
     if window:
         rc = lib.tempo_prefill_window(*args, window, 0.125, SOMEWHERE, workspace, None)
     else:
@@ -219,7 +220,8 @@ def test_ring_prompts_with_the_least_workspace(lib, shape):
     ring = T.tempo_ring_blocks(window, Z, min(count, 128 // G))
     kv = store(T.TEMPO_BF16, Hkv, D, Z, ring, ring)
     need = least_prompt_workspace(lib, kv, B, Hkv * G, t, count, window)
-    launches = prefill(lib, kv, B, Hkv * G, t, count, window, need)
+    # (rows that are not 16-byte aligned: else a prompt from step 0 on would be answered from them)
+    launches = prefill(lib, kv, B, Hkv * G, t, count, window, need, rows=SOMEWHERE + 8, out=1 << 45)
     assert_all_keys_launched(launches, G, t, count)
     names = [n for n, _ in launches]
     if shape in STAGED:
@@ -284,3 +286,75 @@ def test_prompts_that_are_read_from_the_callers_rows(lib, what, Hq, Hkv, D, batc
         if workspace == 1 << 50:
             assert [n for n, _ in launches] == names
         assert_all_keys_launched(launches, Hq // Hkv, t, count)
+
+
+def assert_rows_are_read_before_answers_stand_over_them(launches, base, size, Hq, Hkv, D, esz, batch):
+    """Plays the launches on the bytes base .. base+size-1: no launch may read a row that answers were written over."""
+    over = np.zeros(size, dtype=bool)
+
+    def spans(at, n, steps, heads):                      # n steps of each sequence, `steps` apart
+        for b in range(batch):
+            lo = at - base + b * steps * heads * D * esz
+            yield max(lo, 0), max(min(lo + n * heads * D * esz, size), 0)
+
+    for name, f in launches:
+        if name == "stream_copy":
+            lo = f["from"] - base
+            assert not over[max(lo, 0):max(lo + f["bytes"], 0)].any(), (name, f)
+            continue
+        n = f["count"] if "count" in f else f["queries"]
+        for rows in (f["k"], f["v"]):
+            for lo, hi in spans(rows, n, f["steps"], Hkv) if rows else ():
+                assert not over[lo:hi].any(), (name, f)
+        if f.get("direct") or "combine" in name:
+            for lo, hi in spans(f["out"], n, f["steps"], Hq):
+                over[lo:hi] = True
+            for rows in (f["k"], f["v"]):                # ... nor write answers over rows that it reads itself
+                for lo, hi in spans(rows, n, f["steps"], Hkv) if rows else ():
+                    assert not over[lo:hi].any(), (name, f)
+
+
+# (dtype, batch, Hkv, G, D, t, count, window, ring): prompts of one launch, of several blocks and of several chunks of a ring
+OVERLAPS = [(T.TEMPO_BF16, 1, 1, 3, 64, 16000, 70, 0, False), (T.TEMPO_BF16, 2, 1, 3, 128, 30000, 90, 0, False),
+            (T.TEMPO_BF16, 2, 2, 3, 128, 0, 90, 0, False), (T.TEMPO_F32, 2, 2, 3, 64, 0, 90, 0, False),
+            (T.TEMPO_BF16, 1, 2, 3, 128, 0, 900, 100, True), (T.TEMPO_BF16, 2, 2, 1, 64, 0, 700, 100, True),
+            (T.TEMPO_BF16, 2, 1, 3, 64, 77, 500, 64, True), (T.TEMPO_F32, 2, 2, 3, 64, 0, 400, 50, True),
+            (T.TEMPO_F32, 2, 2, 1, 64, 100, 500, 50, True), (T.TEMPO_F32, 1, 2, 4, 64, 5, 60, 20, True),
+            (T.TEMPO_F32, 1, 2, 16, 64, 5, 20, 20, True)]
+
+
+@pytest.mark.parametrize("dtype,batch,Hkv,G,D,t,count,window,ring", OVERLAPS)
+@pytest.mark.parametrize("where", ["k", "v", "k's second half", "k's end", "between"])
+def test_out_over_the_rows(lib, dtype, batch, Hkv, G, D, t, count, window, ring, where):
+    """With the workspace the library asks for, and with the least that is accepted."""
+    esz, Z = 2 if dtype == T.TEMPO_BF16 else 4, 64
+    row, base = batch * count * Hkv * D * esz, 1 << 33
+    R = T.tempo_ring_blocks(window, Z, min(count, 128 // G)) if ring else 0
+    kv = store(dtype, Hkv, D, Z, R or (t + count) // Z + 1, R)
+    k = base + row * G
+    v = k + row + 4096
+    out = {"k": k, "v": v, "k's second half": k + row // 2 // 256 * 256, "k's end": k + row - D * esz * Hkv,
+           "between": k - row // 3 // 256 * 256}[where]
+    most = T.tempo_prefill_workspace_bytes(kv, batch, Hkv * G, t + count - 1)
+    args = (ctypes.byref(kv), SOMEWHERE, k, v, out, batch, Hkv * G, t, count, None)
+    taken_at = []
+    for workspace in (most, least_prompt_workspace(lib, kv, batch, Hkv * G, t, count, window)):
+        lib.host_launches_take()
+        rc = (lib.tempo_prefill_window(*args, window, 0.125, SOMEWHERE, workspace, None) if window else
+              lib.tempo_prefill_causal(*args, 0.125, SOMEWHERE, workspace, None))
+        launches = taken(lib)
+        taken_at.append([n for n, _ in launches])
+        if rc != T.TEMPO_OK:                             # only without room for a copy, and before anything is launched
+            assert rc == T.TEMPO_ERR_WORKSPACE and workspace < most and ring and not launches
+            continue
+        assert_all_keys_launched(launches, G, t, count)
+        assert_rows_are_read_before_answers_stand_over_them(launches, base - row * G, row * (3 * G + 3) + 8192, Hkv * G, Hkv, D,
+                                                            esz, batch)
+        for name, f in launches:                         # a copy lies in the workspace, behind the partials
+            if name == "stream_copy":
+                assert SOMEWHERE + least_prompt_workspace(lib, kv, batch, Hkv * G, t, count, window) <= f["to"]
+                assert f["to"] + f["bytes"] <= SOMEWHERE + workspace and f["bytes"] == row
+    if t and not ring:                                   # several blocks: all written first, or each before its answers
+        blocks, apart = -(-count // (128 // G)), prefill(lib, kv, batch, Hkv * G, t, count, window, rows=k, out=1 << 45)
+        assert blocks > 1 and taken_at[0].count("append") == blocks and taken_at[0][:blocks] == ["append"] * blocks
+        assert [n for n, _ in apart] == ["append", "block_bf16", "combine"] * blocks
