@@ -28,7 +28,9 @@
  *    nothing, never synchronises, keeps no state between calls (one exception:
  *    tempo_decode_step_causal_noalloc, see there), and every launch is
  *    asynchronous on `stream`; calls may be captured in a HIP graph.
- *  - `out` must not alias q, the pools or the workspace.  (It may lie over k_new and v_new.)
+ *  - `out` must not alias q, the pools or the workspace, and in a single step that also writes
+ *    the store (tempo_decode_step_*, tempo_rope_decode_step_*) not k_new or v_new either, which
+ *    the same launch reads.  A prompt's may lie over them (tempo_prefill_*).
  *  - Results are deterministic: same inputs and same arguments, same bits.
  *  - Every entry point validates its arguments on the host and returns a
  *    negative tempo_status before launching anything if they are bad.  Block
