@@ -446,9 +446,9 @@ int do_combine(const tempo_kv* kv, void* out, int32_t batch, int32_t Hq, int32_t
 // the mean, 16% at most).  One workgroup of 8 wavefronts per compute unit: about 3.4 us before its first group and
 // after its last one (at D = 64 three quarters of it), then its share of the stream or, if that takes longer, its
 // wavefronts' arithmetic, 1 us a group and tile of 32 columns; the combine reads and writes a partial per
-// column and split.
+// column and split.  max_splits: no more than this.
 void make_stream_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t window, bool ragged,
-                      int32_t queries, tempo_plan* plan) {
+                      int32_t queries, int64_t max_splits, tempo_plan* plan) {
   constexpr double kFixedNs = 3400.0, kGroupNs = 1000.0, kFewNs = 5000.0, kManyNs = 8000.0, kPartialBytesPerNs = 4800.0;
   const int D = kv->head_dim, columns = queries * (Hq / kv->num_kv_heads);
   const int tiles = columns <= 32 ? 1 : columns <= 64 ? 2 : 4;
@@ -466,14 +466,14 @@ void make_stream_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, 
     const double stream = (double)per_split * D * 4 / rate, work = (double)((per_split + 255) / 256) * kGroupNs * tiles * wide;
     costs[k] = (double)rounds * (kFixedNs * (D == 128 ? 1.0 : 0.75) + (stream > work ? stream : work));
     if (splits > 1) costs[k] += (splits > 8 ? kManyNs : kFewNs) + 2.0 * batch * queries * Hq * (double)splits * D * 4 / kPartialBytesPerNs;
-    if (splits <= kMaxSplits && (best < 0.0 || costs[k] < best)) best = costs[k];
+    if (splits <= max_splits && (best < 0.0 || costs[k] < best)) best = costs[k];
     last = k;
     if (splits == 1) break;
   }
   int chosen = last;
-  while (splits_bound(t_eff, w_eff, chosen) > kMaxSplits) ++chosen;
+  while (splits_bound(t_eff, w_eff, chosen) > max_splits) ++chosen;
   for (int k = 7; k <= last; ++k) {  // the longest within 2% of the best
-    if (splits_bound(t_eff, w_eff, k) <= kMaxSplits && costs[k] <= best * 1.02) chosen = k;
+    if (splits_bound(t_eff, w_eff, k) <= max_splits && costs[k] <= best * 1.02) chosen = k;
   }
   plan->tokens_per_split = 1 << chosen;
   plan->num_splits = splits_bound(t_eff, w_eff, chosen);
@@ -489,7 +489,7 @@ void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, i
   if (kv->dtype != TEMPO_BF16) return;
   const int columns = queries * (Hq / kv->num_kv_heads);
   if (columns > kNarrowColumns && block_streams(kv->head_dim, columns, (int64_t)batch * kv->num_kv_heads, block_keys(t, queries, window))) {
-    make_stream_plan(kv, batch, Hq, t, window, ragged, queries, plan);
+    make_stream_plan(kv, batch, Hq, t, window, ragged, queries, max_splits, plan);
     return;
   }
   if (columns > kNarrowColumns) {
@@ -801,15 +801,16 @@ int tempo_decode_step_causal_noalloc(const tempo_kv* kv, const void* q, const vo
   if ((rc = check_heads(kv, batch, num_q_heads)) != TEMPO_OK) return rc;
   if (t < 0 || t > INT32_MAX - 64) return TEMPO_ERR_RANGE;
   // the partials of this call's own plan must fit the static array
-  // (fp32 shares a key/value read among a group's query heads, so it wants more splits than fit there
-  // for many heads and long ranges: then the best plan that fits)
   const int64_t rows = (int64_t)batch * num_q_heads;
   int64_t max_splits = kMaxSplits;
-  if (kv->dtype == TEMPO_F32) {
-    while (max_splits > 1 && plan_bytes(kv, rows, (int32_t)max_splits) > kScratchBytes) --max_splits;
-  }
   tempo_plan plan;
   make_block_plan(kv, batch, num_q_heads, t, 0, t_per_seq != nullptr, 1, &plan, max_splits);
+  // (fp32, and the stream kernel for bf16 groups of more than 16 heads, want more splits than fit there
+  // for many heads and long ranges: then the best plan that fits)
+  if (plan_bytes(kv, rows, plan.num_splits) > kScratchBytes && (kv->dtype == TEMPO_F32 || num_q_heads / kv->num_kv_heads > kNarrowColumns)) {
+    while (max_splits > 1 && plan_bytes(kv, rows, (int32_t)max_splits) > kScratchBytes) --max_splits;
+    make_block_plan(kv, batch, num_q_heads, t, 0, t_per_seq != nullptr, 1, &plan, max_splits);
+  }
   const size_t need = plan_bytes(kv, rows, plan.num_splits);
   if (need > kScratchBytes) {
     fprintf(stderr, "libtempo: tempo_decode_step_causal_noalloc: this step needs %zu bytes of split partials, "

@@ -106,6 +106,24 @@ def test_no_alloc_f32_step_takes_a_plan_that_fits_the_array(lib, Hq, Hkv, D, bat
     assert [n for n, _ in rest] == (["combine"] if f["num_splits"] > 1 else [])
 
 
+@pytest.mark.parametrize("G,Hkv,D,batch,t,ragged", [(17, 8, 64, 33, 16383, False), (33, 1, 64, 128, 40000, False),
+                                                    (24, 4, 64, 17, 65535, False), (40, 8, 128, 20, 30000, True), (64, 8, 128, 3, 5000, False)])
+def test_no_alloc_bf16_step_of_a_wide_group_takes_a_plan_that_fits_the_array(lib, G, Hkv, D, batch, t, ragged):
+    """And the plan of the call with a workspace, if that one fits."""
+    kv, plan, Hq = store(T.TEMPO_BF16, Hkv, D, 64, t // 64 + 1), T.tempo_plan(), G * Hkv
+    lib.host_launches_take()
+    rc = lib.tempo_decode_step_causal_noalloc(ctypes.byref(kv), SOMEWHERE, SOMEWHERE, SOMEWHERE, SOMEWHERE, batch, Hq, t,
+                                              SOMEWHERE if ragged else None, 0.125, None)
+    assert rc == T.TEMPO_OK
+    _, (name, f), *rest = taken(lib)
+    assert name == "block_bf16" and f["num_splits"] * batch * Hq * (D + 2) * 4 <= 8 << 20
+    assert f["grid_splits"] >= (t >> f["tps_log2"]) + 1
+    assert [n for n, _ in rest] == (["combine"] if f["num_splits"] > 1 else [])
+    assert lib.tempo_attn_plan(ctypes.byref(kv), batch, Hq, t, 0, ragged, ctypes.byref(plan)) == T.TEMPO_OK
+    fits = plan.num_splits * batch * Hq * (D + 2) * 4 <= 8 << 20
+    assert (plan.num_splits == f["num_splits"]) == fits and fits == (batch == 3)
+
+
 def test_no_alloc_bf16_step_that_does_not_fit_stays_refused(lib, capfd):
     kv = store(T.TEMPO_BF16, 8, 128, 256, 32)
     lib.host_launches_take()
