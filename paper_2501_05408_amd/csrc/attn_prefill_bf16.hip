@@ -93,6 +93,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   const unsigned block_first = (unsigned)c0 * (unsigned)p.G + (unsigned)work.skip, group_columns = 32u * (unsigned)p.G;
   const int write_first = kFrom != kRows ? 0 : (int)((block_first + group_columns - 1) / group_columns);
   const int write_past = kFrom != kRows ? 0 : (int)((block_first + (unsigned)ncols + group_columns - 1) / group_columns);
+  // ... the last one, if the call goes on in it behind the block's last step, from a copy of its own
+  const bool write_tail = kFrom == kRows && cut_tail(work) && t_last + 1 < work.all_steps && g_last >= write_first && g_last < write_past;
+  const int write_loop = write_tail ? g_last : write_past;
   uint32_t tile_lo, tile_hi;
   auto fetch_entry = [&]() {
     if (kFrom == kRows) {                           // of group write_first + lane (at most 9 groups)
@@ -176,19 +179,25 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
                                           : static_cast<const char*>(p.v_stage) + (u - KU) * 1024);
   }
   const uint32_t lane_bytes = 16u * (uint32_t)lane;
-  auto issue = [&](int at, int g) {                 // `at`: the buffer's offset in LDS, in 16-byte pieces
+  // kRows: rows outside the block's range read as zeros, as the pools' way masks them (a value that is not finite would
+  // show through its weight of 0): those behind the block's last step lie beyond the buffer, `hidden` ones are
+  // asked for there.  The copies beyond the range's last group hold all of that group's rows, to be written.
+  auto bytes_of = [&](int count) { return (uint32_t)((count < 32 ? count : 32) - 1) * row_stride + kRowBytes; };
+  const uint32_t last_bytes = bytes_of(t_last + 1 - 32 * g_last), tail_bytes = bytes_of(work.all_steps - 32 * g_last);
+  // `at`: the buffer's offset in LDS, in 16-byte pieces; `hidden` (kRows): first rows whose values read as zeros
+  auto issue = [&](int at, int g, int hidden = 0) {
     const int gc = g < g_last ? g : g_last;
     if (kFrom == kRows) {
-      // rows beyond the sequence's last step are beyond the buffer: zeros
-      const int left = work.all_steps - 32 * gc;
-      const uint32_t bytes = (uint32_t)((left < 32 ? left : 32) - 1) * row_stride + kRowBytes;
+      const uint32_t bytes = g < g_last ? bytes_of(32) : g == g_last ? last_bytes : tail_bytes;
       const uint64_t from = (((uint64_t)b * (uint32_t)p.io_steps + 32u * (uint32_t)gc) * (uint32_t)p.Hkv + (uint32_t)hkv) * kRowBytes;
       char* const rows[2] = {const_cast<char*>(static_cast<const char*>(p.k_new)) + from,
                              const_cast<char*>(static_cast<const char*>(p.v_new)) + from};
 #pragma unroll
       for (int i = 0; i < PER_WAVE; ++i) {
         const auto group = __builtin_amdgcn_make_buffer_rsrc(rows[i / (PER_WAVE / 2)], 0, (int)bytes, 0x00020000);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(group, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, (int)row_piece[i], 0, 0, 0);
+        uint32_t piece = row_piece[i];
+        if (i >= PER_WAVE / 2 && hidden > 0 && (wave + NW * i - KU) * kUnitRows + lane / kPieces < hidden) piece = 0x7FFFFF00u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(group, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, (int)piece, 0, 0, 0);
       }
       return;
     }
@@ -217,7 +226,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(unit, (lds_ptr)(lds + at + (wave + NW * i) * 64), 16, lane_bytes, 0, 0, 0);
     }
   };
-  // (kRows: every row of the call is written, and what lies beyond reads as zeros)
   const bool head = kFrom != kRows && cut_head(work), tail = kFrom != kRows && cut_tail(work);
   auto mask_values = [&](int g, int at) {  // the buffer of group g: the first, and head, or the last, and tail
     uint32_t keep[4];
@@ -334,7 +342,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
   // logits are computed one group ahead) and, with early operand reads, one more are in LDS.
   constexpr int kAhead = 2 * kPair;            // of grp, which may be the second of a pair
   auto finish = [&]() {
-    if (kFrom == kRows && grp >= write_first && grp < write_past) write_group(grp, at0);
+    if (kFrom == kRows && grp >= write_first && grp < write_loop) write_group(grp, at0);
     if (kPair == 1 || ((grp - g_first) & 1)) {
       landed();
       if (tail && g_last <= grp + kAhead && g_last > grp + kAhead - kPair) mask_values(g_last, next(g_last - grp));
@@ -344,8 +352,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
     ++grp;
   };
 
+  // (a first group that its range cuts is an earlier block's to write)
 #pragma unroll
-  for (int i = 0; i < NBUF - kPair; ++i) issue(i * kBuf, g_first + i);
+  for (int i = 0; i < NBUF - kPair; ++i) issue(i * kBuf, g_first + i, kFrom == kRows && i == 0 ? start & 31 : 0);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int s = 0; s < KT; ++s) {
@@ -469,6 +478,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_prefill_bf16(PromptParams p) 
         p.ws_ml[part * 2 + 1] = l_j;
       }
     }
+  }
+  if (write_tail) {                            // uniform over the workgroup
+    meet();
+    write_group(g_last, at0);                  // (the first copy beyond the last group's)
   }
 }
 

@@ -494,3 +494,35 @@ def test_steps_around_the_ranges_whose_last_group_stands_apart(B, Hkv, G, D, fir
             qt = st.rope_rotate(qt, torch.empty_like(qt), first + i)
         ref = oracle.attend(np64(qt), K64, V64, first + i, window, 1.0 / np.sqrt(D))
         assert_close(got[i], ref, dtype, f"step {first + i} w={window} rope={rope}")
+
+
+# (Hkv, G, D, count, window, j): the value of step j is infinite; and the steps that see it or share a block of columns
+# with one that does.  Blocks have 128 columns here, or (few columns) 64.
+@pytest.mark.parametrize("Hkv,G,D,count,window,j,touched", [
+    (8, 3, 128, 700, 0, 50, range(42, 700)), (8, 3, 64, 700, 0, 50, range(42, 700)),       # later than the block's last step
+    (2, 8, 64, 100, 0, 17, range(16, 100)), (8, 4, 128, 700, 40, 10, range(0, 64)),        # earlier than its first key
+    (8, 3, 128, 700, 5, 35, range(0, 43)), (1, 16, 64, 200, 3, 4, range(0, 8)),            # in a group that it writes
+    (8, 3, 64, 700, 1, 36, range(0, 43)), (1, 1, 128, 130, 2, 126, range(64, 128))])
+@pytest.mark.parametrize("aligned", [True, False])
+def test_values_that_are_not_finite_stay_in_the_blocks_that_see_them(Hkv, G, D, count, window, j, touched, aligned):
+    """Read from the call's rows as through the store: the same store, and nothing of such a value in other blocks."""
+    B, Hq, dtype = 2, Hkv * G, T.TEMPO_BF16
+    q, K, V = host_inputs(94, B, count, Hq, Hkv, D, dtype)
+    qd = dev(np.ascontiguousarray(np.transpose(q, (1, 0, 2, 3))), dtype)
+    got = []
+    for bad in (False, True):
+        rows = [dev(K, dtype), dev(V, dtype)]
+        if bad:
+            rows[1][:, j] = float("inf")
+        if not aligned:
+            rows = [torch.cat([x.new_zeros(4), x.reshape(-1)])[4:].view(x.shape) for x in rows]
+        st = BlockStore(B, Hq, Hkv, D, 32, count - 1, dtype, fill="nan")
+        out = torch.empty_like(qd)
+        st.prefill_attend(qd, rows[0], rows[1], out, 0, count, window)
+        kg, vg = st.gather(0, count)
+        assert torch.equal(kg, rows[0]) and torch.equal(vg, rows[1])
+        got.append(out)
+    for c in range(count):
+        sees = c >= j and (window == 0 or c - j < window)
+        assert not sees or not torch.isfinite(got[1][:, c]).any(), c
+        assert c in touched or torch.equal(got[1][:, c], got[0][:, c]), c
