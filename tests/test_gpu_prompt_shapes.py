@@ -80,7 +80,7 @@ def test_ring_prompt_shapes(B, Hkv, G, D, Z, t, count, window, least_workspace):
     run_prompt(B, Hkv, G, D, Z, t, count, window, True, T.TEMPO_BF16, least_workspace=least_workspace, aligned=False)
 
 
-@pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 37), (64, 2, 1021, 20)])
+@pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 37), (64, 2, 1021, 20), (128, 3, 1500, 5), (64, 3, 9000, 70)])
 def test_rope_prompt_with_split_ranges(D, G, t, count):
     """Few unrotated columns behind a long history: the bits of rotating first."""
     B, Hkv, Z, dtype = 1, 2, 32, T.TEMPO_BF16
@@ -105,10 +105,14 @@ def test_rope_prompt_with_split_ranges(D, G, t, count):
     assert torch.equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("D,G,t,count", [(128, 3, 1500, 1), (128, 3, 1500, 5), (128, 4, 3000, 8), (64, 4, 3000, 12),
-                                         (64, 3, 9000, 70), (128, 20, 4000, 3)])
+ROPE_BY_BLOCKS = [(128, 3, 1500, 1), (128, 3, 3000, 5), (128, 4, 3000, 8), (64, 4, 3000, 12), (64, 3, 16000, 70),
+                  (128, 3, 16000, 60), (128, 20, 4000, 3)]
+
+
+@pytest.mark.parametrize("D,G,t,count", ROPE_BY_BLOCKS)
 def test_rope_prompt_by_blocks(D, G, t, count):
-    """Those that go in blocks of columns: each size of kernel, two blocks, and groups wider than the single-step kernel."""
+    """Those that go in blocks of columns (test_host_launches.py looks that they do): each size of kernel, two blocks, and
+    groups wider than the single-step kernel."""
     test_rope_prompt_with_split_ranges(D, G, t, count)
 
 

@@ -12,6 +12,8 @@ import pytest
 
 from paper_2501_05408_amd import tempo as T
 
+from test_gpu_prompt_shapes import ROPE_BY_BLOCKS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOMEWHERE = 1 << 20                       # pointers that are checked for NULL and alignment, never read
 
@@ -376,3 +378,15 @@ def test_out_over_the_rows(lib, dtype, batch, Hkv, G, D, t, count, window, ring,
         blocks, apart = -(-count // (128 // G)), prefill(lib, kv, batch, Hkv * G, t, count, window, rows=k, out=1 << 45)
         assert blocks > 1 and taken_at[0].count("append") == blocks and taken_at[0][:blocks] == ["append"] * blocks
         assert [n for n, _ in apart] == ["append", "block_bf16", "combine"] * blocks
+
+
+@pytest.mark.parametrize("D,G,t,count", ROPE_BY_BLOCKS)
+def test_rope_prompts_by_blocks_go_by_blocks(lib, D, G, t, count):
+    """The shapes that test_gpu_prompt_shapes.py answers on the GPU, two kv heads of one sequence."""
+    kv, rope = store(T.TEMPO_BF16, 2, D, 32, (t + count) // 32 + 1), T.tempo_rope(SOMEWHERE, SOMEWHERE, t + count, D)
+    lib.host_launches_take()
+    assert lib.tempo_rope_prefill_causal(ctypes.byref(kv), ctypes.byref(rope), SOMEWHERE, SOMEWHERE, SOMEWHERE, 1 << 45, 1, 2 * G,
+                                         t, count, None, 0.125, SOMEWHERE, 1 << 50, None) == T.TEMPO_OK
+    launches, blocks = taken(lib), -(-count // (128 // G))
+    assert [n for n, _ in launches] == ["append", "block_bf16" if G * count > 16 else "partial_bf16", "combine"] * blocks
+    assert_all_keys_launched(launches, G, t, count)
