@@ -39,9 +39,11 @@ const char* host_launches_take() {
 }
 
 namespace tempo {
-static hipError_t attend(const char* what, const AttnParams& p, int grid_splits, int waves) {
-  return say("%s t=%d queries=%d window=%d tps_log2=%d num_splits=%d grid_splits=%d direct=%d waves=%d out=%zu steps=%d k=%zu v=%zu",
-             what, p.t, p.queries, p.window, p.tps_log2, p.num_splits, grid_splits, p.direct, waves, (size_t)p.out, p.io_steps,
+// stream: does a wide block go to the kernel that streams its keys?  k, v: of a prompt that is read from its rows.
+static hipError_t attend(const char* what, const AttnParams& p, int grid_splits, int waves, bool stream = false) {
+  return say("%s t=%d queries=%d window=%d tps_log2=%d num_splits=%d grid_splits=%d direct=%d waves=%d stream=%d out=%zu steps=%d "
+             "k=%zu v=%zu",
+             what, p.t, p.queries, p.window, p.tps_log2, p.num_splits, grid_splits, p.direct, waves, stream, (size_t)p.out, p.io_steps,
              (size_t)p.k_new, (size_t)p.v_new);
 }
 hipError_t launch_append(const StoreParams& p, const void* k, const void* v, int, int, hipStream_t) {
@@ -59,14 +61,14 @@ hipError_t launch_partial_bf16(const AttnParams& p, int, int, int grid_splits, i
 size_t partial_bf16_lds_bytes(int waves, int columns, int D) {  // as next to the kernel
   return (size_t)waves * (32 + (size_t)columns * D) * sizeof(float) + (size_t)4 * D;
 }
-int prefill_bf16_block_steps(int G, int waves) { return 32 * waves / G; }
 hipError_t launch_prefill_bf16(const PromptParams& p, int, int, int waves, int grid_splits, hipStream_t) {
   return attend(p.k_stage ? "prompt_staged" : "prompt", p, grid_splits, waves);
 }
 hipError_t launch_prompt_combine(const PromptParams& p, int, int, hipStream_t) { return attend("prompt_combine", p, 0, 0); }
 hipError_t launch_short_prompt_bf16(const AttnParams& p, int, int, hipStream_t) { return attend("short_prompt", p, 1, 0); }
-hipError_t launch_block_bf16(const AttnParams& p, int, int, int grid_splits, hipStream_t) {
-  return attend("block_bf16", p, grid_splits, 0);
+hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t) {
+  const bool stream = block_streams(D, p.queries * p.G, (int64_t)batch * p.Hkv, block_keys(p.t, p.queries, p.window));
+  return attend("block_bf16", p, grid_splits, 0, stream);
 }
 hipError_t launch_partial_f32(const AttnParams& p, int, int, int grid_splits, int waves, hipStream_t) {
   return attend("partial_f32", p, grid_splits, waves);

@@ -73,11 +73,11 @@ def assert_all_keys_launched(launches, G, t, count):
         if name not in ("prompt", "prompt_staged", "short_prompt", "block_bf16", "partial_bf16", "partial_f32", "step_f32"):
             continue
         assert f["t"] == step
-        together = {"prompt": 32 * f["waves"] // G, "prompt_staged": 32 * f["waves"] // G,
-                    "short_prompt": 128 // G}.get(name, f["queries"])
-        for c in range(0, f["queries"], together):
-            last = step + min(c + together, f["queries"]) - 1
-            first = max(0, step + c - f["window"] + 1) if f["window"] else 0
+        # the (step, head) columns that share a workgroup: a block may begin and end between the heads of a step
+        columns = {"prompt": 32 * f["waves"], "prompt_staged": 32 * f["waves"], "short_prompt": 128}.get(name, f["queries"] * G)
+        for k in range(0, f["queries"] * G, columns):
+            lo, last = step + k // G, step + (min(k + columns, f["queries"] * G) - 1) // G
+            first = max(0, lo - f["window"] + 1) if f["window"] else 0
             assert (last >> f["tps_log2"]) - (first >> f["tps_log2"]) + 1 <= f["grid_splits"], (name, f, first, last)
         step += f["queries"]
     assert step == t + count
@@ -267,10 +267,7 @@ def test_splits_reach_over_blocks_that_begin_between_the_heads_of_a_step(lib, Hq
     launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, 100), batch, Hq, t, count, window)
     (_, f), = [l for l in launches if l[0] == "prompt"]
     assert f["grid_splits"] > 1
-    for k in range(0, count * G, 32 * f["waves"]):
-        first, last = t + k // G, t + (min(k + 32 * f["waves"], count * G) - 1) // G
-        lo = max(0, first - window + 1) if window else 0
-        assert (last >> f["tps_log2"]) - (lo >> f["tps_log2"]) + 1 <= f["grid_splits"]
+    assert_all_keys_launched(launches, G, t, count)
 
 
 @pytest.mark.parametrize("what,Hq,Hkv,D,batch,t,count,window,ring,apart,names", [
@@ -305,6 +302,7 @@ def test_prompts_that_are_read_from_the_callers_rows(lib, what, Hq, Hkv, D, batc
         assert [n for n, _ in launches if n != "prompt_combine"] == [n for n in names if n != "prompt_combine"]
         if workspace == 1 << 50:
             assert [n for n, _ in launches] == names
+        assert launches[0][1]["k"] == k and all(f["k"] == 0 for _, f in launches[1:])   # the write's, or the attention's, rows
         assert_all_keys_launched(launches, Hq // Hkv, t, count)
 
 
@@ -390,3 +388,21 @@ def test_rope_prompts_by_blocks_go_by_blocks(lib, D, G, t, count):
     launches, blocks = taken(lib), -(-count // (128 // G))
     assert [n for n, _ in launches] == ["append", "block_bf16" if G * count > 16 else "partial_bf16", "combine"] * blocks
     assert_all_keys_launched(launches, G, t, count)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,batch,t,queries,window,stream", [
+    (24, 8, 128, 1, 10, 6, 0, 1), (32, 1, 128, 1, 5, 1, 0, 1), (33, 1, 128, 1, 191, 1, 0, 0), (33, 1, 128, 1, 192, 1, 0, 1),
+    (33, 1, 128, 1, 5000, 1, 192, 0), (24, 8, 128, 16, 4075, 21, 0, 1), (64, 1, 128, 1, 500, 1, 0, 1), (65, 1, 128, 1, 60000, 1, 0, 0),
+    (24, 8, 128, 16, 4075, 42, 0, 0), (64, 1, 64, 1, 10, 1, 0, 1), (65, 1, 64, 1, 65534, 1, 0, 0), (65, 1, 64, 1, 65535, 1, 0, 1),
+    (65, 8, 64, 2, 4095, 16, 100, 0)])
+def test_kernel_of_a_wide_block(lib, Hq, Hkv, D, batch, t, queries, window, stream):
+    Hq = Hq // Hkv * Hkv
+    kv = store(T.TEMPO_BF16, Hkv, D, 64, (t + queries) // 64 + 1)
+    lib.host_launches_take()
+    args = (ctypes.byref(kv), SOMEWHERE, 1 << 45, batch, Hq, queries, t, None)
+    rc = (lib.tempo_attn_block_window(*args, window, 0.125, SOMEWHERE, 1 << 50, None) if window else
+          lib.tempo_attn_block_causal(*args, 0.125, SOMEWHERE, 1 << 50, None))
+    assert rc == T.TEMPO_OK
+    launches = taken(lib)
+    assert launches[0][0] == "block_bf16" and launches[0][1]["stream"] == stream
+    assert_all_keys_launched(launches, Hq // Hkv, t, queries)
