@@ -84,8 +84,7 @@ __device__ inline void combine_heads(const float* ml, const float* acc, int S, i
       float4 A = {0.f, 0.f, 0.f, 0.f};
       for (int i = 0; i < R; ++i) {
         const float* slot = smem + (i * cols + col) * 6;
-        if (slot[1] == 0.f) continue;  // a lane that had no split, or none with a key of this row
-        const float w = exp2f(slot[0] - M);
+        const float w = exp2f(slot[0] - M);  // (a lane without a split, or without a key of this row: 0, and 0 of it)
         L = fmaf(w, slot[1], L);
         A.x = fmaf(w, slot[2], A.x); A.y = fmaf(w, slot[3], A.y);
         A.z = fmaf(w, slot[4], A.z); A.w = fmaf(w, slot[5], A.w);
