@@ -313,10 +313,9 @@ int tempo_decode_step_ragged(const tempo_kv* kv, const void* q, const void* k_ne
  *     returns for it) exceed 8 MiB is refused with TEMPO_ERR_WORKSPACE and a message on
  *     stderr; nothing is launched.  (The headline shape needs 0.4 MiB, a single sequence
  *     at t = 65535 3.2 MiB, a ragged batch of 64 at t <= 8191 6.4 MiB.)
- *     fp32, and bf16 groups of 17 to 64 query heads: such a step is planned with as many
- *     splits as fit instead (its sums are then taken in another order than
- *     tempo_decode_step_causal's), and refused if none do.  (bf16 groups of more than 64
- *     heads at head_dim 64: likewise, or refused as long as batch * num_kv_heads * (t + 1) < 65536.)
+ *     fp32, and bf16 groups of more than 16 query heads: such a step is planned with as
+ *     many splits as fit instead (its sums are then taken in another order than
+ *     tempo_decode_step_causal's), and refused if none do.
  *   - The device that `stream` belongs to must be the current device.  The first call on
  *     a device looks the array's address up (hipGetSymbolAddress) and keeps it: this is
  *     the one piece of state the library holds.  Make that first call outside stream

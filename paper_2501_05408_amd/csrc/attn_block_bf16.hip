@@ -1,8 +1,8 @@
 // Wide blocks, bf16, MFMA on gfx950: up to 128 columns of one or a few
 // query steps in front of a key range (chunked prompt processing, speculative decoding
 // with many steps, query groups of more than 16 heads).  Computes what the decode kernel
-// computes for each of those steps (Section 2, Eq. 1; Section 4.3 index masks).  Blocks of fewer columns
-// are the stream kernel's (attn_stream_bf16.hip; block_streams() in tempo_internal.h).
+// computes for each of those steps (Section 2, Eq. 1; Section 4.3 index masks).  Blocks of fewer
+// columns over longer ranges are the stream kernel's (attn_stream_bf16.hip; block_streams() in tempo_internal.h).
 //
 // Mapping.  The key range is cut into splits as in the decode kernel; one workgroup =
 // one (sequence, kv head, split), its columns are the block's (step, head) pairs, 16 per
@@ -11,8 +11,8 @@
 // the range).  The key/value image of a 32-slot group (16 KiB at D = 128) is the same for
 // all wavefronts: the workgroup copies it once from the pool into LDS (it is already in
 // MFMA operand order there, 1 KiB units) and every wavefront reads its operands from LDS.
-// Two key and two value buffers (32 KiB at D = 128, 16 at D = 64): at D = 128 three workgroups of 4
-// wavefronts or two of 8 (registers) fit a compute unit, and it is their number that
+// Two key and two value buffers (32 KiB at D = 128, 16 at D = 64): at D = 128 five workgroups of 2
+// wavefronts (LDS), three of 4 or two of 8 (registers) fit a compute unit, and it is their number that
 // hides the latency of the stream.  The prompt kernel (attn_prefill_bf16.hip: 32 columns per
 // wavefront, deeper buffers of 64 KiB) is the faster one for whole prompts and the slower one here:
 // 21 steps of 3 heads, 16 sequences, t = 4075: 60.3 us per call with this kernel, 62.6 us with that one (and 53
@@ -311,16 +311,12 @@ hipError_t launch_block_nw(const AttnParams& p, int batch, int D, int grid_split
     return stream_once ? launch((attn_block_bf16<128, NW, false, true>), grid, block, lds, stream, p)
                        : launch((attn_block_bf16<128, NW, false, false>), grid, block, lds, stream, p);
   }
-  if constexpr (NW == 4) {
-    return hipErrorInvalidConfiguration;  // the stream kernel's
-  } else {
-    if (p.rope_cos) {
-      return stream_once ? launch((attn_block_bf16<64, NW, true, true>), grid, block, lds, stream, p)
-                         : launch((attn_block_bf16<64, NW, true, false>), grid, block, lds, stream, p);
-    }
-    return stream_once ? launch((attn_block_bf16<64, NW, false, true>), grid, block, lds, stream, p)
-                       : launch((attn_block_bf16<64, NW, false, false>), grid, block, lds, stream, p);
+  if (p.rope_cos) {
+    return stream_once ? launch((attn_block_bf16<64, NW, true, true>), grid, block, lds, stream, p)
+                       : launch((attn_block_bf16<64, NW, true, false>), grid, block, lds, stream, p);
   }
+  return stream_once ? launch((attn_block_bf16<64, NW, false, true>), grid, block, lds, stream, p)
+                     : launch((attn_block_bf16<64, NW, false, false>), grid, block, lds, stream, p);
 }
 
 }  // namespace
@@ -338,13 +334,14 @@ hipError_t launch_short_prompt_bf16(const AttnParams& p, int batch, int D, hipSt
   return launch((attn_block_bf16<128, NW, false, false, true>), grid, dim3(64 * NW), lds, stream, p);
 }
 
-// A block of few columns gets a workgroup of just enough wavefronts (4 or 8), so that
+// A block of few columns gets a workgroup of just enough wavefronts (2, 4 or 8), so that
 // several workgroups share a compute unit and the kernel stays bound by HBM.
 hipError_t launch_block_bf16(const AttnParams& p, int batch, int D, int grid_splits, hipStream_t stream) {
   const int columns = p.queries * p.G;
   if (columns > 128) return hipErrorInvalidConfiguration;
   if (block_streams(D, columns, (int64_t)batch * p.Hkv, block_keys(p.t, p.queries, p.window)))
     return launch_stream_block_bf16(p, batch, D, grid_splits, stream);
+  if (columns <= 32) return launch_block_nw<2>(p, batch, D, grid_splits, stream);
   if (columns <= 64) return launch_block_nw<4>(p, batch, D, grid_splits, stream);
   return launch_block_nw<8>(p, batch, D, grid_splits, stream);
 }

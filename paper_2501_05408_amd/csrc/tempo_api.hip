@@ -496,20 +496,21 @@ void make_block_plan(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, i
     // The LDS-staged kernel: its workgroups do more arithmetic per key than the decode
     // kernel's, so two per compute unit are wanted (measured at batch 16 x 8 heads,
     // t = 4095: 4 splits of 1024 keys 59-68 us for 63-126 columns, 2 splits 82-83 us,
-    // 8 splits 68-81 us).
-    // Longest split length of at least 256 keys that gives >= 512 workgroups, else 256.
+    // 8 splits 68-81 us).  Up to 32 columns a workgroup has only two wavefronts: twice as many
+    // workgroups (measured there: 8 splits of 512 keys 52.8-53.8 us, 4 splits of 1024 keys 55.5-56.1 us).
+    // Longest split length of at least 256 keys that gives as many workgroups, else 256.
     const int32_t t_eff = last_step(t, queries), w_eff = union_window(window, queries);
     const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
-    const int64_t want = 2 * (int64_t)kComputeUnits;
+    const int64_t want = (columns <= 32 ? 4 : 2) * (int64_t)kComputeUnits;
     int k = 8;
     for (int cand = 30; cand >= 8; --cand) {
       if (pairs * splits_bound(t_eff, w_eff, cand) >= want) { k = cand; break; }
     }
-    while (splits_bound(t_eff, w_eff, k) > kMaxSplits) ++k;
-    if (ragged && k > 10 && splits_bound(t_eff, w_eff, 10) <= kMaxSplits) k = 10;  // as for single steps
+    while (splits_bound(t_eff, w_eff, k) > max_splits) ++k;
+    if (ragged && k > 10 && splits_bound(t_eff, w_eff, 10) <= max_splits) k = 10;  // as for single steps
     plan->tokens_per_split = 1 << k;
     plan->num_splits = splits_bound(t_eff, w_eff, k);
-    plan->waves = 8;  // ignored: the launch picks 4 or 8 wavefronts by the column count
+    plan->waves = 8;  // ignored: the launch picks 2, 4 or 8 wavefronts by the column count
     return;
   }
   while (plan->waves > 1 && partial_bf16_lds_bytes(plan->waves, columns, kv->head_dim) > kMaxLds) plan->waves /= 2;
@@ -805,7 +806,7 @@ int tempo_decode_step_causal_noalloc(const tempo_kv* kv, const void* q, const vo
   int64_t max_splits = kMaxSplits;
   tempo_plan plan;
   make_block_plan(kv, batch, num_q_heads, t, 0, t_per_seq != nullptr, 1, &plan, max_splits);
-  // (fp32, and the stream kernel for bf16 groups of more than 16 heads, want more splits than fit there
+  // (fp32, and the kernels for bf16 groups of more than 16 heads, want more splits than fit there
   // for many heads and long ranges: then the best plan that fits)
   if (plan_bytes(kv, rows, plan.num_splits) > kScratchBytes && (kv->dtype == TEMPO_F32 || num_q_heads / kv->num_kv_heads > kNarrowColumns)) {
     while (max_splits > 1 && plan_bytes(kv, rows, (int32_t)max_splits) > kScratchBytes) --max_splits;

@@ -392,6 +392,41 @@ def test_wide_blocks_where_the_kernel_and_its_tiles_change(G, C, D, B, steps, wi
     assert_close(np64(out), ref, T.TEMPO_BF16, f"{(G, C, D, B, steps, window, k, ragged)}")
 
 
+@pytest.mark.parametrize("D,G,C,B,steps,k", [
+    (64, 2, 16, 65, 192, 0), (64, 2, 16, 65, 193, 0), (64, 2, 16, 65, 150, 7), (64, 2, 9, 36, 40, 0), (64, 4, 16, 36, 256, 0),
+    (64, 4, 16, 36, 257, 0), (64, 3, 11, 65, 300, 6), (64, 4, 32, 36, 300, 0), (128, 3, 7, 40, 224, 0), (128, 3, 7, 40, 225, 0),
+    (128, 4, 8, 33, 100, 6), (128, 3, 21, 36, 256, 0), (128, 3, 21, 36, 257, 0), (128, 3, 11, 65, 400, 0)])
+def test_wide_blocks_of_many_pairs(D, G, C, B, steps, k):
+    """Of 8 kv heads: the lines between the two kernels for wide blocks where pairs are more than the compute units;
+    queries turned to their positions by the kernel and before the call give the same bits.  k as above."""
+    Hkv, Hq, Z, t0 = 8, 8 * G, 32, steps - C
+    q = synth.normal_as(59, 1, (B, C, Hq, D), "bf16")
+    K, V = synth.normal_as(59, 2, (B, steps, Hkv, D), "bf16"), synth.normal_as(59, 3, (B, steps, Hkv, D), "bf16")
+    table, nb = random_table(59, B, (steps - 1) // Z + 1)
+    st = BlockStore(B, Hq, Hkv, D, Z, steps - 1, T.TEMPO_BF16, num_blocks=nb, block_table=table, fill="nan")
+    st.append_block(dev(K, T.TEMPO_BF16), dev(V, T.TEMPO_BF16), 0, steps)
+    angle = torch.arange(steps, device=DEV)[:, None] * 0.7 ** torch.arange(D // 2, device=DEV)[None, :]
+    st.set_rope(torch.cos(angle).float(), torch.sin(angle).float())
+    plan = T.tempo_attn_block_plan(st.kv, B, Hq, C, t0, 0)
+    if k:
+        plan.tokens_per_split, plan.num_splits = 1 << k, ((steps - 1) >> k) + 1
+    nbytes = T.tempo_attn_plan_workspace_bytes(st.kv, B * C, Hq, plan)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+
+    def answer(x):
+        out = torch.full_like(x, float("nan"))
+        T.tempo_attn_block_with_plan(st.kv, x, out, B, Hq, C, t0, None, 0, st.scale, plan, ws, nbytes)
+        return out
+
+    qd = dev(q, T.TEMPO_BF16)
+    ref = np.stack([oracle.attend(q[:, c].astype(np.float64), K.astype(np.float64), V.astype(np.float64), t0 + c, 0,
+                                  1.0 / np.sqrt(D)) for c in range(C)], axis=1)
+    assert_close(np64(answer(qd)), ref, T.TEMPO_BF16, f"{(D, G, C, B, steps, k)}")
+    if not k:
+        turned = torch.stack([st.rope_rotate(qd[:, c].contiguous(), torch.empty_like(qd[:, c]), t0 + c) for c in range(C)], dim=1)
+        assert torch.equal(st.attend_block(qd, torch.full_like(qd, float("nan")), t0, C, rope=True), answer(turned.contiguous()))
+
+
 @pytest.mark.parametrize("G,C,D,steps,k", [(3, 7, 128, 150, 0), (3, 21, 128, 700, 0), (3, 21, 128, 1500, 7), (20, 1, 128, 200, 0),
                                            (4, 5, 64, 150, 0), (4, 16, 64, 400, 0), (4, 16, 64, 400, 5), (4, 31, 64, 3000, 9),
                                            (3, 40, 128, 500, 0)])

@@ -109,7 +109,8 @@ def test_no_alloc_f32_step_takes_a_plan_that_fits_the_array(lib, Hq, Hkv, D, bat
 
 
 @pytest.mark.parametrize("G,Hkv,D,batch,t,ragged", [(17, 8, 64, 33, 16383, False), (33, 1, 64, 128, 40000, False),
-                                                    (24, 4, 64, 17, 65535, False), (40, 8, 128, 20, 30000, True), (64, 8, 128, 3, 5000, False)])
+                                                    (24, 4, 64, 17, 65535, False), (40, 8, 128, 20, 30000, True), (64, 8, 128, 3, 5000, False),
+                                                    (100, 8, 128, 4, 30000, False), (70, 8, 64, 40, 700, False)])
 def test_no_alloc_bf16_step_of_a_wide_group_takes_a_plan_that_fits_the_array(lib, G, Hkv, D, batch, t, ragged):
     """And the plan of the call with a workspace, if that one fits."""
     kv, plan, Hq = store(T.TEMPO_BF16, Hkv, D, 64, t // 64 + 1), T.tempo_plan(), G * Hkv
@@ -391,10 +392,17 @@ def test_rope_prompts_by_blocks_go_by_blocks(lib, D, G, t, count):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,batch,t,queries,window,stream", [
-    (24, 8, 128, 1, 10, 6, 0, 1), (32, 1, 128, 1, 5, 1, 0, 1), (33, 1, 128, 1, 191, 1, 0, 0), (33, 1, 128, 1, 192, 1, 0, 1),
+    (24, 8, 128, 1, 10, 6, 0, 1), (32, 1, 128, 1, 5, 1, 0, 1), (24, 8, 128, 26, 58, 6, 0, 0), (24, 8, 128, 25, 58, 6, 0, 1), (33, 1, 128, 1, 191, 1, 0, 0), (33, 1, 128, 1, 192, 1, 0, 1),
     (33, 1, 128, 1, 5000, 1, 192, 0), (24, 8, 128, 16, 4075, 21, 0, 1), (64, 1, 128, 1, 500, 1, 0, 1), (65, 1, 128, 1, 60000, 1, 0, 0),
-    (24, 8, 128, 16, 4075, 42, 0, 0), (64, 1, 64, 1, 10, 1, 0, 1), (65, 1, 64, 1, 65534, 1, 0, 0), (65, 1, 64, 1, 65535, 1, 0, 1),
-    (65, 8, 64, 2, 4095, 16, 100, 0)])
+    (24, 8, 128, 16, 4075, 42, 0, 0), (64, 1, 64, 1, 128, 1, 0, 1), (64, 1, 64, 1, 127, 1, 0, 0), (65, 1, 64, 1, 65535, 1, 0, 0),
+    (65, 1, 64, 1, 65536, 1, 0, 1), (65, 8, 64, 2, 4095, 16, 100, 0),
+    # more pairs than compute units, and than fill the part twice
+    (24, 8, 128, 33, 218, 6, 0, 0), (24, 8, 128, 33, 219, 6, 0, 1), (24, 8, 128, 64, 218, 6, 0, 0), (24, 8, 128, 33, 235, 21, 0, 0),
+    (24, 8, 128, 33, 236, 21, 0, 1), (24, 8, 128, 64, 1003, 21, 0, 0), (24, 8, 128, 64, 1004, 21, 0, 1), (32, 8, 64, 33, 10, 8, 0, 1),
+    (32, 8, 64, 64, 184, 8, 0, 0), (32, 8, 64, 64, 185, 8, 0, 1), (32, 8, 64, 63, 240, 16, 0, 0), (32, 8, 64, 63, 241, 16, 0, 1),
+    (32, 8, 64, 64, 432, 16, 0, 0), (32, 8, 64, 64, 433, 16, 0, 1), (32, 8, 64, 70, 752, 16, 0, 0), (32, 8, 64, 49, 993, 31, 0, 0),
+    (32, 8, 64, 50, 226, 31, 0, 1), (32, 8, 64, 64, 1505, 31, 0, 0), (32, 8, 64, 64, 1506, 31, 0, 1), (32, 8, 64, 70, 1761, 31, 0, 0),
+    (24, 8, 128, 97, 619, 21, 0, 0), (24, 8, 128, 97, 620, 21, 0, 1)])
 def test_kernel_of_a_wide_block(lib, Hq, Hkv, D, batch, t, queries, window, stream):
     Hq = Hq // Hkv * Hkv
     kv = store(T.TEMPO_BF16, Hkv, D, 64, (t + queries) // 64 + 1)
