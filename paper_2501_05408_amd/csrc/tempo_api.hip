@@ -958,41 +958,44 @@ bool short_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int3
 // are made for many columns; a block's attention spreads a long range over the whole part.
 //   fp32: one block does, always (1 sequence, 24/8 heads, 1 step behind 2000 keys 12.6 us, in one launch 37;
 //   behind 30000 49, 128).  More do not (2 blocks behind 2000 keys 62, 51).
-//   bf16, at most 16 columns, which the single-step kernel takes: always (24/8 heads, 1 step, 1 sequence behind
+//   bf16, a range of few groups, which no kernel splits: one launch where the merge of a block's wavefronts, by column
+//   or tile of 32 columns, takes longer than the prompt kernel's beginning (us, by blocks / in one launch, D = 64, 60 columns,
+//   16 keys 9.3 / 6.9, 143 keys 9.2 / 8.1; D = 128, 15 columns, 8 keys 9.9 / 7.0, 10 columns 8.0 / 7.1, 6 columns 7.0 / 7.2;
+//   30 columns, 22 keys 8.1 / 7.2; queries to be turned to their position hide it below 25 columns, 7.9 / 8.4).
+//   bf16, at most 16 columns, which the single-step kernel takes: by blocks else (24/8 heads, 1 step, 1 sequence behind
 //   8000 keys 14, 27; 16 sequences behind 300 keys 10, 12), but for one or two (sequence, head) pairs with a
 //   few columns behind a short range, whose many splits cost more to combine (1 sequence, 8/1 heads, 2 steps
 //   behind 1000 keys 14.0, 11.1).
-//   bf16, more columns: by two estimates in us, fitted to 884 measured prompts of 1 to 128 pairs (on the mean
-//   0.2% from the better of the two), unless their blocks fill the part.  A block takes a time of its own and a
-//   share of its keys' stream from HBM, both by the kernel its columns go to (33 to 64 columns: 12.5 at the least with
-//   D = 128; with D = 64, 2 more where splits are combined); one launch 8 and the longer of a workgroup's walk through
-//   an eighth of the keys and 1.2 times the stream (33 to 64 columns, D = 64: 0.06 a step for the rows it writes) (us, by blocks / in one launch: 2 sequences,
-//   32/8 heads of 64, 5 steps behind 8000 keys 13.3 / 22.3, 1 sequence, 16/16 heads of 64, 48 steps behind 8000 17.0 / 24.4,
-//   4 sequences, 24/8 heads of 128, 21 steps behind 8000 35.6 / 31.5).
-bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window) {
+//   bf16, more columns: by two estimates in us, fitted to 4754 measured prompts of 1 to 255 blocks of all pairs (on the mean
+//   0.3% from the better of the two, 21% at most), unless their blocks fill the part.  A block takes a time of its own and a
+//   share of its keys' stream from HBM, both by the kernel its columns go to; one launch 7.7 and the longer of a
+//   workgroup's walk through an eighth of the keys and 1.63 times the stream (us, by blocks / in one launch: 2 sequences,
+//   32/8 heads of 64, 5 steps behind 8000 keys 13.3 / 22.3, 24/8 heads of 128, 6 sequences, 15 steps behind 3600 29.4 / 34.7,
+//   1 sequence, 16 steps behind 1650 16.5 / 15.4).
+bool prompt_by_blocks(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window, bool rope) {
   const int32_t G = Hq / kv->num_kv_heads, block = kMaxColumns / G;
   if (kv->dtype != TEMPO_BF16) return count <= block;
   if (prompt_fills_part(kv, batch, G, count)) return false;
+  const bool narrow = kv->head_dim == 64;
   const int64_t pairs = (int64_t)batch * kv->num_kv_heads, columns = (int64_t)count * G;
   const int64_t keys = window > 0 && window <= t ? (int64_t)window + count - 1 : (int64_t)t + count;
   if (columns <= kNarrowColumns) {
+    if (narrow ? columns >= 12 && keys <= 32 : (columns > 8 && keys <= 32) || (columns > 13 && keys <= 64)) return false;
     tempo_plan plan;
     make_block_plan(kv, batch, Hq, t, window, false, count, &plan);
     return !(pairs < kManyPairs && plan.num_splits > 8 && columns >= 8 && count > 1 && keys <= 2200);
   }
   if (short_prompt(kv, batch, Hq, t, count, window)) return false;
-  const bool narrow = kv->head_dim == 64;
+  if (columns <= 32 && (narrow ? keys <= 32 : columns > 24 ? keys <= 64 : keys <= 32 && !rope)) return false;
+  if (narrow && columns > 32 && columns <= 64 && keys <= 256) return false;
   const double stream = (double)pairs * keys * kv->head_dim * 4 / (kSustainedBytesPerNs * 1000.0);
   const int64_t blocks = (count + block - 1) / block, widest = columns < kMaxColumns ? columns : kMaxColumns;
   const int size = widest <= 32 ? 0 : widest <= 64 ? 1 : 2;
-  constexpr double kOwn[2][3] = {{8.0, 5.6, 14.1}, {5.7, 8.4, 14.6}}, kShare[2][3] = {{0.6, 1.8, 1.46}, {0.9, 0.8, 1.0}};
-  double block_time = kOwn[narrow][size] + kShare[narrow][size] * stream;
-  if (!narrow && size == 1 && block_time < 12.5) block_time = 12.5;
-  if (narrow && size == 1 && keys > 512) block_time += 2.0;
-  const double by_blocks = (double)blocks * block_time;
+  constexpr double kOwn[2][3] = {{5.0, 13.0, 14.1}, {7.0, 9.6, 12.5}}, kShare[2][3] = {{0.73, 0.51, 2.23}, {1.12, 0.68, 0.72}};
+  const double by_blocks = (double)blocks * (kOwn[narrow][size] + kShare[narrow][size] * stream);
   const int64_t workgroups = 8 * pairs * blocks, rounds = (workgroups + 2 * kComputeUnits - 1) / (2 * kComputeUnits);
-  const double walk = (workgroups <= kComputeUnits ? 0.55 : 0.78) * (narrow ? 0.68 : 1.0) * (columns > 64 ? 1.1 : 1.0) * rounds * (double)keys / 256.0;
-  const double one_launch = 8.0 + (walk > 1.2 * stream ? walk : 1.2 * stream) + (narrow && size == 1 ? 0.06 * count : 0.0);
+  const double walk = (workgroups <= kComputeUnits ? 0.74 : 0.85) * (narrow ? 0.35 : 1.0) * (columns > 64 ? 1.36 : 1.0) * rounds * (double)keys / 256.0;
+  const double one_launch = 7.7 + (walk > 1.63 * stream ? walk : 1.63 * stream) + (narrow && size == 1 ? 0.06 * count : 0.0);
   return by_blocks < one_launch;
 }
 
@@ -1369,7 +1372,7 @@ static int prefill(const tempo_kv* kv, const void* q, const void* k_new, const v
   }
   // (several blocks on a ring, answers over rows: the chunks looked at above, not the blocks)
   const bool blocks_stand = !kv->ring_blocks || count <= block || rows_apart(kv, k_new, v_new, out, batch, Hq, count);
-  if (!count_per_seq && blocks_stand && prompt_by_blocks(kv, batch, Hq, t, count, window))
+  if (!count_per_seq && blocks_stand && prompt_by_blocks(kv, batch, Hq, t, count, window, rope != nullptr))
     return prefill_by_blocks(kv, q, k_new, v_new, out, batch, Hq, t, count, window, scale, workspace, s, rope);
   // Write the prompt, then answer it in one launch; on a ring store in chunks that it can hold.
   if (one_launch) {

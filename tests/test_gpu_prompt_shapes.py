@@ -116,6 +116,21 @@ def test_rope_prompt_by_blocks(D, G, t, count):
     test_rope_prompt_with_split_ranges(D, G, t, count)
 
 
+# ((B, Hkv, G, D, t, count, window), by blocks): a few columns over a few groups, on both sides of the lines
+FEW_GROUPS = [((2, 8, 3, 128, 26, 3, 0), False), ((2, 8, 3, 128, 29, 3, 0), False), ((2, 8, 3, 128, 30, 3, 0), True), ((1, 1, 8, 128, 30, 1, 0), True),
+              ((1, 2, 7, 128, 62, 2, 0), False), ((1, 2, 7, 128, 63, 2, 0), True), ((3, 2, 12, 64, 31, 1, 0), False),
+              ((3, 2, 11, 64, 31, 1, 0), True), ((3, 2, 4, 64, 30, 3, 0), True), ((1, 4, 3, 128, 24, 8, 0), False), ((1, 4, 3, 128, 25, 8, 0), True),
+              ((1, 4, 3, 128, 55, 9, 0), False), ((1, 4, 3, 128, 56, 9, 0), True), ((2, 2, 1, 64, 15, 17, 0), False),
+              ((2, 2, 1, 64, 16, 17, 0), True), ((2, 8, 4, 64, 1, 15, 0), False), ((1, 2, 4, 64, 240, 16, 0), False),
+              ((1, 2, 4, 64, 400, 12, 244), False)]
+
+
+@pytest.mark.parametrize("shape,blocks", FEW_GROUPS)
+def test_prompts_of_few_columns_over_few_groups(shape, blocks):
+    B, Hkv, G, D, t, count, window = shape
+    run_prompt(B, Hkv, G, D, 32, t, count, window, False, T.TEMPO_BF16)
+
+
 @pytest.mark.parametrize("dtype,B,Hkv,G,D,t,count,window,ring", [
     (T.TEMPO_BF16, 1, 1, 3, 64, 16000, 70, 0, False), (T.TEMPO_BF16, 1, 1, 8, 128, 32000, 42, 0, False),   # several blocks
     (T.TEMPO_BF16, 2, 2, 3, 128, 0, 90, 0, False), (T.TEMPO_F32, 2, 2, 3, 64, 0, 90, 0, False),            # one launch

@@ -12,7 +12,7 @@ import pytest
 
 from paper_2501_05408_amd import tempo as T
 
-from test_gpu_prompt_shapes import ROPE_BY_BLOCKS
+from test_gpu_prompt_shapes import FEW_GROUPS, ROPE_BY_BLOCKS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOMEWHERE = 1 << 20                       # pointers that are checked for NULL and alignment, never read
@@ -414,3 +414,12 @@ def test_kernel_of_a_wide_block(lib, Hq, Hkv, D, batch, t, queries, window, stre
     launches = taken(lib)
     assert launches[0][0] == "block_bf16" and launches[0][1]["stream"] == stream
     assert_all_keys_launched(launches, Hq // Hkv, t, queries)
+
+
+@pytest.mark.parametrize("shape,blocks", FEW_GROUPS)
+def test_prompts_of_few_columns_over_few_groups(lib, shape, blocks):
+    B, Hkv, G, D, t, count, window = shape
+    launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 32, (t + count) // 32 + 1), B, Hkv * G, t, count, window)
+    names = [n for n, _ in launches]
+    assert names[0] == "append" and names[1] in (("block_bf16", "partial_bf16") if blocks else ("prompt",))
+    assert_all_keys_launched(launches, G, t, count)
