@@ -1022,7 +1022,7 @@ struct PromptPlan {
 // workgroup's beginning and end: the better shape only for long ranges at D = 128 (us with 4 / 8:
 // 16 x 200 steps 32.7 / 35.7, 16 x 1000 185 / 200, 4 x 4000 449 / 437; D = 64, 8 x 1500 125 / 147).
 PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t, int32_t count, int32_t window,
-                       size_t workspace_bytes) {
+                       size_t workspace_bytes, bool rows) {
   const int G = Hq / kv->num_kv_heads;
   const double scale = kv->head_dim == 128 ? 1.0 : 0.68;
   PromptPlan best = {4, kWholeRange, 1};
@@ -1035,15 +1035,19 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
     if (G > waves * kWaveColumns) break;
     const int32_t QB = prompt_block_span(G, waves * kWaveColumns);
     const int64_t blocks = prompt_blocks(count, G, waves * kWaveColumns);
-    const int64_t keys = window > 0 && window + QB < t + count ? window + QB : t + count;  // of the longest block
+    // keys of the longest block; from the store in whole steps, as the constants were fitted (with a step more of 3 heads a
+    // window of 107 crossed into a fifth group for 2 wavefronts and got 4: 125 steps, 2 sequences, 15.3 -> 17.5 us; from
+    // rows that step decides the other way: 122 steps, 3 sequences, window 21 8.6 by 2 wavefronts, 10.9 by 4)
+    const int64_t seen = (int64_t)window + (rows ? QB : waves * kWaveColumns / G);
+    const int64_t keys = window > 0 && seen < (int64_t)t + count ? seen : (int64_t)t + count;
     const int resident = 2;  // (at D = 64 more would fit; the constants were fitted with 2 there too)
     for (int k = kWholeRange; k >= 7; k = k == kWholeRange ? 13 : k - 1) {
       const int splits = k == kWholeRange ? 1 : splits_bound(t + count - 1, union_window(window, QB), k);
       if (k != kWholeRange && !may_split) break;
       if (k != kWholeRange && splits == 1) continue;
       if (splits > 8) break;  // the combine reads up to 8 splits in one batch
-      const int64_t rows = (int64_t)batch * count * Hq;
-      if (k != kWholeRange && (rows * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, rows, splits) > workspace_bytes)) break;
+      const int64_t answers = (int64_t)batch * count * Hq;
+      if (k != kWholeRange && (answers * splits * kv->head_dim > INT32_MAX || plan_bytes(kv, answers, splits) > workspace_bytes)) break;
       const int64_t workgroups = blocks * pairs * splits;
       const int64_t rounds = (workgroups + resident * kComputeUnits - 1) / (resident * kComputeUnits);
       const bool shared = workgroups > kComputeUnits;  // two workgroups on some compute unit
@@ -1051,7 +1055,7 @@ PromptPlan plan_prompt(const tempo_kv* kv, int32_t batch, int32_t Hq, int32_t t,
       // a causal prompt's blocks are half the longest on average: beyond the first round that counts
       const double mean = window == 0 && rounds > 1 ? (double)(t + count / 2) / (t + count) : 1.0;
       double ns = (double)rounds * (5000.0 + mean * (double)((span + 31) / 32) * (!shared ? 550.0 : waves == 4 ? 780.0 : 640.0) * scale);
-      if (splits > 1) ns += 1500.0 + 2.0 * (double)rows * splits * kv->head_dim * 4 / 4000.0;
+      if (splits > 1) ns += 1500.0 + 2.0 * (double)answers * splits * kv->head_dim * 4 / 4000.0;
       if (best_ns < 0.0 || ns < 0.97 * best_ns) {  // the wider workgroup and the fewer splits unless clearly slower
         best_ns = ns;
         best = {waves, k, splits};
@@ -1177,7 +1181,7 @@ int attend_prompt(const tempo_kv* kv, const void* q, void* out, int32_t batch, i
   // (and staged keys/values lie where the partials of split ranges would)
   const bool is_short = bf16 && !staged && !rows && short_prompt(kv, batch, Hq, t, count, window);
   const PromptPlan plan = is_short ? PromptPlan{8, kWholeRange, 1}
-                          : bf16   ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes)
+                          : bf16   ? plan_prompt(kv, batch, Hq, t, count, window, count_per_seq || staged ? 0 : workspace_bytes, rows != nullptr)
                                    : plan_prompt_f32(kv, batch, Hq, t, count, window, workspace_bytes);
   const tempo_plan cut = {32, plan.splits, plan.waves};  // (its split length is set below)
   PromptParams p;

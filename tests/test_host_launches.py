@@ -423,3 +423,10 @@ def test_prompts_of_few_columns_over_few_groups(lib, shape, blocks):
     names = [n for n, _ in launches]
     assert names[0] == "append" and names[1] in (("block_bf16", "partial_bf16") if blocks else ("prompt",))
     assert_all_keys_launched(launches, G, t, count)
+
+
+@pytest.mark.parametrize("batch,t,count,window,waves", [(2, 3993, 125, 107, 2), (3, 0, 122, 21, 2)])
+def test_wavefronts_of_a_windowed_prompt(lib, batch, t, count, window, waves):
+    """From the store, and from rows."""
+    launches = prefill(lib, store(T.TEMPO_BF16, 8, 128, 64, (t + count) // 64 + 1), batch, 24, t, count, window, out=1 << 45)
+    assert launches[-1][0] == "prompt" and launches[-1][1]["waves"] == waves
