@@ -1151,22 +1151,45 @@ bool rows_readable(const tempo_kv* kv, const void* k_new, const void* v_new, con
          rows_apart(kv, k_new, v_new, out, batch, Hq, count);
 }
 
-// And is it the faster way?  fp32: at D = 64 (of 96 shapes all but one, 0.95 to 1.74), and at D = 128 up to about
-// 4.5e9 flops (us, write and attend / from rows: 8/8 heads, 4 x 128 steps 17.5 / 10.4, 24/8 heads, 16 x 128 75.6 / 74.8, 16 x 300
-// (9e9) 326 / 337).  bf16: it saves a launch and a pass over memory, and costs a little per group and workgroup: the faster way for all windowed prompts and for
-// causal ones up to about 1.15e11 flops (us, write and attend / from rows, 1 to 16 sequences; 24/8 heads of 128:
-// 1 x 40 steps 11.2 / 8.8, 16 x 160 23.6 / 16.8, 16 x 640 83.6 / 77.2, 4 x 1900 (9e10) 117 / 110, 16 x 1300 (1.7e11)
-// 243 / 247, 16 x 2700 808 / 832; 32/8 heads of 64: 16 x 900 94.0 / 91.1, 16 x 1900 (2.4e11) 321 / 335; 16/16 heads of
-// 64: 16 x 320 25.0 / 17.1, 16 x 1900 (1.2e11) 207 / 214; window 256, 24/8 heads of 128: 16 x 4000 508 / 471, on a
-// ring, staged before, 529 / 447; 357 shapes measured, 1.20 times as fast on the geometric mean; the slower way taken in none by more than 4%).
+// And is it the faster way?  It saves a launch and a pass over memory, and costs a little per group and workgroup, which
+// shows where the longest walk or the last round decides.  (us, write and attend / from rows)
+//   bf16, causal: up to about 1.15e11 flops (24/8 heads of 128: 16 x 160 steps 23.6 / 16.8, 16 x 1300 (1.7e11) 243 / 247;
+//   16/16 heads of 64: 16 x 320 25.0 / 17.1, 16 x 1900 (1.2e11) 207 / 214).  Less at D = 128: groups of 1 head, with more
+//   blocks than units, up to 1320 steps, or 1700 with blocks for two rounds (8 heads: 3 sequences of 1591 steps 54.3 / 59.3,
+//   2 of 2339 71.7 / 81.4; but 2 of 1568, 208 blocks, 43.2 / 39.4, 6 of 1459 71.0 / 65.0); of 2 or 3 heads up to 2800 steps (1
+//   sequence of 2888 steps 83.0 / 90.0, 2175 65.6 / 61.8), or 1700 with more than 1024 blocks (5% on the mean).
+//   Windows: all, but for linear stores and windows so short that the block kernel takes the written prompt, with
+//   blocks for many rounds (8 heads a group, 52 keys, 2400 blocks 64.6 / 69.1, 780 28.4 / 27.9; 3 heads, 36 keys, 3072 blocks
+//   98.5 / 101.2, 1800 64.8 / 63.6).
+//   fp32: at D = 128 up to about 4.5e9 flops (8/8 heads: 4 x 128 17.5 / 10.4, 1 x 1534 (4.8e9) 124.5 / 124.4); at D = 64 but
+//   for long walks with tiles for a little more than one round of the units, of few pairs (2 pairs, 4 heads
+//   a group: 948 steps, 474 tiles 25.0 / 30.7, 414 steps 14.2 / 10.1, 1254 steps, 628 tiles 40.7 / 36.2; 8 pairs, 1 head: 674
+//   steps, 344 tiles 24.4 / 28.5, 854 steps, 432 tiles 32.2 / 31.1).
 constexpr double kRowsMostFlops = 1.15e11, kRowsMostFlopsF32 = 4.5e9;
 
 bool prompt_from_rows(const tempo_kv* kv, const void* k_new, const void* v_new, const void* out, int32_t batch, int32_t Hq,
                       int32_t t, int32_t count, int32_t window) {
   if (t != 0 || !prompt_in_one_launch(kv, batch, Hq, count)) return false;
+  const int32_t G = Hq / kv->num_kv_heads;
+  const int64_t pairs = (int64_t)batch * kv->num_kv_heads;
   const double mean_keys = window > 0 && window < count / 2 ? window : 0.5 * count;
   const double flops = 4.0 * batch * Hq * kv->head_dim * count * mean_keys;
-  if (kv->dtype == TEMPO_BF16 ? window == 0 && flops > kRowsMostFlops : kv->head_dim == 128 && flops > kRowsMostFlopsF32) return false;
+  if (kv->dtype == TEMPO_BF16) {
+    const int64_t blocks = (int64_t)prompt_blocks(count, G, kMaxColumns) * pairs;
+    if (window == 0) {
+      if (flops > kRowsMostFlops) return false;
+      if (kv->head_dim == 128 && (G == 1 ? blocks > 240 && count > (blocks <= 2 * kComputeUnits ? 1320 : 1700)
+                                         : G < 4 && (count > 2800 || (count > 1700 && blocks > 1024))))
+        return false;
+    } else if (kv->ring_blocks == 0 && window < count && short_prompt(kv, batch, Hq, t, count, window) && blocks >= (G < 8 ? 2048 : 1400)) {
+      return false;
+    }
+  } else if (kv->head_dim == 128) {
+    if (flops > kRowsMostFlopsF32) return false;
+  } else {
+    const int64_t tiles = ((int64_t)count * G + 15) / 16 * pairs;
+    if (count >= 530 && tiles > kComputeUnits && tiles <= (pairs < 8 ? 2 * kComputeUnits : pairs == 8 ? 352 : 0)) return false;
+  }
   return rows_readable(kv, k_new, v_new, out, batch, Hq, count);
 }
 

@@ -425,6 +425,27 @@ def test_prompts_of_few_columns_over_few_groups(lib, shape, blocks):
     assert_all_keys_launched(launches, G, t, count)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,batch,count,window,rows", [
+    (24, 8, 128, 1, 2800, 0, True), (24, 8, 128, 1, 2801, 0, False), (24, 8, 128, 4, 1700, 0, True), (24, 8, 128, 4, 1701, 0, False),
+    (8, 8, 128, 3, 1320, 0, True), (8, 8, 128, 3, 1321, 0, False), (8, 8, 128, 6, 1700, 0, True), (8, 8, 128, 6, 1701, 0, False),
+    (8, 8, 128, 2, 1920, 0, True), (8, 8, 128, 2, 1921, 0, False), (32, 4, 128, 1, 3700, 0, True), (16, 16, 64, 2, 2500, 0, True),
+    (64, 8, 128, 10, 480, 52, False), (64, 8, 128, 10, 272, 52, True), (24, 8, 128, 10, 1088, 36, False), (24, 8, 128, 10, 1066, 36, True),
+    (64, 8, 128, 10, 480, 200, True)])
+def test_bf16_prompts_read_from_rows(lib, Hq, Hkv, D, batch, count, window, rows):
+    launches = prefill(lib, store(T.TEMPO_BF16, Hkv, D, 64, count // 64 + 1), batch, Hq, 0, count, window, out=1 << 45)
+    assert [n for n, _ in launches][0] == ("prompt" if rows else "append")
+    assert bool(dict(launches[-1][1])["k"]) == rows or not rows
+    assert_all_keys_launched(launches, Hq // Hkv, 0, count)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,batch,count,rows", [
+    (8, 2, 64, 1, 512, True), (8, 2, 64, 1, 529, True), (8, 2, 64, 1, 530, False), (8, 2, 64, 1, 1024, False), (8, 2, 64, 1, 1025, True),
+    (8, 8, 64, 1, 700, False), (8, 8, 64, 1, 705, True), (8, 8, 64, 2, 700, True)])
+def test_f32_prompts_read_from_rows(lib, Hq, Hkv, D, batch, count, rows):
+    launches = prefill(lib, store(T.TEMPO_F32, Hkv, D, 64, count // 64 + 1), batch, Hq, 0, count, out=1 << 45)
+    assert [n for n, _ in launches] == (["partial_f32"] if rows else ["append", "partial_f32"])
+
+
 @pytest.mark.parametrize("batch,t,count,window,waves", [(2, 3993, 125, 107, 2), (3, 0, 122, 21, 2)])
 def test_wavefronts_of_a_windowed_prompt(lib, batch, t, count, window, waves):
     """From the store, and from rows."""
