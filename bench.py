@@ -343,7 +343,7 @@ def other_workloads(torch, T, BlockStore, synth, dev, kv_bytes_per_token):
 
     dt = gpu_timed(torch, rope_block, 200, 20)["median"]
     out[f"rope_block{C}_b16_t{4096 - C}"] = {"us_per_call": us(dt), "us_per_query_step": us(dt / C),
-                                             "roofline": hbm_roofline("attn_block_bf16<128, 4, true, true>", block_bytes, dt),
+                                             "roofline": hbm_roofline("attn_stream_bf16<128, 2, 8, true>", block_bytes, dt),
                                              "note": "rotating block write + block attention with unrotated queries"}
     del qc, kc, vc, oc
     del sts

@@ -30,14 +30,6 @@ __device__ inline float half_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Online softmax of one group for this kernel, with a LAZY reference: weights are
-// 2^(x - ref) where ref follows the running maximum only when the maximum has
-// grown by more than kSlack (in log2 units) since ref was set, so weights stay
-// below 2^kSlack (exact in fp32 sums, same relative rounding in bf16) and the
-// accumulators are rescaled a few times per column instead of at every new
-// maximum.  The result acc / sum does not depend on ref.
-constexpr float kSlack = 8.0f;
-
 // Maximum of this lane's sixteen logits.  x holds the RAW dot products (masked ones are -inf).
 __device__ inline float tile_max(const f32x16& x) {
   const float a = max3(x[0], x[1], x[2]), b = max3(x[3], x[4], x[5]), c = max3(x[6], x[7], x[8]);
@@ -45,8 +37,8 @@ __device__ inline float tile_max(const f32x16& x) {
   return max3(max3(a, b, c), max3(d, e, x[15]), x[15]);
 }
 
-// First half: move the reference if this group's maximum calls for it.  A lane's
-// sixteen logits, its accumulators and its share of the sum all belong to ONE column,
+// Online softmax of one group (lazy reference: kSlack), first half: move the reference if this
+// group's maximum calls for it.  A lane's sixteen logits, its accumulators and its share of the sum all belong to ONE column,
 // so the rescale factor needs no exchange.  Most groups move nothing, so that case is one
 // comparison: of the lane's own raw maximum (the lanes of a column meet only behind the branch)
 // with `limit`, the raw dot product from which on the reference has to move.

@@ -312,6 +312,13 @@ __device__ inline float column_sum(float v) {
   return c;
 }
 
+// The kernels that share a group among many columns (blocks, prompts) take a LAZY softmax reference: weights are
+// 2^(x - ref) where ref follows the running maximum only when the maximum has grown by
+// more than kSlack (in log2 units) since ref was set, so weights stay below 2^kSlack (exact
+// in fp32 sums, same relative rounding in bf16) and the accumulators are rescaled a
+// few times per column instead of at every new maximum.  The result acc / sum does not depend on ref.
+constexpr float kSlack = 8.0f;
+
 // Online-softmax update of (m, l), rescale of acc, and the bf16 weights of this group.
 template <int D>
 __device__ inline bf16x8 softmax_update(const float* x, int lane, WaveState<D>& st) {

@@ -35,17 +35,9 @@ __device__ inline float max3(float a, float b, float c) {
   return r;
 }
 
-// Online softmax of one group for this kernel, with a LAZY reference: weights are
-// 2^(x - ref) where ref follows the running maximum only when the maximum has
-// grown by more than kSlack (in log2 units) since ref was set, so weights stay
-// below 2^kSlack (exact in fp32 sums, same relative rounding in bf16) and the
-// accumulators are rescaled a few times per column instead of at every new
-// maximum.  The result acc / sum does not depend on ref.  The running sum is one
-// more accumulator tile (weights times a column of ones on the matrix cores).
-constexpr float kSlack = 8.0f;
-
-// First half: move the reference if this group's maximum calls for it.  x holds the
-// RAW dot products (masked ones are -inf); `scale` > 0 is s * log2(e).
+// Online softmax of one group (lazy reference: kSlack), first half: move the reference if this group's maximum
+// calls for it.  x holds the RAW dot products (masked ones are -inf); `scale` > 0 is s * log2(e).  The running
+// sum is one more accumulator tile (weights times a column of ones on the matrix cores).
 template <int D>
 __device__ inline void softmax_reference(const float* x, float scale, int lane, float& ref, f32x4* acc,
                                          f32x4& acc_l) {

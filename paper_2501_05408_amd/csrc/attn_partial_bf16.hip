@@ -307,11 +307,6 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) st.acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // In one body the requests for the next group stand behind a condition each, and the compiler has to allow for
-  // keys that were requested and values that were not: a wait for keys becomes one for the values as well, and
-  // nothing is in flight while a wavefront computes.  With the last group apart (kPeel) the waits are for what
-  // is needed (us a step, one body / two; 24/8 heads of 128: window 512, 16 sequences 9.62 / 9.31, t = 4095 45.2 / 44.7,
-  // 1 sequence, t = 65535 45.7 / 45.1).
   // Group grp; `more`: and request group nxt.
   auto group = [&](int nxt, bool more) __attribute__((always_inline)) {
     const int64_t base_nxt = more ? group_base<D>(p, b, hkv, nxt) : 0;  // scalar loads, off the vector path
@@ -345,8 +340,8 @@ __global__ __launch_bounds__(512) void attn_partial_bf16(AttnParams p) {
   };
   // In one body the requests for the next group stand behind a condition each, and the compiler has to allow for
   // keys that were requested and values that were not: a wait for keys becomes one for the values as well, and
-  // nothing is in flight while a wavefront computes.  With the last group apart the waits are for what is needed (us
-  // a step, one body / two, 24/8 heads of 128: window 512, 16 sequences 9.62 / 9.28, t = 4095 45.2 / 44.7, 1 sequence,
+  // nothing is in flight while a wavefront computes.  With the last group apart (kPeel) the waits are for what is
+  // needed (us a step, one body / two, 24/8 heads of 128: window 512, 16 sequences 9.61 / 9.28, t = 4095 45.2 / 44.7, 1 sequence,
   // t = 65535 45.7 / 45.1, rotary, t = 299 6.15 / 5.94).
   if constexpr (kPeel) {
     for (; grp + nwaves <= g_last; grp += nwaves) group(grp + nwaves, true);
