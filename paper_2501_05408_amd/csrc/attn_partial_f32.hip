@@ -306,8 +306,8 @@ __global__ __launch_bounds__(512) void attn_partial_f32(AttnParams p) {
     base = base_nxt;
   };
   // The last group apart, so that a wait for keys is not one for the values requested behind them (see the bf16
-  // decode kernel; 16 sequences, 24/8 heads of 128, t = 2047, 48.3 -> 46.8 us a step, 9000 keys at D = 64 3 to 7%; ranges of
-  // 256 and 2048 keys at D = 64 up to 2% slower).
+  // decode kernel; 16 sequences, 24/8 heads of 128, t = 2047, 48.3 -> 46.8 us a step; D = 64, 100 to 9000 keys of 1 to 64
+  // sequences, 94 shapes 4% on the mean, one more than 1% slower: 32/8 heads, 16 of 4096 keys 48.2 -> 48.9).
   if (any) {
     for (; grp + nwaves <= g_last; grp += nwaves) group(grp + nwaves, true);
     if (grp <= g_last) group(grp + nwaves, false);

@@ -40,7 +40,7 @@
 // values row by row and turned by gfx950's transposing LDS read (two of 8 bytes where the pools' order
 // takes one of 16), and the workgroup whose columns begin a group's first step writes that group to the
 // store while it lies in LDS.  One launch instead of a write and a launch that waits for it: 499 steps of
-// one sequence, 32/8 heads of 64, 14.7 -> 12.0 us, 40 steps 8.2 -> 5.8; 4 x 2048 with window 512 on a
+// one sequence, 32/8 heads of 64, 14.7 -> 11.8 us, 40 steps 8.2 -> 5.8; 4 x 2048 with window 512 on a
 // ring, which had staged its rows in the workspace, 102.7 -> 84.5.  The extra reads cost 3 to 4% of a long
 // causal prompt's loop (prompt_from_rows() in tempo_api.hip draws the line).
 //
