@@ -1136,7 +1136,7 @@ bool answers_over_later_rows(const tempo_kv* kv, const void* rows, const void* o
   const int64_t row = step_bytes * kv->num_kv_heads, answer = step_bytes * Hq;
   const int64_t apart = (int64_t)(reinterpret_cast<uintptr_t>(out) - reinterpret_cast<uintptr_t>(rows));
   for (int32_t b = 0; b < batch; ++b) {
-    const int64_t from = apart + b * count * answer, to = from + c * answer;  // sequence b's answers, from the first row
+    const int64_t from = apart + (int64_t)b * count * answer, to = from + c * answer;  // sequence b's answers, from the first row
     const int64_t other = from > 0 ? from / (count * row) : 0;                // the first sequence whose rows end behind `from`
     if (other < batch && (other * count + c) * row < to) return true;
   }
