@@ -150,28 +150,32 @@ inline int64_t block_keys(int t, int queries, int window) {
 // Does the stream kernel (attn_stream_bf16.hip) take a bf16 block of more than 16 columns, or the one that shares
 // each group among its wavefronts through LDS (attn_block_bf16.hip)?  The stream kernel has one workgroup of 8
 // wavefronts per compute unit, so nothing covers its beginning and its merge (one per tile of 32 columns), and
-// pairs beyond the 256 units are a second round.  Several workgroups of the other share a unit, and one split
-// of up to 256 keys, or as many pairs as fill the part twice, needs no combine.  So it is a matter of how many keys
-// pay for a round: 2200 blocks, 0.2% from the faster one on the mean, 20% at most, where stream throughout below 65
-// columns was 5% and up to 2.0 times (us a call, LDS / stream, each with its plan, with the write: D = 64, 72 columns, 256 pairs, 208
-// keys 16.8 / 22.9, 290 38.4 / 30.7; 48 columns, 768 pairs, 153 keys 22.0 / 36.1, 600 47.6 / 48.3; D = 128, 56 columns,
-// 512 pairs, 150 keys 22.4 / 30.9, 1400 102 / 101; 24 columns, 512 pairs, 154 keys 25.2 / 29.9, 400 60.3 / 48.6).
+// pairs beyond the 256 units are a second round.  Several workgroups of the other share a unit, and one split of up to
+// 256 keys, or as many pairs as fill the part twice (four times up to 32 columns), needs no combine.  So it is a matter of
+// how many keys pay for a round: 3684 blocks, from pools in and out of the caches, 0.2% from the faster one on the mean, 22% at
+// most, where stream throughout below 65 columns was up to 2.0 times (us a call, LDS / stream, each with its plan, with the
+// write: D = 128, 32 columns, 640 pairs, 256 keys 25.8 / 32.3, 257 48.8 / 35.4, 1024 pairs, 256 36.2 / 44.4; 56 columns, 512
+// pairs, 150 keys 22.4 / 30.9, 1400 102 / 101; D = 64, 72 columns, 256 pairs, 208 keys 16.8 / 22.9, 290 38.4 / 30.7; 48
+// columns, 768 pairs, 153 keys 22.0 / 36.1, 600 47.6 / 48.3).
 // Beyond 64 columns at D = 128 registers do not hold a wavefront's accumulators.
 inline bool block_streams(int D, int columns, int64_t pairs, int64_t keys) {
   const int tiles = columns <= 32 ? 0 : columns <= 64 ? 1 : 2;
-  if (D == 128 && tiles == 2) return false;
   const bool wide = D == 128;
-  int64_t most = 0;  // keys up to which the LDS kernel is the faster one
+  if (wide && tiles == 2) return false;
+  int64_t most;  // keys up to which the LDS kernel is the faster one
   if (pairs <= 256) {
-    if (tiles == 0) most = wide && pairs > 200 ? 64 : 0;
-    if (tiles == 1) most = wide ? (pairs <= 64 ? 192 : 256) : pairs <= 128 ? 128 : 160;
-    if (tiles == 2) most = pairs * 256 >= 65536 ? 256 : 65536 / pairs;
-  } else if (pairs < 512) {
-    most = wide ? (tiles == 0 ? 224 : 256) : tiles == 0 ? 0 : tiles == 1 || pairs >= 400 ? 256 : 1024;
+    if (tiles == 0) most = 32;
+    else if (tiles == 1) most = !wide ? 176 : pairs <= 64 ? 192 : 256;
+    else most = pairs > 96 ? 256 : 65536 / pairs;
+  } else if (pairs < 512) {  // a second round for some units, a combine for the LDS kernel
+    if (tiles == 0) most = wide ? 224 : 32;
+    else most = tiles == 1 || pairs >= 400 ? 256 : 1024;
   } else {
-    const bool twice = pairs < 560;  // the part filled twice and little more
-    if (wide) most = tiles == 0 ? 224 : pairs <= 768 ? 1024 : 640;
-    else most = tiles == 0 ? 192 : tiles == 1 ? (twice ? 448 : 768) : twice ? 1536 : 1792;
+    const bool two_rounds = pairs == 512;
+    if (tiles == 0) most = wide ? (pairs < 1024 ? 256 : 340) : two_rounds ? 32 : pairs < 1024 ? 192 : 272;
+    else if (tiles == 2) most = two_rounds ? 1300 : pairs <= 768 ? 2048 : 1800;
+    else if (!wide) most = two_rounds ? 640 : pairs <= 768 ? 900 : 1100;
+    else most = two_rounds ? 1200 : pairs < 640 ? 1800 : pairs <= 768 ? 1200 : pairs <= 1100 ? 640 : 1000;
   }
   return keys > most;
 }

@@ -395,7 +395,8 @@ def test_wide_blocks_where_the_kernel_and_its_tiles_change(G, C, D, B, steps, wi
 @pytest.mark.parametrize("D,G,C,B,steps,k", [
     (64, 2, 16, 65, 192, 0), (64, 2, 16, 65, 193, 0), (64, 2, 16, 65, 150, 7), (64, 2, 9, 36, 40, 0), (64, 4, 16, 36, 256, 0),
     (64, 4, 16, 36, 257, 0), (64, 3, 11, 65, 300, 6), (64, 4, 32, 36, 300, 0), (128, 3, 7, 40, 224, 0), (128, 3, 7, 40, 225, 0),
-    (128, 4, 8, 33, 100, 6), (128, 3, 21, 36, 256, 0), (128, 3, 21, 36, 257, 0), (128, 3, 11, 65, 400, 0)])
+    (128, 4, 8, 33, 100, 6), (128, 3, 21, 36, 256, 0), (128, 3, 21, 36, 257, 0), (128, 3, 11, 65, 400, 0),
+    (128, 4, 8, 65, 256, 0), (128, 4, 8, 65, 257, 0), (128, 3, 6, 128, 340, 0), (128, 3, 6, 4, 32, 0), (128, 3, 6, 4, 33, 0)])
 def test_wide_blocks_of_many_pairs(D, G, C, B, steps, k):
     """Of 8 kv heads: the lines between the two kernels for wide blocks where pairs are more than the compute units;
     queries turned to their positions by the kernel and before the call give the same bits.  k as above."""

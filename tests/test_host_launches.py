@@ -392,17 +392,21 @@ def test_rope_prompts_by_blocks_go_by_blocks(lib, D, G, t, count):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,batch,t,queries,window,stream", [
-    (24, 8, 128, 1, 10, 6, 0, 1), (32, 1, 128, 1, 5, 1, 0, 1), (24, 8, 128, 26, 58, 6, 0, 0), (24, 8, 128, 25, 58, 6, 0, 1), (33, 1, 128, 1, 191, 1, 0, 0), (33, 1, 128, 1, 192, 1, 0, 1),
-    (33, 1, 128, 1, 5000, 1, 192, 0), (24, 8, 128, 16, 4075, 21, 0, 1), (64, 1, 128, 1, 500, 1, 0, 1), (65, 1, 128, 1, 60000, 1, 0, 0),
-    (24, 8, 128, 16, 4075, 42, 0, 0), (64, 1, 64, 1, 128, 1, 0, 1), (64, 1, 64, 1, 127, 1, 0, 0), (65, 1, 64, 1, 65535, 1, 0, 0),
-    (65, 1, 64, 1, 65536, 1, 0, 1), (65, 8, 64, 2, 4095, 16, 100, 0),
-    # more pairs than compute units, and than fill the part twice
-    (24, 8, 128, 33, 218, 6, 0, 0), (24, 8, 128, 33, 219, 6, 0, 1), (24, 8, 128, 64, 218, 6, 0, 0), (24, 8, 128, 33, 235, 21, 0, 0),
-    (24, 8, 128, 33, 236, 21, 0, 1), (24, 8, 128, 64, 1003, 21, 0, 0), (24, 8, 128, 64, 1004, 21, 0, 1), (32, 8, 64, 33, 10, 8, 0, 1),
-    (32, 8, 64, 64, 184, 8, 0, 0), (32, 8, 64, 64, 185, 8, 0, 1), (32, 8, 64, 63, 240, 16, 0, 0), (32, 8, 64, 63, 241, 16, 0, 1),
-    (32, 8, 64, 64, 432, 16, 0, 0), (32, 8, 64, 64, 433, 16, 0, 1), (32, 8, 64, 70, 752, 16, 0, 0), (32, 8, 64, 49, 993, 31, 0, 0),
-    (32, 8, 64, 50, 226, 31, 0, 1), (32, 8, 64, 64, 1505, 31, 0, 0), (32, 8, 64, 64, 1506, 31, 0, 1), (32, 8, 64, 70, 1761, 31, 0, 0),
-    (24, 8, 128, 97, 619, 21, 0, 0), (24, 8, 128, 97, 620, 21, 0, 1)])
+    (24, 8, 128, 1, 26, 6, 0, 0), (24, 8, 128, 1, 27, 6, 0, 1), (32, 1, 128, 1, 5, 1, 0, 0), (24, 8, 128, 26, 58, 6, 0, 1),
+    (33, 1, 128, 1, 191, 1, 0, 0), (33, 1, 128, 1, 192, 1, 0, 1), (33, 1, 128, 1, 5000, 1, 192, 0), (24, 8, 128, 16, 4075, 21, 0, 1),
+    (64, 1, 128, 1, 500, 1, 0, 1), (65, 1, 128, 1, 60000, 1, 0, 0), (24, 8, 128, 16, 4075, 42, 0, 0), (64, 1, 64, 1, 176, 1, 0, 1),
+    (64, 1, 64, 1, 175, 1, 0, 0), (65, 1, 64, 1, 65535, 1, 0, 0), (65, 1, 64, 1, 65536, 1, 0, 1), (65, 8, 64, 2, 4095, 16, 100, 0),
+    (32, 8, 64, 13, 225, 31, 0, 0), (32, 8, 64, 13, 226, 31, 0, 1),
+    # more pairs than compute units, and than fill the part twice and four times
+    (24, 8, 128, 33, 218, 6, 0, 0), (24, 8, 128, 33, 219, 6, 0, 1), (24, 8, 128, 64, 250, 6, 0, 0), (24, 8, 128, 64, 251, 6, 0, 1),
+    (24, 8, 128, 128, 334, 6, 0, 0), (24, 8, 128, 128, 335, 6, 0, 1), (24, 8, 128, 33, 235, 21, 0, 0), (24, 8, 128, 33, 236, 21, 0, 1),
+    (24, 8, 128, 64, 1179, 21, 0, 0), (24, 8, 128, 64, 1180, 21, 0, 1), (24, 8, 128, 70, 1779, 21, 0, 0), (24, 8, 128, 70, 1780, 21, 0, 1),
+    (24, 8, 128, 97, 619, 21, 0, 0), (24, 8, 128, 97, 620, 21, 0, 1), (32, 8, 64, 64, 24, 8, 0, 0), (32, 8, 64, 33, 25, 8, 0, 1),
+    (32, 8, 64, 65, 184, 8, 0, 0), (32, 8, 64, 65, 185, 8, 0, 1), (32, 8, 64, 128, 264, 8, 0, 0), (32, 8, 64, 128, 265, 8, 0, 1),
+    (32, 8, 64, 63, 240, 16, 0, 0), (32, 8, 64, 63, 241, 16, 0, 1), (32, 8, 64, 64, 624, 16, 0, 0), (32, 8, 64, 64, 625, 16, 0, 1),
+    (32, 8, 64, 70, 884, 16, 0, 0), (32, 8, 64, 70, 885, 16, 0, 1), (32, 8, 64, 97, 1084, 16, 0, 0), (32, 8, 64, 49, 993, 31, 0, 0),
+    (32, 8, 64, 50, 226, 31, 0, 1), (32, 8, 64, 64, 1269, 31, 0, 0), (32, 8, 64, 64, 1270, 31, 0, 1), (32, 8, 64, 70, 2017, 31, 0, 0),
+    (32, 8, 64, 97, 1770, 31, 0, 1)])
 def test_kernel_of_a_wide_block(lib, Hq, Hkv, D, batch, t, queries, window, stream):
     Hq = Hq // Hkv * Hkv
     kv = store(T.TEMPO_BF16, Hkv, D, 64, (t + queries) // 64 + 1)
