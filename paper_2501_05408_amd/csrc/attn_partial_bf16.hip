@@ -403,11 +403,17 @@ hipError_t launch_partial_bf16(const AttnParams& p, int batch, int D, int grid_s
   const size_t lds = partial_bf16_lds_bytes(waves, p.queries * p.G, D);
   // The last group apart (kPeel) pays between these lines (us a step, one body / two): below, where a wavefront has
   // one group, the two bodies only lie further apart (32/4 heads of 128, 8 wavefronts, window 64 5.17 / 5.41, 100
-  // 5.30 / 5.45, 150 alike, 300 1% faster on the mean of 36 shapes); beyond, at D = 64, where 16 wavefronts share a compute
-  // unit, more bytes in flight slow the stream down (32/8 heads, 1 sequence, 600 keys 6.1 / 5.6, 16 sequences of 4096 25.5 /
-  // 26.9).  With rotated queries at D = 128 always (148 shapes of 12 to 140 keys 4% on the mean, all of them).
+  // 5.30 / 5.45, 150 alike, 300 1% faster on the mean of 36 shapes; 32/8 heads of 64, up to 24 sequences, 160 keys 1 to 3%
+  // slower, 256 1, 600 4% faster); beyond, at D = 64, where 16 wavefronts share a compute unit, more bytes in flight
+  // slow the stream down (16 sequences of 4096 25.5 / 26.9; just over 256 pairs, where some units have two
+  // workgroups, from 600 keys: 33 sequences of 600 to 1100 keys 2 to 5%, 48 alike).  With rotated
+  // queries at D = 128 always (148 shapes of 12 to 140 keys 4% on the mean, all of them).
   const int64_t last = (int64_t)p.t + p.queries, keys = p.window > 0 && p.window < last ? p.window : last;
-  const bool peel = D == 128 ? keys > 256 : keys > 96 && keys <= 1536;
+  const int64_t pairs = (int64_t)batch * p.Hkv;
+  const bool one_each = pairs <= 256, some_two = !one_each && pairs < 384;
+  const bool peel = D == 128       ? keys > 256
+                    : p.rope_cos ? keys > 96 && keys <= 1536
+                                 : keys > (one_each ? 192 : 96) && keys <= (some_two ? 512 : 1536);
   if (p.worklist) {
     if (p.rope_cos) return hipErrorInvalidConfiguration;  // no caller combines the two
     if (D == 128) return launch((attn_partial_bf16<128, false, true, true>), grid, block, lds, stream, p);
