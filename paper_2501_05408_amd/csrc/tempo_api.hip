@@ -1158,7 +1158,7 @@ bool rows_readable(const tempo_kv* kv, const void* k_new, const void* v_new, con
 //   blocks than units, up to 1320 steps, or 1700 with blocks for two rounds (8 heads: 3 sequences of 1591 steps 54.3 / 59.3,
 //   2 of 2339 71.7 / 81.4; but 2 of 1568, 208 blocks, 43.2 / 39.4, 6 of 1459 71.0 / 65.0); of 2 or 3 heads up to 2800 steps (1
 //   sequence of 2888 steps 83.0 / 90.0, 2175 65.6 / 61.8), or 1700 with more than 1024 blocks (5% on the mean).
-//   Windows: all, but for linear stores and windows so short that the block kernel takes the written prompt, with
+//   Windows: all, but for stores that hold the prompt and windows so short that the block kernel takes the written prompt, with
 //   blocks for many rounds (8 heads a group, 52 keys, 2400 blocks 64.6 / 69.1, 780 28.4 / 27.9; 3 heads, 36 keys, 3072 blocks
 //   98.5 / 101.2, 1800 64.8 / 63.6).
 //   fp32: at D = 128 up to about 4.5e9 flops (8/8 heads: 4 x 128 17.5 / 10.4, 1 x 1534 (4.8e9) 124.5 / 124.4); at D = 64 but
@@ -1181,7 +1181,8 @@ bool prompt_from_rows(const tempo_kv* kv, const void* k_new, const void* v_new, 
       if (kv->head_dim == 128 && (G == 1 ? blocks > 240 && count > (blocks <= 2 * kComputeUnits ? 1320 : 1700)
                                          : G < 4 && (count > 2800 || (count > 1700 && blocks > 1024))))
         return false;
-    } else if (kv->ring_blocks == 0 && window < count && short_prompt(kv, batch, Hq, t, count, window) && blocks >= (G < 8 ? 2048 : 1400)) {
+    } else if ((kv->ring_blocks == 0 || count <= (int64_t)kv->ring_blocks * kv->block_size) && window < count &&
+               short_prompt(kv, batch, Hq, t, count, window) && blocks >= (G < 8 ? 2048 : 1400)) {
       return false;
     }
   } else if (kv->head_dim == 128) {

@@ -442,6 +442,12 @@ def test_bf16_prompts_read_from_rows(lib, Hq, Hkv, D, batch, count, window, rows
     assert_all_keys_launched(launches, Hq // Hkv, 0, count)
 
 
+@pytest.mark.parametrize("ring,rows", [(8, False), (4, True)])  # holds 480 steps, or not
+def test_prompts_on_a_ring_read_from_rows(lib, ring, rows):
+    launches = prefill(lib, store(T.TEMPO_BF16, 8, 128, 64, ring, ring), 10, 64, 0, 480, 52, out=1 << 45)
+    assert [n for n, _ in launches] == (["prompt"] if rows else ["append", "short_prompt"])
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,batch,count,rows", [
     (8, 2, 64, 1, 512, True), (8, 2, 64, 1, 529, True), (8, 2, 64, 1, 530, False), (8, 2, 64, 1, 1024, False), (8, 2, 64, 1, 1025, True),
     (8, 8, 64, 1, 700, False), (8, 8, 64, 1, 705, True), (8, 8, 64, 2, 700, True)])
